@@ -27,37 +27,46 @@ static inline bool ld_aligned(const void* p, size_t a) {
 
 static inline size_t ld_round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Per-step scalars of an Adam replay window, prepared on the host in double.
+// Per-step scalars of an Adam replay window, prepared on the host in double. Folded (see
+// ld_adam_step): root_scale = sqrt(1 / (1 - beta2^s)) / lr_bc1 and eps_s = eps / lr_bc1, with lr_bc1 =
+// lr / (1 - beta1^s); general: root_scale = sqrt(1 / (1 - beta2^s)) and eps_s = eps.
 #define LD_MAX_ADAM_STEPS 64
 struct LdAdamSteps {
-    float lr_over_bc1[LD_MAX_ADAM_STEPS];  // lr / (1 - beta1^s)
-    float inv_bc2[LD_MAX_ADAM_STEPS];      // 1 / (1 - beta2^s)
-    float beta1, one_m_beta1, beta2, one_m_beta2, eps;
+    float lr_bc1[LD_MAX_ADAM_STEPS];      // lr / (1 - beta1^s), general form only
+    float root_scale[LD_MAX_ADAM_STEPS];
+    float eps_s[LD_MAX_ADAM_STEPS];
+    float beta1, one_m_beta1, beta2, one_m_beta2;
 };
+
+// Whether a replay runs the general form of ld_adam_step: an eps so small next to the roots that a
+// denormal v must not count as zero (the root then misses up to 1.1e-19 times the root scale of the
+// corrected moment, largest at step 1), or a learning rate or eps whose quotients leave the comfortable
+// part of the float range. Decided without the step number, so that every way to cut a window into
+// calls decides alike.
+static inline bool ld_adam_general(float lr, float beta2, float eps) {
+    const float mag = lr < 0.0f ? -lr : lr;
+    return !(static_cast<double>(eps) * sqrt(1.0 - static_cast<double>(beta2)) >= 1e-12 && eps <= 1e3f &&
+             mag >= 1e-10f && mag <= 1e3f);
+}
 
 // Scalars of steps step0+1 .. step0+W (W <= LD_MAX_ADAM_STEPS).
 static inline void ld_fill_adam_steps(LdAdamSteps& a, int32_t W, int64_t step0, float lr, float beta1,
-                                      float beta2, float eps) {
-    for (int32_t t = 0; t < LD_MAX_ADAM_STEPS; ++t) {
-        a.lr_over_bc1[t] = 0.0f;
-        a.inv_bc2[t] = 0.0f;
-    }
+                                      float beta2, float eps, bool general) {
+    for (int32_t t = 0; t < LD_MAX_ADAM_STEPS; ++t) a.lr_bc1[t] = a.root_scale[t] = a.eps_s[t] = 0.0f;
     for (int32_t t = 0; t < W; ++t) {
         const double s = static_cast<double>(step0 + 1 + t);
         const double bc1 = 1.0 - pow(static_cast<double>(beta1), s);
         const double bc2 = 1.0 - pow(static_cast<double>(beta2), s);
-        a.lr_over_bc1[t] = static_cast<float>(static_cast<double>(lr) / bc1);
-        a.inv_bc2[t] = static_cast<float>(1.0 / bc2);
+        const double lr_bc1 = static_cast<double>(lr) / bc1, fold = general ? 1.0 : lr_bc1;
+        a.lr_bc1[t] = static_cast<float>(lr_bc1);
+        a.root_scale[t] = static_cast<float>(1.0 / (sqrt(bc2) * fold));
+        a.eps_s[t] = static_cast<float>(static_cast<double>(eps) / fold);
     }
     a.beta1 = beta1;
     a.one_m_beta1 = 1.0f - beta1;
     a.beta2 = beta2;
     a.one_m_beta2 = 1.0f - beta2;
-    a.eps = eps;
 }
-
-// Whether a replay with this eps needs the square root that handles denormal arguments.
-static inline bool ld_adam_careful(float eps) { return !(eps >= 1e-12f); }
 
 #ifdef __HIPCC__
 
@@ -71,6 +80,21 @@ __device__ __forceinline__ void ld_nt_store(ld_f32x4 x, ld_f32x4* p) { __builtin
 __device__ __forceinline__ void ld_nt_store(ld_u32x4 x, ld_u32x4* p) { __builtin_nontemporal_store(x, p); }
 
 __device__ __forceinline__ int ld_lane() { return __lane_id(); }
+
+// The piece of work of workgroup `b` of a grid of `grid` workgroups (a multiple of 8). Consecutive
+// workgroups go to the 8 XCDs in turn: every XCD is given runs of CHUNK consecutive pieces, so that
+// all XCDs together walk the arrays in address order; the pieces past the last whole round of
+// 8 CHUNK are dealt out in eighths.
+template <uint32_t CHUNK>
+__device__ __forceinline__ uint32_t ld_xcd_piece(uint32_t b, uint32_t grid) {
+    const uint32_t whole = grid / (8u * CHUNK) * (8u * CHUNK);
+    if (b < whole) {
+        const uint32_t q = b / 8u;
+        return q / CHUNK * (8u * CHUNK) + (b % 8u) * CHUNK + q % CHUNK;
+    }
+    const uint32_t rest = b - whole;
+    return whole + (rest % 8u) * ((grid - whole) / 8u) + rest / 8u;
+}
 
 // |x| as an integer that orders like the magnitude (sign bit cleared).
 __device__ __forceinline__ uint32_t ld_key(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
@@ -114,30 +138,35 @@ __device__ __forceinline__ float ld_bf16_widen(uint32_t h) { return __uint_as_fl
 // One Adam step on one element (Eq. (4); bias-corrected, eps added to the root of the
 // corrected second moment). The only place the arithmetic is written: every replay
 // kernel, fused window or single step, dense or sparse gradient, runs these operations.
-//   lr_bc1 = lr / (1 - beta1^s), ibc2 = 1 / (1 - beta2^s), both prepared on the host in double
-// The hardware square root takes a denormal argument for zero. Next to an eps of ordinary size
-// that is far below the tolerance (the root of a denormal is below 1.1e-19); with eps = 0, or an eps
-// that small, it would decide the result (a zero denominator). TINY_EPS (chosen per call from eps,
-// see ld_adam_careful) scales such arguments into the normal range first: sqrt(x) =
-// sqrt(x * 2^64) * 2^-32, exact scalings.
-template <bool TINY_EPS>
-__device__ __forceinline__ void ld_adam_step(float& w, float& m, float& v, float g, float b1,
-                                             float omb1, float b2, float omb2, float eps,
-                                             float lr_bc1, float ibc2) {
-    m = __fmaf_rn(b1, m, __fmul_rn(omb1, g));
-    v = __fmaf_rn(b2, v, __fmul_rn(__fmul_rn(omb2, g), g));
-    float x = __fmul_rn(v, ibc2), root;
-    if (TINY_EPS) {
-        const bool tiny = x < 0x1p-96f;
-        x = tiny ? __fmul_rn(x, 0x1p+64f) : x;
-        root = __builtin_amdgcn_sqrtf(x);
+//   g1 = (1 - beta1) g, g2 = ((1 - beta2) g) g  (ld_adam_terms)
+// The folded form divides numerator and denominator of the update by lr / (1 - beta1^s): two
+// moments, a square root, a fused multiply-add for the denominator, a reciprocal and a fused
+// multiply-add for w - four full-rate operations and two of four issue slots each, and fewer
+// roundings than the formula as written.
+// The general form keeps the learning rate apart. The hardware square root takes a denormal
+// argument for zero, which with eps = 0 (or tiny) would decide the result (a zero denominator):
+// it scales such arguments into the normal range first: sqrt(x) = sqrt(x * 2^64) * 2^-32, exact
+// scalings. ld_adam_general says which form a call runs.
+__device__ __forceinline__ void ld_adam_terms(float g, float omb1, float omb2, float& g1, float& g2) {
+    g1 = __fmul_rn(omb1, g);
+    g2 = __fmul_rn(__fmul_rn(omb2, g), g);
+}
+
+template <bool GENERAL>
+__device__ __forceinline__ void ld_adam_step(float& w, float& m, float& v, float g1, float g2, float b1, float b2,
+                                             float lr_bc1, float root_scale, float eps_s) {
+    m = __fmaf_rn(b1, m, g1);
+    v = __fmaf_rn(b2, v, g2);
+    if (GENERAL) {
+        const bool tiny = v < 0x1p-96f;
+        float root = __builtin_amdgcn_sqrtf(tiny ? __fmul_rn(v, 0x1p+64f) : v);
         root = tiny ? __fmul_rn(root, 0x1p-32f) : root;
+        const float denom = __fmaf_rn(root, root_scale, eps_s);
+        w = __fmaf_rn(-__fmul_rn(lr_bc1, m), __builtin_amdgcn_rcpf(denom), w);
     } else {
-        root = __builtin_amdgcn_sqrtf(x);
+        const float denom = __fmaf_rn(__builtin_amdgcn_sqrtf(v), root_scale, eps_s);
+        w = __fmaf_rn(-m, __builtin_amdgcn_rcpf(denom), w);
     }
-    const float denom = __fadd_rn(root, eps);
-    const float upd = __fmul_rn(__fmul_rn(lr_bc1, m), __builtin_amdgcn_rcpf(denom));
-    w = __fsub_rn(w, upd);
 }
 
 // Device-scope load that is not served from a stale per-CU cache line.

@@ -99,7 +99,7 @@ typedef uint32_t ld_u32x2 __attribute__((ext_vector_type(2)));
 // lane), and all loads are issued before the first value is used. Consecutive
 // workgroups go to different XCDs, so each XCD is given one contiguous eighth of
 // the arrays (its address translations and DRAM pages stay its own).
-template <int WT, bool TINY_EPS>
+template <int WT, bool GENERAL>
 __global__ __launch_bounds__(kAdamThreads) void k_adam(float* __restrict__ w, float* __restrict__ m,
                                                        float* __restrict__ v, int64_t n, AdamArgs a, int t0) {
     const int64_t per = (static_cast<int64_t>(gridDim.x) + 7) / 8;
@@ -135,12 +135,13 @@ __global__ __launch_bounds__(kAdamThreads) void k_adam(float* __restrict__ w, fl
             for (int t = 0; t < WT; ++t) {
                 if (t0 + t < a.W) {
                     const uint32_t gw[2] = {gq[t][h].x, gq[t][h].y};
-                    const float lr_bc1 = a.s.lr_over_bc1[t0 + t], ibc2 = a.s.inv_bc2[t0 + t];
+                    const float lr_bc1 = a.s.lr_bc1[t0 + t], scale = a.s.root_scale[t0 + t], eps_s = a.s.eps_s[t0 + t];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const uint32_t half = (e & 1) ? (gw[e >> 1] >> 16) : (gw[e >> 1] & 0xFFFFu);
-                        ld_adam_step<TINY_EPS>(ww[e], mm[e], v4_[e], ld_bf16_widen(half), a.s.beta1, a.s.one_m_beta1, a.s.beta2,
-                                  a.s.one_m_beta2, a.s.eps, lr_bc1, ibc2);
+                        float g1, g2;
+                        ld_adam_terms(ld_bf16_widen(half), a.s.one_m_beta1, a.s.one_m_beta2, g1, g2);
+                        ld_adam_step<GENERAL>(ww[e], mm[e], v4_[e], g1, g2, a.s.beta1, a.s.beta2, lr_bc1, scale, eps_s);
                     }
                 }
             }
@@ -152,9 +153,12 @@ __global__ __launch_bounds__(kAdamThreads) void k_adam(float* __restrict__ w, fl
         // the last, ragged workgroup: element by element
         for (int64_t e = b0 + threadIdx.x; e < n; e += kAdamThreads) {
             float ww = w[e], mm = m[e], v1 = v[e];
-            for (int t = t0; t < t0 + WT && t < a.W; ++t)
-                ld_adam_step<TINY_EPS>(ww, mm, v1, ld_bf16_widen(a.grad[t][e]), a.s.beta1, a.s.one_m_beta1, a.s.beta2,
-                          a.s.one_m_beta2, a.s.eps, a.s.lr_over_bc1[t], a.s.inv_bc2[t]);
+            for (int t = t0; t < t0 + WT && t < a.W; ++t) {
+                float g1, g2;
+                ld_adam_terms(ld_bf16_widen(a.grad[t][e]), a.s.one_m_beta1, a.s.one_m_beta2, g1, g2);
+                ld_adam_step<GENERAL>(ww, mm, v1, g1, g2, a.s.beta1, a.s.beta2, a.s.lr_bc1[t], a.s.root_scale[t],
+                                      a.s.eps_s[t]);
+            }
             w[e] = ww;
             m[e] = mm;
             v[e] = v1;
@@ -238,7 +242,8 @@ extern "C" ld_status ld_merge_dense_adam(float* w, float* m, float* v, int64_t n
         if (!ld_aligned(grads_bf16[t], 16)) return LD_ERR_ALIGN;
         a.grad[t] = static_cast<const uint16_t*>(grads_bf16[t]);
     }
-    ld_fill_adam_steps(a.s, W, step0, lr, beta1, beta2, eps);
+    const bool general = ld_adam_general(lr, beta2, eps);
+    ld_fill_adam_steps(a.s, W, step0, lr, beta1, beta2, eps, general);
     a.W = W;
     const int64_t blocks = (n + kAdamBlockElems - 1) / kAdamBlockElems;
     if (blocks > INT32_MAX - 8) return LD_ERR_RANGE;
@@ -247,11 +252,10 @@ extern "C" ld_status ld_merge_dense_adam(float* w, float* m, float* v, int64_t n
     ld_begin_call();
     // steps are fused four (or eight) at a time; the state round-trips through fp32
     // memory between passes, which is exactly what it does between two calls
-    const bool careful = ld_adam_careful(eps);
     int t0 = 0;
     while (t0 < W) {
         const int left = W - t0;
-        if (careful) {
+        if (general) {
             if (left > 4) { k_adam<8, true><<<grid, block, 0, s>>>(w, m, v, n, a, t0); t0 += 8; }
             else if (left > 2) { k_adam<4, true><<<grid, block, 0, s>>>(w, m, v, n, a, t0); t0 += 4; }
             else if (left > 1) { k_adam<2, true><<<grid, block, 0, s>>>(w, m, v, n, a, t0); t0 += 2; }

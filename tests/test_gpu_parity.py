@@ -624,6 +624,31 @@ def test_sparse_adam_replay_parity(n, W, dens, step0):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
 
 
+@pytest.mark.parametrize("n,W,dens", [(1023, 3, 0.02), (1025, 2, 0.024), (49153, 5, 0.0234), (1 << 18, 3, 0.0235),
+                                      ((1 << 18) + 5, 65, 0.003), (300000, 4, 0.2)])
+@pytest.mark.parametrize("lr,eps", [(1e-4, 1e-8), (-1e-3, 1e-8), (1e-11, 1e-8), (2e3, 1e-8), (1e-3, 1e-12)])
+def test_sparse_adam_windows_and_forms(n, W, dens, lr, eps):
+    # either side of the densities where one record window per diff becomes two, sub-tile edges, more
+    # than one group of diffs, and learning rates / eps on either side of the folded form's range
+    rs = np.random.RandomState(n + W)
+    w0 = synth.base_weights(n).numpy()
+    m0 = (rs.standard_normal(n) * 1e-4).astype(np.float32)
+    v0 = (rs.standard_normal(n) ** 2 * 1e-6).astype(np.float32)
+    K = max(1, int(n * dens))
+    idxs = [np.sort(rs.choice(n, K, replace=False)).astype(np.int32) for _ in range(W)]
+    vals = [(rs.standard_normal(K) * 1e-2).astype(np.float32) for _ in range(W)]
+    w, m, v = to_gpu(w0), to_gpu(m0), to_gpu(v0)
+    hp = dict(lr=lr, beta1=0.9, beta2=0.999, eps=eps)
+    ld.ld_merge_sparse_adam(w, m, v, [to_gpu(i) for i in idxs], [to_gpu(x) for x in vals], 2, **hp)
+    torch.cuda.synchronize()
+    ref = oracle.sparse_adam_replay(w0, m0, v0, idxs, vals, 2, **hp)
+    # a step moves an element by at most about lr: each is a few ulp of its own size off
+    scale = max(1.0, abs(lr) * W * 10)
+    np.testing.assert_allclose(w.cpu().numpy(), ref[0], rtol=1e-6, atol=1e-7 * scale)
+    np.testing.assert_allclose(m.cpu().numpy(), ref[1], rtol=1e-6, atol=1e-7)
+    np.testing.assert_allclose(v.cpu().numpy(), ref[2], rtol=1e-6, atol=0)
+
+
 def test_sparse_adam_equals_dense_adam_on_full_diffs():
     # diffs that record every position with bf16-representable values are dense gradients:
     # both entry points must then agree bit for bit (they share the per-element step)
