@@ -20,7 +20,7 @@
 //             of the fine bins that the later passes lay over the keys above tau.
 //             When the whole segment fits in the sample the three are exact.
 //   k_main    the only full pass, 12 bytes per element. One wave per 4096-element
-//             tile, each XCD walking one contiguous eighth of the tiles in address
+//             tile, the tiles dealt to the XCDs in short runs in address
 //             order. Elements with key >= tau
 //             go, in index order, into the tile's candidate slot. The residual is
 //             written as if T_est were the threshold: +0 where key >= T_est, r + g
@@ -571,17 +571,23 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__
 
 // -------------------------------------------------------------------- k_main
 
+// How the tiles are dealt to the XCDs: one by one in address order below kMainRunGroups groups
+// (180 M elements), in runs of 16 tiles (256 KB per array) above. Measured, us per compress call with
+// eighths of the arrays per XCD / single tiles / runs of 16: 48 M elements 180 / 169 / 174,
+// 128 M 352 / 336 / 341, 160 M 433 / 407 / 409, 200 M 508 / 487 / 483, 512 M 1224 / 1184 / 1156, 1.2 G
+// 2838 / 2782 / 2672; runs of 2, 8, 32 and 64 lie between or behind.
+constexpr int32_t kMainRunGroups = 700;
 constexpr int kMainWaves = 1;                                // waves per tile
 constexpr int kMainRows = kTile / (kMainWaves * LD_WAVE * 4);  // float4 rows per lane
 constexpr int kMainWaveTile = LD_WAVE * 4 * kMainRows;      // consecutive elements per wave
 
 // SMALL: the slots have the minimum size (every call at the usual densities): a constant then.
-template <bool SMALL>
+// RUN: consecutive tiles an XCD is given at a time (see ld_xcd_piece and kMainRunGroups).
+template <bool SMALL, uint32_t RUN>
 __global__ __launch_bounds__(kMainWaves * LD_WAVE) void k_main(const float* __restrict__ g, float* __restrict__ r, Ctx c) {
     const int32_t slot_size = SMALL ? kSlotMin : c.slot;
     __shared__ uint32_t wtot[kMainWaves];
-    // consecutive workgroups go to different XCDs: each XCD streams one contiguous eighth of the tiles
-    const int32_t tile = static_cast<int32_t>((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8);
+    const int32_t tile = static_cast<int32_t>(ld_xcd_piece<RUN>(blockIdx.x, gridDim.x));
     const GroupDesc gd = group_range(c, tile / kTilesPerGroup);
     const int lane = ld_lane();
     const int w = threadIdx.x >> 6;
@@ -1937,8 +1943,14 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     if (n_group == 0) return LD_OK;
     const dim3 grid(static_cast<uint32_t>(n_group));
     const dim3 mgrid(static_cast<uint32_t>(n_group * kTilesPerGroup)), mblock(kMainWaves * LD_WAVE);
-    if (slot == kSlotMin) k_main<true><<<mgrid, mblock, 0, st>>>(grad, residual, c);
-    else k_main<false><<<mgrid, mblock, 0, st>>>(grad, residual, c);
+    const bool runs = n_group >= kMainRunGroups;
+    if (slot == kSlotMin) {
+        if (runs) k_main<true, 16><<<mgrid, mblock, 0, st>>>(grad, residual, c);
+        else k_main<true, 1><<<mgrid, mblock, 0, st>>>(grad, residual, c);
+    } else {
+        if (runs) k_main<false, 16><<<mgrid, mblock, 0, st>>>(grad, residual, c);
+        else k_main<false, 1><<<mgrid, mblock, 0, st>>>(grad, residual, c);
+    }
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     if (K == 0) return LD_OK;
     const dim3 hgrid(static_cast<uint32_t>((n_group + kHistGroups - 1) / kHistGroups)), hblock(kHistGroups * kThreads);
