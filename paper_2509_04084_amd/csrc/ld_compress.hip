@@ -77,14 +77,12 @@ constexpr int kGroup = kTile * kTilesPerGroup;    // 262144 elements per small-p
 constexpr int kBins = 2048;
 constexpr int kTopBin = kBins - 1;
 constexpr int kShift1 = 20, kShift2 = 9;          // radix digits: [30:20] [19:9] [8:0]
-constexpr int kPrepThreads = 512;
 constexpr int kSample = 16384;                        // sampled elements per segment
-constexpr int kSampleItems = kSample / kPrepThreads;
-static_assert(kSampleItems <= 32 && kSampleItems % 8 == 0, "valid mask is 32 bits; loads go in batches of 8");
 constexpr int kSampleRuns = kSample / LD_WAVE;        // as 256 runs of 64 consecutive elements
 constexpr float kSampleZ = 6.5f;                  // safety margin of the rank estimate, in sigmas
 constexpr int kGatherBase = 4096;                 // gather list of a segment: kGatherBase + n_s / kGatherPer keys
 constexpr int kGatherPer = 4096;
+constexpr int32_t kPrepWide = 256;                // segments up to which k_prep runs 1024 threads each
 constexpr int kSegPerLaunch = 448;
 constexpr int kFullGrid = 1024;                   // most workgroups of the (normally idle) k_full kernel
 constexpr uint32_t kModeCand = 0, kModeFull = 1, kModeTies = 2;
@@ -271,50 +269,101 @@ __device__ __forceinline__ void flush_hist(uint32_t* h, const uint32_t* lh) {
     }
 }
 
+// In R histograms of kBins counters in LDS at h + own[i] * kBins: the bin of rank kr[i], counted from
+// the top bin down, as in find_bin. The R scans share their barriers. `sh` holds R * NT/64 words;
+// res[3i], res[3i+1], res[3i+2] = bin, rank inside it, its count. The caller's counts are complete
+// (a barrier has passed); ends with a barrier.
+template <int NT, int R>
+__device__ __forceinline__ void find_bins(const uint32_t* h, const int (&own)[R], const uint32_t (&kr)[R],
+                                          uint32_t* sh, uint32_t* res) {
+    constexpr int per = kBins / NT, NW = NT / LD_WAVE;
+    const int top = kBins - 1 - static_cast<int>(threadIdx.x) * per;  // this thread's highest bin
+    const int w = threadIdx.x >> 6;
+    uint32_t v[R][per], sum[R], inc[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        sum[i] = 0;
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            v[i][j] = h[own[i] * kBins + top - j];
+            sum[i] += v[i][j];
+        }
+        inc[i] = sum[i];
+    }
+#pragma unroll
+    for (int d = 1; d < LD_WAVE; d <<= 1) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const uint32_t y = __shfl_up(inc[i], d, LD_WAVE);
+            if (ld_lane() >= d) inc[i] += y;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (ld_lane() == LD_WAVE - 1) sh[i * NW + w] = inc[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        uint32_t above = inc[i] - sum[i];
+#pragma unroll
+        for (int u = 0; u < NW; ++u) above += u < w ? sh[i * NW + u] : 0u;
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            if (above < kr[i] && kr[i] <= above + v[i][j]) {
+                res[3 * i] = static_cast<uint32_t>(top - j);
+                res[3 * i + 1] = kr[i] - above;
+                res[3 * i + 2] = v[i][j];
+            }
+            above += v[i][j];
+        }
+    }
+    __syncthreads();
+}
+
 // The keys at R ranks (1 = largest), each rounded DOWN to a multiple of
 // 2^kShift2: two radix levels resolve the top 22 bits, which is all an estimate
 // needs. The ranks share one pass over the keys per level; ranks whose prefixes
-// coincide share a histogram. `lh` holds R * kBins words, `res` 2 * R.
+// coincide share a histogram. `lh` holds (1 + R) * kBins words, cleared, with a barrier since;
+// `res` 3 * R. res[3i + 2] is left as the number of keys that round down to out[i].
 template <int NT, int ITEMS, int R>
-__device__ void block_select_multi(const uint32_t (&key)[ITEMS], uint32_t valid_mask, const uint32_t (&rank)[R],
-                                   uint32_t* lh, uint32_t* sh, uint32_t* res, uint32_t (&out)[R]) {
-    uint32_t p[R], kr[R];
+__device__ __forceinline__ void block_select_multi(const uint32_t (&key)[ITEMS], uint32_t valid_mask,
+                                                   const uint32_t (&rank)[R], uint32_t* lh, uint32_t* sh,
+                                                   uint32_t* res, uint32_t (&out)[R]) {
+    int own[R];
+    uint32_t kr[R];
 #pragma unroll
-    for (int i = 0; i < R; ++i) { p[i] = 0; kr[i] = rank[i]; }
-#pragma unroll 1
-    for (int level = 0; level < 2; ++level) {
-        const int match_shift = (level == 0) ? 31 : kShift1;
-        const int digit_shift = (level == 0) ? kShift1 : kShift2;
-        int own[R];  // the first rank with the same prefix: its histogram serves this one too
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            own[i] = i;
-#pragma unroll
-            for (int j = i - 1; j >= 0; --j)
-                if (p[j] == p[i]) own[i] = j;
-        }
-        for (int b = threadIdx.x; b < R * kBins; b += NT) lh[b] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < ITEMS; ++q) {
-            if (!((valid_mask >> q) & 1u)) continue;
-            const uint32_t d = (key[q] >> digit_shift) & 0x7FFu;
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-                if (own[i] == i && (key[q] >> match_shift) == (p[i] >> match_shift)) atomicAdd(&lh[i * kBins + d], 1u);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < R; ++i) find_bin<NT, false>(lh + own[i] * kBins, kr[i], sh, res + 2 * i);
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            p[i] |= res[2 * i] << digit_shift;
-            kr[i] = res[2 * i + 1];
-        }
-        __syncthreads();
+    for (int i = 0; i < R; ++i) {
+        own[i] = 0;
+        kr[i] = rank[i];
     }
 #pragma unroll
-    for (int i = 0; i < R; ++i) out[i] = p[i];
+    for (int q = 0; q < ITEMS; ++q)
+        if ((valid_mask >> q) & 1u) atomicAdd(&lh[key[q] >> kShift1], 1u);
+    __syncthreads();
+    find_bins<NT, R>(lh, own, kr, sh, res);
+    uint32_t p[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        p[i] = res[3 * i];
+        kr[i] = res[3 * i + 1];
+        own[i] = i;  // the first rank with the same prefix: its histogram serves this one too
+#pragma unroll
+        for (int j = i - 1; j >= 0; --j)
+            if (p[j] == p[i]) own[i] = j;
+    }
+    uint32_t* l1 = lh + kBins;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        if (!((valid_mask >> q) & 1u)) continue;
+        const uint32_t d = (key[q] >> kShift2) & 0x7FFu;
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            if (own[i] == i && (key[q] >> kShift1) == p[i]) atomicAdd(&l1[i * kBins + d], 1u);
+    }
+    __syncthreads();
+    find_bins<NT, R>(l1, own, kr, sh, res);
+#pragma unroll
+    for (int i = 0; i < R; ++i) out[i] = (p[i] << kShift1) | (res[3 * i] << kShift2);
 }
 
 __device__ __forceinline__ uint32_t mbcnt(uint64_t mask) {  // set bits of `mask` below this lane
@@ -423,12 +472,19 @@ __device__ __forceinline__ SegDesc desc_from_table(const PackedTable& pt, int32_
                    static_cast<int32_t>(found[4])};
 }
 
-__global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__ g,
-                                                       const float* __restrict__ r, Ctx c,
-                                                       int32_t no_estimate, PackedTable pt) {
-    __shared__ uint32_t lh[3 * kBins];
-    __shared__ uint32_t sh[kPrepThreads / LD_WAVE];
-    __shared__ uint32_t res[6];
+// NT threads: 1024 while every segment finds a CU of its own (the launch is then one chain of
+// latencies: sixteen items per thread, all loads in flight at once), 512 beyond (two workgroups per CU:
+// the sampled bytes bound it). Measured: one segment 20.2 -> 15.4 us, ResNet-50's 161 30.3 -> 16.1 (a
+// segment that fits the sample waited for memory once per item), GPT-2 XL's 580 40.7 -> 31.9.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_prep(const float* __restrict__ g, const float* __restrict__ r, Ctx c,
+                                             int32_t no_estimate, PackedTable pt) {
+    constexpr int kItems = kSample / NT;
+    static_assert(kItems <= 32 && kItems % 8 == 0, "valid mask is 32 bits; loads go in batches of 8");
+    __shared__ uint32_t lh[4 * kBins];
+    __shared__ uint32_t sh[3 * NT / LD_WAVE];
+    __shared__ uint32_t res[9];
+    for (int b = threadIdx.x; b < 4 * kBins; b += NT) lh[b] = 0;  // the barrier in the sampling below follows
     const int s = blockIdx.x;
     SegDesc d;
     int64_t end;
@@ -449,38 +505,49 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__
     const int32_t k = d.k;
     const int32_t ngroup = groups_of(off, end);
     if (threadIdx.x < sizeof(SegState) / 4) reinterpret_cast<uint32_t*>(&c.state[s])[threadIdx.x] = 0;
-    for (int b = threadIdx.x; b < kBins; b += kPrepThreads) c.hist[static_cast<int64_t>(s) * kBins + b] = 0;
+    for (int b = threadIdx.x; b < kBins; b += NT) c.hist[static_cast<int64_t>(s) * kBins + b] = 0;
 
     // candidate threshold, guessed threshold and bin width from a sample of |r + g|
     const int64_t ns = end - off;
     uint32_t tau = 0xFFFFFFFFu, test = 0xFFFFFFFFu, binsh = 0, tied = 0;
     if (k > 0 && !no_estimate) {
-        uint32_t key[kSampleItems];
+        uint32_t key[kItems];
         uint32_t valid = 0;
         const bool whole = ns <= kSample;
         const int lane = threadIdx.x & 63;
         const int64_t stride = ns / kSampleRuns;
+        // no load depends on a lane's bounds: those of a batch are issued together (one memory
+        // round trip per batch, not per item)
+        constexpr int kLoadBatch = NT == 1024 ? 16 : 8;
         if (whole) {
+            constexpr int kBatch = 4;
 #pragma unroll
-            for (int i = 0; i < kSampleItems; ++i) {
-                const int64_t e = off + i * kPrepThreads + threadIdx.x;
-                key[i] = 0;
-                if (e < end) {
-                    key[i] = ld_key(__fadd_rn(r[e], g[e]));
-                    valid |= 1u << i;
+            for (int i0 = 0; i0 < kItems; i0 += kBatch) {
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) key[i0 + i] = 0;
+                if (i0 * NT < ns) {  // uniform
+                    float rv[kBatch], gv[kBatch];
+#pragma unroll
+                    for (int i = 0; i < kBatch; ++i) {
+                        const int64_t e = off + (i0 + i) * NT + threadIdx.x;
+                        const int64_t at = e < end ? e : end - 1;  // past the end: any element, not used
+                        rv[i] = r[at];
+                        gv[i] = g[at];
+                        valid |= static_cast<uint32_t>(e < end) << (i0 + i);
+                    }
+#pragma unroll
+                    for (int i = 0; i < kBatch; ++i) key[i0 + i] = ld_key(__fadd_rn(rv[i], gv[i]));
                 }
             }
         } else {
-            // every run lies inside the segment: no bounds checks, and the loads of kLoadBatch
-            // items are issued together (one memory round trip per batch, not per item)
-            constexpr int kLoadBatch = 8;
-            valid = 0xFFFFFFFFu >> (32 - kSampleItems);
+            // every run lies inside the segment: no bounds checks
+            valid = 0xFFFFFFFFu >> (32 - kItems);
 #pragma unroll
-            for (int i0 = 0; i0 < kSampleItems; i0 += kLoadBatch) {
+            for (int i0 = 0; i0 < kItems; i0 += kLoadBatch) {
                 float rv[kLoadBatch], gv[kLoadBatch];
 #pragma unroll
                 for (int i = 0; i < kLoadBatch; ++i) {
-                    const int run = (i0 + i) * (kPrepThreads / LD_WAVE) + (threadIdx.x >> 6);
+                    const int run = (i0 + i) * (NT / LD_WAVE) + (threadIdx.x >> 6);
                     const int64_t jitter = __umulhi(hash32(static_cast<uint32_t>(run) * 2654435761u + static_cast<uint32_t>(s)),
                                                     static_cast<uint32_t>(stride - LD_WAVE + 1));
                     const int64_t e = off + run * stride + jitter + lane;
@@ -491,6 +558,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__
                 for (int i = 0; i < kLoadBatch; ++i) key[i0 + i] = ld_key(__fadd_rn(rv[i], gv[i]));
             }
         }
+        __syncthreads();  // the cleared counters, before the first count
         // Sample ranks (1 = largest). The selected keys are rounded down to 2^kShift2, which only
         // adds a few candidates.
         uint32_t rank[3], sel[3];
@@ -517,7 +585,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__
             tau = 0;  // k too large for an estimate: everything is a candidate, nothing is pre-zeroed
             binsh = kShift1;
         } else {
-            block_select_multi<kPrepThreads, kSampleItems, 3>(key, valid, rank, lh, sh, res, sel);
+            block_select_multi<NT, kItems, 3>(key, valid, rank, lh, sh, res, sel);
             tau = sel[0];
             if (whole) {
                 test = tau + (1u << kShift2);
@@ -526,29 +594,28 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__
                 // How often does the sample hold the candidate threshold's own key? (The selected keys
                 // are rounded down to 2^kShift2: look at the sample keys of that bucket; if they are
                 // many and all one value, that value is massively repeated in the segment.)
-                uint32_t same = 0, kmin = 0xFFFFFFFFu, kmax = 0;
+                if (res[2] >= kTieSuspect) {  // uniform
+                    uint32_t kmin = 0xFFFFFFFFu, kmax = 0;
 #pragma unroll
-                for (int i = 0; i < kSampleItems; ++i) {
-                    if ((key[i] >> kShift2) == (tau >> kShift2)) {
-                        ++same;
-                        kmin = umin(kmin, key[i]);
-                        kmax = key[i] > kmax ? key[i] : kmax;
+                    for (int i = 0; i < kItems; ++i) {
+                        if ((key[i] >> kShift2) == (tau >> kShift2)) {
+                            kmin = umin(kmin, key[i]);
+                            kmax = key[i] > kmax ? key[i] : kmax;
+                        }
                     }
-                }
-                __syncthreads();
-                if (threadIdx.x == 0) { res[0] = 0; res[1] = 0xFFFFFFFFu; res[2] = 0; }
-                __syncthreads();
-                same = ld_wave_sum(same);
-                if ((threadIdx.x & 63) == 0 && same) atomicAdd(&res[0], same);
-                if (kmin <= kmax) {
-                    atomicMin(&res[1], kmin);
-                    atomicMax(&res[2], kmax);
-                }
-                __syncthreads();
-                if (res[0] >= kTieSuspect && res[1] == res[2] && res[1] != 0x7FFFFFFFu) {
-                    tied = 1;  // candidates: the keys above it; no pre-zeroing (see SegState::tied)
-                    tau = res[1] + 1u;
-                    test = 0xFFFFFFFFu;
+                    __syncthreads();
+                    if (threadIdx.x == 0) { res[0] = 0xFFFFFFFFu; res[1] = 0; }
+                    __syncthreads();
+                    if (kmin <= kmax) {
+                        atomicMin(&res[0], kmin);
+                        atomicMax(&res[1], kmax);
+                    }
+                    __syncthreads();
+                    if (res[0] == res[1] && res[0] != 0x7FFFFFFFu) {
+                        tied = 1;  // candidates: the keys above it; no pre-zeroing (see SegState::tied)
+                        tau = res[0] + 1u;
+                        test = 0xFFFFFFFFu;
+                    }
                 }
                 const uint32_t top = sel[2] | ((1u << kShift2) - 1u);
                 const uint32_t range = top > tau ? top - tau : 0u;
@@ -564,7 +631,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__
         c.state[s].kmin = 0xFFFFFFFFu;
         c.state[s].tied = tied;
     }
-    for (int32_t q = threadIdx.x; q < ngroup; q += kPrepThreads)
+    for (int32_t q = threadIdx.x; q < ngroup; q += NT)
         c.gdesc[d.group0 + q] = GroupDesc{align_down4(off) + static_cast<int64_t>(q) * kGroup, off, end, d.out0,
                                           s, k, d.group0, ngroup, tau, binsh, test, tied};
 }
@@ -577,29 +644,27 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const float* __restrict__
 // 128 M 352 / 336 / 341, 160 M 433 / 407 / 409, 200 M 508 / 487 / 483, 512 M 1224 / 1184 / 1156, 1.2 G
 // 2838 / 2782 / 2672; runs of 2, 8, 32 and 64 lie between or behind.
 constexpr int32_t kMainRunGroups = 700;
-constexpr int kMainWaves = 1;                                // waves per tile
-constexpr int kMainRows = kTile / (kMainWaves * LD_WAVE * 4);  // float4 rows per lane
-constexpr int kMainWaveTile = LD_WAVE * 4 * kMainRows;      // consecutive elements per wave
+constexpr int kMainRows = kTile / (LD_WAVE * 4);  // float4 rows per lane
 
 // SMALL: the slots have the minimum size (every call at the usual densities): a constant then.
 // RUN: consecutive tiles an XCD is given at a time (see ld_xcd_piece and kMainRunGroups).
+// A workgroup is one wave: with two, four and eight tiles per workgroup a call on 1.56 G elements took
+// 3275, 3517 and 3546 us instead of 3255, on ResNet-50 136, 141 and 156 instead of 128 (a workgroup's
+// registers are held until its last wave is done).
 template <bool SMALL, uint32_t RUN>
-__global__ __launch_bounds__(kMainWaves * LD_WAVE) void k_main(const float* __restrict__ g, float* __restrict__ r, Ctx c) {
+__global__ __launch_bounds__(LD_WAVE) void k_main(const float* __restrict__ g, float* __restrict__ r, Ctx c) {
     const int32_t slot_size = SMALL ? kSlotMin : c.slot;
-    __shared__ uint32_t wtot[kMainWaves];
     const int32_t tile = static_cast<int32_t>(ld_xcd_piece<RUN>(blockIdx.x, gridDim.x));
     const GroupDesc gd = group_range(c, tile / kTilesPerGroup);
     const int lane = ld_lane();
-    const int w = threadIdx.x >> 6;
-    const int64_t tbase = gd.base + static_cast<int64_t>(tile % kTilesPerGroup) * kTile;
-    const int64_t t = tbase + w * kMainWaveTile;
+    const int64_t t = gd.base + static_cast<int64_t>(tile % kTilesPerGroup) * kTile;
     const int64_t seg_lo = gd.lo, seg_hi = gd.hi;
-    if (tbase >= seg_hi) {  // tile slot past the end of the segment
-        if (threadIdx.x == 0) c.cnt[tile] = 0;
+    if (t >= seg_hi) {  // tile slot past the end of the segment
+        if (lane == 0) c.cnt[tile] = 0;
         return;
     }
     const uint32_t tau = gd.tau, test = gd.test;
-    const bool interior = t >= seg_lo && t + kMainWaveTile <= seg_hi;
+    const bool interior = t >= seg_lo && t + kTile <= seg_hi;
     float a[kMainRows][4];
     uint32_t mask[kMainRows];
     if (interior) {  // unconditional 16-byte streaming accesses
@@ -629,7 +694,7 @@ __global__ __launch_bounds__(kMainWaves * LD_WAVE) void k_main(const float* __re
             for (int q = 0; q < 4; ++q) a[j][q] = __fadd_rn(rv[q], gv[q]);
         }
     }
-    // candidates, in element order (wave, row, lane, component)
+    // candidates, in element order (row, lane, component)
     uint32_t flag[kMainRows], zero[kMainRows], pos0[kMainRows], total = 0;
 #pragma unroll
     for (int j = 0; j < kMainRows; ++j) {
@@ -647,20 +712,8 @@ __global__ __launch_bounds__(kMainWaves * LD_WAVE) void k_main(const float* __re
             total += __popcll(m);
         }
     }
-    uint32_t wbase = 0, btot = total;
-    if (kMainWaves > 1) {
-        if (lane == 0) wtot[w] = total;
-        __syncthreads();
-        btot = 0;
-#pragma unroll
-        for (int u = 0; u < kMainWaves; ++u) {
-            const uint32_t x = wtot[u];
-            if (u < w) wbase += x;
-            btot += x;
-        }
-    }
-    const bool fits = btot <= static_cast<uint32_t>(slot_size);  // else: the residual keeps r + g everywhere, the slot stays unused
-    if (threadIdx.x == 0) c.cnt[tile] = fits ? btot : kOverflow;
+    const bool fits = total <= static_cast<uint32_t>(slot_size);  // else: the residual keeps r + g everywhere, the slot stays unused
+    if (lane == 0) c.cnt[tile] = fits ? total : kOverflow;
     // residual: +0 where the guessed threshold selects, r + g elsewhere
 #pragma unroll
     for (int j = 0; j < kMainRows; ++j) {
@@ -678,8 +731,8 @@ __global__ __launch_bounds__(kMainWaves * LD_WAVE) void k_main(const float* __re
 #pragma unroll
     for (int j = 0; j < kMainRows; ++j) {
         if (flag[j] == 0) continue;
-        uint32_t pos = wbase + pos0[j];
-        const uint32_t local = w * kMainWaveTile + (j * LD_WAVE + lane) * 4;
+        uint32_t pos = pos0[j];
+        const uint32_t local = (j * LD_WAVE + lane) * 4;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if ((flag[j] >> q) & 1u) {
@@ -1938,11 +1991,13 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     }
     const dim3 block(kThreads);
     const dim3 sgrid(static_cast<uint32_t>(n_seg));
-    k_prep<<<sgrid, dim3(kPrepThreads), 0, st>>>(grad, residual, c, strategy == LD_COMPRESS_FULL ? 1 : 0, pt);
+    const int32_t no_estimate = strategy == LD_COMPRESS_FULL ? 1 : 0;
+    if (n_seg <= kPrepWide) k_prep<1024><<<sgrid, dim3(1024), 0, st>>>(grad, residual, c, no_estimate, pt);
+    else k_prep<512><<<sgrid, dim3(512), 0, st>>>(grad, residual, c, no_estimate, pt);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     if (n_group == 0) return LD_OK;
     const dim3 grid(static_cast<uint32_t>(n_group));
-    const dim3 mgrid(static_cast<uint32_t>(n_group * kTilesPerGroup)), mblock(kMainWaves * LD_WAVE);
+    const dim3 mgrid(static_cast<uint32_t>(n_group * kTilesPerGroup)), mblock(LD_WAVE);
     const bool runs = n_group >= kMainRunGroups;
     if (slot == kSlotMin) {
         if (runs) k_main<true, 16><<<mgrid, mblock, 0, st>>>(grad, residual, c);
