@@ -72,8 +72,13 @@ constexpr int kTile = 4096;                       // elements per k_main workgro
 #endif
 constexpr int kSlotMin = LD_SLOT_MIN;             // candidate slots per tile: 128 serve densities up to ~1 % (a denser
 constexpr int kSlotMax = 2048;                    // layout of the slots made the candidate passes slower); denser calls get more (multiples of 64)
-constexpr int kTilesPerGroup = 64;
-constexpr int kGroup = kTile * kTilesPerGroup;    // 262144 elements per small-pass workgroup
+// Tiles per group, the unit of the passes over the candidates (a workgroup each): 64, or 16 for tables of
+// fewer than kSmallGroups groups of 64, whose passes would leave most of the chip idle and whose small
+// segments would cost k_main 64 tile slots each. Measured, us per call with 64 / 16: flat 1 M 59.9 /
+// 50.6, ResNet-50 128 / 109, 5 M at 2 % 85 / 65, 64 M 193 / 186; the same at 128 M elements (500 groups of
+// 64); GPT-2 XL 3268 / 3322.
+constexpr int kTilesPerGroup = 64, kTilesPerSmallGroup = 16;
+constexpr int64_t kSmallGroups = 512;
 constexpr int kBins = 2048;
 constexpr int kTopBin = kBins - 1;
 constexpr int kShift1 = 20, kShift2 = 9;          // radix digits: [30:20] [19:9] [8:0]
@@ -153,6 +158,7 @@ struct Ctx {
     int32_t n_seg;
     int32_t n_group;
     int32_t slot;           // candidates a tile can store (kSlotMin .. kSlotMax, multiple of 64)
+    int32_t tiles;          // tiles per group: kTilesPerGroup or kTilesPerSmallGroup
 };
 
 struct UploadBatch {
@@ -189,9 +195,10 @@ __host__ __device__ inline uint32_t gather_cap(int64_t lo, int64_t hi) {
     return static_cast<uint32_t>(kGatherBase + hi / kGatherPer - lo / kGatherPer);
 }
 
-__host__ __device__ inline int32_t groups_of(int64_t off, int64_t end) {
+__host__ __device__ inline int32_t groups_of(int64_t off, int64_t end, int32_t tiles) {
     if (end <= off) return 0;
-    return static_cast<int32_t>((end - align_down4(off) + kGroup - 1) / kGroup);
+    const int64_t len = static_cast<int64_t>(tiles) * kTile;
+    return static_cast<int32_t>((end - align_down4(off) + len - 1) / len);
 }
 
 // ------------------------------------------------------------ block helpers
@@ -432,7 +439,7 @@ __global__ __launch_bounds__(512) void k_upload(UploadBatch ub, Ctx c) {
     __shared__ uint32_t sh[512 / LD_WAVE];
     const int j = threadIdx.x;
     const bool live = j < ub.count;
-    const uint32_t my_groups = live ? static_cast<uint32_t>(groups_of(ub.off[j], ub.off[j + 1])) : 0u;
+    const uint32_t my_groups = live ? static_cast<uint32_t>(groups_of(ub.off[j], ub.off[j + 1], c.tiles)) : 0u;
     const uint32_t my_k = live ? static_cast<uint32_t>(ub.k[j]) : 0u;  // the batch's sum is below 2^31
     uint32_t total;
     const uint32_t groups = block_escan<512>(my_groups, sh, total);
@@ -450,7 +457,7 @@ __global__ __launch_bounds__(512) void k_upload(UploadBatch ub, Ctx c) {
 // Descriptor of segment `s` and the end of its range from the packed table. The host has summed
 // the segments of every bucket of 64; what is left is a prefix over the segments of the own
 // bucket before `s`: one lane per segment, three scans across the first wave.
-__device__ __forceinline__ SegDesc desc_from_table(const PackedTable& pt, int32_t s, int64_t& end) {
+__device__ __forceinline__ SegDesc desc_from_table(const PackedTable& pt, int32_t s, int32_t tiles, int64_t& end) {
     __shared__ uint32_t found[5];
     if (threadIdx.x < LD_WAVE) {
         const int bucket = s / LD_WAVE, lane = threadIdx.x;
@@ -460,7 +467,7 @@ __device__ __forceinline__ SegDesc desc_from_table(const PackedTable& pt, int32_
         const uint32_t len = live ? pt.len[code] : 0u, kk = live ? pt.k[code] : 0u;
         const uint32_t off = pt.off0[bucket] + ld_wave_iscan(len) - len;   // n <= 2^31 - 1: the sums fit 32 bits
         const uint32_t out0 = pt.out0[bucket] + ld_wave_iscan(kk) - kk;
-        const uint32_t groups = static_cast<uint32_t>(groups_of(off, static_cast<int64_t>(off) + len));
+        const uint32_t groups = static_cast<uint32_t>(groups_of(off, static_cast<int64_t>(off) + len, tiles));
         const uint32_t group0 = pt.group0[bucket] + ld_wave_iscan(groups) - groups;
         if (j == s) {
             found[0] = off; found[1] = len; found[2] = out0; found[3] = kk; found[4] = group0;
@@ -489,11 +496,11 @@ __global__ __launch_bounds__(NT) void k_prep(const float* __restrict__ g, const 
     SegDesc d;
     int64_t end;
     if (pt.n_seg > 0) {
-        d = desc_from_table(pt, s, end);
+        d = desc_from_table(pt, s, c.tiles, end);
         if (threadIdx.x == 0) {
             c.desc[s] = d;
             if (s == pt.n_seg - 1)
-                c.desc[s + 1] = SegDesc{end, d.out0 + d.k, 0, d.group0 + groups_of(d.off, end)};
+                c.desc[s + 1] = SegDesc{end, d.out0 + d.k, 0, d.group0 + groups_of(d.off, end, c.tiles)};
             if (s == 0)
                 for (int i = 0; i < kSyncWords; ++i) c.fail_count[i] = 0;
         }
@@ -503,7 +510,7 @@ __global__ __launch_bounds__(NT) void k_prep(const float* __restrict__ g, const 
     }
     const int64_t off = d.off;
     const int32_t k = d.k;
-    const int32_t ngroup = groups_of(off, end);
+    const int32_t ngroup = groups_of(off, end, c.tiles);
     if (threadIdx.x < sizeof(SegState) / 4) reinterpret_cast<uint32_t*>(&c.state[s])[threadIdx.x] = 0;
     for (int b = threadIdx.x; b < kBins; b += NT) c.hist[static_cast<int64_t>(s) * kBins + b] = 0;
 
@@ -632,22 +639,22 @@ __global__ __launch_bounds__(NT) void k_prep(const float* __restrict__ g, const 
         c.state[s].tied = tied;
     }
     for (int32_t q = threadIdx.x; q < ngroup; q += NT)
-        c.gdesc[d.group0 + q] = GroupDesc{align_down4(off) + static_cast<int64_t>(q) * kGroup, off, end, d.out0,
+        c.gdesc[d.group0 + q] = GroupDesc{align_down4(off) + static_cast<int64_t>(q) * c.tiles * kTile, off, end, d.out0,
                                           s, k, d.group0, ngroup, tau, binsh, test, tied};
 }
 
 // -------------------------------------------------------------------- k_main
 
-// How the tiles are dealt to the XCDs: one by one in address order below kMainRunGroups groups
+// How the tiles are dealt to the XCDs: one by one in address order below kMainRunTiles
 // (180 M elements), in runs of 16 tiles (256 KB per array) above. Measured, us per compress call with
 // eighths of the arrays per XCD / single tiles / runs of 16: 48 M elements 180 / 169 / 174,
 // 128 M 352 / 336 / 341, 160 M 433 / 407 / 409, 200 M 508 / 487 / 483, 512 M 1224 / 1184 / 1156, 1.2 G
 // 2838 / 2782 / 2672; runs of 2, 8, 32 and 64 lie between or behind.
-constexpr int32_t kMainRunGroups = 700;
+constexpr int64_t kMainRunTiles = 700 * 64;
 constexpr int kMainRows = kTile / (LD_WAVE * 4);  // float4 rows per lane
 
 // SMALL: the slots have the minimum size (every call at the usual densities): a constant then.
-// RUN: consecutive tiles an XCD is given at a time (see ld_xcd_piece and kMainRunGroups).
+// RUN: consecutive tiles an XCD is given at a time (see ld_xcd_piece and kMainRunTiles).
 // A workgroup is one wave: with two, four and eight tiles per workgroup a call on 1.56 G elements took
 // 3275, 3517 and 3546 us instead of 3255, on ResNet-50 136, 141 and 156 instead of 128 (a workgroup's
 // registers are held until its last wave is done).
@@ -655,9 +662,11 @@ template <bool SMALL, uint32_t RUN>
 __global__ __launch_bounds__(LD_WAVE) void k_main(const float* __restrict__ g, float* __restrict__ r, Ctx c) {
     const int32_t slot_size = SMALL ? kSlotMin : c.slot;
     const int32_t tile = static_cast<int32_t>(ld_xcd_piece<RUN>(blockIdx.x, gridDim.x));
-    const GroupDesc gd = group_range(c, tile / kTilesPerGroup);
+    const int shift = c.tiles == kTilesPerGroup ? 6 : 4;
+    static_assert(kTilesPerGroup == 1 << 6 && kTilesPerSmallGroup == 1 << 4, "");
+    const GroupDesc gd = group_range(c, tile >> shift);
     const int lane = ld_lane();
-    const int64_t t = gd.base + static_cast<int64_t>(tile % kTilesPerGroup) * kTile;
+    const int64_t t = gd.base + static_cast<int64_t>(tile & (c.tiles - 1)) * kTile;
     const int64_t seg_lo = gd.lo, seg_hi = gd.hi;
     if (t >= seg_hi) {  // tile slot past the end of the segment
         if (lane == 0) c.cnt[tile] = 0;
@@ -762,32 +771,35 @@ __global__ __launch_bounds__(LD_WAVE) void k_main(const float* __restrict__ g, f
 // stored) for batches of 64 candidates (one per lane, index order, called by all
 // lanes together; `local` is the element's offset inside the tile, `stored` tells
 // that the candidate comes from the slot); then end(u).
-constexpr int kTilesPerWave = kTilesPerGroup / kWaves;
 constexpr int kPerLane = 8;                   // candidates per lane
 
 // Shape of the fast path: ROW lanes per tile (16, 32 or 64, chosen per call from the densities),
-// so a trip serves 64 / ROW tiles of at most ROW * 8 candidates each.
-template <int ROW>
+// so a trip serves 64 / ROW tiles of at most ROW * 8 candidates each; TILES tiles per group.
+template <int ROW, int TILES>
 struct Rows {
+    static constexpr int kRow = ROW, kGroupTiles = TILES;
+    static constexpr int kTilesPerWave = TILES / kWaves;
     static constexpr int kTiles = LD_WAVE / ROW;                 // tiles per trip
     static constexpr uint32_t kFast = ROW * kPerLane;            // candidates a tile may hold
     static constexpr int kTrips = kTilesPerWave / kTiles;
+    static constexpr int kAhead = kTrips < 4 ? kTrips : 4;       // trips requested together
 };
 
 // Slot size as the candidate passes see it: calls that run them with 16 lanes per tile expect at
 // most 128 candidates per tile and always get the minimum slot, a constant.
-template <int ROW>
-__device__ __forceinline__ int32_t slot_of(const Ctx& c) { return ROW == 16 ? kSlotMin : c.slot; }
+template <class RW>
+__device__ __forceinline__ int32_t slot_of(const Ctx& c) { return RW::kRow == 16 ? kSlotMin : c.slot; }
 
 __device__ __forceinline__ int wave_in_group() { return static_cast<int>(threadIdx.x >> 6) & (kWaves - 1); }
 
-// Lane u < kTilesPerWave: the candidate count of the wave's tile u (k_main writes a
+// Lane u < RW::kTilesPerWave: the candidate count of the wave's tile u (k_main writes a
 // count for every tile slot of every group, 0 past the end of a segment). Fetched
 // first, so that it travels together with the group descriptor.
+template <class RW>
 __device__ __forceinline__ uint32_t wave_counts(const Ctx& c, int32_t group) {
     const int lane = ld_lane();
-    const int32_t tile0 = group * kTilesPerGroup + wave_in_group() * kTilesPerWave;
-    return lane < kTilesPerWave ? c.cnt[tile0 + lane] : 0u;
+    const int32_t tile0 = group * RW::kGroupTiles + wave_in_group() * RW::kTilesPerWave;
+    return lane < RW::kTilesPerWave ? c.cnt[tile0 + lane] : 0u;
 }
 
 template <int ROW>
@@ -820,17 +832,15 @@ struct Trip {
 // scattered slots: reading whole slots regardless of the counts made them a third slower). The
 // trips of a batch are requested together.
 struct TripRaw { ld_f32x4 a, b; ld_u32x4 xi; };
-constexpr int kAhead = 4;   // trips requested together
 
-template <bool IDX, int ROW>
+template <bool IDX, class RW>
 __device__ __forceinline__ void trip_issue(const Ctx& c, int32_t tile0, uint32_t mycnt, int q, TripRaw& R) {
-    typedef Rows<ROW> RW;
     const int lane = ld_lane();
-    const int u = RW::kTiles * q + lane / ROW;
+    const int u = RW::kTiles * q + lane / RW::kRow;
     const uint32_t cn = static_cast<uint32_t>(__shfl(static_cast<int>(mycnt), u, LD_WAVE));
     const uint32_t n = cn <= RW::kFast ? cn : 0u;
-    const uint32_t first = static_cast<uint32_t>(lane & (ROW - 1)) * kPerLane;
-    const int64_t at = static_cast<int64_t>(tile0 + u) * slot_of<ROW>(c) + first;
+    const uint32_t first = static_cast<uint32_t>(lane & (RW::kRow - 1)) * kPerLane;
+    const int64_t at = static_cast<int64_t>(tile0 + u) * slot_of<RW>(c) + first;
     R.a = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     R.b = R.a;
     R.xi = ld_u32x4{0u, 0u, 0u, 0u};
@@ -839,14 +849,13 @@ __device__ __forceinline__ void trip_issue(const Ctx& c, int32_t tile0, uint32_t
     if (IDX && first < n) R.xi = *reinterpret_cast<const ld_u32x4*>(c.cidx + at);
 }
 
-template <bool IDX, int ROW>
+template <bool IDX, class RW>
 __device__ __forceinline__ void trip_finish(const TripRaw& R, uint32_t mycnt, int q, Trip& Q) {
-    typedef Rows<ROW> RW;
     const int lane = ld_lane();
-    const int u = RW::kTiles * q + lane / ROW;
+    const int u = RW::kTiles * q + lane / RW::kRow;
     const uint32_t cn = static_cast<uint32_t>(__shfl(static_cast<int>(mycnt), u, LD_WAVE));
     const uint32_t n = cn <= RW::kFast ? cn : 0u;
-    const uint32_t first = static_cast<uint32_t>(lane & (ROW - 1)) * kPerLane;
+    const uint32_t first = static_cast<uint32_t>(lane & (RW::kRow - 1)) * kPerLane;
     Q.v[0] = R.a.x; Q.v[1] = R.a.y; Q.v[2] = R.a.z; Q.v[3] = R.a.w;
     Q.v[4] = R.b.x; Q.v[5] = R.b.y; Q.v[6] = R.b.z; Q.v[7] = R.b.w;
     if (IDX) {
@@ -861,48 +870,48 @@ __device__ __forceinline__ void trip_finish(const TripRaw& R, uint32_t mycnt, in
 
 // Runs body(Q) for every trip of the wave, kAhead trips requested at a time. `first` holds the
 // first batch, requested by the caller as early as it could.
-template <bool IDX, int ROW, class Body>
-__device__ __forceinline__ void for_trips(const Ctx& c, int32_t tile0, uint32_t mycnt, TripRaw (&first)[kAhead],
+template <bool IDX, class RW, class Body>
+__device__ __forceinline__ void for_trips(const Ctx& c, int32_t tile0, uint32_t mycnt, TripRaw (&first)[RW::kAhead],
                                           Body&& body) {
-    static_assert(Rows<ROW>::kTrips % kAhead == 0, "trips come in whole batches");
+    static_assert(RW::kTrips % RW::kAhead == 0, "trips come in whole batches");
 #pragma unroll 1
-    for (int q0 = 0; q0 < Rows<ROW>::kTrips; q0 += kAhead) {
+    for (int q0 = 0; q0 < RW::kTrips; q0 += RW::kAhead) {
         if (q0 > 0) {
 #pragma unroll
-            for (int a = 0; a < kAhead; ++a) trip_issue<IDX, ROW>(c, tile0, mycnt, q0 + a, first[a]);
+            for (int a = 0; a < RW::kAhead; ++a) trip_issue<IDX, RW>(c, tile0, mycnt, q0 + a, first[a]);
         }
 #pragma unroll
-        for (int a = 0; a < kAhead; ++a) {
+        for (int a = 0; a < RW::kAhead; ++a) {
             Trip Q;
-            trip_finish<IDX, ROW>(first[a], mycnt, q0 + a, Q);
+            trip_finish<IDX, RW>(first[a], mycnt, q0 + a, Q);
             body(Q, q0 + a);
         }
     }
 }
 
-template <bool IDX, int ROW>
-__device__ __forceinline__ void first_trips(const Ctx& c, int32_t tile0, uint32_t mycnt, TripRaw (&first)[kAhead]) {
+template <bool IDX, class RW>
+__device__ __forceinline__ void first_trips(const Ctx& c, int32_t tile0, uint32_t mycnt, TripRaw (&first)[RW::kAhead]) {
 #pragma unroll
-    for (int a = 0; a < kAhead; ++a) trip_issue<IDX, ROW>(c, tile0, mycnt, a, first[a]);
+    for (int a = 0; a < RW::kAhead; ++a) trip_issue<IDX, RW>(c, tile0, mycnt, a, first[a]);
 }
 
-template <bool IDX, int ROW, class Begin, class Item, class End>
+template <bool IDX, class RW, class Begin, class Item, class End>
 __device__ __forceinline__ void slow_tiles(const Ctx& c, const float* __restrict__ r, const GroupRange& gr,
                                            int32_t group, uint32_t mycnt, uint32_t tau, Begin&& begin, Item&& item,
                                            End&& end) {
     const int lane = ld_lane();
-    const int tl0 = wave_in_group() * kTilesPerWave;
-    const int32_t tile0 = group * kTilesPerGroup + tl0;
+    const int tl0 = wave_in_group() * RW::kTilesPerWave;
+    const int32_t tile0 = group * RW::kGroupTiles + tl0;
     const int64_t tbase0 = gr.base + static_cast<int64_t>(tl0) * kTile;
     // tiles of the wave that are not served by the fast path
-    uint64_t todo = __ballot(lane < kTilesPerWave && mycnt > Rows<ROW>::kFast);
+    uint64_t todo = __ballot(lane < RW::kTilesPerWave && mycnt > RW::kFast);
     while (todo) {
         const int u = __builtin_ctzll(todo);
         todo &= todo - 1;
         const uint32_t cn = static_cast<uint32_t>(__shfl(static_cast<int>(mycnt), u, LD_WAVE));
         const bool stored = cn != kOverflow;
         const uint32_t total = stored ? cn : static_cast<uint32_t>(kTile);
-        const int64_t slot = static_cast<int64_t>(tile0 + u) * slot_of<ROW>(c);
+        const int64_t slot = static_cast<int64_t>(tile0 + u) * slot_of<RW>(c);
         const int64_t tbase = tbase0 + static_cast<int64_t>(u) * kTile;
         begin(u);
         // kAhead batches of 64 are requested before the first is handed on: a tile read back from
@@ -970,22 +979,22 @@ __device__ __forceinline__ GroupRange seg_range(const Ctx& c, int32_t s) {
 // belong to the same segment are summed in LDS first and added once.
 constexpr int kHistGroups = 4;
 
-template <int ROW>
+template <class RW>
 __global__ __launch_bounds__(kHistGroups * kThreads) void k_hist(const float* __restrict__ r, Ctx c) {
     __shared__ uint32_t lh[kHistGroups][kBins];
     __shared__ int32_t qseg[kHistGroups];
     const int q = threadIdx.x / kThreads, tid = threadIdx.x % kThreads;
     const int32_t group = blockIdx.x * kHistGroups + q;
     const bool inside = group < c.n_group;
-    const int32_t tile0 = group * kTilesPerGroup + wave_in_group() * kTilesPerWave;
+    const int32_t tile0 = group * RW::kGroupTiles + wave_in_group() * RW::kTilesPerWave;
     uint32_t mycnt = 0;
     GroupRange gr;
     gr.k = 0;
-    TripRaw raw[kAhead];
+    TripRaw raw[RW::kAhead];
     if (inside) {
-        mycnt = wave_counts(c, group);
+        mycnt = wave_counts<RW>(c, group);
         gr = group_range(c, group);
-        first_trips<false, ROW>(c, tile0, mycnt, raw);
+        first_trips<false, RW>(c, tile0, mycnt, raw);
     }
     const bool live = inside && gr.k != 0;
     const uint32_t tau = gr.tau, binsh = gr.sh;
@@ -996,7 +1005,7 @@ __global__ __launch_bounds__(kHistGroups * kThreads) void k_hist(const float* __
         // keys above the binned range all land in the top bin (a third of the candidates, more
         // at higher densities): counted in a register, added once per wave
         uint32_t top = 0;
-        for_trips<false, ROW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
+        for_trips<false, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
 #pragma unroll
             for (int j = 0; j < kPerLane; ++j) {
                 if (static_cast<uint32_t>(j) < Q.have) {
@@ -1005,7 +1014,7 @@ __global__ __launch_bounds__(kHistGroups * kThreads) void k_hist(const float* __
                 }
             }
         });
-        slow_tiles<false, ROW>(
+        slow_tiles<false, RW>(
             c, r, gr, group, mycnt, tau, [](int) {},
             [&](bool have, float v, uint32_t, bool) {
                 const uint32_t bin = fine_bin(ld_key(v), tau, binsh);
@@ -1122,13 +1131,13 @@ __device__ __attribute__((noinline)) Unplaced gather_lane_keys(SegState* st, uin
 
 // Per tile: candidates in bins above the threshold bin; the keys inside the bin
 // are gathered per segment.
-template <int ROW>
+template <class RW>
 __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r, Ctx c) {
     __shared__ uint32_t wsum[2][kWaves];
-    const uint32_t mycnt = wave_counts(c, blockIdx.x);
+    const uint32_t mycnt = wave_counts<RW>(c, blockIdx.x);
     const GroupRange gr = group_range(c, blockIdx.x);
-    TripRaw raw[kAhead];
-    first_trips<false, ROW>(c, blockIdx.x * kTilesPerGroup + (threadIdx.x >> 6) * kTilesPerWave, mycnt, raw);
+    TripRaw raw[RW::kAhead];
+    first_trips<false, RW>(c, blockIdx.x * RW::kGroupTiles + (threadIdx.x >> 6) * RW::kTilesPerWave, mycnt, raw);
     SegState* st = c.state + gr.seg;
     const uint32_t mode = st->mode;
     if (gr.k == 0 || mode == kModeFull) return;
@@ -1141,7 +1150,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
     uint32_t* gkey = c.gkey + gather_first(gr.seg, gr.lo);
     int32_t* gtile = c.gtile + gather_first(gr.seg, gr.lo);
     const uint32_t gcap = gather_cap(gr.lo, gr.hi);
-    const int32_t tile0 = blockIdx.x * kTilesPerGroup + w * kTilesPerWave;
+    const int32_t tile0 = blockIdx.x * RW::kGroupTiles + w * RW::kTilesPerWave;
     // Keys of the threshold bin go to the segment's gather list, one reservation per wave and
     // batch. When the list is full (massive ties: millions of equal keys) nothing more is
     // reserved (a wave learns that from its first reservation that comes back beyond the end);
@@ -1151,16 +1160,16 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
     uint32_t part_gt = 0, part_eq = 0;  // fast path: the first lane of a row sums the row's tiles
     uint32_t wave_ties = 0;
     if (ties_mode) {  // the repeated key tau - 1, counted per tile in the residual
-        const int tl0 = w * kTilesPerWave;
+        const int tl0 = w * RW::kTilesPerWave;
 #pragma unroll 1
-        for (int u = 0; u < kTilesPerWave; ++u) {
+        for (int u = 0; u < RW::kTilesPerWave; ++u) {
             const int64_t tbase = gr.base + static_cast<int64_t>(tl0 + u) * kTile;
             const uint32_t t = tbase < gr.hi ? count_key_in_tile(r, tbase, gr.lo, gr.hi, tau - 1u) : 0u;
             if (lane == 0) c.tile_eq[tile0 + u] = t;
             wave_ties += t;
         }
     }
-    for_trips<false, ROW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
+    for_trips<false, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
         uint32_t cnt = 0, in = 0;
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
@@ -1195,10 +1204,10 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
                 }
             }
         }
-        const uint32_t both = row_sum<ROW>(cnt | (n_in << 16));  // a tile holds at most 512 here
+        const uint32_t both = row_sum<RW::kRow>(cnt | (n_in << 16));  // a tile holds at most 512 here
         cnt = both & 0xFFFFu;
         const uint32_t eqc = both >> 16;
-        if ((lane & (ROW - 1)) == 0 && Q.cn <= Rows<ROW>::kFast) {
+        if ((lane & (RW::kRow - 1)) == 0 && Q.cn <= RW::kFast) {
             c.tile_gt[tile0 + Q.u] = cnt;
             if (!ties_mode) c.tile_eq[tile0 + Q.u] = eqc;  // keys in the threshold bin; k_select takes out those that are not T
             part_gt += cnt;
@@ -1207,7 +1216,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
     });
     uint32_t slow_gt = 0, slow_eq = 0, gt = 0, eq = 0;
     int32_t tile_of_item = 0;
-    slow_tiles<false, ROW>(
+    slow_tiles<false, RW>(
         c, r, gr, blockIdx.x, mycnt, tau,
         [&](int u) {
             gt = 0;
@@ -1356,10 +1365,10 @@ __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
             if (key == T) continue;
             const int32_t tile = gtile[p];
             atomicSub(c.tile_eq + tile, 1u);
-            seen |= atomicSub(c.group_eq + tile / kTilesPerGroup, 1u);
+            seen |= atomicSub(c.group_eq + tile / c.tiles, 1u);
             if (key > T) {
                 atomicAdd(c.tile_gt + tile, 1u);
-                seen |= atomicAdd(c.group_gt + tile / kTilesPerGroup, 1u);
+                seen |= atomicAdd(c.group_gt + tile / c.tiles, 1u);
             }
         }
     }
@@ -1397,18 +1406,18 @@ __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
 // stored candidate's key reaches T_est; only where that guess and the selection
 // differ is the residual written again. A segment handed to the full path gets
 // every pre-zeroed position back instead.
-template <int ROW>
+template <class RW>
 __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_t* __restrict__ out_idx,
                                                    float* __restrict__ out_val, Ctx c) {
-    __shared__ uint32_t tile_out[kTilesPerGroup], tile_eqb[kTilesPerGroup], tile_take[kTilesPerGroup];
-    constexpr int kTiles = Rows<ROW>::kTiles;
-    constexpr uint32_t kFast = Rows<ROW>::kFast;
+    __shared__ uint32_t tile_out[RW::kGroupTiles], tile_eqb[RW::kGroupTiles], tile_take[RW::kGroupTiles];
+    constexpr int ROW = RW::kRow, kTiles = RW::kTiles, kTilesPerWave = RW::kTilesPerWave;
+    constexpr uint32_t kFast = RW::kFast;
     __shared__ int32_t stage_i[kWaves][kTiles * kFast];
     __shared__ float stage_v[kWaves][kTiles * kFast];
-    uint32_t mycnt = wave_counts(c, blockIdx.x);
+    uint32_t mycnt = wave_counts<RW>(c, blockIdx.x);
     const GroupRange gr = group_range(c, blockIdx.x);
-    TripRaw raw[kAhead];
-    first_trips<true, ROW>(c, blockIdx.x * kTilesPerGroup + (threadIdx.x >> 6) * kTilesPerWave, mycnt, raw);
+    TripRaw raw[RW::kAhead];
+    first_trips<true, RW>(c, blockIdx.x * RW::kGroupTiles + (threadIdx.x >> 6) * kTilesPerWave, mycnt, raw);
     const SegState* st = c.state + gr.seg;
     if (gr.k == 0) return;
     const uint32_t mode = st->mode;
@@ -1416,16 +1425,16 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
     const int lane = ld_lane();
     const int w = threadIdx.x >> 6;
     const int tl0 = w * kTilesPerWave;
-    const int32_t tile0 = blockIdx.x * kTilesPerGroup + tl0;
+    const int32_t tile0 = blockIdx.x * RW::kGroupTiles + tl0;
     int64_t tbase = 0;
     if (mode == kModeFull) {
-        for_trips<true, ROW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
+        for_trips<true, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
             float* rt = r + gr.base + static_cast<int64_t>(tl0 + Q.u) * kTile;
 #pragma unroll
             for (int j = 0; j < kPerLane; ++j)
                 if (static_cast<uint32_t>(j) < Q.have && ld_key(Q.v[j]) >= test) rt[Q.x[j]] = Q.v[j];
         });
-        slow_tiles<true, ROW>(
+        slow_tiles<true, RW>(
             c, r, gr, blockIdx.x, mycnt, tau,
             [&](int u) { tbase = gr.base + static_cast<int64_t>(tl0 + u) * kTile; },
             [&](bool have, float v, uint32_t local, bool stored) {
@@ -1434,15 +1443,18 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
             [](int) {});
         return;
     }
-    if (w == 0) {  // offsets of the group's 64 tiles
-        const int32_t tile = blockIdx.x * kTilesPerGroup + lane;
-        const bool live = gr.base + static_cast<int64_t>(lane) * kTile < gr.hi;
+    if (w == 0) {  // offsets of the group's tiles
+        const int32_t tile = blockIdx.x * RW::kGroupTiles + lane;
+        const bool live = lane < RW::kGroupTiles && gr.base + static_cast<int64_t>(lane) * kTile < gr.hi;
         const uint32_t cg = live ? c.tile_gt[tile] : 0u, ce = live ? c.tile_eq[tile] : 0u;
         const uint32_t eq_before = c.group_eq[blockIdx.x] + ld_wave_iscan(ce) - ce;
         const uint32_t take = umin(eq_before + ce, m) - umin(eq_before, m);
-        tile_out[lane] = c.group_gt[blockIdx.x] + ld_wave_iscan(cg + take) - (cg + take);
-        tile_eqb[lane] = eq_before;
-        tile_take[lane] = take;
+        const uint32_t out_before = c.group_gt[blockIdx.x] + ld_wave_iscan(cg + take) - (cg + take);
+        if (lane < RW::kGroupTiles) {
+            tile_out[lane] = out_before;
+            tile_eqb[lane] = eq_before;
+            tile_take[lane] = take;
+        }
     }
     __syncthreads();
     // kModeTies: the ties are not among the stored candidates. A tile that keeps some of them is
@@ -1450,7 +1462,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
     // ties come in index order; keys at or above T pass the filter there.
     const uint32_t keep_from = mode == kModeTies ? T : tau;
     if (mode == kModeTies && lane < kTilesPerWave && tile_take[tl0 + lane] > 0) mycnt = kOverflow;
-    for_trips<true, ROW>(c, tile0, mycnt, raw, [&](const Trip& Q, int q) {
+    for_trips<true, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int q) {
         const uint32_t out_tile = tile_out[tl0 + Q.u], eq_tile = tile_eqb[tl0 + Q.u];
         uint32_t gtm = 0, eqm = 0;
 #pragma unroll
@@ -1502,7 +1514,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
     });
     uint32_t run_out = 0;  // records of the segment emitted before this point
     uint32_t run_eq = 0;   // ties seen before this point
-    slow_tiles<true, ROW>(
+    slow_tiles<true, RW>(
         c, r, gr, blockIdx.x, mycnt, keep_from,
         [&](int u) {
             run_out = tile_out[tl0 + u];
@@ -1540,7 +1552,8 @@ __device__ __forceinline__ FullRange full_range(const Ctx& c, int32_t g) {
     FullRange f;
     f.gr = group_range(c, g);
     f.cs = f.gr.base < f.gr.lo ? f.gr.lo : f.gr.base;
-    f.ce = (f.gr.base + kGroup) > f.gr.hi ? f.gr.hi : (f.gr.base + kGroup);
+    const int64_t ge = f.gr.base + static_cast<int64_t>(c.tiles) * kTile;
+    f.ce = ge > f.gr.hi ? f.gr.hi : ge;
     return f;
 }
 
@@ -1748,10 +1761,10 @@ struct Layout {
         fail_groups, fail_count, total;
 };
 
-Layout layout(int32_t n_seg, int64_t n_group, int32_t slot) {
+Layout layout(int32_t n_seg, int64_t n_group, int32_t tiles, int32_t slot) {
     Layout L;
     size_t o = 0;
-    const size_t ns = static_cast<size_t>(n_seg), ng = static_cast<size_t>(n_group), nt = ng * kTilesPerGroup;
+    const size_t ns = static_cast<size_t>(n_seg), ng = static_cast<size_t>(n_group), nt = ng * static_cast<size_t>(tiles);
     auto take = [&](size_t bytes) { const size_t at = o; o += ld_round_up(bytes, 256); return at; };
     L.desc = take(sizeof(SegDesc) * (ns + 1));
     L.gdesc = take(sizeof(GroupDesc) * ng);
@@ -1774,15 +1787,24 @@ Layout layout(int32_t n_seg, int64_t n_group, int32_t slot) {
 }
 
 // Counts groups; returns -1 on a malformed offset table.
-int64_t count_groups(int32_t n_seg, const int64_t* seg_off) {
+int64_t count_groups(int32_t n_seg, const int64_t* seg_off, int32_t tiles) {
     if (n_seg < 0 || (n_seg > 0 && !seg_off)) return -1;
     if (n_seg > 0 && seg_off[0] != 0) return -1;
     int64_t total = 0;
     for (int32_t s = 0; s < n_seg; ++s) {
         if (seg_off[s + 1] < seg_off[s]) return -1;
-        total += groups_of(seg_off[s], seg_off[s + 1]);
+        total += groups_of(seg_off[s], seg_off[s + 1], tiles);
     }
     return total;
+}
+
+// Groups of a segment table, and how many tiles they have (see kSmallGroups); -1 on a malformed table.
+int64_t count_groups(int32_t n_seg, const int64_t* seg_off, int32_t* tiles) {
+    *tiles = kTilesPerGroup;
+    const int64_t large = count_groups(n_seg, seg_off, kTilesPerGroup);
+    if (large < 0 || large >= kSmallGroups) return large;
+    *tiles = kTilesPerSmallGroup;
+    return count_groups(n_seg, seg_off, kTilesPerSmallGroup);
 }
 
 // Slot size that holds the candidates of a tile in all but a few tiles: the candidate threshold
@@ -1810,7 +1832,7 @@ int32_t wanted_slot(int32_t n_seg, const int64_t* seg_off, const int32_t* seg_k,
     return static_cast<int32_t>(slot);
 }
 
-Ctx make_ctx(void* workspace, const Layout& L, int32_t n_seg, int64_t n_group, int32_t slot) {
+Ctx make_ctx(void* workspace, const Layout& L, int32_t n_seg, int64_t n_group, int32_t tiles, int32_t slot) {
     char* ws = static_cast<char*>(workspace);
     Ctx c;
     c.desc = reinterpret_cast<SegDesc*>(ws + L.desc);
@@ -1831,6 +1853,7 @@ Ctx make_ctx(void* workspace, const Layout& L, int32_t n_seg, int64_t n_group, i
     c.n_seg = n_seg;
     c.n_group = static_cast<int32_t>(n_group);
     c.slot = slot;
+    c.tiles = tiles;
     return c;
 }
 
@@ -1842,7 +1865,7 @@ __global__ __launch_bounds__(kThreads) void k_paths(Ctx c, int32_t* __restrict__
     const SegDesc d = c.desc[s], dn = c.desc[s + 1];
     uint32_t over = 0;
     if (d.k > 0) {
-        const int64_t t0 = static_cast<int64_t>(d.group0) * kTilesPerGroup, t1 = static_cast<int64_t>(dn.group0) * kTilesPerGroup;
+        const int64_t t0 = static_cast<int64_t>(d.group0) * c.tiles, t1 = static_cast<int64_t>(dn.group0) * c.tiles;
         for (int64_t t = t0 + threadIdx.x; t < t1; t += kThreads) over += c.cnt[t] == kOverflow;
     }
     uint32_t total;
@@ -1857,7 +1880,7 @@ __global__ __launch_bounds__(kThreads) void k_paths(Ctx c, int32_t* __restrict__
 
 // Packs the segment table for k_prep's arguments; false when it has too many segments or too
 // many distinct (length, k) pairs.
-bool pack_table(int32_t n_seg, const int64_t* seg_off, const int32_t* seg_k, PackedTable& pt) {
+bool pack_table(int32_t n_seg, const int64_t* seg_off, const int32_t* seg_k, int32_t tiles, PackedTable& pt) {
     pt.n_seg = 0;
     if (n_seg > kDictSegs) return false;
     int used = 0, last = 0;
@@ -1884,7 +1907,7 @@ bool pack_table(int32_t n_seg, const int64_t* seg_off, const int32_t* seg_k, Pac
         pt.group0[b] = static_cast<uint32_t>(group0);
         for (int32_t s = s0; s < n_seg && s < s0 + LD_WAVE; ++s) {
             out0 += seg_k[s];
-            group0 += groups_of(seg_off[s], seg_off[s + 1]);
+            group0 += groups_of(seg_off[s], seg_off[s + 1], tiles);
         }
     }
     for (int d = used; d < kDictMax; ++d) pt.len[d] = pt.k[d] = 0;
@@ -1914,18 +1937,37 @@ int32_t full_grid_limit() {
     return v;
 }
 
+// The passes over the candidates.
+template <class RW>
+ld_status candidate_passes(const Ctx& c, float* residual, int32_t* out_idx, float* out_val, hipStream_t st) {
+    const dim3 groups(static_cast<uint32_t>(c.n_group)), segments(static_cast<uint32_t>(c.n_seg)), block(kThreads);
+    const dim3 hgroups(static_cast<uint32_t>((c.n_group + kHistGroups - 1) / kHistGroups));
+    k_hist<RW><<<hgroups, dim3(kHistGroups * kThreads), 0, st>>>(residual, c);
+    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+    k_bin<<<segments, block, 0, st>>>(c);
+    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+    k_gather<RW><<<groups, block, 0, st>>>(residual, c);
+    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+    k_select<<<segments, block, 0, st>>>(c);
+    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+    k_emit<RW><<<groups, block, 0, st>>>(residual, out_idx, out_val, c);
+    return ld_launch_status();
+}
+
 }  // namespace
 
 extern "C" size_t ld_compress_topk_workspace(int32_t n_seg, const int64_t* seg_off) {
-    const int64_t n_group = count_groups(n_seg, seg_off);
+    int32_t tiles;
+    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
     if (n_group < 0) return 0;
-    return layout(n_seg, n_group, kSlotMin).total;
+    return layout(n_seg, n_group, tiles, kSlotMin).total;
 }
 
 extern "C" size_t ld_compress_topk_workspace_for(int32_t n_seg, const int64_t* seg_off, const int32_t* seg_k) {
-    const int64_t n_group = count_groups(n_seg, seg_off);
+    int32_t tiles;
+    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
     if (n_group < 0 || (n_seg > 0 && !seg_k)) return 0;
-    return layout(n_seg, n_group, wanted_slot(n_seg, seg_off, seg_k)).total;
+    return layout(n_seg, n_group, tiles, wanted_slot(n_seg, seg_off, seg_k)).total;
 }
 
 extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residual, const int64_t* seg_off,
@@ -1935,8 +1977,9 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     if (n_seg < 0 || (strategy != LD_COMPRESS_AUTO && strategy != LD_COMPRESS_FULL)) return LD_ERR_RANGE;
     if (n_seg == 0) return LD_OK;
     if (!seg_off || !seg_k) return LD_ERR_NULL;
-    const int64_t n_group = count_groups(n_seg, seg_off);
-    if (n_group < 0 || n_group > INT32_MAX / kTilesPerGroup) return LD_ERR_RANGE;
+    int32_t tiles;
+    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
+    if (n_group < 0 || n_group > INT32_MAX / tiles) return LD_ERR_RANGE;
     const int64_t n = seg_off[n_seg];
     if (n > INT32_MAX) return LD_ERR_RANGE;
     int64_t K = 0;
@@ -1950,22 +1993,22 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     if (!ld_aligned(grad, 16) || !ld_aligned(residual, 16) || !ld_aligned(out_idx, 4) ||
         !ld_aligned(out_val, 4))
         return LD_ERR_ALIGN;
-    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < layout(n_seg, n_group, kSlotMin).total)
+    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < layout(n_seg, n_group, tiles, kSlotMin).total)
         return LD_ERR_WORKSPACE;
     // the largest slot, up to the one this call's densities ask for, that the workspace holds
     int32_t per_tile = 0;
     int32_t slot = wanted_slot(n_seg, seg_off, seg_k, &per_tile);
-    while (slot > kSlotMin && layout(n_seg, n_group, slot).total > workspace_bytes) slot -= 64;
-    const Layout L = layout(n_seg, n_group, slot);
+    while (slot > kSlotMin && layout(n_seg, n_group, tiles, slot).total > workspace_bytes) slot -= 64;
+    const Layout L = layout(n_seg, n_group, tiles, slot);
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const Ctx c = make_ctx(workspace, L, n_seg, n_group, slot);
+    const Ctx c = make_ctx(workspace, L, n_seg, n_group, tiles, slot);
 
     ld_begin_call();
     // The segment table travels as kernel arguments: packed into k_prep's own when it has few
     // distinct (length, k) pairs, else through k_upload launches of kSegPerLaunch segments each.
     PackedTable pt;
-    if (!pack_table(n_seg, seg_off, seg_k, pt)) {
+    if (!pack_table(n_seg, seg_off, seg_k, tiles, pt)) {
         int64_t out0 = 0;
         int32_t group0 = 0;
         for (int32_t s0 = 0; s0 < n_seg; s0 += kSegPerLaunch) {
@@ -1983,22 +2026,20 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
             }
             for (int32_t j = 0; j < cnt; ++j) {
                 out0 += seg_k[s0 + j];
-                group0 += groups_of(seg_off[s0 + j], seg_off[s0 + j + 1]);
+                group0 += groups_of(seg_off[s0 + j], seg_off[s0 + j + 1], tiles);
             }
             k_upload<<<dim3(1), dim3(512), 0, st>>>(ub, c);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
         }
     }
-    const dim3 block(kThreads);
     const dim3 sgrid(static_cast<uint32_t>(n_seg));
     const int32_t no_estimate = strategy == LD_COMPRESS_FULL ? 1 : 0;
     if (n_seg <= kPrepWide) k_prep<1024><<<sgrid, dim3(1024), 0, st>>>(grad, residual, c, no_estimate, pt);
     else k_prep<512><<<sgrid, dim3(512), 0, st>>>(grad, residual, c, no_estimate, pt);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     if (n_group == 0) return LD_OK;
-    const dim3 grid(static_cast<uint32_t>(n_group));
-    const dim3 mgrid(static_cast<uint32_t>(n_group * kTilesPerGroup)), mblock(LD_WAVE);
-    const bool runs = n_group >= kMainRunGroups;
+    const dim3 mgrid(static_cast<uint32_t>(n_group * tiles)), mblock(LD_WAVE);
+    const bool runs = n_group * tiles >= kMainRunTiles;
     if (slot == kSlotMin) {
         if (runs) k_main<true, 16><<<mgrid, mblock, 0, st>>>(grad, residual, c);
         else k_main<true, 1><<<mgrid, mblock, 0, st>>>(grad, residual, c);
@@ -2008,31 +2049,25 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     }
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     if (K == 0) return LD_OK;
-    const dim3 hgrid(static_cast<uint32_t>((n_group + kHistGroups - 1) / kHistGroups)), hblock(kHistGroups * kThreads);
     // lanes per tile in the candidate passes: enough for the candidates a tile is expected to hold
     const int row = (per_tile <= 128 && slot == kSlotMin) ? 16 : (per_tile <= 256 ? 32 : 64);  // 16 implies the minimum slot
-    if (row == 16) k_hist<16><<<hgrid, hblock, 0, st>>>(residual, c);
-    else if (row == 32) k_hist<32><<<hgrid, hblock, 0, st>>>(residual, c);
-    else k_hist<64><<<hgrid, hblock, 0, st>>>(residual, c);
-    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    k_bin<<<sgrid, block, 0, st>>>(c);
-    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    if (row == 16) k_gather<16><<<grid, block, 0, st>>>(residual, c);
-    else if (row == 32) k_gather<32><<<grid, block, 0, st>>>(residual, c);
-    else k_gather<64><<<grid, block, 0, st>>>(residual, c);
-    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    k_select<<<sgrid, block, 0, st>>>(c);
-    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    if (row == 16) k_emit<16><<<grid, block, 0, st>>>(residual, out_idx, out_val, c);
-    else if (row == 32) k_emit<32><<<grid, block, 0, st>>>(residual, out_idx, out_val, c);
-    else k_emit<64><<<grid, block, 0, st>>>(residual, out_idx, out_val, c);
-    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+    ld_status passes;
+    if (tiles == kTilesPerGroup) {
+        if (row == 16) passes = candidate_passes<Rows<16, kTilesPerGroup>>(c, residual, out_idx, out_val, st);
+        else if (row == 32) passes = candidate_passes<Rows<32, kTilesPerGroup>>(c, residual, out_idx, out_val, st);
+        else passes = candidate_passes<Rows<64, kTilesPerGroup>>(c, residual, out_idx, out_val, st);
+    } else {
+        if (row == 16) passes = candidate_passes<Rows<16, kTilesPerSmallGroup>>(c, residual, out_idx, out_val, st);
+        else if (row == 32) passes = candidate_passes<Rows<32, kTilesPerSmallGroup>>(c, residual, out_idx, out_val, st);
+        else passes = candidate_passes<Rows<64, kTilesPerSmallGroup>>(c, residual, out_idx, out_val, st);
+    }
+    if (passes != LD_OK) return passes;
     // segments handed to the full path (normally none: the launch returns at once). Its grid must be
     // resident as a whole (the phases hand over through a barrier across it).
     const int32_t resident = full_grid_limit();
     if (resident <= 0) return LD_ERR_HIP;
     const dim3 fgrid(static_cast<uint32_t>(n_group < resident ? n_group : resident));
-    k_full<<<fgrid, block, 0, st>>>(residual, out_idx, out_val, c);
+    k_full<<<fgrid, dim3(kThreads), 0, st>>>(residual, out_idx, out_val, c);
     return ld_launch_status();
 }
 
@@ -2042,12 +2077,13 @@ extern "C" ld_status ld_compress_topk_paths(const void* workspace, size_t worksp
     if (n_seg < 0) return LD_ERR_RANGE;
     if (n_seg == 0) return LD_OK;
     if (!seg_off || !paths) return LD_ERR_NULL;
-    const int64_t n_group = count_groups(n_seg, seg_off);
-    if (n_group < 0 || n_group > INT32_MAX / kTilesPerGroup) return LD_ERR_RANGE;
+    int32_t tiles;
+    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
+    if (n_group < 0 || n_group > INT32_MAX / tiles) return LD_ERR_RANGE;
     if (!ld_aligned(paths, 4) || !ld_aligned(overflowed_tiles, 4)) return LD_ERR_ALIGN;
-    const Layout L = layout(n_seg, n_group, kSlotMin);  // the slot size only moves the candidate arrays
+    const Layout L = layout(n_seg, n_group, tiles, kSlotMin);  // the slot size only moves the candidate arrays
     if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < L.total) return LD_ERR_WORKSPACE;
-    const Ctx c = make_ctx(const_cast<void*>(workspace), L, n_seg, n_group, kSlotMin);
+    const Ctx c = make_ctx(const_cast<void*>(workspace), L, n_seg, n_group, tiles, kSlotMin);
     ld_begin_call();
     k_paths<<<dim3(static_cast<uint32_t>(n_seg)), dim3(kThreads), 0, static_cast<hipStream_t>(stream)>>>(
         c, paths, overflowed_tiles);

@@ -106,6 +106,21 @@ def test_compress_thousands_of_small_segments():
     check_compress(g, r, off, k2, tag="3000 segments random k")
 
 
+@pytest.mark.parametrize("n_seg", [255, 257, 511, 512, 513])
+def test_compress_segment_counts_around_the_launch_rules(n_seg):
+    # either side of the segment counts where k_prep's workgroups and the groups' size change (every
+    # segment is at least one group), with segments around the sample size and the tile edges
+    rs = np.random.RandomState(n_seg)
+    sizes = list(rs.randint(1, 3000, n_seg))
+    for at, size in ((0, 16383), (1, 16384), (2, 16385), (3, 4097), (4, 65537), (n_seg - 1, 70001)):
+        sizes[at] = size
+    off, k = synth.seg_offsets(sizes), synth.seg_topk(sizes, 1, 50)
+    n = int(off[-1])
+    g = (rs.standard_t(3, n) * 1e-3).astype(np.float32)
+    r = (rs.standard_normal(n) * 1e-3).astype(np.float32)
+    check_compress(g, r, off, k, tag=f"n_seg={n_seg}")
+
+
 @pytest.mark.parametrize("n", [150001])
 def test_compress_adversarial(n):
     off = np.array([0, 1000, 70000, n], np.int64)
