@@ -6,14 +6,14 @@
 // p = fl32(lr*val); w[idx] = fl32(w[idx] - p).
 //
 // Two strategies with identical results:
-//  * sweep   - one streaming pass over w.  A wave owns an 8192-element sub-tile
-//              held in LDS, pulls the records of every diff that fall into it and
+//  * sweep   - one streaming pass over w.  A wave owns a sub-tile of 2048 to 8192
+//              elements held in LDS, pulls the records of every diff that fall into it and
 //              applies them diff after diff.  LDS operations of one wave execute
 //              in issue order, so the cross-diff order on an element needs no
 //              barrier.  Where a diff's records for the sub-tile start is not
 //              looked up in a table: a small kernel finds the record range of
-//              every chunk of 6 sub-tiles by binary search, the wave
-//              interpolates inside its chunk, loads a 128-record window a little
+//              every 49152-element chunk by binary search, the wave
+//              interpolates inside its chunk, loads a window of 64 or 128 records a little
 //              before the guess and keeps the records that fall into its
 //              sub-tile.  The guess is checked (the window must begin before the
 //              sub-tile does, and end after it); a miss costs a binary search
@@ -27,13 +27,13 @@
 
 namespace {
 
-constexpr int kSub = 8192;                 // elements per wave sub-tile (32 KB of LDS, 5 waves per CU)
-constexpr int kChunkSubs = 6;              // sub-tiles per chunk of the range table
-static_assert(static_cast<int64_t>(kSub) * kChunkSubs == kChunk, "sub-tiles must tile a chunk");
+constexpr int kSub = 8192;                 // elements of the largest sub-tile of a sweep (32 KB of LDS, 5 waves per CU)
+constexpr int64_t kFewSubs = 80000000;     // elements below which such sub-tiles are too few
 constexpr int kMargin = 24;                // records the window starts before the interpolated position
 constexpr int kSweepGroup = kTableMax;     // diffs per sweep: a lane keeps the chunk ranges of two of them
 // Windows loaded ahead, as <diffs per batch, 64-record windows per diff>: 10 x 2 for the usual
-// densities (~80 records per diff and sub-tile at 1 %), 20 x 1 for long windows of very sparse
+// densities (~80 records per diff and 8192 elements at 1 %), 10 x 1 where a sub-tile's records fit one
+// window, 20 x 1 for long windows of very sparse
 // diffs (a handful of records each: half as many rounds of loads, each a memory round trip).
 
 __device__ __forceinline__ void apply_record(float* tile, int32_t local, float val, float lr) {
@@ -42,16 +42,22 @@ __device__ __forceinline__ void apply_record(float* tile, int32_t local, float v
 }
 
 // N records per lane of ONE diff (so no two of the wave's 64 N records name the same element):
-// those inside [lo, hi) are all read before any is written - one round trip to LDS instead of N.
-template <int N>
+// all are read before any is written - one round trip to LDS instead of N. Records outside the
+// sub-tile land on the spare word behind it (an unsigned minimum instead of two comparisons and a
+// branch around every access: these waves are bound by the instructions they issue).
+template <int SUB, int N>
 __device__ __forceinline__ void apply_records(float* tile, const int32_t (&i)[N], const float (&v)[N], int32_t lo,
-                                              int32_t hi, float lr) {
+                                              float lr) {
     float cur[N];
+    uint32_t at[N];
 #pragma unroll
-    for (int u = 0; u < N; ++u) cur[u] = (i[u] >= lo && i[u] < hi) ? tile[i[u] - lo] : 0.0f;
+    for (int u = 0; u < N; ++u) {
+        const uint32_t e = static_cast<uint32_t>(i[u]) - static_cast<uint32_t>(lo);
+        at[u] = e < static_cast<uint32_t>(SUB) ? e : static_cast<uint32_t>(SUB);
+        cur[u] = tile[at[u]];
+    }
 #pragma unroll
-    for (int u = 0; u < N; ++u)
-        if (i[u] >= lo && i[u] < hi) tile[i[u] - lo] = __fsub_rn(cur[u], __fmul_rn(lr, v[u]));   // rounded product: never fused
+    for (int u = 0; u < N; ++u) tile[at[u]] = __fsub_rn(cur[u], __fmul_rn(lr, v[u]));   // rounded product: never fused
 }
 
 // Applies the records of one diff at positions [p, end) that fall into [lo, hi), up to the
@@ -60,6 +66,7 @@ __device__ __forceinline__ void apply_records(float* tile, const int32_t (&i)[N]
 // for memory once per batch.
 constexpr int kDeep = 8;
 
+template <int SUB>
 __device__ __forceinline__ void apply_from(float* tile, const int32_t* __restrict__ idx,
                                            const float* __restrict__ val, int32_t p, int32_t end,
                                            int32_t lo, int32_t hi, float lr, int lane) {
@@ -73,8 +80,8 @@ __device__ __forceinline__ void apply_from(float* tile, const int32_t* __restric
             i[u] = have ? idx[q] : INT_MAX;
             v[u] = have ? val[q] : 0.0f;
         }
-        apply_records(tile, i, v, lo, hi, lr);
-        if (__ballot(i[kDeep - 1] >= hi)) break;
+        apply_records<SUB>(tile, i, v, lo, lr);
+        if (__builtin_amdgcn_readlane(i[kDeep - 1], LD_WAVE - 1) >= hi) break;  // ascending
     }
 }
 
@@ -120,31 +127,33 @@ __device__ __forceinline__ void load_batch(Batch<PRE, WIN>& X, const DiffTable& 
     }
 }
 
-template <int PRE, int WIN, int SETS>
+template <int SUB, int PRE, int WIN, int SETS>
 __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, int64_t n, int32_t nchunk,
                                                          DiffTable tb, int32_t W,
                                                          const int32_t* __restrict__ ctab, float lr) {
-    __shared__ float tile[kSub];
+    constexpr int kParts = static_cast<int>(kChunk / SUB);  // sub-tiles per chunk of the range table
+    static_assert(static_cast<int64_t>(SUB) * kParts == kChunk, "sub-tiles must tile a chunk");
+    __shared__ float tile[SUB + 4];  // and the spare word
     const int lane = threadIdx.x;
     // consecutive workgroups go to different XCDs (each with an L2 of its own): give every XCD one
     // contiguous eighth of w, so that the overlapping record windows of neighbouring sub-tiles hit its L2
     const int64_t per = (static_cast<int64_t>(gridDim.x) + 7) / 8;
     const int64_t sub = static_cast<int64_t>(blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (sub * kSub >= n) return;
-    const int64_t lo64 = sub * kSub;
-    const int32_t len = static_cast<int32_t>((n - lo64) < kSub ? (n - lo64) : kSub);
+    if (sub * SUB >= n) return;
+    const int64_t lo64 = sub * SUB;
+    const int32_t len = static_cast<int32_t>((n - lo64) < SUB ? (n - lo64) : SUB);
     const int32_t lo = static_cast<int32_t>(lo64), hi = lo + len;  // n <= INT_MAX
-    const bool full = (len == kSub);
+    const bool full = (len == SUB);
 
-    ld_f32x4 x[kSub / 4 / LD_WAVE];
+    ld_f32x4 x[SUB / 4 / LD_WAVE];
     if (full) {
         const ld_f32x4* src = reinterpret_cast<const ld_f32x4*>(w + lo64);
 #pragma unroll
-        for (int j = 0; j < kSub / 4 / LD_WAVE; ++j) x[j] = ld_nt_load(src + j * LD_WAVE + lane);
+        for (int j = 0; j < SUB / 4 / LD_WAVE; ++j) x[j] = ld_nt_load(src + j * LD_WAVE + lane);
     }
 
     // lane t: where the records of diffs t and t + 64 lie in this chunk, and the guesses for this sub-tile
-    const int32_t chunk = static_cast<int32_t>(sub / kChunkSubs), part = static_cast<int32_t>(sub % kChunkSubs);
+    const int32_t chunk = static_cast<int32_t>(sub / kParts), part = static_cast<int32_t>(sub % kParts);
     Ranges<SETS> R;
 #pragma unroll
     for (int h = 0; h < SETS; ++h) {
@@ -155,7 +164,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
             R.c0[h] = row[0];
             R.c1[h] = row[1];
         }
-        R.start[h] = R.c0[h] + ((R.c1[h] - R.c0[h]) * part) / kChunkSubs - kMargin;
+        R.start[h] = R.c0[h] + ((R.c1[h] - R.c0[h]) * part) / kParts - kMargin;
         if (R.start[h] < R.c0[h]) R.start[h] = R.c0[h];
     }
 
@@ -166,7 +175,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
 
     if (full) {
 #pragma unroll
-        for (int j = 0; j < kSub / 4 / LD_WAVE; ++j) reinterpret_cast<ld_f32x4*>(tile)[j * LD_WAVE + lane] = x[j];
+        for (int j = 0; j < SUB / 4 / LD_WAVE; ++j) reinterpret_cast<ld_f32x4*>(tile)[j * LD_WAVE + lane] = x[j];
     } else {
         for (int32_t e = lane; e < len; e += LD_WAVE) tile[e] = w[lo64 + e];
     }
@@ -183,13 +192,13 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
                     // the window begins before the sub-tile's records do; ascending indices: a record
                     // at or beyond hi (or the padding past the chunk's end) in the last window says
                     // that nothing of this sub-tile follows
-                    apply_records(tile, A.ri[g], A.rv[g], lo, hi, lr);
-                    const bool more = !__ballot(A.ri[g][WIN - 1] >= hi);
-                    if (more) apply_from(tile, tb.idx[t], tb.val[t], A.s[g] + WIN * LD_WAVE, A.e[g], lo, hi, lr, lane);
+                    apply_records<SUB>(tile, A.ri[g], A.rv[g], lo, lr);
+                    const bool more = __builtin_amdgcn_readlane(A.ri[g][WIN - 1], LD_WAVE - 1) < hi;
+                    if (more) apply_from<SUB>(tile, tb.idx[t], tb.val[t], A.s[g] + WIN * LD_WAVE, A.e[g], lo, hi, lr, lane);
                 } else {
                     // guess too late: find the first record of the sub-tile inside the chunk
                     const int32_t p = lower_bound_idx(tb.idx[t], A.b[g], A.s[g], lo);
-                    apply_from(tile, tb.idx[t], tb.val[t], p, A.e[g], lo, hi, lr, lane);
+                    apply_from<SUB>(tile, tb.idx[t], tb.val[t], p, A.e[g], lo, hi, lr, lane);
                 }
             }
             __builtin_amdgcn_wave_barrier();  // keep diff g's LDS traffic ahead of diff g+1's
@@ -200,7 +209,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
     if (full) {
         ld_f32x4* dst = reinterpret_cast<ld_f32x4*>(w + lo64);
 #pragma unroll
-        for (int j = 0; j < kSub / 4 / LD_WAVE; ++j)
+        for (int j = 0; j < SUB / 4 / LD_WAVE; ++j)
             ld_nt_store(reinterpret_cast<const ld_f32x4*>(tile)[j * LD_WAVE + lane], dst + j * LD_WAVE + lane);
     } else {
         for (int32_t e = lane; e < len; e += LD_WAVE) w[lo64 + e] = tile[e];
@@ -492,7 +501,14 @@ __global__ __launch_bounds__(256) void k_merge_scatter(float* __restrict__ w,
     w[i] = __fsub_rn(w[i], p);
 }
 
-int32_t sub_tiles(int64_t n) { return static_cast<int32_t>((n + kSub - 1) / kSub); }
+template <int SUB, int PRE, int WIN>
+void launch_sweep(float* w, int64_t n, int32_t nchunk, const DiffTable& tb, int32_t W, const int32_t* ctab, float lr,
+                  hipStream_t s) {
+    const int64_t nsub = (n + SUB - 1) / SUB;
+    const dim3 grid(static_cast<uint32_t>((nsub + 7) / 8 * 8)), wave(LD_WAVE);
+    if (W <= LD_WAVE) k_merge_sweep<SUB, PRE, WIN, 1><<<grid, wave, 0, s>>>(w, n, nchunk, tb, W, ctab, lr);
+    else k_merge_sweep<SUB, PRE, WIN, 2><<<grid, wave, 0, s>>>(w, n, nchunk, tb, W, ctab, lr);
+}
 
 }  // namespace
 
@@ -561,7 +577,7 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
 
     if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < chunk_table_bytes(n, W))
         return LD_ERR_WORKSPACE;
-    const int32_t nsub = sub_tiles(n), nchunk = chunks(n);
+    const int32_t nchunk = chunks(n);
     int32_t* ctab = static_cast<int32_t*>(workspace);
     for (int32_t g0 = 0; g0 < W; g0 += kSweepGroup) {
         const int32_t gw = (W - g0) < kSweepGroup ? (W - g0) : kSweepGroup;
@@ -576,7 +592,7 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
             if (live && K[g0 + t] > most) most = K[g0 + t];
             if (live && !(ld_aligned(idx[g0 + t], 16) && ld_aligned(val[g0 + t], 16))) aligned16 = false;
         }
-        const dim3 grid((nsub + 7) / 8 * 8), wave(LD_WAVE);
+        const dim3 wave(LD_WAVE);
         const bool thin = thin_group(n, gw, most);
         if (thin && aligned16 && workspace_bytes >= sub_table_bytes(n, gw)) {  // a lane per diff (else: the sweep below)
             const int32_t tsub = static_cast<int32_t>((n + kThinSub - 1) / kThinSub);
@@ -590,14 +606,19 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
         }
         launch_chunks(tb, gw, n, nchunk, ctab, s);
         if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-        // at most ~16 records per diff and sub-tile: one window per diff is plenty
-        if (gw <= LD_WAVE) {
-            if (thin) k_merge_sweep<20, 1, 1><<<grid, wave, 0, s>>>(w, n, nchunk, tb, gw, ctab, lr);
-            else k_merge_sweep<10, 2, 1><<<grid, wave, 0, s>>>(w, n, nchunk, tb, gw, ctab, lr);
-        } else {
-            if (thin) k_merge_sweep<20, 1, 2><<<grid, wave, 0, s>>>(w, n, nchunk, tb, gw, ctab, lr);
-            else k_merge_sweep<10, 2, 2><<<grid, wave, 0, s>>>(w, n, nchunk, tb, gw, ctab, lr);
-        }
+        // Sub-tile and record windows by the records of the densest diff in 8192 elements and by how many
+        // sub-tiles there are. 2048 elements (20 waves per CU instead of 5) while the sub-tiles of 8192 make
+        // only a few rounds of the chip, with one window per diff where its records fit: 25.6 M elements,
+        // 50 diffs of 1 %: 124 -> 96 us, 20 diffs of 2 %: 118 -> 73; the same at 100 M. Beyond, a wave with
+        // more records per diff than its windows hold fetches the rest by itself: smaller sub-tiles up to
+        // where the windows fit again (400 M, 10 diffs of 2 %: 850 / 673 / 693 us with 8192 / 4096 / 2048,
+        // of 4 %: 1007 / 915 / 836); else 8192, fewest windows (GPT-2 XL: 2555 / 2634 / 2746).
+        const int64_t dense = most * kSub / n;
+        if (thin) launch_sweep<kSub, 20, 1>(w, n, nchunk, tb, gw, ctab, lr, s);
+        else if (n < kFewSubs && dense <= 100) launch_sweep<2048, 10, 1>(w, n, nchunk, tb, gw, ctab, lr, s);
+        else if (n < kFewSubs || dense > 200) launch_sweep<2048, 10, 2>(w, n, nchunk, tb, gw, ctab, lr, s);
+        else if (dense > 100) launch_sweep<4096, 10, 2>(w, n, nchunk, tb, gw, ctab, lr, s);
+        else launch_sweep<kSub, 10, 2>(w, n, nchunk, tb, gw, ctab, lr, s);
         if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     }
     return LD_OK;

@@ -327,6 +327,27 @@ def test_merge_ragged_and_dense_windows(n, W, dens):
         np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(ref), err_msg=f"strategy {strategy}")
 
 
+@pytest.mark.parametrize("n", [2047, 2049, 49152, 100003])
+@pytest.mark.parametrize("per8192", [2, 99, 101, 201, 900])
+@pytest.mark.parametrize("W", [3, 66])
+def test_merge_sweep_shapes(n, per8192, W):
+    # the sub-tiles and record windows that a sweep picks by its densest diff, at the edges of sub-tiles and
+    # chunks, with one and two sets of diffs per lane and records bunched at one end in every other diff
+    rs = np.random.RandomState(n + per8192 + W)
+    K = max(1, n * per8192 // 8192)
+    idxs = []
+    for t in range(W):
+        hi = n if t % 2 == 0 else max(K, n // 3)
+        idxs.append(np.sort(rs.choice(hi, K, replace=False)).astype(np.int32))
+    vals = [(rs.standard_normal(K) * 1e-2).astype(np.float32) for _ in range(W)]
+    w0 = synth.base_weights(n).numpy()
+    w = to_gpu(w0)
+    ws = torch.empty(int(ld.load().ld_merge_sparse_workspace(n, W, None)), dtype=torch.uint8, device=DEV)
+    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, ws, strategy=ld.LD_MERGE_SWEEP)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
 @pytest.mark.parametrize("case", ["random", "identical", "pairs", "clustered", "short_then_long"])
 def test_merge_thin_long_windows(case):
     # Long windows of very sparse diffs run a lane per diff: every lane holds its diff's records for
