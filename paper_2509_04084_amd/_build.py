@@ -13,6 +13,31 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+MARSHAL = os.path.join(PKG, "_marshal.so")
+
+
+def build_marshal(force: bool = True) -> str:
+    """Compiles the binding's argument marshalling (a CPython module against torch's headers); returns its path."""
+    src = os.path.join(CSRC, "ld_marshal.cpp")
+    if not force and os.path.exists(MARSHAL) and os.path.getmtime(MARSHAL) >= os.path.getmtime(src):
+        return MARSHAL
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    base = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += ["-isystem" + d for d in cpp_extension.include_paths()] + ["-I", sysconfig.get_paths()["include"]]
+    cmd += [src, "-o", MARSHAL + ".tmp", "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        print(res.stdout)
+        print(res.stderr)
+        raise RuntimeError("g++ failed building _marshal.so")
+    os.replace(MARSHAL + ".tmp", MARSHAL)
+    return MARSHAL
+
+
 def build_library(force: bool = True, verbose: bool = False) -> str:
     """Compiles every HIP source into liblowdiff.so; returns its path."""
     srcs = [os.path.join(CSRC, s) for s in SOURCES]

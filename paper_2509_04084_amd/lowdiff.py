@@ -23,6 +23,7 @@ LD_MAX_WINDOW = 4096
 LD_MAX_ADAM_WINDOW = 64
 
 _lib = None
+_gather = None  # _marshal.gather (csrc/ld_marshal.cpp)
 
 
 class LowDiffError(RuntimeError):
@@ -37,11 +38,15 @@ def library_path() -> str:
 
 def load() -> ctypes.CDLL:
     """Loads liblowdiff.so (building it only if no built library is present)."""
-    global _lib
+    global _lib, _gather
     if _lib is not None:
         return _lib
     if not os.path.exists(_build.LIB):
         _build.build_library(force=True)
+    if not os.path.exists(_build.MARSHAL):
+        _build.build_marshal(force=True)
+    from . import _marshal
+    _gather = _marshal.gather
     lib = ctypes.CDLL(_build.LIB)
     vp, i32, i64, f32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
     lib.ld_status_string.argtypes = [i32]
@@ -126,6 +131,32 @@ def _same_device(*tensors) -> None:
     devs = {t.device for t in tensors if t is not None}
     if len(devs) > 1:
         raise ValueError(f"tensors lie on different devices: {sorted(map(str, devs))}")
+
+
+class _Table:
+    """Addresses, sizes and device of a list of tensors, for a call that takes host arrays of pointers."""
+
+    def __init__(self, tensors: Sequence[torch.Tensor], dtype, pinned: bool = False):
+        self.tensors, self.dtype, self.pinned = tensors, dtype, pinned
+        self.ptr, self.sizes, self.device, self.bad = _gather(tensors, dtype, pinned)
+
+    def numel(self) -> np.ndarray:
+        return np.frombuffer(self.sizes, dtype=np.int64) if self.sizes else np.zeros(0, np.int64)
+
+    def checked(self, name: str) -> bytes:
+        """The addresses; raises if a tensor cannot be handed to the library."""
+        if self.bad >= 0:
+            (_dev_or_pinned if self.pinned else _dev)(self.tensors[self.bad], self.dtype, name)
+            raise TypeError(f"{name}: expected a contiguous {self.dtype} tensor on the GPU")
+        return self.ptr
+
+
+def _one_device(first: torch.Tensor, others: Sequence, *tables: _Table) -> None:
+    """_same_device over single tensors and the tensors of tables."""
+    at = first.get_device()
+    if at >= 0 and all(t is None or t.get_device() == at for t in others) and all(b.device == at or not b.sizes for b in tables):
+        return
+    _same_device(first, *others, *(t for b in tables for t in b.tensors))
 
 
 def _record(t: torch.Tensor, *streams) -> torch.Tensor:
@@ -235,16 +266,15 @@ def ld_snapshot_layer(grad_bf16: torch.Tensor, snap_bf16: torch.Tensor, stream=N
 
 
 def ld_snapshot_layers(srcs: Sequence[torch.Tensor], dsts: Sequence[torch.Tensor], stream=None) -> None:
+    lib = load()
     n = len(srcs)
     if len(dsts) != n:
         raise ValueError("srcs and dsts differ in length")
-    sp = (ctypes.c_void_p * max(n, 1))(*[_dev(t, torch.bfloat16, "src").value or 0 for t in srcs])
-    dp = (ctypes.c_void_p * max(n, 1))(*[_dev_or_pinned(t, torch.bfloat16, "dst").value or 0 for t in dsts])
-    for a, b in zip(srcs, dsts):
-        if a.numel() != b.numel():
-            raise ValueError("snapshot source and destination differ in size")
-    ne = np.array([t.numel() for t in srcs], dtype=np.int64)
-    st = load().ld_snapshot_layers(sp, dp, _hp(ne), n, _stream(stream))
+    s, d = _Table(srcs, torch.bfloat16), _Table(dsts, torch.bfloat16, pinned=True)
+    sp, dp = s.checked("src"), d.checked("dst")
+    if s.sizes != d.sizes:
+        raise ValueError("snapshot source and destination differ in size")
+    st = lib.ld_snapshot_layers(sp, dp, s.sizes, n, _stream(stream))
     _check("ld_snapshot_layers", st)
 
 
@@ -261,13 +291,12 @@ def ld_merge_sparse(w: torch.Tensor, idx: Sequence[torch.Tensor], val: Sequence[
     W = len(idx)
     if len(val) != W:
         raise ValueError("idx and val differ in length")
-    K = np.array([t.numel() for t in idx], dtype=np.int64)
-    for a, b in zip(idx, val):
-        if a.numel() != b.numel():
-            raise ValueError("idx[t] and val[t] differ in size")
-    _same_device(w, workspace, *idx, *val)
-    ip = (ctypes.c_void_p * max(W, 1))(*[_dev(t, torch.int32, "idx").value or 0 for t in idx])
-    vp = (ctypes.c_void_p * max(W, 1))(*[_dev(t, torch.float32, "val").value or 0 for t in val])
+    gi, gv = _Table(idx, torch.int32), _Table(val, torch.float32)
+    if gi.sizes != gv.sizes:
+        raise ValueError("idx[t] and val[t] differ in size")
+    K = gi.numel()
+    _one_device(w, (workspace,), gi, gv)
+    ip, vp = gi.checked("idx"), gv.checked("val")
     if workspace is None:
         workspace = _scratch(lib.ld_merge_sparse_workspace(w.numel(), W, _hp(K)), w.device, stream)
     st = lib.ld_merge_sparse_strategy(_dev(w, torch.float32, "w"), w.numel(), ip, vp, _hp(K), W,
@@ -284,16 +313,16 @@ def ld_merge_sparse_static(w: torch.Tensor, idx: Sequence[torch.Tensor], val: Se
                            stream=None) -> None:
     """ld_merge_sparse without a workspace and without any allocation (the chunk table lies in a
     device array of the library); refuses windows beyond ld_merge_sparse_static_limit()."""
+    lib = load()
     W = len(idx)
     if len(val) != W:
         raise ValueError("idx and val differ in length")
-    K = np.array([t.numel() for t in idx], dtype=np.int64)
-    for a, b in zip(idx, val):
-        if a.numel() != b.numel():
-            raise ValueError("idx[t] and val[t] differ in size")
-    ip = (ctypes.c_void_p * max(W, 1))(*[_dev(t, torch.int32, "idx").value or 0 for t in idx])
-    vp = (ctypes.c_void_p * max(W, 1))(*[_dev(t, torch.float32, "val").value or 0 for t in val])
-    st = load().ld_merge_sparse_static(_dev(w, torch.float32, "w"), w.numel(), ip, vp, _hp(K), W,
+    gi, gv = _Table(idx, torch.int32), _Table(val, torch.float32)
+    if gi.sizes != gv.sizes:
+        raise ValueError("idx[t] and val[t] differ in size")
+    K = gi.numel()
+    ip, vp = gi.checked("idx"), gv.checked("val")
+    st = lib.ld_merge_sparse_static(_dev(w, torch.float32, "w"), w.numel(), ip, vp, _hp(K), W,
                                        ctypes.c_float(lr), _stream(stream))
     _check("ld_merge_sparse_static", st)
 
@@ -301,15 +330,16 @@ def ld_merge_sparse_static(w: torch.Tensor, idx: Sequence[torch.Tensor], val: Se
 def ld_merge_dense_adam(w: torch.Tensor, m: torch.Tensor, v: torch.Tensor, grads_bf16: Sequence[torch.Tensor],
                         step0: int, lr: float, beta1: float, beta2: float, eps: float, stream=None) -> None:
     """Replays the bf16 gradients as Adam steps step0+1.. onto (w, m, v), in place."""
+    lib = load()
     W = len(grads_bf16)
     if m.numel() != w.numel() or v.numel() != w.numel():
         raise ValueError("w, m, v differ in size")
-    for g in grads_bf16:
-        if g.numel() != w.numel():
-            raise ValueError("gradient and parameter sizes differ")
-    _same_device(w, m, v, *grads_bf16)
-    gp = (ctypes.c_void_p * max(W, 1))(*[_dev(t, torch.bfloat16, "grad").value or 0 for t in grads_bf16])
-    st = load().ld_merge_dense_adam(_dev(w, torch.float32, "w"), _dev(m, torch.float32, "m"),
+    g = _Table(grads_bf16, torch.bfloat16)
+    if np.any(g.numel() != w.numel()):
+        raise ValueError("gradient and parameter sizes differ")
+    _one_device(w, (m, v), g)
+    gp = g.checked("grad")
+    st = lib.ld_merge_dense_adam(_dev(w, torch.float32, "w"), _dev(m, torch.float32, "m"),
                                     _dev(v, torch.float32, "v"), w.numel(), gp, W, int(step0),
                                     ctypes.c_float(lr), ctypes.c_float(beta1), ctypes.c_float(beta2),
                                     ctypes.c_float(eps), _stream(stream))
@@ -386,13 +416,12 @@ def ld_merge_sparse_adam(w: torch.Tensor, m: torch.Tensor, v: torch.Tensor, idx:
         raise ValueError("idx and val differ in length")
     if m.numel() != w.numel() or v.numel() != w.numel():
         raise ValueError("w, m, v differ in size")
-    K = np.array([t.numel() for t in idx], dtype=np.int64)
-    for a, b in zip(idx, val):
-        if a.numel() != b.numel():
-            raise ValueError("idx[t] and val[t] differ in size")
-    _same_device(w, m, v, workspace, *idx, *val)
-    ip = (ctypes.c_void_p * max(W, 1))(*[_dev(t, torch.int32, "idx").value or 0 for t in idx])
-    vp = (ctypes.c_void_p * max(W, 1))(*[_dev(t, torch.float32, "val").value or 0 for t in val])
+    gi, gv = _Table(idx, torch.int32), _Table(val, torch.float32)
+    if gi.sizes != gv.sizes:
+        raise ValueError("idx[t] and val[t] differ in size")
+    K = gi.numel()
+    _one_device(w, (m, v, workspace), gi, gv)
+    ip, vp = gi.checked("idx"), gv.checked("val")
     if workspace is None:
         workspace = _scratch(lib.ld_merge_sparse_adam_workspace(w.numel(), W, _hp(K)), w.device, stream)
     st = lib.ld_merge_sparse_adam(_dev(w, torch.float32, "w"), _dev(m, torch.float32, "m"),
@@ -415,10 +444,10 @@ def ld_combine_sparse(idx: Sequence[torch.Tensor], val: Sequence[torch.Tensor], 
     N = len(idx)
     if len(val) != N:
         raise ValueError("idx and val differ in length")
-    for a, b in zip(idx, val):
-        if a.numel() != b.numel():
-            raise ValueError("idx[r] and val[r] differ in size")
-    K = np.array([t.numel() for t in idx], dtype=np.int64)
+    gi, gv = _Table(idx, torch.int32), _Table(val, torch.float32)
+    if gi.sizes != gv.sizes:
+        raise ValueError("idx[r] and val[r] differ in size")
+    K = gi.numel()
     dev = idx[0].device if N else torch.device("cuda", torch.cuda.current_device())
     total = int(K.sum())
     if out_idx is None:
@@ -428,9 +457,8 @@ def ld_combine_sparse(idx: Sequence[torch.Tensor], val: Sequence[torch.Tensor], 
     if out_count is None:
         out_count = _record(torch.empty(1, dtype=torch.int64, device=dev), stream)
     cap = min(out_idx.numel(), out_val.numel())
-    _same_device(out_idx, out_val, out_count, workspace, *idx, *val)
-    ip = (ctypes.c_void_p * max(N, 1))(*[_dev(t, torch.int32, "idx").value or 0 for t in idx])
-    vp = (ctypes.c_void_p * max(N, 1))(*[_dev(t, torch.float32, "val").value or 0 for t in val])
+    _one_device(out_idx, (out_val, out_count, workspace), gi, gv)
+    ip, vp = gi.checked("idx"), gv.checked("val")
     if workspace is None:
         workspace = _scratch(lib.ld_combine_sparse_workspace(int(n), N), dev, stream)
     st = lib.ld_combine_sparse(ip, vp, _hp(K), N, int(n), ctypes.c_float(scale),
