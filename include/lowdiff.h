@@ -191,7 +191,7 @@ ld_status ld_snapshot_layers(const void* const* src, void* const* dst, const int
  *   workspace  dev, 256-byte aligned, ld_merge_sparse_workspace() bytes. With K = NULL
  *              the query gives the minimum (the call fails with less); with K it
  *              gives what the window's shape asks for, which is more for long windows
- *              of very sparse diffs (they then run a lane per diff instead of as
+ *              of sparse diffs (they then run a lane per record instead of as
  *              ordinary sweeps; same result, less time)
  * Errors: LD_ERR_NULL, LD_ERR_RANGE, LD_ERR_ALIGN, LD_ERR_WORKSPACE, LD_ERR_HIP.
  */

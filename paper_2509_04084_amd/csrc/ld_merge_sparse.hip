@@ -36,11 +36,6 @@ constexpr int kSweepGroup = kTableMax;     // diffs per sweep: a lane keeps the 
 // window, 20 x 1 for long windows of very sparse
 // diffs (a handful of records each: half as many rounds of loads, each a memory round trip).
 
-__device__ __forceinline__ void apply_record(float* tile, int32_t local, float val, float lr) {
-    const float p = __fmul_rn(lr, val);        // rounded product: never fused
-    tile[local] = __fsub_rn(tile[local], p);
-}
-
 // N records per lane of ONE diff (so no two of the wave's 64 N records name the same element):
 // all are read before any is written - one round trip to LDS instead of N. Records outside the
 // sub-tile land on the spare word behind it (an unsigned minimum instead of two comparisons and a
@@ -216,37 +211,28 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
     }
 }
 
-// ------------------------------------------------------- thin long windows: a lane per diff
+// ------------------------------------------------------- thin long windows: a lane per record
 //
-// A long window of very sparse diffs (config 3: 100 diffs of 0.1 %, eight records per diff and
-// sub-tile) leaves the sweep above with a wave's 64 lanes serving eight records at a time, a
-// hundred times in a row. Here the roles are turned round: lane t holds ALL the records of diff t
-// (and t + 64) that fall into the wave's sub-tile and the diffs are applied side by side. Where
+// A long window of very sparse diffs (config 3: 100 diffs of 0.1 %, eight records per diff and 8192
+// elements) leaves the sweep above with a wave's 64 lanes serving eight records at a time, a
+// hundred times in a row. Here the records of all diffs that fall into the wave's sub-tile form one
+// list in diff order, and the lanes take 64 of it at a time. Where
 // exactly a diff's records for a sub-tile begin comes from a table of its own (k_subtab: one
-// streaming pass over the index arrays, which are small when diffs are this sparse).
+// streaming pass over the index arrays, which are small when diffs are this sparse); the diff that a
+// list position belongs to comes from a binary search over the diffs' running counts in LDS.
 //
-// Order: an element that only one diff of the window touches can be updated at any time. Elements
-// touched by several diffs are found first (two bitmaps in LDS: seen, seen again) and their
-// records are held back; these are then applied in rounds: every pending record bids for its
-// element's slot of a small owner table with (diff, element) as the key, the smallest key wins the
-// slot (atomic minimum), applies its update and leaves; so the updates of one element go through
-// in diff order whatever else shares the slot.
-#ifndef LD_THIN_SUB
-#define LD_THIN_SUB 4096
-#endif
-#ifndef LD_THIN_CAP
-#define LD_THIN_CAP 24
-#endif
-#ifndef LD_THIN_OWNER
-#define LD_THIN_OWNER 128
-#endif
-constexpr int kThinSub = LD_THIN_SUB;    // elements of a wave's sub-tile in this kernel
-constexpr int kThinCap = LD_THIN_CAP;    // records of one diff in one sub-tile that a lane can hold
-constexpr int kThinSlots = (kThinCap + 3 + 3) / 4 * 4;  // register slots: the records come in aligned blocks of four
-constexpr int kConfLane = 4;             // held-back records a lane can keep
-constexpr int kBitWords = kThinSub / 32;
-constexpr int kOwner = LD_THIN_OWNER;    // slots of the owner table
-static_assert(kThinSub % (4 * LD_WAVE) == 0 && kThinSub % 32 == 0 && kThinSub <= 8192, "whole rows of 16-byte accesses; 13 bits of element in a key");
+// Order: rows of 64 go through one after another. Inside a row, every pending record bids for
+// its element's slot of a small owner table with its lane, the smallest lane wins the
+// slot (atomic minimum), applies its update and leaves; lanes are in diff order, so the updates of one
+// element go through in diff order whatever else shares the slot, and any number of records is served.
+//
+// Bound by the instructions and LDS round trips per row (two to three bids each), next the tile's 16 KB
+// of LDS, which leave eight waves per CU. 124 M elements, 100 diffs of 0.1 %: 296 -> 235 us against a lane per
+// DIFF, whose slots were mostly empty; sub-tiles of 2048 / 8192 elements: 272 / 267 us, 1024 owner slots: 239.
+constexpr int kThinSub = 4096;     // elements of a wave's sub-tile in this kernel
+constexpr int kThinAhead = 8;      // rows of 64 records requested together
+constexpr int kOwner = 256;        // slots of the owner table
+static_assert(kThinSub % (4 * LD_WAVE) == 0 && (kOwner & (kOwner - 1)) == 0, "whole rows of 16-byte accesses");
 
 // tab[t * (nsub + 1) + s] = number of records of diff t with idx < s * kThinSub, s = 0 .. nsub.
 // A thread looks at four consecutive records (one 16-byte load; the arrays of this path are
@@ -280,22 +266,15 @@ __global__ __launch_bounds__(256) void k_subtab(DiffTable tb, int32_t nsub, int3
     }
 }
 
-__device__ __forceinline__ int32_t wave_max(int32_t x) {
-#pragma unroll
-    for (int d = LD_WAVE / 2; d > 0; d >>= 1) {
-        const int32_t y = __shfl_xor(x, d, LD_WAVE);
-        x = y > x ? y : x;
-    }
-    return x;
-}
-
-template <int SETS>
 __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, int64_t n, int32_t nsub,
                                                         DiffTable tb, int32_t W, const int32_t* __restrict__ tab,
                                                         float lr) {
     __shared__ float tile[kThinSub];
-    __shared__ uint32_t seen[kBitWords], multi[kBitWords];
+    __shared__ uint32_t before[kTableMax];                   // records of the sub-tile before diff t's
+    __shared__ const int32_t* ibase[kTableMax];              // diff t's record with list position k: ibase[t][k]
+    __shared__ const float* vbase[kTableMax];
     __shared__ uint32_t owner[kOwner];
+    constexpr int kSets = kTableMax / LD_WAVE;
     const int lane = threadIdx.x;
     const int64_t per = (static_cast<int64_t>(gridDim.x) + 7) / 8;   // each XCD walks one contiguous eighth of w
     const int64_t sub = static_cast<int64_t>(blockIdx.x % 8) * per + blockIdx.x / 8;
@@ -305,177 +284,93 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
     const int32_t lo = static_cast<int32_t>(lo64);
     const bool full = (len == kThinSub);
 
+    // lane t: the records of diffs t and t + 64 inside this sub-tile
+    int32_t p0[kSets];
+    uint32_t cnt[kSets];
+#pragma unroll
+    for (int h = 0; h < kSets; ++h) {
+        const int t = h * LD_WAVE + lane;
+        p0[h] = 0;
+        cnt[h] = 0;
+        if (t < W) {
+            const int32_t* row = tab + static_cast<int64_t>(t) * (nsub + 1) + sub;
+            p0[h] = row[0];
+            cnt[h] = static_cast<uint32_t>(row[1] - p0[h]);
+        }
+    }
     ld_f32x4 x[kThinSub / 4 / LD_WAVE];
     if (full) {
         const ld_f32x4* src = reinterpret_cast<const ld_f32x4*>(w + lo64);
 #pragma unroll
         for (int j = 0; j < kThinSub / 4 / LD_WAVE; ++j) x[j] = ld_nt_load(src + j * LD_WAVE + lane);
     }
-    // lane t: the records of diffs t (and t + 64) inside this sub-tile
-    int32_t p0[SETS], cnt[SETS];
-    const int32_t* ip[SETS];
-    const float* vp[SETS];
-    int32_t most = 0, slots = 0;
+    uint32_t total = 0;
 #pragma unroll
-    for (int h = 0; h < SETS; ++h) {
+    for (int h = 0; h < kSets; ++h) {
         const int t = h * LD_WAVE + lane;
-        p0[h] = cnt[h] = 0;
-        ip[h] = nullptr;
-        vp[h] = nullptr;
-        if (t < W) {
-            const int32_t* row = tab + static_cast<int64_t>(t) * (nsub + 1) + sub;
-            p0[h] = row[0];
-            cnt[h] = row[1] - p0[h];
-            ip[h] = tb.idx[t];
-            vp[h] = tb.val[t];
-        }
-        most = cnt[h] > most ? cnt[h] : most;
-        const int32_t used = (p0[h] & 3) + cnt[h];   // slots of 16-byte blocks the lane's records reach into
-        slots = used > slots ? used : slots;
-    }
-    most = wave_max(most);
-    slots = wave_max(slots);
-    if (full) {
-#pragma unroll
-        for (int j = 0; j < kThinSub / 4 / LD_WAVE; ++j) reinterpret_cast<ld_f32x4*>(tile)[j * LD_WAVE + lane] = x[j];
-    } else {
-        for (int32_t e = lane; e < len; e += LD_WAVE) tile[e] = w[lo64 + e];
+        const uint32_t inc = ld_wave_iscan(cnt[h]);
+        const uint32_t first = total + inc - cnt[h];
+        before[t] = first;
+        // only positions first .. first + cnt - 1 are ever looked up through these
+        ibase[t] = t < W ? tb.idx[t] + (static_cast<int64_t>(p0[h]) - first) : nullptr;
+        vbase[t] = t < W ? tb.val[t] + (static_cast<int64_t>(p0[h]) - first) : nullptr;
+        total += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), LD_WAVE - 1));
     }
     for (int q = lane; q < kOwner; q += LD_WAVE) owner[q] = 0xFFFFFFFFu;
     __syncthreads();  // one wave: orders the fills before what follows
 
-    if (most > kThinCap) {
-        // some diff has more records here than a lane holds: diff after diff, the lanes sharing
-        // the records of one diff (no two of them touch the same element)
-        for (int t = 0; t < W; ++t) {
-            const int h = t / LD_WAVE, l = t % LD_WAVE;
-            const int32_t b = __shfl(SETS == 1 ? p0[0] : (h == 0 ? p0[0] : p0[SETS - 1]), l, LD_WAVE);
-            const int32_t c = __shfl(SETS == 1 ? cnt[0] : (h == 0 ? cnt[0] : cnt[SETS - 1]), l, LD_WAVE);
-            const int32_t* __restrict__ di = tb.idx[t];
-            const float* __restrict__ dv = tb.val[t];
-            for (int32_t q = lane; q < c; q += LD_WAVE) {
-                const int32_t e = di[b + q] - lo;
-                if (static_cast<uint32_t>(e) < static_cast<uint32_t>(len)) apply_record(tile, e, dv[b + q], lr);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    } else {
-        // The lane's records, fetched as whole 16-byte blocks of four (the index and value arrays
-        // of this path are 16-byte aligned): slot j holds record (p0 & ~3) + j; slots before p0 or
-        // past the lane's count are marked empty (a negative index). (Single 4-byte loads, one
-        // record per lane and instruction, pulled a cache line per lane and record from L2.) Both
-        // sets of diffs are requested before the first is worked on.
-        int32_t ri_[SETS][kThinSlots];
-        float rp_[SETS][kThinSlots];
+    // The list's records in diff order, 64 at a time, kThinAhead rows requested together. Lane and row give
+    // the position; the diff it belongs to is the last one with `before` at or below it.
+    bool staged = false;
+#pragma unroll 1
+    for (uint32_t k0 = 0; k0 < total || !staged; k0 += kThinAhead * LD_WAVE) {
+        int32_t ri[kThinAhead];
+        float rv[kThinAhead];
 #pragma unroll
-        for (int h = 0; h < SETS; ++h) {
-            const int32_t k0 = p0[h] & ~3, sh = p0[h] - k0;
+        for (int u = 0; u < kThinAhead; ++u) {
+            const uint32_t k = k0 + u * LD_WAVE + lane;
+            ri[u] = 0;
+            rv[u] = 0.0f;
+            if (k0 + u * LD_WAVE < total) {  // uniform
+                int t = 0;
 #pragma unroll
-            for (int v = 0; v < kThinSlots / 4; ++v) {
-                ld_u32x4 qi = {0u, 0u, 0u, 0u};
-                ld_f32x4 qv = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (4 * v < slots) {  // wave-uniform
-                    if (4 * v < sh + cnt[h]) {
-                        qi = *reinterpret_cast<const ld_u32x4*>(ip[h] + k0 + 4 * v);
-                        qv = *reinterpret_cast<const ld_f32x4*>(vp[h] + k0 + 4 * v);
-                    }
-                }
-                const uint32_t ei[4] = {qi.x, qi.y, qi.z, qi.w};
-                const float ev[4] = {qv.x, qv.y, qv.z, qv.w};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int j = 4 * v + c;
-                    const int32_t e = static_cast<int32_t>(ei[c]) - lo;
-                    const bool have = j >= sh && j < sh + cnt[h] && static_cast<uint32_t>(e) < static_cast<uint32_t>(len);
-                    ri_[h][j] = have ? e : -1;  // ascending, in-range indices never fail the last test
-                    rp_[h][j] = ev[c];
+                for (int step = kTableMax / 2; step > 0; step >>= 1) t += before[t + step] <= k ? step : 0;
+                if (k < total) {
+                    ri[u] = ibase[t][k];
+                    rv[u] = vbase[t][k];
                 }
             }
         }
+        if (!staged) {  // the tile arrives while the first records travel
+            staged = true;
+            if (full) {
 #pragma unroll
-        for (int h = 0; h < SETS; ++h) {
-            const uint32_t t = static_cast<uint32_t>(h * LD_WAVE + lane);
-            const int32_t (&ri)[kThinSlots] = ri_[h];
-            const float (&rp)[kThinSlots] = rp_[h];
-            for (int q = lane; q < kBitWords; q += LD_WAVE) {
-                seen[q] = 0;
-                multi[q] = 0;
-            }
-            __builtin_amdgcn_wave_barrier();
-            // which elements do several diffs of this set touch?
-            uint32_t again = 0;
-#pragma unroll
-            for (int i = 0; i < kThinSlots; ++i) {
-                if (i < slots && ri[i] >= 0) {
-                    const uint32_t bit = 1u << (ri[i] & 31);
-                    if (atomicOr(&seen[ri[i] >> 5], bit) & bit) again |= 1u << i;
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < kThinSlots; ++i)
-                if ((again >> i) & 1u) atomicOr(&multi[ri[i] >> 5], 1u << (ri[i] & 31));
-            __builtin_amdgcn_wave_barrier();
-            // elements of one diff only: updated now; the others are held back
-            int32_t ce[kConfLane];
-            float cp[kConfLane];
-            int nc = 0;
-#pragma unroll
-            for (int q = 0; q < kConfLane; ++q) { ce[q] = 0; cp[q] = 0.0f; }
-#pragma unroll
-            for (int i = 0; i < kThinSlots; ++i) {
-                if (i < slots && ri[i] >= 0) {
-                    const float p = __fmul_rn(lr, rp[i]);   // rounded product: never fused
-                    if ((multi[ri[i] >> 5] >> (ri[i] & 31)) & 1u) {
-#pragma unroll
-                        for (int q = 0; q < kConfLane; ++q)
-                            if (nc == q) { ce[q] = ri[i]; cp[q] = p; }
-                        ++nc;
-                    } else {
-                        tile[ri[i]] = __fsub_rn(tile[ri[i]], p);
-                    }
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (__ballot(nc > kConfLane)) {
-                // more held back than a lane keeps (heavily overlapping diffs): the lanes take turns in
-                // diff order, each applying what it holds back
-                uint64_t turn = __ballot(nc > 0);
-                while (turn) {
-                    const int l = __builtin_ctzll(turn);
-                    turn &= turn - 1;
-                    if (lane == l) {
-#pragma unroll
-                        for (int i = 0; i < kThinSlots; ++i) {
-                            if (i < slots && ri[i] >= 0 && ((multi[ri[i] >> 5] >> (ri[i] & 31)) & 1u))
-                                tile[ri[i]] = __fsub_rn(tile[ri[i]], __fmul_rn(lr, rp[i]));
-                        }
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
+                for (int j = 0; j < kThinSub / 4 / LD_WAVE; ++j) reinterpret_cast<ld_f32x4*>(tile)[j * LD_WAVE + lane] = x[j];
             } else {
-                uint32_t pend = (1u << nc) - 1u;
-                while (__ballot(pend != 0)) {
+                for (int32_t e = lane; e < len; e += LD_WAVE) tile[e] = w[lo64 + e];
+            }
+            __syncthreads();
+        }
 #pragma unroll
-                    for (int q = 0; q < kConfLane; ++q)
-                        if ((pend >> q) & 1u) atomicMin(&owner[ce[q] & (kOwner - 1)], (t << 13) | static_cast<uint32_t>(ce[q]));
+        for (int u = 0; u < kThinAhead; ++u) {
+            if (k0 + u * LD_WAVE < total) {  // uniform
+                const uint32_t e = static_cast<uint32_t>(ri[u] - lo);
+                const float p = __fmul_rn(lr, rv[u]);   // rounded product: never fused
+                uint32_t* own = owner + (e & (kOwner - 1));
+                bool pend = k0 + u * LD_WAVE + lane < total && e < static_cast<uint32_t>(len);
+                while (__ballot(pend)) {
+                    if (pend) atomicMin(own, static_cast<uint32_t>(lane));
                     __builtin_amdgcn_wave_barrier();
-                    uint32_t won = 0;
-#pragma unroll
-                    for (int q = 0; q < kConfLane; ++q) {
-                        if (((pend >> q) & 1u) && owner[ce[q] & (kOwner - 1)] == ((t << 13) | static_cast<uint32_t>(ce[q]))) {
-                            tile[ce[q]] = __fsub_rn(tile[ce[q]], cp[q]);
-                            won |= 1u << q;
-                        }
+                    const bool won = pend && *own == static_cast<uint32_t>(lane);
+                    __builtin_amdgcn_wave_barrier();
+                    if (won) {
+                        tile[e] = __fsub_rn(tile[e], p);
+                        *own = 0xFFFFFFFFu;
                     }
                     __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int q = 0; q < kConfLane; ++q)
-                        if ((won >> q) & 1u) owner[ce[q] & (kOwner - 1)] = 0xFFFFFFFFu;
-                    __builtin_amdgcn_wave_barrier();
-                    pend &= ~won;
+                    pend = pend && !won;
                 }
             }
-            __builtin_amdgcn_wave_barrier();
         }
     }
 
@@ -514,9 +409,11 @@ void launch_sweep(float* w, int64_t n, int32_t nchunk, const DiffTable& tb, int3
 
 namespace {
 
-// A group of `gw` diffs whose largest holds `most` records is "thin" when a diff brings at most ~16
-// records to a sub-tile and the group is long: it then runs a lane per diff (k_merge_thin).
-bool thin_group(int64_t n, int32_t gw, int64_t most) { return gw > 10 && most * kSub <= 16 * n; }
+// A group of `gw` diffs whose largest holds `most` records is "thin" when a diff brings at most ~48
+// records to 8192 elements and the group is long: it then runs a lane per record (k_merge_thin). Measured,
+// us with the sweep / a lane per record: 20 diffs of 0.25 % on 100 M elements 164 / 148, 60 of 0.5 % on 25 M
+// 113 / 84, 40 of 0.5 % on 100 M 240 / 228; 20 of 1 % on 100 M 199 / 225.
+bool thin_group(int64_t n, int32_t gw, int64_t most) { return gw > 10 && most * kSub <= 48 * n; }
 
 size_t chunk_table_bytes(int64_t n, int32_t W) {
     const int64_t group = W < kSweepGroup ? W : kSweepGroup;
@@ -594,13 +491,12 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
         }
         const dim3 wave(LD_WAVE);
         const bool thin = thin_group(n, gw, most);
-        if (thin && aligned16 && workspace_bytes >= sub_table_bytes(n, gw)) {  // a lane per diff (else: the sweep below)
+        if (thin && aligned16 && workspace_bytes >= sub_table_bytes(n, gw)) {  // a lane per record (else: the sweep below)
             const int32_t tsub = static_cast<int32_t>((n + kThinSub - 1) / kThinSub);
             const dim3 tgrid((tsub + 7) / 8 * 8);
             k_subtab<<<dim3(static_cast<uint32_t>(most / (256 * kSubtabPer) + 1), gw), dim3(256), 0, s>>>(tb, tsub, ctab);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-            if (gw <= LD_WAVE) k_merge_thin<1><<<tgrid, wave, 0, s>>>(w, n, tsub, tb, gw, ctab, lr);
-            else k_merge_thin<2><<<tgrid, wave, 0, s>>>(w, n, tsub, tb, gw, ctab, lr);
+            k_merge_thin<<<tgrid, wave, 0, s>>>(w, n, tsub, tb, gw, ctab, lr);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
             continue;
         }
@@ -614,7 +510,7 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
         // where the windows fit again (400 M, 10 diffs of 2 %: 850 / 673 / 693 us with 8192 / 4096 / 2048,
         // of 4 %: 1007 / 915 / 836); else 8192, fewest windows (GPT-2 XL: 2555 / 2634 / 2746).
         const int64_t dense = most * kSub / n;
-        if (thin) launch_sweep<kSub, 20, 1>(w, n, nchunk, tb, gw, ctab, lr, s);
+        if (gw > 10 && dense <= 16) launch_sweep<kSub, 20, 1>(w, n, nchunk, tb, gw, ctab, lr, s);
         else if (n < kFewSubs && dense <= 100) launch_sweep<2048, 10, 1>(w, n, nchunk, tb, gw, ctab, lr, s);
         else if (n < kFewSubs || dense > 200) launch_sweep<2048, 10, 2>(w, n, nchunk, tb, gw, ctab, lr, s);
         else if (dense > 100) launch_sweep<4096, 10, 2>(w, n, nchunk, tb, gw, ctab, lr, s);

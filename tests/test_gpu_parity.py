@@ -348,9 +348,29 @@ def test_merge_sweep_shapes(n, per8192, W):
     np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
 
 
+@pytest.mark.parametrize("n", [100, 4095, 4097, 100003])
+@pytest.mark.parametrize("per8192", [3, 47, 49])
+@pytest.mark.parametrize("W", [11, 64, 65, 128, 131])
+def test_merge_lane_per_record_edges(n, per8192, W):
+    # the window rule's edge, ragged last sub-tiles, one and two diffs per lane, a second group of diffs, empty
+    # diffs among them, and the same elements in neighbouring diffs
+    rs = np.random.RandomState(n + per8192 + W)
+    K = max(1, n * per8192 // 8192)
+    idxs = [np.sort(rs.choice(n, 0 if t % 7 == 3 else K, replace=False)).astype(np.int32) for t in range(W)]
+    for t in range(5, W, 9):
+        idxs[t] = idxs[t - 1].copy()
+    vals = [(rs.standard_normal(i.size) * 1e-2).astype(np.float32) for i in idxs]
+    w0 = synth.base_weights(n).numpy()
+    w = to_gpu(w0)
+    ws = torch.empty(ld.ld_merge_sparse_workspace(n, [i.size for i in idxs]), dtype=torch.uint8, device=DEV)
+    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, ws, strategy=ld.LD_MERGE_SWEEP)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
 @pytest.mark.parametrize("case", ["random", "identical", "pairs", "clustered", "short_then_long"])
 def test_merge_thin_long_windows(case):
-    # Long windows of very sparse diffs run a lane per diff: every lane holds its diff's records for
+    # Long windows of sparse diffs run a lane per record: the lanes take the records of a
     # the wave's sub-tile, elements touched by several diffs are held back and applied in diff order.
     #   random          a few elements shared by two or three diffs
     #   identical       every diff records the same positions: every record is held back, more per
