@@ -370,8 +370,8 @@ def test_merge_lane_per_record_edges(n, per8192, W):
 
 @pytest.mark.parametrize("case", ["random", "identical", "pairs", "clustered", "short_then_long"])
 def test_merge_thin_long_windows(case):
-    # Long windows of sparse diffs run a lane per record: the lanes take the records of a
-    # the wave's sub-tile, elements touched by several diffs are held back and applied in diff order.
+    # Long windows of sparse diffs run a lane per record: the records of a sub-tile go through in rows of
+    # 64, elements touched by several diffs of a row are applied in diff order.
     #   random          a few elements shared by two or three diffs
     #   identical       every diff records the same positions: every record is held back, more per
     #                   lane than it keeps (the lanes take turns)
