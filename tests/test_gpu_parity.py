@@ -106,7 +106,7 @@ def test_compress_thousands_of_small_segments():
     check_compress(g, r, off, k2, tag="3000 segments random k")
 
 
-@pytest.mark.parametrize("n_seg", [255, 257, 511, 512, 513])
+@pytest.mark.parametrize("n_seg", [229, 230, 231, 255, 257, 511, 512, 513])
 def test_compress_segment_counts_around_the_launch_rules(n_seg):
     # either side of the segment counts where k_prep's workgroups and the groups' size change (every
     # segment is at least one group), with segments around the sample size and the tile edges
