@@ -24,6 +24,7 @@
 #include <atomic>
 
 #include "ld_sparse_common.h"
+#include "ld_thin.h"
 
 namespace {
 
@@ -257,11 +258,9 @@ __global__ __launch_bounds__(256) void k_subtab(DiffTable tb, int32_t nsub, int3
     for (int c = 0; c < kSubtabPer; ++c) {
         const int32_t j = j0 + c;
         if (j > K) break;
-        int32_t b = j == K ? nsub : v[c] / kThinSub;
-        if (a >= nsub) a = nsub - 1;   // an index outside [0, n) breaks the caller's contract: stay inside the row
-        if (a < -1) a = -1;
-        if (b > nsub) b = nsub;
-        for (int32_t s = a + 1; s <= b; ++s) row[s] = j;
+        const int32_t b = j == K ? nsub : v[c] / kThinSub;
+        const LdThinEntries fill = ld_thin_entries(a, b, nsub);
+        for (int32_t s = fill.first; s <= fill.last; ++s) row[s] = j;
         a = b;
     }
 }
@@ -295,7 +294,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
         if (t < W) {
             const int32_t* row = tab + static_cast<int64_t>(t) * (nsub + 1) + sub;
             p0[h] = row[0];
-            cnt[h] = static_cast<uint32_t>(row[1] - p0[h]);
+            cnt[h] = ld_thin_count(p0[h], row[1], kThinSub);
         }
     }
     ld_f32x4 x[kThinSub / 4 / LD_WAVE];

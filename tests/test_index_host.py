@@ -1,0 +1,77 @@
+"""Index arithmetic that kernels share with the host, built with g++ and tried on what no GPU run may be given:
+record lists that break the contract of the merges (damaged files)."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2509_04084_amd", "csrc")
+
+SHIM = """
+#include "ld_thin.h"
+extern "C" {
+// the table row of one diff, each entry taken by the first (order 0) or the last (1) of the records that fill it
+void thin_row(const int32_t* idx, int32_t K, int32_t sub, int32_t nsub, int32_t order, int32_t* row) {
+    for (int32_t s = 0; s <= nsub; ++s) row[s] = -1;
+    for (int32_t j = 0; j <= K; ++j) {
+        const LdThinEntries f = ld_thin_entries(j == 0 ? -1 : idx[j - 1] / sub, j == K ? nsub : idx[j] / sub, nsub);
+        for (int32_t s = f.first; s <= f.last; ++s)
+            if (order == 1 || row[s] < 0) row[s] = j;
+    }
+}
+uint32_t thin_count(int32_t begin, int32_t end, int32_t elements) { return ld_thin_count(begin, end, elements); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    d = tmp_path_factory.mktemp("index")
+    src, lib = str(d / "shim.cpp"), str(d / "shim.so")
+    with open(src, "w") as f:
+        f.write(SHIM)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-fPIC", "-shared", "-fsanitize=undefined",
+                    "-fno-sanitize-recover", "-I", CSRC, src, "-o", lib], check=True)
+    L = ctypes.CDLL(lib)
+    L.thin_count.restype = ctypes.c_uint32
+    return L
+
+
+def rows(shim, idx, n, sub):
+    nsub = (n + sub - 1) // sub
+    for order in (0, 1):
+        row = np.full(nsub + 3, -7, np.int32)  # a word either side of the row
+        shim.thin_row(ctypes.c_void_p(idx.ctypes.data), idx.size, sub, nsub, order, ctypes.c_void_p(row.ctypes.data + 4))
+        assert row[0] == -7 and row[-1] == -7
+        yield row[1:-1]
+
+
+@pytest.mark.parametrize("kind", ["ascending", "descending", "random", "zeros", "repeated", "outside", "two_runs"])
+@pytest.mark.parametrize("n,K", [(5, 3), (40960, 500), (100003, 4096), (100003, 60000)])
+def test_sub_tile_counts_stay_inside_any_list(shim, kind, n, K):
+    sub = 4096
+    rs = np.random.RandomState(K)
+    up = np.sort(rs.choice(n, min(K, n), replace=False))
+    idx = {"ascending": up, "descending": up[::-1], "random": rs.permutation(up), "zeros": np.zeros(K, np.int64),
+           "repeated": np.full(K, n - 1), "outside": rs.randint(-2 ** 31, 2 ** 31, K),
+           "two_runs": np.concatenate([up, up])}[kind]
+    idx = np.ascontiguousarray(idx, np.int32)
+    for row in rows(shim, idx, n, sub):
+        assert row.min() >= 0 and row.max() <= idx.size      # every entry filled, and with a position of the list
+        for b, e in zip(row[:-1], row[1:]):
+            count = shim.thin_count(int(b), int(e), sub)
+            assert 0 <= count <= sub and b + count <= idx.size
+            if kind == "ascending":
+                assert count == e - b
+        if kind == "ascending":
+            np.testing.assert_array_equal(row, np.searchsorted(up, np.minimum(np.arange(row.size) * sub, n)))
+
+
+def test_sub_tile_count_of_any_two_entries(shim):
+    ends = [0, 1, 5, 4095, 4096, 4097, 2 ** 31 - 1]
+    for b in ends:
+        for e in ends:
+            assert shim.thin_count(b, e, 4096) == min(max(e - b, 0), 4096)
