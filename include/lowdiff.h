@@ -101,7 +101,10 @@ const char* ld_status_string(ld_status s);
  *              about 1 % at full speed; the results are the same at any
  *              density, but denser calls run faster with the
  *              ld_compress_topk_workspace_for() size of their seg_k (the call
- *              uses as much of a larger workspace as its densities ask for)
+ *              uses as much of a larger workspace as its densities ask for).
+ *              The size need not grow with the table (small tables are cut
+ *              finer), but the size asked for one table serves every table
+ *              with no more segments, none of them longer
  * Errors: LD_ERR_NULL, LD_ERR_RANGE (bad table, n > 2^31-1), LD_ERR_ALIGN,
  * LD_ERR_WORKSPACE, LD_ERR_HIP.
  */

@@ -103,7 +103,7 @@ constexpr int kDictSegs = 2048;                   // segments of a packed segmen
 struct SegDesc {        // one per segment plus a sentinel
     int64_t off;        // first element
     int64_t out0;       // first output record
-    int32_t k;          // records to keep
+    int32_t k;          // records to keep; in the sentinel: the call's tiles per group
     int32_t group0;     // first group
 };
 
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(512) void k_upload(UploadBatch ub, Ctx c) {
     const int s = ub.first + j;
     c.desc[s] = SegDesc{ub.off[j], ub.out0 + ks, ub.k[j], ub.group0 + static_cast<int32_t>(groups)};
     if (s == ub.n_seg - 1)
-        c.desc[s + 1] = SegDesc{ub.off[j + 1], ub.out0 + ks + my_k, 0,
+        c.desc[s + 1] = SegDesc{ub.off[j + 1], ub.out0 + ks + my_k, c.tiles,
                                 ub.group0 + static_cast<int32_t>(groups + my_groups)};
     if (s == 0)
         for (int i = 0; i < kSyncWords; ++i) c.fail_count[i] = 0;
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(NT) void k_prep(const float* __restrict__ g, const 
         if (threadIdx.x == 0) {
             c.desc[s] = d;
             if (s == pt.n_seg - 1)
-                c.desc[s + 1] = SegDesc{end, d.out0 + d.k, 0, d.group0 + groups_of(d.off, end, c.tiles)};
+                c.desc[s + 1] = SegDesc{end, d.out0 + d.k, c.tiles, d.group0 + groups_of(d.off, end, c.tiles)};
             if (s == 0)
                 for (int i = 0; i < kSyncWords; ++i) c.fail_count[i] = 0;
         }
@@ -1846,13 +1846,17 @@ int64_t count_groups(int32_t n_seg, const int64_t* seg_off, int32_t tiles) {
     return total;
 }
 
-// Groups of a segment table, and how many tiles they have (see kSmallGroups); -1 on a malformed table.
-int64_t count_groups(int32_t n_seg, const int64_t* seg_off, int32_t* tiles) {
-    *tiles = kTilesPerGroup;
-    const int64_t large = count_groups(n_seg, seg_off, kTilesPerGroup);
-    if (large < 0 || large >= kSmallGroups) return large;
-    *tiles = kTilesPerSmallGroup;
-    return count_groups(n_seg, seg_off, kTilesPerSmallGroup);
+// How a segment table is cut into groups.
+struct Cut {
+    int32_t tiles;      // tiles per group
+    int64_t n_group;    // -1: malformed table
+};
+
+// The cut that a table runs fastest with (see kSmallGroups).
+Cut wanted_cut(int32_t n_seg, const int64_t* seg_off) {
+    const Cut large{kTilesPerGroup, count_groups(n_seg, seg_off, kTilesPerGroup)};
+    if (large.n_group < 0 || large.n_group >= kSmallGroups) return large;
+    return Cut{kTilesPerSmallGroup, count_groups(n_seg, seg_off, kTilesPerSmallGroup)};
 }
 
 // Slot size that holds the candidates of a tile in all but a few tiles: the candidate threshold
@@ -1878,6 +1882,19 @@ int32_t wanted_slot(int32_t n_seg, const int64_t* seg_off, const int32_t* seg_k,
     if (slot < kSlotMin) slot = kSlotMin;
     if (slot > kSlotMax) slot = kSlotMax;
     return static_cast<int32_t>(slot);
+}
+
+size_t layout_bytes(int32_t n_seg, const Cut& cut, int32_t slot) { return layout(n_seg, cut.n_group, cut.tiles, slot).total; }
+
+// The cut of a call with this workspace and these slots: the wanted one unless only groups of 64 fit. The
+// descriptors of four times the groups make the layout of large segments in small groups up to 66 KB
+// larger, so without this a workspace sized for a table just above kSmallGroups would not serve one just below it.
+Cut call_cut(int32_t n_seg, const int64_t* seg_off, int32_t slot, size_t workspace_bytes) {
+    const Cut cut = wanted_cut(n_seg, seg_off);
+    if (cut.n_group < 0 || cut.tiles == kTilesPerGroup || workspace_bytes >= layout_bytes(n_seg, cut, slot)) return cut;
+    const Cut large{kTilesPerGroup, count_groups(n_seg, seg_off, kTilesPerGroup)};
+    const bool small_fits = workspace_bytes >= layout_bytes(n_seg, cut, kSlotMin);
+    return workspace_bytes >= layout_bytes(n_seg, large, small_fits ? slot : kSlotMin) ? large : cut;
 }
 
 Ctx make_ctx(void* workspace, const Layout& L, int32_t n_seg, int64_t n_group, int32_t tiles, int32_t slot) {
@@ -1907,9 +1924,12 @@ Ctx make_ctx(void* workspace, const Layout& L, int32_t n_seg, int64_t n_group, i
 
 // One workgroup per segment: the path the last call took for it, and how many of its tiles
 // overflowed their candidate slot.
-__global__ __launch_bounds__(kThreads) void k_paths(Ctx c, int32_t* __restrict__ paths, int32_t* __restrict__ overflowed) {
+__global__ __launch_bounds__(kThreads) void k_paths(Ctx wanted, Ctx large, int32_t* __restrict__ paths,
+                                                    int32_t* __restrict__ overflowed) {
     __shared__ uint32_t sh[kWaves];
     const int32_t s = blockIdx.x;
+    // the descriptors lie at the same place whatever the cut; the sentinel tells which one the call ran with
+    const Ctx c = large.desc[large.n_seg].k == wanted.tiles ? wanted : large;
     const SegDesc d = c.desc[s], dn = c.desc[s + 1];
     uint32_t over = 0;
     if (d.k > 0) {
@@ -2021,17 +2041,15 @@ ld_status candidate_passes(const Ctx& c, float* residual, int32_t* out_idx, floa
 }  // namespace
 
 extern "C" size_t ld_compress_topk_workspace(int32_t n_seg, const int64_t* seg_off) {
-    int32_t tiles;
-    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
-    if (n_group < 0) return 0;
-    return layout(n_seg, n_group, tiles, kSlotMin).total;
+    const Cut cut = wanted_cut(n_seg, seg_off);
+    if (cut.n_group < 0) return 0;
+    return layout_bytes(n_seg, cut, kSlotMin);
 }
 
 extern "C" size_t ld_compress_topk_workspace_for(int32_t n_seg, const int64_t* seg_off, const int32_t* seg_k) {
-    int32_t tiles;
-    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
-    if (n_group < 0 || (n_seg > 0 && !seg_k)) return 0;
-    return layout(n_seg, n_group, tiles, wanted_slot(n_seg, seg_off, seg_k)).total;
+    const Cut cut = wanted_cut(n_seg, seg_off);
+    if (cut.n_group < 0 || (n_seg > 0 && !seg_k)) return 0;
+    return layout_bytes(n_seg, cut, wanted_slot(n_seg, seg_off, seg_k));
 }
 
 extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residual, const int64_t* seg_off,
@@ -2041,9 +2059,8 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     if (n_seg < 0 || (strategy != LD_COMPRESS_AUTO && strategy != LD_COMPRESS_FULL)) return LD_ERR_RANGE;
     if (n_seg == 0) return LD_OK;
     if (!seg_off || !seg_k) return LD_ERR_NULL;
-    int32_t tiles;
-    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
-    if (n_group < 0 || n_group > INT32_MAX / tiles) return LD_ERR_RANGE;
+    const Cut wanted = wanted_cut(n_seg, seg_off);
+    if (wanted.n_group < 0 || wanted.n_group > INT32_MAX / wanted.tiles) return LD_ERR_RANGE;
     const int64_t n = seg_off[n_seg];
     if (n > INT32_MAX) return LD_ERR_RANGE;
     int64_t K = 0;
@@ -2057,11 +2074,14 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     if (!ld_aligned(grad, 16) || !ld_aligned(residual, 16) || !ld_aligned(out_idx, 4) ||
         !ld_aligned(out_val, 4))
         return LD_ERR_ALIGN;
-    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < layout(n_seg, n_group, tiles, kSlotMin).total)
-        return LD_ERR_WORKSPACE;
-    // the largest slot, up to the one this call's densities ask for, that the workspace holds
     int32_t per_tile = 0;
     int32_t slot = wanted_slot(n_seg, seg_off, seg_k, &per_tile);
+    const Cut cut = call_cut(n_seg, seg_off, slot, workspace_bytes);
+    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < layout_bytes(n_seg, cut, kSlotMin))
+        return LD_ERR_WORKSPACE;
+    const int32_t tiles = cut.tiles;
+    const int64_t n_group = cut.n_group;
+    // the largest slot, up to the one this call's densities ask for, that the workspace holds
     while (slot > kSlotMin && layout(n_seg, n_group, tiles, slot).total > workspace_bytes) slot -= 64;
     const Layout L = layout(n_seg, n_group, tiles, slot);
 
@@ -2148,16 +2168,19 @@ extern "C" ld_status ld_compress_topk_paths(const void* workspace, size_t worksp
     if (n_seg < 0) return LD_ERR_RANGE;
     if (n_seg == 0) return LD_OK;
     if (!seg_off || !paths) return LD_ERR_NULL;
-    int32_t tiles;
-    const int64_t n_group = count_groups(n_seg, seg_off, &tiles);
-    if (n_group < 0 || n_group > INT32_MAX / tiles) return LD_ERR_RANGE;
+    const Cut wanted = wanted_cut(n_seg, seg_off);
+    if (wanted.n_group < 0 || wanted.n_group > INT32_MAX / wanted.tiles) return LD_ERR_RANGE;
     if (!ld_aligned(paths, 4) || !ld_aligned(overflowed_tiles, 4)) return LD_ERR_ALIGN;
-    const Layout L = layout(n_seg, n_group, tiles, kSlotMin);  // the slot size only moves the candidate arrays
-    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < L.total) return LD_ERR_WORKSPACE;
-    const Ctx c = make_ctx(const_cast<void*>(workspace), L, n_seg, n_group, tiles, kSlotMin);
+    const Cut large{kTilesPerGroup, count_groups(n_seg, seg_off, kTilesPerGroup)};
+    // the slot size only moves the candidate arrays
+    const Layout L = layout(n_seg, wanted.n_group, wanted.tiles, kSlotMin), G = layout(n_seg, large.n_group, large.tiles, kSlotMin);
+    if (!workspace || !ld_aligned(workspace, 256) || (workspace_bytes < L.total && workspace_bytes < G.total))
+        return LD_ERR_WORKSPACE;
+    void* ws = const_cast<void*>(workspace);
     ld_begin_call();
     k_paths<<<dim3(static_cast<uint32_t>(n_seg)), dim3(kThreads), 0, static_cast<hipStream_t>(stream)>>>(
-        c, paths, overflowed_tiles);
+        make_ctx(ws, L, n_seg, wanted.n_group, wanted.tiles, kSlotMin),
+        make_ctx(ws, G, n_seg, large.n_group, large.tiles, kSlotMin), paths, overflowed_tiles);
     return ld_launch_status();
 }
 

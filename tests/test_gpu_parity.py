@@ -121,6 +121,63 @@ def test_compress_segment_counts_around_the_launch_rules(n_seg):
     check_compress(g, r, off, k, tag=f"n_seg={n_seg}")
 
 
+@pytest.mark.parametrize("rho", [(1, 100), (10, 100)])
+def test_compress_workspace_that_holds_only_groups_of_64(rho):
+    # The query for a table of few groups counts groups of 16 tiles, whose descriptors take more room than those
+    # of 64 when the segments are large (a workspace sized for a larger table can be smaller): the call then runs
+    # with groups of 64, and the paths hook reads what it left whichever size it is given.
+    sizes = [262144] * 39 + [262143]
+    off, k = synth.seg_offsets(sizes), synth.seg_topk(sizes, *rho)
+    rs = np.random.RandomState(rho[0])
+    n = int(off[-1])
+    g = (rs.standard_t(3, n) * 1e-3).astype(np.float32)
+    r = (rs.standard_normal(n) * 1e-3).astype(np.float32)
+    oi, ov, orr = oracle.topk_ef(g, r, off, k, select=True)
+    # 160 and 40 groups: descriptors of 64 bytes, three words each; pieces of 256 bytes
+    pieces = lambda groups: -(-groups * 64 // 256) + 3 * -(-groups * 4 // 256)
+    gap = (pieces(160) - pieces(40)) * 256
+    least, best = ld.ld_compress_topk_workspace(off), ld.ld_compress_topk_workspace(off, k)
+    whole = torch.empty(best, dtype=torch.uint8, device=DEV)
+    over = {}
+    for size in (best, best - 256, best - gap, least, least - 256, least - gap):
+        r_gpu = to_gpu(r)
+        idx, val = ld.ld_compress_topk(to_gpu(g), r_gpu, off, k, workspace=whole[:size])
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(idx.cpu().numpy(), oi)
+        np.testing.assert_array_equal(bits(val.cpu().numpy()), bits(ov))
+        np.testing.assert_array_equal(bits(r_gpu.cpu().numpy()), bits(orr))
+        for ws in (whole[:size], whole):
+            path, tied, over[size] = compress_paths(ws, off)
+            assert np.all(path == ld.LD_PATH_CANDIDATES) and not np.any(tied)
+    assert not np.any(over[best - gap]), "slots of the size that the call asks for"
+    np.testing.assert_array_equal(over[least], over[least - gap])   # the same tiles overflow in either cut
+    assert rho[0] == 1 or np.all(over[least] > 0)
+    with pytest.raises(ld.LowDiffError, match="WORKSPACE"):
+        ld.ld_compress_topk(to_gpu(g), to_gpu(r), off, k, workspace=whole[:least - gap - 1])
+
+
+def test_compress_takes_a_workspace_sized_for_a_larger_table():
+    # one segment either side of the size where the groups change: the larger table asks for fewer bytes, and what
+    # it asks for serves the smaller one
+    n = 511 * 262144
+    off, k = np.array([0, n], np.int64), np.array([n // 1000], np.int32)
+    size = ld.ld_compress_topk_workspace(np.array([0, n + 262144], np.int64))
+    own = ld.ld_compress_topk_workspace(off, k)
+    assert size < own
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    g = torch.randn(n, device=DEV, generator=gen)
+    outs = []
+    for nbytes in (size, own):
+        r = torch.zeros(n, device=DEV)
+        idx, val = ld.ld_compress_topk(g, r, off, k, workspace=torch.empty(nbytes, dtype=torch.uint8, device=DEV))
+        outs.append((idx, val.view(torch.int32), r.view(torch.int32)))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    idx, val, r = outs[0]
+    assert torch.equal(val, g[idx.long()].view(torch.int32)) and int((r == 0).sum()) >= k[0]
+    assert float(g[idx.long()].abs().min()) >= float(r.view(torch.float32).abs().max())
+
+
 @pytest.mark.parametrize("n", [150001])
 def test_compress_adversarial(n):
     off = np.array([0, 1000, 70000, n], np.int64)
