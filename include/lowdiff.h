@@ -219,7 +219,9 @@ ld_status ld_merge_sparse(float* w, int64_t n,
  *   group      1 <= group <= 64: diffs per stage (a larger group means fewer
  *              passes over w and a longer wait before the first merge)
  *   staging    dev, 256-byte aligned, ld_merge_sparse_from_host_staging() bytes
- *   workspace  dev, 256-byte aligned, ld_merge_sparse_workspace(n, group, K) bytes
+ *   workspace  dev, 256-byte aligned, at least ld_merge_sparse_workspace(n, group, NULL)
+ *              bytes; a group of sparse diffs is merged faster with what the query
+ *              gives for its K
  *   copy_stream, merge_stream  may be the same stream (then nothing overlaps).
  *              w is ready when merge_stream has passed the call.
  * The call creates and destroys four HIP events (it allocates no device memory), so

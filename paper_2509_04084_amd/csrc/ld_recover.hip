@@ -86,7 +86,8 @@ extern "C" ld_status ld_merge_sparse_from_host_events(float* w, int64_t n, const
     const size_t slot = slot_bytes(K, W, group);
     if (slot == 0) return LD_OK;  // every diff is empty
     if (!staging || !ld_aligned(staging, 256) || staging_bytes < kSlots * slot) return LD_ERR_WORKSPACE;
-    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < ld_merge_sparse_workspace(n, group, K))
+    // the least that ld_merge_sparse takes; what it makes of more depends on each group's records
+    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < ld_merge_sparse_workspace(n, group, nullptr))
         return LD_ERR_WORKSPACE;
     hipStream_t cs = static_cast<hipStream_t>(copy_stream), ms = static_cast<hipStream_t>(merge_stream);
     Events ev;

@@ -139,6 +139,24 @@ def test_merge_from_host_argument_errors():
     assert call(W=0) == 0 and call(n=0) == 0
 
 
+def test_merge_from_host_takes_the_least_workspace_of_the_merge():
+    # windows of sparse diffs ask for more than they need (a table that makes them faster): that is no reason to
+    # refuse. Of the argument checks the events come last, so a call that passes the workspace's ends there.
+    lib = ld.load()
+    V = ctypes.c_void_p
+    n, W = 100_000_000, 20
+    hp = (ctypes.c_void_p * W)(*[FAKE] * W)
+    none = (ctypes.c_void_p * 4)()
+    for per8192 in (8, 16, 17, 47, 49, 80):
+        K = np.full(W, n * per8192 // 8192, np.int64)
+        least = lib.ld_merge_sparse_workspace(n, W, V(0))
+        assert lib.ld_merge_sparse_workspace(n, W, _p(K)) > least or per8192 > 48
+        stg = lib.ld_merge_sparse_from_host_staging(_p(K), W, W)
+        call = lambda wsb: lib.ld_merge_sparse_from_host_events(V(FAKE), n, hp, hp, _p(K), W, ctypes.c_float(0.1), W,
+                                                                V(FAKE), stg, V(FAKE), wsb, V(0), V(0), none)
+        assert call(least) == -1 and call(least - 1) == -3
+
+
 def test_dense_argument_errors():
     lib = ld.load()
     V = ctypes.c_void_p

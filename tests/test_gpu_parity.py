@@ -911,6 +911,24 @@ def test_snapshot_into_pinned_host_memory():
 
 # ------------------------------------------------------------ pipelined recovery
 
+@pytest.mark.parametrize("least", [True, False])
+def test_merge_from_pinned_host_with_the_least_workspace(least):
+    # a group of sparse diffs runs a lane per record where the workspace holds its table, as a sweep otherwise
+    n, W = 500_003, 24
+    rs = np.random.RandomState(7)
+    w0 = (rs.standard_normal(n) * 0.02).astype(np.float32)
+    idxs = [np.sort(rs.choice(n, n * 30 // 8192, replace=False)).astype(np.int32) for _ in range(W)]
+    vals = [rs.standard_normal(i.size).astype(np.float32) for i in idxs]
+    need = [int(ld.load().ld_merge_sparse_workspace(n, 12, None)), ld.ld_merge_sparse_workspace(n, [i.size for i in idxs[:12]])]
+    assert need[0] < need[1]
+    w = to_gpu(w0)
+    ld.ld_merge_sparse_from_host(w, [torch.from_numpy(i).pin_memory() for i in idxs],
+                                 [torch.from_numpy(v).pin_memory() for v in vals], 0.1, group=12,
+                                 workspace=torch.empty(need[0 if least else 1], dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
 @pytest.mark.parametrize("group", [1, 2, 3, 64])
 def test_merge_from_pinned_host_equals_the_window_merge(group):
     # diffs in page-locked host memory, copied group by group on one stream while the previous
