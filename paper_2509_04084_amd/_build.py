@@ -25,16 +25,16 @@ def build_marshal(force: bool = True) -> str:
     import torch
     from torch.utils import cpp_extension
     base = os.path.dirname(torch.__file__)
+    tmp = f"{MARSHAL}.{os.getpid()}.tmp"  # ranks that build at once must not write into each other's file
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DLD_BUILT_FOR_TORCH="{torch.__version__}"']
     cmd += ["-isystem" + d for d in cpp_extension.include_paths()] + ["-I", sysconfig.get_paths()["include"]]
-    cmd += [src, "-o", MARSHAL + ".tmp", "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    cmd += [src, "-o", tmp, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
-        print(res.stdout)
-        print(res.stderr)
-        raise RuntimeError("g++ failed building _marshal.so")
-    os.replace(MARSHAL + ".tmp", MARSHAL)
+        raise RuntimeError("g++ failed building _marshal.so\n" + res.stdout + res.stderr)
+    os.replace(tmp, MARSHAL)
     return MARSHAL
 
 
@@ -46,12 +46,13 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
     if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", LIB + ".tmp"] + srcs
+    tmp = f"{LIB}.{os.getpid()}.tmp"
+    cmd = [hipcc] + FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", tmp] + srcs
     res = subprocess.run(cmd, capture_output=True, text=True)
     if verbose or res.returncode != 0:
         print(res.stdout)
         print(res.stderr)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed building liblowdiff.so")
-    os.replace(LIB + ".tmp", LIB)
+    os.replace(tmp, LIB)
     return LIB

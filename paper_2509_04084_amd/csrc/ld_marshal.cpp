@@ -6,6 +6,8 @@
 // reported by its index, and the binding raises.
 #include <Python.h>
 
+#include <string.h>
+
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -73,4 +75,22 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }
+// Torch's classes are used here as its headers lay them out: a module built for another torch or another
+// Python must not run. It fails to import, and the binding builds it anew or does without.
+PyMODINIT_FUNC PyInit__marshal(void) {
+    PyObject* torch = PyImport_ImportModule("torch");
+    PyObject* version = torch ? PyObject_GetAttrString(torch, "__version__") : nullptr;
+    PyObject* have = version ? PyObject_Str(version) : nullptr;
+    const char* text = have ? PyUnicode_AsUTF8(have) : nullptr;
+    const bool same = text && strcmp(text, LD_BUILT_FOR_TORCH) == 0 &&
+                      strncmp(Py_GetVersion(), PY_VERSION, strlen(PY_VERSION)) == 0;
+    PyErr_Clear();
+    Py_XDECREF(torch);
+    Py_XDECREF(version);
+    Py_XDECREF(have);
+    if (!same) {
+        PyErr_SetString(PyExc_ImportError, "_marshal was built for torch " LD_BUILT_FOR_TORCH " and Python " PY_VERSION);
+        return nullptr;
+    }
+    return PyModule_Create(&module);
+}
