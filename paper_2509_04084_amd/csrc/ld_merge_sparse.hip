@@ -226,6 +226,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
 // its element's slot of a small owner table with its lane, the smallest lane wins the
 // slot (atomic minimum), applies its update and leaves; lanes are in diff order, so the updates of one
 // element go through in diff order whatever else shares the slot, and any number of records is served.
+// Sub-tiles where the diffs are dense go through diff after diff (kThinDense).
 //
 // Bound by the instructions and LDS round trips per row (two to three bids each), next the tile's 16 KB
 // of LDS, which leave eight waves per CU. 124 M elements, 100 diffs of 0.1 %: 296 -> 235 us against a lane per
@@ -233,7 +234,13 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
 constexpr int kThinSub = 4096;     // elements of a wave's sub-tile in this kernel
 constexpr int kThinAhead = 8;      // rows of 64 records requested together
 constexpr int kOwner = 256;        // slots of the owner table
-static_assert(kThinSub % (4 * LD_WAVE) == 0 && (kOwner & (kOwner - 1)) == 0, "whole rows of 16-byte accesses");
+// Records per diff from which a sub-tile goes through diff after diff (rows of an embedding that every iteration
+// touches) instead of in rows of the list, and the rows of 64 of one diff requested together there. 50 diffs of
+// 0.4 % on 124 M elements, all of them the same dense rows of 64 / 192 / 768 / 8192 elements: 264 / 251 / 292 / 478 us, as
+// a list 309 / 422 / 838 / 2031, and with the line at 64 or 256 records 347 / 251 and 295 / 297 for the first two.
+constexpr uint32_t kThinDense = 128;
+constexpr int kThinDeep = 16;
+static_assert(kThinSub % (4 * LD_WAVE) == 0 && kThinSub <= 4096 && kOwner == 256, "whole rows of 16-byte accesses; see ld_thin_slot");
 
 // tab[t * (nsub + 1) + s] = number of records of diff t with idx < s * kThinSub, s = 0 .. nsub.
 // A thread looks at four consecutive records (one 16-byte load; the arrays of this path are
@@ -268,7 +275,7 @@ __global__ __launch_bounds__(256) void k_subtab(DiffTable tb, int32_t nsub, int3
 __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, int64_t n, int32_t nsub,
                                                         DiffTable tb, int32_t W, const int32_t* __restrict__ tab,
                                                         float lr) {
-    __shared__ float tile[kThinSub];
+    __shared__ float tile[kThinSub + 4];                     // and the spare word of apply_records
     __shared__ uint32_t before[kTableMax];                   // records of the sub-tile before diff t's
     __shared__ const int32_t* ibase[kTableMax];              // diff t's record with list position k: ibase[t][k]
     __shared__ const float* vbase[kTableMax];
@@ -318,9 +325,46 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
     for (int q = lane; q < kOwner; q += LD_WAVE) owner[q] = 0xFFFFFFFFu;
     __syncthreads();  // one wave: orders the fills before what follows
 
+    bool staged = false;
+    auto stage = [&]() {
+        staged = true;
+        if (full) {
+#pragma unroll
+            for (int j = 0; j < kThinSub / 4 / LD_WAVE; ++j) reinterpret_cast<ld_f32x4*>(tile)[j * LD_WAVE + lane] = x[j];
+        } else {
+            for (int32_t e = lane; e < len; e += LD_WAVE) tile[e] = w[lo64 + e];
+        }
+        __syncthreads();
+    };
+    if (total >= kThinDense * static_cast<uint32_t>(W)) {
+        // no two records of one diff name the same element: nothing is bid for
+        total = 0;  // nothing left for the list
+        stage();
+#pragma unroll 1
+        for (int t = 0; t < W; ++t) {
+            static_assert(kSets == 2, "");
+            const int32_t c = __builtin_amdgcn_readlane(static_cast<int32_t>(t < LD_WAVE ? cnt[0] : cnt[1]), t & (LD_WAVE - 1));
+            const int32_t p = __builtin_amdgcn_readlane(t < LD_WAVE ? p0[0] : p0[1], t & (LD_WAVE - 1));
+            const int32_t* __restrict__ ip = tb.idx[t];
+            const float* __restrict__ vp = tb.val[t];
+#pragma unroll 1
+            for (int32_t q = 0; q < c; q += kThinDeep * LD_WAVE) {
+                int32_t i[kThinDeep];
+                float v[kThinDeep];
+#pragma unroll
+                for (int u = 0; u < kThinDeep; ++u) {
+                    const int32_t k = q + u * LD_WAVE + lane;
+                    i[u] = k < c ? ip[p + k] : INT_MAX;
+                    v[u] = k < c ? vp[p + k] : 0.0f;
+                }
+                apply_records<kThinSub>(tile, i, v, lo, lr);
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    }
+
     // The list's records in diff order, 64 at a time, kThinAhead rows requested together. Lane and row give
     // the position; the diff it belongs to is the last one with `before` at or below it.
-    bool staged = false;
 #pragma unroll 1
     for (uint32_t k0 = 0; k0 < total || !staged; k0 += kThinAhead * LD_WAVE) {
         int32_t ri[kThinAhead];
@@ -340,22 +384,13 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
                 }
             }
         }
-        if (!staged) {  // the tile arrives while the first records travel
-            staged = true;
-            if (full) {
-#pragma unroll
-                for (int j = 0; j < kThinSub / 4 / LD_WAVE; ++j) reinterpret_cast<ld_f32x4*>(tile)[j * LD_WAVE + lane] = x[j];
-            } else {
-                for (int32_t e = lane; e < len; e += LD_WAVE) tile[e] = w[lo64 + e];
-            }
-            __syncthreads();
-        }
+        if (!staged) stage();  // the tile arrives while the first records travel
 #pragma unroll
         for (int u = 0; u < kThinAhead; ++u) {
             if (k0 + u * LD_WAVE < total) {  // uniform
                 const uint32_t e = static_cast<uint32_t>(ri[u] - lo);
                 const float p = __fmul_rn(lr, rv[u]);   // rounded product: never fused
-                uint32_t* own = owner + (e & (kOwner - 1));
+                uint32_t* own = owner + ld_thin_slot(e);
                 bool pend = k0 + u * LD_WAVE + lane < total && e < static_cast<uint32_t>(len);
                 while (__ballot(pend)) {
                     if (pend) atomicMin(own, static_cast<uint32_t>(lane));

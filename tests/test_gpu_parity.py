@@ -425,6 +425,42 @@ def test_merge_lane_per_record_edges(n, per8192, W):
     np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
 
 
+@pytest.mark.parametrize("n", [999_937, 999_424 + 5])
+@pytest.mark.parametrize("W", [11, 64, 65, 131])
+@pytest.mark.parametrize("case", ["line", "rows", "full", "column", "columns"])
+def test_merge_lane_per_record_dense_sub_tiles_and_columns(n, W, case):
+    # Windows that the rule takes for sparse (at most 48 records per 8192 elements of all) and that are not evenly so:
+    #   line     every sub-tile a few records either side of where it goes through diff after diff
+    #   rows     runs of 768 elements in the first, a middle and the ragged last sub-tile, the same in every diff
+    #   full     whole sub-tiles, four trips of records and more
+    #   column   the same elements 256 apart in every diff
+    #   columns  another column in each diff, 1024 apart
+    rs = np.random.RandomState(W)
+    limit = 48 * n // 8192
+    idxs = []
+    for t in range(W):
+        if case == "line":
+            at = [s * 4096 + rs.choice(min(4096, n - s * 4096), min(126 + t % 4, n - s * 4096), replace=False)
+                  for s in (0, 1, 17, 200, (n - 1) // 4096)]
+        elif case == "rows":
+            at = [np.arange(s, s + 768) for s in (0, 4096 * 100 - 300, n - 768)]
+        elif case == "full":
+            at = [np.arange(4096 * 7 - t, 4096 * 8 + t), np.arange(n - 700, n)]
+        elif case == "column":
+            at = [np.arange(5, n, 256)]
+        else:
+            at = [np.arange(37 * t % 1024, n, 1024)]
+        idxs.append(np.sort(np.concatenate(at)).astype(np.int32))
+        assert idxs[-1].size <= limit
+    vals = [(rs.standard_normal(i.size) * 1e-2).astype(np.float32) for i in idxs]
+    w0 = synth.base_weights(n).numpy()
+    w = to_gpu(w0)
+    ws = torch.empty(ld.ld_merge_sparse_workspace(n, [i.size for i in idxs]), dtype=torch.uint8, device=DEV)
+    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, ws, strategy=ld.LD_MERGE_SWEEP)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
 @pytest.mark.parametrize("case", ["random", "identical", "pairs", "clustered", "short_then_long"])
 def test_merge_thin_long_windows(case):
     # Long windows of sparse diffs run a lane per record: the records of a sub-tile go through in rows of

@@ -1,5 +1,5 @@
-"""Index arithmetic that kernels share with the host, built with g++ and tried on what no GPU run may be given:
-record lists that break the contract of the merges (damaged files)."""
+"""Index arithmetic that kernels share with the host, built with g++: tried over its whole range, and on what no GPU
+run may be given (record lists that break the contract of the merges, as a damaged file's)."""
 import ctypes
 import os
 import subprocess
@@ -23,6 +23,7 @@ void thin_row(const int32_t* idx, int32_t K, int32_t sub, int32_t nsub, int32_t 
     }
 }
 uint32_t thin_count(int32_t begin, int32_t end, int32_t elements) { return ld_thin_count(begin, end, elements); }
+uint32_t thin_slot(uint32_t e) { return ld_thin_slot(e); }
 }
 """
 
@@ -36,7 +37,7 @@ def shim(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-fPIC", "-shared", "-fsanitize=undefined",
                     "-fno-sanitize-recover", "-I", CSRC, src, "-o", lib], check=True)
     L = ctypes.CDLL(lib)
-    L.thin_count.restype = ctypes.c_uint32
+    L.thin_count.restype = L.thin_slot.restype = ctypes.c_uint32
     return L
 
 
@@ -75,3 +76,18 @@ def test_sub_tile_count_of_any_two_entries(shim):
     for b in ends:
         for e in ends:
             assert shim.thin_count(b, e, 4096) == min(max(e - b, 0), 4096)
+
+
+def test_owner_slots_keep_equidistant_elements_apart(shim):
+    # a row of 64 records of one diff bids once per record that shares a slot: columns of a matrix must not pile up
+    slot = np.array([shim.thin_slot(e) for e in range(4096)])
+    assert slot.min() >= 0 and slot.max() <= 255
+    assert np.bincount(slot, minlength=256).max() <= 18            # 4096 elements over 256 slots
+    for stride in range(1, 4096):
+        if stride % 233 == 0:                                      # 233 * 0x9E37 = 9 * 2^20 + 15: no matrix is that wide
+            continue
+        for first in (0, 5, 77):
+            e = np.arange(first, 4096, stride)[:64]
+            assert np.bincount(slot[e], minlength=256).max() <= 2, stride
+    for e in (4096, 2 ** 31, 2 ** 32 - 1):                         # records outside the sub-tile bid for nothing, but look
+        assert shim.thin_slot(ctypes.c_uint32(e)) <= 255
