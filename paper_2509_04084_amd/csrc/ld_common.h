@@ -5,6 +5,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "ld_map.h"
 #include "lowdiff.h"
 
 #define LD_WAVE 64
@@ -80,21 +81,6 @@ __device__ __forceinline__ void ld_nt_store(ld_f32x4 x, ld_f32x4* p) { __builtin
 __device__ __forceinline__ void ld_nt_store(ld_u32x4 x, ld_u32x4* p) { __builtin_nontemporal_store(x, p); }
 
 __device__ __forceinline__ int ld_lane() { return __lane_id(); }
-
-// The piece of work of workgroup `b` of a grid of `grid` workgroups (a multiple of 8). Consecutive
-// workgroups go to the 8 XCDs in turn: every XCD is given runs of CHUNK consecutive pieces, so that
-// all XCDs together walk the arrays in address order; the pieces past the last whole round of
-// 8 CHUNK are dealt out in eighths.
-template <uint32_t CHUNK>
-__device__ __forceinline__ uint32_t ld_xcd_piece(uint32_t b, uint32_t grid) {
-    const uint32_t whole = grid / (8u * CHUNK) * (8u * CHUNK);
-    if (b < whole) {
-        const uint32_t q = b / 8u;
-        return q / CHUNK * (8u * CHUNK) + (b % 8u) * CHUNK + q % CHUNK;
-    }
-    const uint32_t rest = b - whole;
-    return whole + (rest % 8u) * ((grid - whole) / 8u) + rest / 8u;
-}
 
 // |x| as an integer that orders like the magnitude (sign bit cleared).
 __device__ __forceinline__ uint32_t ld_key(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }

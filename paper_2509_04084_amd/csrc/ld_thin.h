@@ -3,13 +3,7 @@
 // file's), and those are tried on the host.
 #pragma once
 
-#include <stdint.h>
-
-#ifdef __HIPCC__
-#define LD_HD __host__ __device__ __forceinline__
-#else
-#define LD_HD inline
-#endif
+#include "ld_map.h"
 
 // Entries [first, last] of a diff's row of the sub-tile table that one record fills, `before` and `sub` being
 // the sub-tiles of the record ahead of it (-1: none) and its own (nsub: it is the end of the list). Indices

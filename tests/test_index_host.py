@@ -11,6 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2509_04084_amd", "csrc")
 
 SHIM = """
+#include "ld_map.h"
 #include "ld_thin.h"
 extern "C" {
 // the table row of one diff, each entry taken by the first (order 0) or the last (1) of the records that fill it
@@ -24,6 +25,15 @@ void thin_row(const int32_t* idx, int32_t K, int32_t sub, int32_t nsub, int32_t 
 }
 uint32_t thin_count(int32_t begin, int32_t end, int32_t elements) { return ld_thin_count(begin, end, elements); }
 uint32_t thin_slot(uint32_t e) { return ld_thin_slot(e); }
+// the piece of every workgroup of a grid
+void xcd_pieces(uint32_t run, int32_t turned, uint32_t grid, uint32_t* piece) {
+    for (uint32_t b = 0; b < grid; ++b) {
+        if (run == 1) piece[b] = turned ? ld_xcd_piece<1>(b, grid, 7) : ld_xcd_piece<1>(b, grid);
+        if (run == 16) piece[b] = turned ? ld_xcd_piece<16>(b, grid, 7) : ld_xcd_piece<16>(b, grid, 0);
+        if (run == 32) piece[b] = turned ? ld_xcd_piece<32>(b, grid, 7) : ld_xcd_piece<32>(b, grid, 0);
+        if (run == 64) piece[b] = turned ? ld_xcd_piece<64>(b, grid, 7) : ld_xcd_piece<64>(b, grid, 0);
+    }
+}
 }
 """
 
@@ -91,3 +101,25 @@ def test_owner_slots_keep_equidistant_elements_apart(shim):
             assert np.bincount(slot[e], minlength=256).max() <= 2, stride
     for e in (4096, 2 ** 31, 2 ** 32 - 1):                         # records outside the sub-tile bid for nothing, but look
         assert shim.thin_slot(ctypes.c_uint32(e)) <= 255
+
+
+@pytest.mark.parametrize("run", [1, 16, 32, 64])
+def test_xcd_maps_are_permutations(shim, run):
+    for grid in (8, 16, 64, 120, 128, 136, 512, 520, 1024, 1032, 4096, 44800, 44808):
+        for turned in (0, 1):
+            piece = np.zeros(grid, np.uint32)
+            shim.xcd_pieces(run, turned, grid, ctypes.c_void_p(piece.ctypes.data))
+            np.testing.assert_array_equal(np.sort(piece), np.arange(grid))
+
+
+@pytest.mark.parametrize("tiles,run", [(16, 1), (64, 1), (64, 16)])
+@pytest.mark.parametrize("used", [1, 2, 3])
+def test_small_segments_are_spread_over_the_xcds(shim, tiles, run, used):
+    # one group per segment, of whose tile slots only the first are work: no XCD (workgroup number modulo 8) may be given
+    # much more than its eighth of them
+    for n_seg in (64, 500, 520, 3000):
+        grid = n_seg * tiles
+        piece = np.zeros(grid, np.uint32)
+        shim.xcd_pieces(run, 1, grid, ctypes.c_void_p(piece.ctypes.data))
+        work = np.bincount(np.arange(grid)[piece % tiles < used] % 8, minlength=8)
+        assert work.max() <= 1.25 * used * n_seg / 8 + 4 * used, (n_seg, work)
