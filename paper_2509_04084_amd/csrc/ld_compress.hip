@@ -254,7 +254,7 @@ __device__ __forceinline__ bool last_block(uint32_t* counter, uint32_t expected)
 
 // In a histogram of kBins counters (global or LDS), scanned from the top bin
 // down, finds the bin d with #(bins above d) < krem <= #(bins above d) + h[d].
-// The finder writes res[0] = d, res[1] = krem - #(above d); every thread gets the
+// The finder writes res[0] = d, res[1] = krem - #(above d), res[2] = h[d]; every thread gets the
 // histogram total. NT threads, `sh` >= NT/64 words. res is unchanged if krem is
 // 0 or exceeds the total.
 template <int NT, bool GLOBAL>
@@ -274,6 +274,7 @@ __device__ __forceinline__ uint32_t find_bin(const uint32_t* h, uint32_t krem, u
         if (above < krem && krem <= above + v[i]) {
             res[0] = static_cast<uint32_t>(top - i);
             res[1] = krem - above;
+            res[2] = v[i];
         }
         above += v[i];
     }
@@ -1081,7 +1082,7 @@ __global__ __launch_bounds__(GROUPS * kThreads) void k_hist(const float* __restr
     }
 }
 
-// The fine bin that holds the segment's k-th largest key (res[0], and res[1] = the rank inside it),
+// The fine bin that holds the segment's k-th largest key (res[0], res[1] = the rank inside it, res[2] = its keys),
 // found in its histogram by a whole workgroup of kThreads; returns the mode the segment goes on in: the
 // full path when the candidates are fewer than k. `note`: this workgroup writes it all to the
 // segment's state and lists.
@@ -1110,7 +1111,7 @@ __device__ __forceinline__ uint32_t threshold_bin(const Ctx& c, const GroupRange
 
 // One workgroup per segment, where k_gather's workgroups do not look for themselves (Rows::kOwnBin).
 __global__ __launch_bounds__(kThreads) void k_bin(Ctx c) {
-    __shared__ uint32_t sh[kWaves], res[2], list0;
+    __shared__ uint32_t sh[kWaves], res[3], list0;
     const SegDesc d = c.desc[blockIdx.x];
     if (d.k == 0 || c.desc[blockIdx.x + 1].group0 == d.group0) return;
     const GroupRange gr = group_range(c, d.group0);
@@ -1171,11 +1172,18 @@ __device__ __attribute__((noinline)) Unplaced gather_lane_keys(SegState* st, uin
     return un;
 }
 
+// Small groups, keys of the threshold bin beyond which a workgroup of k_gather makes one reservation in the
+// gather list for all of its waves. What the waves of a segment add to its counter queues up, 20 ns each, and small
+// groups are as many waves as batches: 2 segments of 50 M elements with values on a coarse grid (keys of the bin
+// in every wave) 183 -> 64 us, rounded to bf16 95 -> 23.5; the few keys of a small segment are placed
+// 0.6 us sooner each by itself (flat 1 M elements).
+constexpr uint32_t kFewKeys = 256;
+
 // Per tile: candidates in bins above the threshold bin; the keys inside the bin
 // are gathered per segment.
 template <class RW>
 __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r, Ctx c) {
-    __shared__ uint32_t wsum[2][kWaves];
+    __shared__ uint32_t wsum[2][kWaves], wmin[kWaves], wmax[kWaves];
     const uint32_t mycnt = wave_counts<RW>(c, blockIdx.x);
     const GroupRange gr = group_range(c, blockIdx.x);
     TripRaw raw[RW::kAhead];
@@ -1183,11 +1191,13 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
     SegState* st = c.state + gr.seg;
     if (gr.k == 0) return;
     uint32_t mode, b1;
+    bool many = false;  // small groups: one reservation per workgroup (see below)
     if (RW::kOwnBin) {
         // each workgroup finds the threshold bin for itself, the segment's first one notes it down
-        __shared__ uint32_t sh[kWaves], res[2], list0;
+        __shared__ uint32_t sh[kWaves], res[3], list0;
         mode = threshold_bin(c, gr, st, static_cast<int32_t>(blockIdx.x) == gr.group0, sh, res, &list0);
         b1 = res[0];
+        many = mode == kModeCand && res[2] > kFewKeys;
     } else {
         mode = st->mode;
         b1 = st->prefix;
@@ -1206,7 +1216,8 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
     // Keys of the threshold bin go to the segment's gather list, one reservation per wave and
     // batch. When the list is full (massive ties: millions of equal keys) nothing more is
     // reserved (a wave learns that from its first reservation that comes back beyond the end);
-    // the keys that found no room only widen the segment's [kmin, kmax].
+    // the keys that found no room only widen the segment's [kmin, kmax]. With small groups a wave has
+    // no second batch to profit from that: see kFewKeys.
     bool full = false;
     uint32_t lmin = 0xFFFFFFFFu, lmax = 0;
     uint32_t part_gt = 0, part_eq = 0;  // fast path: the first lane of a row sums the row's tiles
@@ -1221,6 +1232,34 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
             wave_ties += t;
         }
     }
+    uint32_t place = 0;  // small groups: where this lane's next key goes
+    if (RW::kOwnBin && many) {  // uniform
+        static_assert(!RW::kOwnBin || RW::kTrips == RW::kAhead, "all trips of a wave are in registers");
+        __shared__ uint32_t wkeys[kWaves], first;
+        uint32_t mine = 0, before = 0, total = 0;
+#pragma unroll
+        for (int a = 0; a < RW::kAhead; ++a) {
+            Trip Q;
+            trip_finish<false, RW>(raw[a], mycnt, a, Q);
+#pragma unroll
+            for (int j = 0; j < kPerLane; ++j)
+                mine += static_cast<uint32_t>(j) < Q.have && fine_bin(ld_key(Q.v[j]), tau, binsh) == b1;
+        }
+        const uint32_t inc = ld_wave_iscan(mine);
+        if (lane == LD_WAVE - 1) wkeys[w] = inc;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kWaves; ++u) {
+            before += u < w ? wkeys[u] : 0u;
+            total += wkeys[u];
+        }
+        if (total > 0) {  // uniform
+            if (threadIdx.x == 0) first = atomicAdd(&st->gcount, total);
+            __syncthreads();
+            place = first + before + inc - mine;
+            full = first + total > gcap;
+        }
+    }
     for_trips<false, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
         uint32_t cnt = 0, in = 0;
 #pragma unroll
@@ -1233,18 +1272,18 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
         const uint32_t n_in = __popc(in);
         const uint64_t who = __ballot(in != 0);
         if (who) {
-            if (full || __popcll(who) >= 4) {  // massive ties: one reservation for the wave, or none
+            if (!RW::kOwnBin && (full || __popcll(who) >= 4)) {  // massive ties: one reservation for the wave, or none
                 const Unplaced un = gather_lane_keys(st, gkey, gtile, gcap, ld_f32x4{Q.v[0], Q.v[1], Q.v[2], Q.v[3]},
                                                      ld_f32x4{Q.v[4], Q.v[5], Q.v[6], Q.v[7]}, in, tile0 + Q.u, full);
                 lmin = umin(lmin, un.kmin);
                 lmax = un.kmax > lmax ? un.kmax : lmax;
                 full = un.full;
-            } else {  // the usual case: a key or two
+            } else {  // the usual case: a key or two; or the lane's own places
 #pragma unroll
                 for (int j = 0; j < kPerLane; ++j) {
                     if ((in >> j) & 1u) {
                         const uint32_t key = ld_key(Q.v[j]);
-                        const uint32_t pos = atomicAdd(&st->gcount, 1u);
+                        const uint32_t pos = many ? place++ : atomicAdd(&st->gcount, 1u);
                         if (pos < gcap) {
                             gkey[pos] = key;
                             gtile[pos] = tile0 + Q.u;
@@ -1317,19 +1356,26 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
             const uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(lmax), d, LD_WAVE));
             lmax = o > lmax ? o : lmax;
         }
-        if (lane == 0) {
-            atomicMin(&st->kmin, lmin);
-            atomicMax(&st->kmax, lmax);
-        }
     }
     const uint32_t wave_gt = ld_wave_sum(part_gt) + slow_gt;
     const uint32_t wave_eq = ld_wave_sum(part_eq) + slow_eq + wave_ties;
     if (lane == 0) {
         wsum[0][w] = wave_gt;
         wsum[1][w] = wave_eq;
+        wmin[w] = lmin;
+        wmax[w] = lmax;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
+#pragma unroll
+        for (int u = 1; u < kWaves; ++u) {
+            lmin = umin(lmin, wmin[u]);
+            lmax = wmax[u] > lmax ? wmax[u] : lmax;
+        }
+        if (lmin <= lmax) {
+            atomicMin(&st->kmin, lmin);
+            atomicMax(&st->kmax, lmax);
+        }
         c.group_gt[blockIdx.x] = wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3];
         c.group_eq[blockIdx.x] = wsum[1][0] + wsum[1][1] + wsum[1][2] + wsum[1][3];
     }
@@ -1343,7 +1389,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
 __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
     __shared__ uint32_t lh[kBins];
     __shared__ uint32_t sh[kWaves];
-    __shared__ uint32_t res[2];
+    __shared__ uint32_t res[3];
     __shared__ uint32_t list0;
     const GroupRange gr = seg_range(c, blockIdx.x);
     SegState* st = c.state + gr.seg;
@@ -1794,7 +1840,7 @@ __global__ __launch_bounds__(kThreads) void k_full(float* __restrict__ r, int32_
                                                    float* __restrict__ out_val, Ctx c) {
     __shared__ uint32_t lh[kBins];
     __shared__ uint32_t sh[kWaves];
-    __shared__ uint32_t res[2];
+    __shared__ uint32_t res[3];
     __shared__ uint32_t part[2][kWaves];
     const uint32_t nlist = c.fail_count[kSyncCount];
     if (nlist == 0) return;

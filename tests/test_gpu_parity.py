@@ -262,6 +262,28 @@ def test_compress_massive_ties_at_the_threshold():
                    synth.seg_topk(sizes, 1, 100), tag="values on a grid")
 
 
+@pytest.mark.parametrize("copies", [1, 250, 256, 257, 1000, 4300, 30_000])
+@pytest.mark.parametrize("spread", [True, False])
+def test_compress_keys_in_the_threshold_bin(copies, spread):
+    # The keys of the threshold bin are placed one by one or a workgroup's at a time, by how many there are: copies of
+    # one key at the threshold, all over the segment or in consecutive elements (whole tiles of them: more than a
+    # tile's slots hold), up to more than the gather list takes. Two segments, so that one workgroup's waves
+    # hold tiles of a second group.
+    rs = np.random.RandomState(copies)
+    n, k_s = 700_001, 7000
+    off = np.array([0, n, n + 90_000], np.int64)
+    g = rs.permutation(np.linspace(1e-4, 1.0, n)).astype(np.float32) ** 8
+    order = np.argsort(-g, kind="stable")
+    at = rs.choice(n - copies, copies, replace=False) if spread else n // 3 + np.arange(copies)
+    x = g[order[k_s - 1]]
+    g[at] = x                                    # some of the copies were above, most below: x stays near rank k
+    g *= np.where(rs.rand(n) < 0.5, 1, -1).astype(np.float32)
+    g = np.concatenate([g, rs.standard_normal(90_000).astype(np.float32)])
+    for rank in (k_s - copies // 2, k_s + copies // 2):
+        check_compress(g, np.zeros_like(g), off, np.array([max(rank, 1), 900], np.int32), tag=f"{copies} copies, k={rank}",
+                       strategies=(ld.LD_COMPRESS_AUTO,))
+
+
 def test_compress_tied_segment_with_and_without_enough_ties():
     # A segment is treated as "tied" when the 16 K-element sample holds the candidate threshold's
     # own key hundreds of times. White-box: the sample positions are rebuilt here (256 jittered runs
