@@ -36,10 +36,19 @@ def compress_paths(ws, seg_off):
 
 
 def check_compress(g, r, seg_off, seg_k, select=True, tag="",
-                   strategies=(ld.LD_COMPRESS_AUTO, ld.LD_COMPRESS_FULL), want=None):
+                   strategies=(ld.LD_COMPRESS_AUTO, ld.LD_COMPRESS_FULL), want=None, large_groups=False):
     """Runs one compress call per strategy on the GPU and once on the oracle;
     returns (idx, val, r_new) of the oracle. `want(path, tied, overflowed)` is called with what
-    the AUTO call reports about the way each segment went."""
+    the AUTO call reports about the way each segment went. With `large_groups` all of it once more
+    with 520 segments of one element behind the others: every segment is a group at least, and from 512 groups of
+    64 tiles on a call runs with those (and other kernels) instead of groups of 16."""
+    if large_groups:
+        more = 520
+        rs = np.random.RandomState(more)
+        ext = lambda a: np.concatenate([a, rs.standard_normal(more).astype(np.float32)])
+        check_compress(ext(g), ext(r), np.concatenate([seg_off, seg_off[-1] + 1 + np.arange(more)]),
+                       np.concatenate([seg_k, np.arange(more) % 2]).astype(np.int32), select, tag + " large groups",
+                       strategies, want)
     print(f"[compress] {tag} n={len(g)} n_seg={len(seg_k)}", flush=True)
     oi, ov, orr = oracle.topk_ef(g, r, seg_off, seg_k, select=select)
     g_gpu = to_gpu(g)
@@ -121,6 +130,45 @@ def test_compress_segment_counts_around_the_launch_rules(n_seg):
     check_compress(g, r, off, k, tag=f"n_seg={n_seg}")
 
 
+@pytest.mark.parametrize("n_seg", [231, 255, 256, 257, 511, 512])
+def test_compress_packed_tables(n_seg):
+    # more segments than travel as they are, of few distinct sizes (a model's): the packed table, with 1024 and 512
+    # threads in k_prep and groups of 16 and (512 segments) of 64 tiles
+    rs = np.random.RandomState(n_seg)
+    sizes = [int(x) for x in rs.choice([1, 3, 64, 768, 4095, 4097, 16383, 16385, 65537, 70001], n_seg,
+                                       p=[.1, .1, .2, .2, .1, .1, .08, .08, .02, .02])]
+    off, k = synth.seg_offsets(sizes), synth.seg_topk(sizes, 1, 50)
+    assert len(set(zip(sizes, k.tolist()))) <= 160
+    n = int(off[-1])
+    check_compress((rs.standard_t(3, n) * 1e-3).astype(np.float32), (rs.standard_normal(n) * 1e-3).astype(np.float32),
+                   off, k, tag=f"packed n_seg={n_seg}")
+
+
+def test_compress_dense_call_of_many_tiles():
+    # 5 % of 184 M elements: slots beyond the smallest and tiles dealt out in runs of 16. The result is shown to be the
+    # top k by its properties (the order is total, so they fix it).
+    n = 184_000_003
+    off, k = np.array([0, n], np.int64), np.array([n // 20], np.int32)
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    g = torch.randn(n, device=DEV, generator=gen)
+    r = torch.zeros(n, device=DEV)
+    ws = torch.empty(ld.ld_compress_topk_workspace(off, k), dtype=torch.uint8, device=DEV)
+    idx, val = ld.ld_compress_topk(g, r, off, k, workspace=ws)
+    torch.cuda.synchronize()
+    path, tied, over = compress_paths(ws, off)
+    assert path[0] == ld.LD_PATH_CANDIDATES and not tied[0]
+    i = idx.long()
+    assert bool((i[1:] > i[:-1]).all()) and int(i[0]) >= 0 and int(i[-1]) < n
+    assert torch.equal(val.view(torch.int32), g[i].view(torch.int32))
+    kept = torch.ones(n, dtype=torch.bool, device=DEV)
+    kept[i] = False
+    assert torch.equal(torch.where(kept, g, 0.0).view(torch.int32), r.view(torch.int32))
+    least = val.abs().min()
+    assert float(r.abs().max()) <= float(least)
+    left = torch.nonzero(kept & (g.abs() == least)).flatten()   # ties at the threshold: the lowest indices were taken
+    assert left.numel() == 0 or int(left[0]) > int(i[val.abs() == least][-1])
+
+
 @pytest.mark.parametrize("rho", [(1, 100), (10, 100)])
 def test_compress_workspace_that_holds_only_groups_of_64(rho):
     # The query for a table of few groups counts groups of 16 tiles, whose descriptors take more room than those
@@ -183,7 +231,7 @@ def test_compress_adversarial(n):
     off = np.array([0, 1000, 70000, n], np.int64)
     for name, g, r in synth.adversarial_cases(n, seed=3):
         for k in ([10, 690, 800], [1000, 1, 80001], [500, 69000, 40000]):
-            check_compress(g, r, off, np.array(k, np.int32), tag=f"{name} k={k}")
+            check_compress(g, r, off, np.array(k, np.int32), tag=f"{name} k={k}", large_groups=True)
 
 
 @pytest.mark.parametrize("rho", [(2, 100), (3, 100), (5, 100), (75, 1000), (10, 100), (25, 100)])
@@ -198,7 +246,7 @@ def test_compress_density_range(rho):
     n = int(off[-1])
     g = (rs.standard_t(3, n) * 1e-3).astype(np.float32)
     r = (rs.standard_t(3, n) * 3e-4).astype(np.float32)
-    oi, ov, orr = check_compress(g, r, off, k, tag=f"rho={rho}", strategies=(ld.LD_COMPRESS_AUTO,))
+    oi, ov, orr = check_compress(g, r, off, k, tag=f"rho={rho}", strategies=(ld.LD_COMPRESS_AUTO,), large_groups=True)
     assert ld.ld_compress_topk_workspace(off, k) >= ld.ld_compress_topk_workspace(off)
     small = torch.empty(ld.ld_compress_topk_workspace(off), dtype=torch.uint8, device=DEV)
     r_gpu = to_gpu(r)
@@ -232,21 +280,21 @@ def test_compress_massive_ties_at_the_threshold():
     # overfull bin, so the segment is redone in full
     def redone(path, tied, over):
         assert path[0] == ld.LD_PATH_FULL
-    check_compress(one, np.zeros(n, np.float32), off, k, tag="one repeated value and close neighbours", want=redone)
+    check_compress(one, np.zeros(n, np.float32), off, k, tag="one repeated value and close neighbours", want=redone, large_groups=True)
     # with the next 300 ranks moved away the repeated value has its bin to itself: candidate path
     def stays(path, tied, over):
         assert path[0] == ld.LD_PATH_CANDIDATES and not tied[0]
     alone = one.copy()
     alone[order[13_000:13_300]] *= np.float32(0.25)
-    check_compress(alone, np.zeros(n, np.float32), off, k, tag="one repeated value across the threshold", want=stays)
+    check_compress(alone, np.zeros(n, np.float32), off, k, tag="one repeated value across the threshold", want=stays, large_groups=True)
     # values on a dyadic grid (exact in fp32, so equal magnitudes are equal keys): ~7000 copies of the
     # threshold value, more than the gather list's 4340 entries, one value per bin
     dyadic = (np.round(base * 4096) / 4096).astype(np.float32)
-    check_compress(dyadic, np.zeros(n, np.float32), off, k, tag="dyadic grid", want=stays)
+    check_compress(dyadic, np.zeros(n, np.float32), off, k, tag="dyadic grid", want=stays, large_groups=True)
     two = one.copy()
     up = np.nextafter(lo_val, np.float32(1.0))
     two[cluster[::2]] = up
-    check_compress(two, np.zeros(n, np.float32), off, k, tag="two adjacent values across the threshold", want=redone)
+    check_compress(two, np.zeros(n, np.float32), off, k, tag="two adjacent values across the threshold", want=redone, large_groups=True)
     # frozen layer next to a live one, and values on a coarse grid (heavy duplication everywhere)
     sizes = [600_000, 400_000]
     off2 = synth.seg_offsets(sizes)
@@ -256,10 +304,10 @@ def test_compress_massive_ties_at_the_threshold():
     def frozen(path, tied, over):
         assert path[0] == ld.LD_PATH_TIES and tied[0], "the zeros of the frozen segment: ties by index"
         assert path[1] == ld.LD_PATH_CANDIDATES and not tied[1]
-    check_compress(g, np.zeros(n, np.float32), off2, synth.seg_topk(sizes, 1, 100), tag="frozen segment", want=frozen)
+    check_compress(g, np.zeros(n, np.float32), off2, synth.seg_topk(sizes, 1, 100), tag="frozen segment", want=frozen, large_groups=True)
     grid = (np.round(base * 3e4) / 3e4).astype(np.float32)
     check_compress(grid, (np.round(base[::-1] * 1e4) / 3e4).astype(np.float32), off2,
-                   synth.seg_topk(sizes, 1, 100), tag="values on a grid")
+                   synth.seg_topk(sizes, 1, 100), tag="values on a grid", large_groups=True)
 
 
 @pytest.mark.parametrize("copies", [1, 250, 256, 257, 1000, 4300, 30_000])
@@ -315,14 +363,15 @@ def test_compress_tied_segment_with_and_without_enough_ties():
     def wrong_guess(path, tied, over):
         assert tied[0], "the sample was built to show a massively repeated key at the threshold"
         assert path[0] == ld.LD_PATH_FULL, "too few ties: the segment must have been redone in full"
-    check_compress(few, z, off, k, tag="tied guess, too few ties", strategies=(ld.LD_COMPRESS_AUTO,), want=wrong_guess)
+    check_compress(few, z, off, k, tag="tied guess, too few ties", strategies=(ld.LD_COMPRESS_AUTO,), want=wrong_guess,
+                   large_groups=True)
     many = base.copy()                                 # (a): 25,000 more copies of +-X elsewhere
     rest = np.setdiff1d(np.arange(ns), pos)
     many[rs.choice(rest, 25_000, replace=False)] = X * sign(25_000)
     def right_guess(path, tied, over):
         assert tied[0] and path[0] == ld.LD_PATH_TIES
     oi, ov, _ = check_compress(many, z, off, k, tag="tied guess, enough ties", strategies=(ld.LD_COMPRESS_AUTO,),
-                               want=right_guess)
+                               want=right_guess, large_groups=True)
     assert np.count_nonzero(np.abs(ov) == X) == k_s - 200 and np.count_nonzero(np.abs(ov) > X) == 200
 
 
@@ -410,8 +459,9 @@ def test_merge_ragged_and_dense_windows(n, W, dens):
 @pytest.mark.parametrize("per8192", [2, 99, 101, 201, 900])
 @pytest.mark.parametrize("W", [3, 66])
 def test_merge_sweep_shapes(n, per8192, W):
-    # the sub-tiles and record windows that a sweep picks by its densest diff, at the edges of sub-tiles and
-    # chunks, with one and two sets of diffs per lane and records bunched at one end in every other diff
+    # the record windows that a sweep of sub-tiles of 2048 elements picks by its densest diff (8192 where at most 16
+    # records per 8192 elements come from each of more than ten), at the edges of sub-tiles and chunks, with one
+    # and two sets of diffs per lane and records bunched at one end in every other diff
     rs = np.random.RandomState(n + per8192 + W)
     K = max(1, n * per8192 // 8192)
     idxs = []
@@ -425,6 +475,48 @@ def test_merge_sweep_shapes(n, per8192, W):
     ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, ws, strategy=ld.LD_MERGE_SWEEP)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
+@pytest.mark.parametrize("n", [79_999_999, 80_000_003])
+@pytest.mark.parametrize("per8192", [82, 150, 300])
+@pytest.mark.parametrize("W", [3, 66])
+@pytest.mark.parametrize("kind", ["even", "bunched"])
+def test_merge_sweep_shapes_of_large_arrays(n, per8192, W, kind):
+    # From 80 M elements on the sub-tile follows the densest diff alone: 8192, 4096 or 2048 elements, with one and
+    # two sets of diffs per lane. Bunched: the records of a chunk crowd at its beginning or its end (the guess of
+    # where a sub-tile's records start comes too late, or the window ends before they do), and other
+    # chunks have none. Against one torch operation per diff (product rounded, then the difference).
+    gen = torch.Generator(device=DEV).manual_seed(n + per8192 + W)
+    count = n * per8192 // 8192
+    base = torch.randn(n, device=DEV, generator=gen)
+    w, ref, lr = base.clone(), base, torch.tensor(0.1, device=DEV)
+    diffs = 3 if W == 3 else 6
+    idxs = []
+    for t in range(diffs):
+        if kind == "even":
+            i = torch.randint(0, n, (count,), device=DEV, generator=gen)
+        else:
+            chunk = torch.randint(0, n // 49152 + 1, (count,), device=DEV, generator=gen)
+            if t % 3 == 2:
+                chunk = chunk // 3
+            x = (torch.rand(count, device=DEV, generator=gen) ** 4 * 49152).long().clamp_(max=49151)
+            i = chunk * 49152 + (x if t % 2 == 0 else 49151 - x)
+            i = i[i < n]
+        i = torch.unique(i)
+        assert kind == "bunched" or i.numel() > count * 0.95
+        idxs.append(i.int())
+    # the last diff has exactly the density; the others may fall short of it by their duplicates
+    step = max(1, n // count)
+    idxs[-1] = torch.arange(count, device=DEV, dtype=torch.int32) * step
+    vals = [torch.randn(i.numel(), device=DEV, generator=gen) * 1e-2 for i in idxs]
+    idx, val = [idxs[t % diffs] for t in range(W)], [vals[t % diffs] for t in range(W)]
+    ws = torch.empty(int(ld.load().ld_merge_sparse_workspace(n, W, None)), dtype=torch.uint8, device=DEV)
+    ld.ld_merge_sparse(w, idx, val, 0.1, ws, strategy=ld.LD_MERGE_SWEEP)
+    for i, v in zip(idx, val):
+        at = i.long()
+        ref[at] = ref[at] - lr * v
+    torch.cuda.synchronize()
+    assert torch.equal(w.view(torch.int32), ref.view(torch.int32))
 
 
 @pytest.mark.parametrize("n", [100, 4095, 4097, 100003])
@@ -488,10 +580,9 @@ def test_merge_thin_long_windows(case):
     # Long windows of sparse diffs run a lane per record: the records of a sub-tile go through in rows of
     # 64, elements touched by several diffs of a row are applied in diff order.
     #   random          a few elements shared by two or three diffs
-    #   identical       every diff records the same positions: every record is held back, more per
-    #                   lane than it keeps (the lanes take turns)
+    #   identical       every diff records the same positions: a row holds each element of its diffs once per diff
     #   pairs           diffs 2j and 2j+1 share all positions, values far apart in magnitude
-    #   clustered       one diff puts 300 records into one sub-tile (more than a lane holds)
+    #   clustered       one diff puts 300 records into two sub-tiles that have a few from the others
     #   short_then_long 70 diffs (two sets of lanes), the first ones empty or tiny
     # Each also with the minimum workspace (no per-sub-tile table: the ordinary sweep) - same bits.
     n = 3_000_017
@@ -819,7 +910,8 @@ def test_sparse_adam_replay_parity(n, W, dens, step0):
 @pytest.mark.parametrize("lr,eps", [(1e-4, 1e-8), (-1e-3, 1e-8), (1e-11, 1e-8), (2e3, 1e-8), (1e-3, 1e-12)])
 def test_sparse_adam_windows_and_forms(n, W, dens, lr, eps):
     # either side of the densities where one record window per diff becomes two, sub-tile edges, more
-    # than one group of diffs, and learning rates / eps on either side of the folded form's range
+    # than one group of diffs, and learning rates / eps on either side of the folded form's range (what small
+    # learning rates do to w: the next test)
     rs = np.random.RandomState(n + W)
     w0 = synth.base_weights(n).numpy()
     m0 = (rs.standard_normal(n) * 1e-4).astype(np.float32)
@@ -837,6 +929,37 @@ def test_sparse_adam_windows_and_forms(n, W, dens, lr, eps):
     np.testing.assert_allclose(w.cpu().numpy(), ref[0], rtol=1e-6, atol=1e-7 * scale)
     np.testing.assert_allclose(m.cpu().numpy(), ref[1], rtol=1e-6, atol=1e-7)
     np.testing.assert_allclose(v.cpu().numpy(), ref[2], rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("lr,eps", [(0.99e-10, 1e-8), (1.01e-10, 1e-8), (1e-11, 1e-8), (-1e-20, 1e-8), (999.0, 1e-8),
+                                    (1001.0, 1e-8), (1e-3, 3.1e-11), (1e-3, 3.3e-11), (1e-3, 999.0), (1e-3, 1001.0)])
+@pytest.mark.parametrize("W", [1, 3])
+def test_adam_updates_either_side_of_the_folded_form(lr, eps, W):
+    # From w = 0, with moments that keep their sign, w is the sum of steps of one sign: it is as exact, relative to
+    # itself, as a step. A step has some ten roundings (two of each moment, root and reciprocal of one unit,
+    # scalars, denominator, product) and w one more per step: below 14 of 6e-8 each, 1e-6 with the scalars' own.
+    n = 5003
+    rs = np.random.RandomState(W)
+    sign = np.where(rs.rand(n) < 0.5, 1, -1)
+    m0 = (sign * rs.uniform(0.5e-4, 2e-4, n)).astype(np.float32)
+    v0 = rs.uniform(1e-9, 1e-6, n).astype(np.float32)
+    z = np.zeros(n, np.float32)
+    idxs = [np.sort(rs.choice(n, 50, replace=False)).astype(np.int32) for _ in range(W)]
+    vals = [rs.uniform(-1e-5, 1e-5, 50).astype(np.float32) for _ in range(W)]
+    hp = dict(lr=lr, beta1=0.9, beta2=0.999, eps=eps)
+    w, m, v = to_gpu(z), to_gpu(m0), to_gpu(v0)
+    ld.ld_merge_sparse_adam(w, m, v, [to_gpu(i) for i in idxs], [to_gpu(x) for x in vals], 4, **hp)
+    ref = oracle.sparse_adam_replay(z, m0, v0, idxs, vals, 4, **hp)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(ref[0]) > 0)
+    np.testing.assert_allclose(w.cpu().numpy(), ref[0], rtol=1e-6, atol=0)
+    # the dense replay runs the same step
+    gb = [to_gpu(rs.uniform(-1e-5, 1e-5, n).astype(np.float32)).bfloat16() for _ in range(W)]
+    w, m, v = to_gpu(z), to_gpu(m0), to_gpu(v0)
+    ld.ld_merge_dense_adam(w, m, v, gb, 4, **hp)
+    every = [np.arange(n, dtype=np.int32)] * W
+    ref = oracle.sparse_adam_replay(z, m0, v0, every, [b.float().cpu().numpy() for b in gb], 4, **hp)
+    np.testing.assert_allclose(w.cpu().numpy(), ref[0], rtol=1e-6, atol=0)
 
 
 def test_sparse_adam_equals_dense_adam_on_full_diffs():
