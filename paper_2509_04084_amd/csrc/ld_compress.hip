@@ -43,7 +43,7 @@
 //     stored unzeroed, and the later passes re-read that tile from the residual;
 //   * a segment with fewer than k candidates, or with more keys in bin b than the
 //     gather list holds, gets its residual restored from the slots and is handed to
-//     the k_full_* kernels: a plain three-level radix select over the whole segment -
+//     k_full: a plain three-level radix select over the whole segment -
 //     unless the overfull bin holds one value only (massive ties: zeros of a frozen
 //     layer, values on a grid): then that value is the threshold and its ties are
 //     taken in index order without leaving the candidate path.
@@ -125,7 +125,7 @@ struct SegState {       // 64 bytes
     uint32_t tau;       // candidate threshold (key); 0: every element, 0xFFFFFFFF: none
     uint32_t sh;        // fine bin of a candidate: min(kTopBin, (key - tau) >> sh)
     uint32_t test;      // guessed threshold T_est >= tau: k_main stores +0 where key >= T_est
-    uint32_t prefix;    // k_bin: threshold bin; k_select: exact threshold T (k_full_*: radix prefix)
+    uint32_t prefix;    // k_bin (small groups: k_gather): threshold bin; k_select: exact threshold T (k_full: radix prefix)
     uint32_t krem;      // rank left inside prefix; finally the number of ties to keep
     uint32_t mode;      // kModeCand | kModeFull | kModeTies
     uint32_t gcount;    // keys gathered from the threshold bin
@@ -146,15 +146,15 @@ struct Ctx {
     GroupDesc* gdesc;       // [n_group]
     SegState* state;        // [n_seg]
     uint32_t* hist;         // [n_seg][kBins]
-    uint32_t* cnt;          // [n_group * 64] candidates stored per tile, or kOverflow
-    float* cval;            // [n_group * 64][slot]
-    uint16_t* cidx;         // [n_group * 64][slot] element offset inside the tile
-    uint32_t* tile_gt;      // [n_group * 64] keys above T
-    uint32_t* tile_eq;      // [n_group * 64] keys equal to T
+    uint32_t* cnt;          // [n_group * tiles] candidates stored per tile, or kOverflow
+    float* cval;            // [n_group * tiles][slot]
+    uint16_t* cidx;         // [n_group * tiles][slot] element offset inside the tile
+    uint32_t* tile_gt;      // [n_group * tiles] keys above T
+    uint32_t* tile_eq;      // [n_group * tiles] keys equal to T
     uint32_t* group_gt;     // [n_group] sums over the group -> records emitted before the group
     uint32_t* group_eq;     // [n_group]                       -> ties before the group
-    uint32_t* gkey;         // [n_seg][kGatherCap]
-    int32_t* gtile;         // [n_seg][kGatherCap]
+    uint32_t* gkey;         // per segment gather_cap entries from gather_first
+    int32_t* gtile;         // per segment gather_cap entries from gather_first
     int32_t* fail_groups;   // [n_group] groups of segments in kModeFull
     uint32_t* fail_count;   // [kSyncWords]: groups listed; arrivals at k_full's grid barrier; its give-up flag
     int32_t n_seg;
@@ -1404,7 +1404,7 @@ __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
     const uint32_t gcap = gather_cap(gr.lo, gr.hi);
     uint32_t T, m;
     uint32_t seen = 0;
-    if (mode == kModeTies) {  // k_bin has found both: nothing to select
+    if (mode == kModeTies) {  // both were found with the threshold bin: nothing to select
         T = st->prefix;
         m = st->krem;
     } else if (ng > gcap) {

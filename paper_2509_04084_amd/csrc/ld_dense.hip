@@ -15,9 +15,10 @@
 namespace {
 
 // Consecutive 16 KB pieces of an array that an XCD is given at a time: runs of 1 MB, so that all
-// XCDs stream the same neighbourhood. Against one contiguous eighth per XCD: a copy of 202 M 16-bit
-// elements 138 -> 131 us, 500 M 336 -> 321, 2 G 1350 -> 1317; the Adam replay of four steps on
-// 2 G elements 11.08 -> 10.47 ms. Runs of 1, 4, 8, 16 and 32 pieces: behind in one or the other.
+// XCDs stream the same neighbourhood. Against one contiguous eighth per XCD (two runs each): a copy of
+// 202 M 16-bit elements 138 -> 130-134 us, 500 M 338-342 -> 324, 2 G 1345 -> 1322; the Adam replay of four
+// steps on 20 M elements 113-115 -> 106 us, on 2 G 10.6-11.2 -> 10.3-10.6 ms, where it moves as much with the
+// placement of the arrays. Runs of 1, 4, 8, 16 and 32 pieces: behind in one or the other.
 constexpr uint32_t kXcdRun = 64;
 
 // ----------------------------------------------------------------- snapshot

@@ -28,7 +28,7 @@
 
 namespace {
 
-constexpr int kSub = 8192;                 // elements of the largest sub-tile of a sweep (32 KB of LDS, 5 waves per CU)
+constexpr int kSub = 8192;                 // elements of the largest sub-tile of a sweep (32 KB of LDS and the spare word: 4 waves per CU)
 constexpr int64_t kFewSubs = 80000000;     // elements below which such sub-tiles are too few
 constexpr int kMargin = 24;                // records the window starts before the interpolated position
 constexpr int kSweepGroup = kTableMax;     // diffs per sweep: a lane keeps the chunk ranges of two of them
@@ -229,8 +229,9 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
 // Sub-tiles where the diffs are dense go through diff after diff (kThinDense).
 //
 // Bound by the instructions and LDS round trips per row (two to three bids each), next the tile's 16 KB
-// of LDS, which leave eight waves per CU. 124 M elements, 100 diffs of 0.1 %: 296 -> 235 us against a lane per
-// DIFF, whose slots were mostly empty; sub-tiles of 2048 / 8192 elements: 272 / 267 us, 1024 owner slots: 239.
+// of LDS, which leave eight waves per CU. 124 M elements, 100 diffs of 0.1 %: 296 -> 235-240 us against a lane per
+// DIFF, whose slots were mostly empty; sub-tiles of 2048 / 8192 elements: 272 / 267 us, 1024 owner slots: 239. Diffs that
+// share half of their positions with the one before (the bids of a row then go through in turn): 265 us.
 constexpr int kThinSub = 4096;     // elements of a wave's sub-tile in this kernel
 constexpr int kThinAhead = 8;      // rows of 64 records requested together
 constexpr int kOwner = 256;        // slots of the owner table
@@ -243,7 +244,7 @@ constexpr int kThinDeep = 16;
 static_assert(kThinSub % (4 * LD_WAVE) == 0 && kThinSub <= 4096 && kOwner == 256, "whole rows of 16-byte accesses; see ld_thin_slot");
 
 // tab[t * (nsub + 1) + s] = number of records of diff t with idx < s * kThinSub, s = 0 .. nsub.
-// A thread looks at four consecutive records (one 16-byte load; the arrays of this path are
+// A thread looks at four consecutive records (one 16-byte load; the index arrays of this path are
 // 16-byte aligned) and at the one before them, and fills the entries between the sub-tiles of
 // neighbouring records; the thread that meets record K closes the row.
 constexpr int kSubtabPer = 4;
@@ -537,7 +538,7 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
         launch_chunks(tb, gw, n, nchunk, ctab, s);
         if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
         // Sub-tile and record windows by the records of the densest diff in 8192 elements and by how many
-        // sub-tiles there are. 2048 elements (20 waves per CU instead of 5) while the sub-tiles of 8192 make
+        // sub-tiles there are. 2048 elements (19 waves per CU instead of 4) while the sub-tiles of 8192 make
         // only a few rounds of the chip, with one window per diff where its records fit: 25.6 M elements,
         // 50 diffs of 1 %: 124 -> 96 us, 20 diffs of 2 %: 118 -> 73; the same at 100 M. Beyond, a wave with
         // more records per diff than its windows hold fetches the rest by itself: smaller sub-tiles up to
