@@ -14,13 +14,14 @@
 // scatter the records that fall into the sub-tile, read the tiles back, apply the shared Adam
 // step to all 16 elements, clear the scattered positions again. The records are found
 // as in ld_merge_sparse: chunk table + interpolated record windows, verified.
-// Bound by the vector ALUs for all but the shortest windows: an element's step is four full-rate
-// operations and two of four issue slots each, 9.5 ms at 39.3 T slots/s for 20 diffs on 1.56 G
-// elements (24 n bytes alone: 6.4 ms). Measured there: 9.6 ms (14.1 ms before, when the
-// step took ten full-rate operations, the window of the next diff was waited for as soon as it
-// was requested, and 2048-element sub-tiles left three waves per SIMD). 2048 elements with the
-// present step: 11.7 ms, bound by latency at two waves per SIMD; 8 KB of LDS and 96 registers
-// let five waves share a SIMD.
+// Bound by the vector ALUs for all but the shortest windows. An element's step is four full-rate operations and two
+// of two issue slots each (measured: v_sqrt_f32 and v_rcp_f32 take 2.1 slots of v_fma_f32; together with the tiles'
+// reads the steps alone take 6.6 ms for 20 diffs on 1.56 G elements), about as long as its 24 n bytes take (6.7 ms
+// without the steps); what a wave does per step and diff besides (addresses, window, scatter, clearing: some 25 vector
+// instructions beside 96) and what of the two does not overlap make it 9.0-9.4 ms. The loop's order (a row of
+// the tiles read while the row before is computed, scalars by lane reads instead of scalar loads, whose counter is
+// the LDS's, windows without masks) took 9.4-9.7 ms to that. 8 KB of LDS and 96 registers let five waves share a SIMD; four
+// run as fast, and so do other waves' priorities and other runs per XCD. 2048-element sub-tiles (two waves per SIMD): 11.7 ms before.
 #include "ld_sparse_common.h"
 
 namespace {
@@ -30,18 +31,42 @@ constexpr int kChunkSubs = 48;             // sub-tiles per chunk of the range t
 static_assert(static_cast<int64_t>(kSub) * kChunkSubs == kChunk, "sub-tiles must tile a chunk");
 constexpr int kRows = kSub / 4 / LD_WAVE;  // 16-byte vectors per lane and array: 4
 constexpr int kMargin = 32;                // records the window starts before the interpolated position
+constexpr int32_t kMany = 1 << 20;
 
-// Writes (or clears) the records of [p, end) that fall into [lo, hi) into the gradient tiles.
+// Adds the records of [p, end) that fall into [lo, hi) to the gradient tiles.
 __device__ __forceinline__ void scatter_from(float* tile1, float* tile2, const int32_t* __restrict__ idx,
                                              const float* __restrict__ val, int32_t p, int32_t end,
-                                             int32_t lo, int32_t hi, bool clear, const LdAdamSteps& a, int lane) {
+                                             int32_t lo, int32_t hi, float omb1, float omb2, int lane) {
     for (; p < end; p += LD_WAVE) {
         const bool have = p + lane < end;
         const int32_t i = have ? idx[p + lane] : INT_MAX;
-        const float v = (have && !clear) ? val[p + lane] : 0.0f;
-        if (i >= lo && i < hi) ld_adam_terms(v, a.one_m_beta1, a.one_m_beta2, tile1[i - lo], tile2[i - lo]);
+        const float v = have ? val[p + lane] : 0.0f;
+        if (i >= lo && i < hi) ld_adam_terms(v, omb1, omb2, tile1[i - lo], tile2[i - lo]);
         if (__ballot(i >= hi)) break;
     }
+}
+
+__device__ __forceinline__ void clear_tiles(float* tile1, float* tile2, int lane) {
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+        reinterpret_cast<ld_f32x4*>(tile1)[j * LD_WAVE + lane] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        reinterpret_cast<ld_f32x4*>(tile2)[j * LD_WAVE + lane] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+}
+
+// First record of the window for sub-tile `part` of a chunk whose records are [b, e): ahead of where the sub-tile's begin
+// if the chunk's are evenly spread. Records of a neighbouring chunk that it reaches do not matter.
+__device__ __forceinline__ int32_t window_begin(int32_t b, int32_t e, int32_t part) {
+    const int32_t p = b + ((e - b) * part) / kChunkSubs - kMargin;
+    return p < 0 ? 0 : p;
+}
+
+// A lane's address as a scalar one of global memory (loads through a flat address would count as LDS accesses too).
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+__device__ __forceinline__ GlobalBytes lane_pointer(uint32_t lo, uint32_t hi, int t) {
+    const uint64_t a = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo), t));
+    const uint64_t b = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hi), t));
+    return reinterpret_cast<GlobalBytes>(a | b << 32);
 }
 
 // WIN 64-record windows per diff are loaded ahead.
@@ -60,6 +85,25 @@ __global__ __launch_bounds__(LD_WAVE, GENERAL || WIN > 1 ? 4 : 5) void k_sparse_
     const int32_t len = static_cast<int32_t>((n - lo64) < kSub ? (n - lo64) : kSub);
     const int32_t lo = static_cast<int32_t>(lo64), hi = lo + len;  // n <= INT_MAX
     const bool full = (len == kSub);
+
+    // lane t: where diff t's records of this chunk lie, its record window's address and its step's
+    // scalars. They are handed to the loop by lane reads: scalar loads there would share their counter
+    // with the LDS reads, and every wait for one of those would be a wait for all.
+    const int32_t chunk = static_cast<int32_t>(sub / kChunkSubs), part = static_cast<int32_t>(sub % kChunkSubs);
+    int32_t c0 = 0, c1 = 0;
+    const int32_t* ip = nullptr;
+    const float* vp = nullptr;
+    float lr_bc1_t = 0.0f, scale_t = 0.0f, eps_t = 0.0f;
+    if (lane < W) {
+        const int32_t* row = ctab + static_cast<int64_t>(lane) * (nchunk + 1) + chunk;
+        c0 = row[0];
+        c1 = row[1];
+        ip = tb.idx[lane];
+        vp = tb.val[lane];
+        if (GENERAL) lr_bc1_t = a.lr_bc1[lane];
+        scale_t = a.root_scale[lane];
+        eps_t = a.eps_s[lane];
+    }
 
     // state of the lane's 16 elements: vector j covers elements (j*64 + lane)*4 .. +3 of the sub-tile
     float ww[kRows][4], mm[kRows][4], vv[kRows][4];
@@ -89,91 +133,129 @@ __global__ __launch_bounds__(LD_WAVE, GENERAL || WIN > 1 ? 4 : 5) void k_sparse_
         }
     }
 
-    // lane t: where diff t's records of this chunk lie (requested first: the record windows wait for it)
-    const int32_t chunk = static_cast<int32_t>(sub / kChunkSubs), part = static_cast<int32_t>(sub % kChunkSubs);
-    int32_t c0 = 0, c1 = 0;
-    if (lane < W) {
-        const int32_t* row = ctab + static_cast<int64_t>(lane) * (nchunk + 1) + chunk;
-        c0 = row[0];
-        c1 = row[1];
-    }
-    // the guess for this sub-tile
-    int32_t start = c0 + ((c1 - c0) * part) / kChunkSubs - kMargin;
-    if (start < c0) start = c0;
-
-#pragma unroll
-    for (int j = 0; j < kRows; ++j) {
-        reinterpret_cast<ld_f32x4*>(tile1)[j * LD_WAVE + lane] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        reinterpret_cast<ld_f32x4*>(tile2)[j * LD_WAVE + lane] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
+    const int32_t start = window_begin(c0, c1, part);
+    const uint64_t ia = reinterpret_cast<uint64_t>(ip + start), va = reinterpret_cast<uint64_t>(vp + start);
+    const uint32_t ia_lo = static_cast<uint32_t>(ia), ia_hi = static_cast<uint32_t>(ia >> 32);
+    const uint32_t va_lo = static_cast<uint32_t>(va), va_hi = static_cast<uint32_t>(va >> 32);
+    // records from the window's begin to the list's end (at most kMany), and whether it begins at or ahead of the chunk's
+    int32_t count = lane < W ? tb.K[lane] - start : 0;
+    if (count > kMany) count = kMany;
+    const int32_t count_t = count * 2 + (start <= c0);
+    clear_tiles(tile1, tile2, lane);
     __syncthreads();  // one wave: only orders the vector fill before the scalar scatters
 
-    // One trip per diff; the record window of the next diff is requested before the current
-    // one is applied (an Adam step over the sub-tile takes longer than a memory round trip).
+    // The scalars are waited for here: left pending, every wait for an LDS read in the loop would be one for all of them.
+    float beta1 = a.beta1, beta2 = a.beta2, omb1 = a.one_m_beta1, omb2 = a.one_m_beta2;
+    asm volatile("" : "+s"(beta1), "+s"(beta2), "+s"(omb1), "+s"(omb2));
+
     struct Window {
-        int32_t s, e, b;        // first position of the window, end and begin of the chunk's records
+        int32_t count;  // as count_t
         int32_t ri[WIN];
         float rv[WIN];
     };
+    // Lanes beyond the list's end take its last record again: twice the same write of the same value. Past W: nothing.
     auto fetch = [&](int32_t t, Window& x) {
-        const int tt = t < W ? t : 0;
-        x.s = __builtin_amdgcn_readlane(start, tt);
-        x.b = __builtin_amdgcn_readlane(c0, tt);
-        x.e = t < W ? __builtin_amdgcn_readlane(c1, tt) : x.s;  // past W: an empty window
-        const int32_t* __restrict__ ip = tb.idx[tt];
-        const float* __restrict__ vp = tb.val[tt];
+        x.count = t < W ? __builtin_amdgcn_readlane(count_t, t) : 1;
+        const int32_t last = (x.count >> 1) - 1;
+        if (last < 0) {
 #pragma unroll
-        for (int u = 0; u < WIN; ++u) {
-            const int32_t p = x.s + u * LD_WAVE + lane;
-            const bool h = p < x.e;
-            x.ri[u] = h ? ip[p] : INT_MAX;
-            x.rv[u] = h ? vp[p] : 0.0f;
+            for (int u = 0; u < WIN; ++u) {
+                x.ri[u] = INT_MAX;
+                x.rv[u] = 0.0f;
+            }
+        } else {
+            const GlobalBytes i0 = lane_pointer(ia_lo, ia_hi, t), v0 = lane_pointer(va_lo, va_hi, t);
+#pragma unroll
+            for (int u = 0; u < WIN; ++u) {
+                int32_t p = u * LD_WAVE + lane;
+                if (p > last) p = last;
+                const uint32_t o = static_cast<uint32_t>(p) * 4u;
+                x.ri[u] = *reinterpret_cast<const __attribute__((address_space(1))) int32_t*>(i0 + o);
+                x.rv[u] = *reinterpret_cast<const __attribute__((address_space(1))) float*>(v0 + o);
+            }
         }
     };
-    Window cur, nxt;
-    fetch(0, cur);
-    // The first window is waited for here: left pending, it would make the compiler wait at the top of
-    // every trip, right after the next window was requested and for that window too.
-#pragma unroll
-    for (int u = 0; u < WIN; ++u) asm volatile("" : "+v"(cur.ri[u]), "+v"(cur.rv[u]));
-#pragma unroll 1
-    for (int32_t t = 0; t < W; ++t) {
-        fetch(t + 1, nxt);
-        // Scatter the step's records. rest: position from which records outside the window follow
-        // (the window ended too early, or began too late), or the end when there are none.
-        uint32_t at[WIN];  // where this lane's records went (kSub and above: nowhere)
-        int32_t rest = cur.e;
-        const int32_t first = __builtin_amdgcn_readfirstlane(cur.ri[0]);
-        const bool hit = cur.s == cur.b || first <= lo;  // the window begins before the sub-tile's records do
+    // Puts the step's records into the (zero) tiles; at: where this lane's went (len and above: nowhere).
+    // True if some did not come from the window: it ended too early, or began too late.
+    auto scatter = [&](int32_t t, const Window& x, uint32_t (&at)[WIN]) {
+        const bool hit = (x.count & 1) || __builtin_amdgcn_readfirstlane(x.ri[0]) <= lo;
+        const bool more = !hit || ((x.count >> 1) > WIN * LD_WAVE && __builtin_amdgcn_readlane(x.ri[WIN - 1], LD_WAVE - 1) < hi);
 #pragma unroll
         for (int u = 0; u < WIN; ++u) {
-            at[u] = static_cast<uint32_t>(cur.ri[u]) - static_cast<uint32_t>(lo);
-            if (!hit || at[u] >= static_cast<uint32_t>(len)) at[u] = kSub;
-            if (at[u] < static_cast<uint32_t>(kSub))
-                ld_adam_terms(cur.rv[u], a.one_m_beta1, a.one_m_beta2, tile1[at[u]], tile2[at[u]]);
+            at[u] = static_cast<uint32_t>(x.ri[u]) - static_cast<uint32_t>(lo);
+            if (at[u] < static_cast<uint32_t>(len))
+                ld_adam_terms(x.rv[u], omb1, omb2, tile1[at[u]], tile2[at[u]]);
         }
-        if (!hit) rest = lower_bound_idx(tb.idx[t], cur.b, cur.s, lo);
-        else if (!__ballot(cur.ri[WIN - 1] >= hi)) rest = cur.s + WIN * LD_WAVE;
-        if (rest < cur.e) scatter_from(tile1, tile2, tb.idx[t], tb.val[t], rest, cur.e, lo, hi, false, a, lane);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        const float lr_bc1 = a.lr_bc1[t], scale = a.root_scale[t], eps_s = a.eps_s[t];
-#pragma unroll
-        for (int j = 0; j < kRows; ++j) {
-            const ld_f32x4 p4 = reinterpret_cast<const ld_f32x4*>(tile1)[j * LD_WAVE + lane];
-            const ld_f32x4 q4 = reinterpret_cast<const ld_f32x4*>(tile2)[j * LD_WAVE + lane];
-            const float g1[4] = {p4.x, p4.y, p4.z, p4.w}, g2[4] = {q4.x, q4.y, q4.z, q4.w};
+        if (more) {  // the records ahead of the window too where it began too late: all there are
+            const int32_t* row = ctab + static_cast<int64_t>(t) * (nchunk + 1) + chunk;
+            const int32_t b = row[0], e = row[1];
+            const int32_t from = hit ? window_begin(b, e, part) + WIN * LD_WAVE : lower_bound_idx(tb.idx[t], b, e, lo);
+            scatter_from(tile1, tile2, tb.idx[t], tb.val[t], from, e, lo, hi, omb1, omb2, lane);
+        }
+        return more;
+    };
+    struct Row { ld_f32x4 g1, g2; };
+    auto read_row = [&](int j) {
+        return Row{reinterpret_cast<const ld_f32x4*>(tile1)[j * LD_WAVE + lane],
+                   reinterpret_cast<const ld_f32x4*>(tile2)[j * LD_WAVE + lane]};
+    };
+
+    // One trip per diff. What the vector units need next is always on its way while they work: a row of
+    // the tiles is read while the row before it is computed, the next step's records go into the tiles (cleared
+    // at once behind the last read: LDS operations of a wave complete in order) before this step's last two
+    // rows are computed, and their window was requested a whole step earlier.
+    Window x0, x1;
+    uint32_t at[WIN];
+    fetch(0, x0);
+    fetch(1, x1);
+    bool more = scatter(0, x0, at);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    Row r0 = read_row(0), r1;
+    auto step = [&](int32_t t, Window& later, const Window& next) {
+        fetch(t + 2, later);
+        const float lr_bc1 = GENERAL ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lr_bc1_t), t)) : 0.0f;
+        const float scale = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scale_t), t));
+        const float eps_s = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(eps_t), t));
+        auto compute = [&](int j, const Row& r) {
+            const float g1[4] = {r.g1.x, r.g1.y, r.g1.z, r.g1.w}, g2[4] = {r.g2.x, r.g2.y, r.g2.z, r.g2.w};
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                ld_adam_step<GENERAL>(ww[j][q], mm[j][q], vv[j][q], g1[q], g2[q], a.beta1, a.beta2, lr_bc1, scale, eps_s);
-            // at most two rows of the tiles in registers at a time (five waves per SIMD: 96 registers)
-            if (j % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-        }
+                ld_adam_step<GENERAL>(ww[j][q], mm[j][q], vv[j][q], g1[q], g2[q], beta1, beta2, lr_bc1, scale, eps_s);
+            // keeps the row's work here (the compiler would sink it below the branches that follow) and the
+            // moments out of the registers the row was read into (they would be moved back every trip)
+            asm volatile("" : "+v"(ww[j][0]), "+v"(ww[j][1]), "+v"(ww[j][2]), "+v"(ww[j][3]) : "v"(r.g1), "v"(r.g2));
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        r1 = read_row(1);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(0, r0);
+        r0 = read_row(2);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(1, r1);
+        r1 = read_row(3);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) {
+            clear_tiles(tile1, tile2, lane);
+        } else {
 #pragma unroll
-        for (int u = 0; u < WIN; ++u)
-            if (at[u] < static_cast<uint32_t>(kSub)) tile1[at[u]] = tile2[at[u]] = 0.0f;
-        if (rest < cur.e) scatter_from(tile1, tile2, tb.idx[t], tb.val[t], rest, cur.e, lo, hi, true, a, lane);
-        cur = nxt;
+            for (int u = 0; u < WIN; ++u)
+                if (at[u] < static_cast<uint32_t>(len)) tile1[at[u]] = tile2[at[u]] = 0.0f;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        more = scatter(t + 1, next, at);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_sched_barrier(0);
+        compute(2, r0);
+        r0 = read_row(0);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(3, r1);
+    };
+#pragma unroll 1
+    for (int32_t t = 0; t < W; t += 2) {
+        step(t, x0, x1);
+        if (t + 1 == W) break;
+        step(t + 1, x1, x0);
     }
 
     int back = lane;  // the addresses are made again here: kept across the loop they would spill

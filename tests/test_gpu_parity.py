@@ -931,6 +931,37 @@ def test_sparse_adam_windows_and_forms(n, W, dens, lr, eps):
     np.testing.assert_allclose(v.cpu().numpy(), ref[2], rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("n", [49152 * 3, 49152 * 2 + 1027])
+def test_sparse_adam_record_windows_that_miss(n):
+    # where the records of a chunk of 49152 elements lie is guessed from its ends: lists shorter than a window of 64,
+    # empty ones, lists that end inside a window, records crowded at a chunk's begin (the window comes too early and
+    # ends too early) or end (too late), and on a few sub-tiles of 1024 alone, all in one window
+    rs = np.random.RandomState(n)
+    chunk = 49152
+
+    def some(lo, hi, k):
+        return lo + rs.choice(hi - lo, k, replace=False)
+
+    idxs = [some(0, n, 63), np.zeros(0, np.int64), some(0, n, 64), some(chunk - 900, chunk, 700), some(chunk, chunk + 1500, 900),
+            np.concatenate([some(0, 1024, 65), some(2 * chunk - 1024, 2 * chunk, 100)]), some(n - 1000, n, 300), some(0, n, 1),
+            np.concatenate([some(chunk, chunk + 1024, 400), some(chunk + 40 * 1024, chunk + 41 * 1024, 20), some(n - 3, n, 3)]),
+            some(0, n, n // 60)]
+    idxs = [np.sort(np.unique(i)).astype(np.int32) for i in idxs]
+    vals = [(rs.standard_normal(i.size) * 1e-2).astype(np.float32) for i in idxs]
+    w0 = synth.base_weights(n).numpy()
+    m0 = (rs.standard_normal(n) * 1e-4).astype(np.float32)
+    v0 = (rs.standard_normal(n) ** 2 * 1e-6).astype(np.float32)
+    hp = dict(lr=1e-4, **synth.ADAM)
+    w, m, v = to_gpu(w0), to_gpu(m0), to_gpu(v0)
+    ld.ld_merge_sparse_adam(w, m, v, [to_gpu(i) for i in idxs], [to_gpu(x) for x in vals], 2, **hp)
+    torch.cuda.synchronize()
+    ref = oracle.sparse_adam_replay(w0, m0, v0, idxs, vals, 2, **hp)
+    # as above: a few roundings of 6e-8 per step; a record put wrong moves v by 1e-7 of its 1e-6
+    np.testing.assert_allclose(w.cpu().numpy(), ref[0], rtol=1e-6, atol=1e-7)
+    np.testing.assert_allclose(m.cpu().numpy(), ref[1], rtol=2e-6, atol=1e-9)
+    np.testing.assert_allclose(v.cpu().numpy(), ref[2], rtol=2e-6, atol=0)
+
+
 @pytest.mark.parametrize("lr,eps", [(0.99e-10, 1e-8), (1.01e-10, 1e-8), (1e-11, 1e-8), (-1e-20, 1e-8), (999.0, 1e-8),
                                     (1001.0, 1e-8), (1e-3, 3.1e-11), (1e-3, 3.3e-11), (1e-3, 999.0), (1e-3, 1001.0)])
 @pytest.mark.parametrize("W", [1, 3])
