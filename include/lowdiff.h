@@ -194,8 +194,8 @@ ld_status ld_snapshot_layers(const void* const* src, void* const* dst, const int
  *   workspace  dev, 256-byte aligned, ld_merge_sparse_workspace() bytes. With K = NULL
  *              the query gives the minimum (the call fails with less); with K it
  *              gives what the window's shape asks for, which is more for long windows
- *              of sparse diffs (they then run a lane per record instead of as
- *              ordinary sweeps; same result, less time)
+ *              of sparse diffs and for small arrays (they then look their records up in
+ *              a table instead of guessing where they lie; same result, less time)
  * Errors: LD_ERR_NULL, LD_ERR_RANGE, LD_ERR_ALIGN, LD_ERR_WORKSPACE, LD_ERR_HIP.
  */
 size_t    ld_merge_sparse_workspace(int64_t n, int32_t W, const int64_t* K /* host, or NULL */);

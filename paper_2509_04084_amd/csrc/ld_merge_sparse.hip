@@ -18,7 +18,10 @@
 //              sub-tile.  The guess is checked (the window must begin before the
 //              sub-tile does, and end after it); a miss costs a binary search
 //              inside the chunk or one more window, never a wrong result.
-//              HBM traffic: 8n + 8*sum(K) bytes + the chunk table.
+//              HBM traffic: 8n + 8*sum(K) bytes + the chunk table. Long windows of
+//              sparse diffs and small arrays know exactly where the records lie, from a table
+//              that one pass over the index arrays makes (k_subtab), if the workspace holds it:
+//              a lane per record (k_merge_thin), a window per diff (k_merge_rows).
 //  * scatter - one kernel per diff, one thread per record; for windows that
 //              touch only a small part of w.
 #include <atomic>
@@ -243,32 +246,47 @@ constexpr uint32_t kThinDense = 128;
 constexpr int kThinDeep = 16;
 static_assert(kThinSub % (4 * LD_WAVE) == 0 && kThinSub <= 4096 && kOwner == 256, "whole rows of 16-byte accesses; see ld_thin_slot");
 
-// tab[t * (nsub + 1) + s] = number of records of diff t with idx < s * kThinSub, s = 0 .. nsub.
-// A thread looks at four consecutive records (one 16-byte load; the index arrays of this path are
+// tab[t * (nsub + 1) + s] = number of records of diff t with idx < s * SUB, s = 0 .. nsub.
+// A thread looks at kSubtabPer consecutive records (16-byte loads; the index arrays of these paths are
 // 16-byte aligned) and at the one before them, and fills the entries between the sub-tiles of
 // neighbouring records; the thread that meets record K closes the row.
-constexpr int kSubtabPer = 4;
+// Records per thread: 4 / 8 / 16 67.1 / 65.3 / 67.8 us per call with 51 MB of indices, 307 / 298 / 312 with 240 MB.
+constexpr int kSubtabPer = 8;
+// Sub-tiles without a record that a thread fills by itself; the lanes of its wave share longer stretches (12 diffs of
+// 1 % in the first tenth of 110 M elements: 1890 us a call with one thread filling the other nine).
+constexpr int32_t kSubtabWide = 16;
 
+template <int SUB>
 __global__ __launch_bounds__(256) void k_subtab(DiffTable tb, int32_t nsub, int32_t* __restrict__ tab) {
     const int t = blockIdx.y;
     const int32_t K = tb.K[t];
     const int32_t* __restrict__ idx = tb.idx[t];
     const int32_t j0 = (static_cast<int32_t>(blockIdx.x) * 256 + static_cast<int32_t>(threadIdx.x)) * kSubtabPer;
-    if (j0 > K) return;
-    // the block of four that holds record j0 lies inside the array's last 16 bytes at worst
-    ld_u32x4 q = {0u, 0u, 0u, 0u};
-    if (j0 < K) q = *reinterpret_cast<const ld_u32x4*>(idx + j0);
-    const int32_t v[kSubtabPer] = {static_cast<int32_t>(q.x), static_cast<int32_t>(q.y), static_cast<int32_t>(q.z),
-                                   static_cast<int32_t>(q.w)};
-    int32_t a = j0 == 0 ? -1 : idx[j0 - 1] / kThinSub;
+    const int lane = ld_lane();
+    // a block of four that begins at a record lies inside the array's last 16 bytes at worst
+    ld_u32x4 q[kSubtabPer / 4];
+#pragma unroll
+    for (int u = 0; u < kSubtabPer / 4; ++u) {
+        q[u] = ld_u32x4{0u, 0u, 0u, 0u};
+        if (j0 + 4 * u < K) q[u] = *reinterpret_cast<const ld_u32x4*>(idx + j0 + 4 * u);
+    }
+    int32_t a = j0 == 0 || j0 > K ? -1 : idx[j0 - 1] / SUB;
     int32_t* row = tab + static_cast<int64_t>(t) * (nsub + 1);
 #pragma unroll
     for (int c = 0; c < kSubtabPer; ++c) {
         const int32_t j = j0 + c;
-        if (j > K) break;
-        const int32_t b = j == K ? nsub : v[c] / kThinSub;
-        const LdThinEntries fill = ld_thin_entries(a, b, nsub);
-        for (int32_t s = fill.first; s <= fill.last; ++s) row[s] = j;
+        const int32_t b = j >= K ? nsub : static_cast<int32_t>(q[c / 4][c % 4]) / SUB;
+        LdThinEntries fill = ld_thin_entries(a, b, nsub);
+        if (j > K) fill = LdThinEntries{0, -1};
+        const bool wide = fill.last - fill.first >= kSubtabWide;
+        if (!wide)
+            for (int32_t s = fill.first; s <= fill.last; ++s) row[s] = j;
+        for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {  // a stretch without records: the wave's lanes share it
+            const int l = __builtin_ctzll(todo);
+            const int32_t first = __builtin_amdgcn_readlane(fill.first, l), last = __builtin_amdgcn_readlane(fill.last, l);
+            const int32_t value = __builtin_amdgcn_readlane(j, l);
+            for (int32_t s = first + lane; s <= last; s += LD_WAVE) row[s] = value;
+        }
         a = b;
     }
 }
@@ -420,6 +438,99 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
     }
 }
 
+// ------------------------------------------------ arrays that are a few rounds of the chip: windows from a table
+//
+// The sweep's windows hold three times the records that a small sub-tile needs: the margins of a guess. While w is not many
+// times what the chip holds at once, that is what its time goes to (25.6 M elements, 50 diffs of 1 %: 87 us, without
+// the windows 36). Here k_subtab says where every diff's records of every sub-tile lie, one pass over the index arrays;
+// a window is those records and no more, and PRE diffs' windows are requested together.
+// 25.6 M elements, 50 diffs of 1 %: 96 -> 72 us with the table's pass (13; 92 -> 66 on records that the last-level cache
+// holds, as in what follows), 5 M, 20 diffs: 32 -> 16, 25 M, 100 diffs: 222 -> 163, 25 M, 50 diffs crowded in the first tenth
+// 250 -> 85. Sub-tiles of 4096: 73 us for the first (nine waves per CU), of 2560: 65; 10 / 13 / 17 / 25 diffs a batch 67.6 / 66.8 /
+// 66.8 / 67.5. The update left to the LDS unit's float add: 25 us more (sub-tiles of 4096).
+constexpr int kRowSub = 2048;
+
+template <int PRE, int WIN, int SETS>
+__global__ __launch_bounds__(LD_WAVE) void k_merge_rows(float* __restrict__ w, int64_t n, int32_t nsub, DiffTable tb,
+                                                        int32_t W, const int32_t* __restrict__ tab, float lr) {
+    __shared__ float tile[kRowSub + 4];  // and the spare word of apply_records
+    const int lane = threadIdx.x;
+    // runs of 16 sub-tiles per XCD (4 / 64: 69.7 / 67.0 us against 66.3), not eighths of w: records crowd in places
+    const int64_t sub = ld_xcd_piece<16>(blockIdx.x, gridDim.x);
+    if (sub * kRowSub >= n) return;
+    const int64_t lo64 = sub * kRowSub;
+    const int32_t len = static_cast<int32_t>((n - lo64) < kRowSub ? (n - lo64) : kRowSub);
+    const int32_t lo = static_cast<int32_t>(lo64);
+    const bool full = (len == kRowSub);
+
+    WindowTable rec[SETS];  // lane t: the records of diffs t and t + 64 inside this sub-tile
+#pragma unroll
+    for (int h = 0; h < SETS; ++h) {
+        const int t = h * LD_WAVE + lane;
+        rec[h] = WindowTable{0u, 0u, 0u, 0u, 0};
+        if (t < W) {
+            const int32_t* row = tab + static_cast<int64_t>(t) * (nsub + 1) + sub;
+            rec[h] = window_at(tb, t, row[0], static_cast<int32_t>(ld_thin_count(row[0], row[1], kRowSub)));
+        }
+    }
+    ld_f32x4 x[kRowSub / 4 / LD_WAVE];
+    if (full) {
+        const ld_f32x4* src = reinterpret_cast<const ld_f32x4*>(w + lo64);
+#pragma unroll
+        for (int j = 0; j < kRowSub / 4 / LD_WAVE; ++j) x[j] = ld_nt_load(src + j * LD_WAVE + lane);
+    }
+    Window<WIN> rows[PRE];
+    auto load_rows = [&](int32_t t0) {
+#pragma unroll
+        for (int g = 0; g < PRE; ++g) {
+            const int32_t t = t0 + g;
+            if (SETS == 1 || t < LD_WAVE) load_window(rows[g], rec[0], t, t < W, lane);
+            else load_window(rows[g], rec[SETS - 1], t - LD_WAVE, t < W, lane);
+        }
+    };
+    load_rows(0);
+    if (full) {
+#pragma unroll
+        for (int j = 0; j < kRowSub / 4 / LD_WAVE; ++j) reinterpret_cast<ld_f32x4*>(tile)[j * LD_WAVE + lane] = x[j];
+    } else {
+        for (int32_t e = lane; e < len; e += LD_WAVE) tile[e] = w[lo64 + e];
+    }
+    __syncthreads();  // one wave: only orders the vector fill before the scalar updates
+#pragma unroll 1
+    for (int32_t t0 = 0; t0 < W; t0 += PRE) {
+        if (t0 > 0) load_rows(t0);
+        bool crowded = false;
+#pragma unroll
+        for (int g = 0; g < PRE; ++g) crowded |= rows[g].count > WIN * LD_WAVE;
+        if (!crowded) {
+#pragma unroll
+            for (int g = 0; g < PRE; ++g) {
+                if (rows[g].count > 0) apply_records<kRowSub>(tile, rows[g].ri, rows[g].rv, lo, lr);
+                __builtin_amdgcn_wave_barrier();  // keep diff g's LDS traffic ahead of diff g+1's
+            }
+        } else {  // diff after diff, eight times 64 records requested together
+#pragma unroll 1
+            for (int32_t t = t0; t < t0 + PRE && t < W; ++t) {
+                const WindowTable& r = SETS == 1 || t < LD_WAVE ? rec[0] : rec[SETS - 1];
+                const int l = t & (LD_WAVE - 1);
+                const int32_t* ip = (const int32_t*)lane_pointer(r.idx_lo, r.idx_hi, l);
+                const float* vp = (const float*)lane_pointer(r.val_lo, r.val_hi, l);
+                apply_from<kRowSub>(tile, ip, vp, 0, __builtin_amdgcn_readlane(r.count, l), lo, INT_MAX, lr, lane);
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    }
+    __syncthreads();
+    if (full) {
+        ld_f32x4* dst = reinterpret_cast<ld_f32x4*>(w + lo64);
+#pragma unroll
+        for (int j = 0; j < kRowSub / 4 / LD_WAVE; ++j)
+            ld_nt_store(reinterpret_cast<const ld_f32x4*>(tile)[j * LD_WAVE + lane], dst + j * LD_WAVE + lane);
+    } else {
+        for (int32_t e = lane; e < len; e += LD_WAVE) w[lo64 + e] = tile[e];
+    }
+}
+
 __global__ __launch_bounds__(256) void k_merge_scatter(float* __restrict__ w,
                                                        const int32_t* __restrict__ idx,
                                                        const float* __restrict__ val, int32_t K,
@@ -440,28 +551,81 @@ void launch_sweep(float* w, int64_t n, int32_t nchunk, const DiffTable& tb, int3
     else k_merge_sweep<SUB, PRE, WIN, 2><<<grid, wave, 0, s>>>(w, n, nchunk, tb, W, ctab, lr);
 }
 
+template <int SUB>
+void launch_subtab(const DiffTable& tb, int32_t gw, int64_t most, int32_t nsub, int32_t* tab, hipStream_t s) {
+    k_subtab<SUB><<<dim3(static_cast<uint32_t>(most / (256 * kSubtabPer) + 1), gw), dim3(256), 0, s>>>(tb, nsub, tab);
+}
+
+template <int PRE, int WIN>
+void launch_rows(float* w, int64_t n, int32_t nsub, const DiffTable& tb, int32_t W, const int32_t* tab, float lr, hipStream_t s) {
+    const dim3 grid(static_cast<uint32_t>((nsub + 7) / 8 * 8)), wave(LD_WAVE);
+    if (W <= LD_WAVE) k_merge_rows<PRE, WIN, 1><<<grid, wave, 0, s>>>(w, n, nsub, tb, W, tab, lr);
+    else k_merge_rows<PRE, WIN, 2><<<grid, wave, 0, s>>>(w, n, nsub, tb, W, tab, lr);
+}
+
 }  // namespace
 
 namespace {
 
-// A group of `gw` diffs whose largest holds `most` records is "thin" when a diff brings at most ~48
-// records to 8192 elements and the group is long: it then runs a lane per record (k_merge_thin). Measured,
-// us with the sweep / a lane per record: 20 diffs of 0.25 % on 100 M elements 164 / 148, 60 of 0.5 % on 25 M
-// 113 / 84, 40 of 0.5 % on 100 M 240 / 228; 20 of 1 % on 100 M 199 / 225.
-bool thin_group(int64_t n, int32_t gw, int64_t most) { return gw > 10 && most * kSub <= 48 * n; }
+// A group of `gw` diffs whose largest holds `most` records is "thin" when a diff brings few records to 8192 elements and the
+// group is long: it then runs a lane per record (k_merge_thin). At most 48 for large arrays; measured,
+// us with the sweep / a lane per record: 20 diffs of 0.25 % on 100 M elements 164 / 148, 40 of 0.5 % 240 / 228; 20 of 1 %
+// 199 / 225. At most 20 for small ones, where k_merge_rows is the other way: 60 diffs of 0.25 % on 25 M 60 us either way, 30 of
+// 0.5 % 49 (a lane per record 62), 100 of 0.1 % 83 (57).
+bool thin_group(int64_t n, int32_t gw, int64_t most) { return gw > 10 && most * kSub <= (n < kFewSubs ? 20 : 48) * n; }
+
+// Windows from a table (k_merge_rows), sweep / rows in us: 200 M elements, 4 diffs of 1 % 280 / 279, 100 M, 20 of 1 % 192 / 176,
+// 60 of 1 % 361 / 298; but 170 M, 30 of 2 % 449 / 462, 300 M, 9 of 0.5 % 413 / 424 and 600 M, 20 of 1 % 996 / 1100: the pass
+// over the index arrays costs what the windows save. Two windows where a sub-tile's records outgrow one (2 % a diff): 25 M, 50 of 3.3 %
+// 170 / 127, 3 M, 20 of 2.5 % 29 / 18, but 100 M, 30 of 3.3 % 358 / 368.
+constexpr int64_t kRowsMost = 120000000;
+int rows_windows(int64_t n, int64_t most) {  // 64-record windows per diff, 0: another way
+    if (n < kRowsMost && most * kSub <= 168 * n) return 1;
+    return n < kFewSubs ? 2 : 0;
+}
+
 
 size_t chunk_table_bytes(int64_t n, int32_t W) {
     const int64_t group = W < kSweepGroup ? W : kSweepGroup;
     return ld_round_up(static_cast<size_t>(group) * (static_cast<size_t>(chunks(n)) + 1) * 4, 256);
 }
 
-size_t sub_table_bytes(int64_t n, int32_t gw) {
-    return ld_round_up(static_cast<size_t>(gw) * (static_cast<size_t>((n + kThinSub - 1) / kThinSub) + 1) * 4, 256);
+size_t sub_table_bytes(int64_t n, int32_t gw, int32_t sub) {
+    return ld_round_up(static_cast<size_t>(gw) * (static_cast<size_t>((n + sub - 1) / sub) + 1) * 4, 256);
+}
+
+// Bytes of the per-sub-tile table that a group would run with (0: it runs as a sweep).
+size_t group_table_bytes(int64_t n, int32_t gw, int64_t most) {
+    if (thin_group(n, gw, most)) return sub_table_bytes(n, gw, kThinSub);
+    return rows_windows(n, most) ? sub_table_bytes(n, gw, kRowSub) : 0;
+}
+
+// Whether a window that would be scattered runs faster in groups with tables, and can. A launch of the scatter takes 3.5 us
+// and 46 ps per record, a group some 10 us and 1.3 ps per element of w (5 M elements, 10 diffs of 0.1 %: 36 us scattered, 13
+// with a table; 25 M, 5 diffs: 22 and 40).
+bool tables_pay(const int32_t* const* idx, const int64_t* K, int32_t W, int64_t n, int64_t total, const void* workspace,
+                size_t workspace_bytes) {
+    const int32_t groups = (W + kSweepGroup - 1) / kSweepGroup;
+    int32_t launches = 0;
+    for (int32_t t = 0; t < W; ++t) launches += K[t] > 0;
+    if (groups * (10.0 + 1.3e-6 * static_cast<double>(n)) >= 3.5 * launches + 46e-6 * static_cast<double>(total)) return false;
+    if (!workspace || !ld_aligned(workspace, 256) || workspace_bytes < chunk_table_bytes(n, W)) return false;
+    for (int32_t g0 = 0; g0 < W; g0 += kSweepGroup) {
+        const int32_t gw = (W - g0) < kSweepGroup ? (W - g0) : kSweepGroup;
+        int64_t most = 0;
+        for (int32_t t = g0; t < g0 + gw; ++t) {
+            most = K[t] > most ? K[t] : most;
+            if (!ld_aligned(idx[t], 16)) return false;
+        }
+        const size_t table = group_table_bytes(n, gw, most);
+        if (table == 0 || workspace_bytes < table) return false;
+    }
+    return true;
 }
 
 }  // namespace
 
-// The chunk table always; for thin groups (when K is given) the larger per-sub-tile table, without
+// The chunk table always; for thin groups and small arrays (when K is given) the larger per-sub-tile table, without
 // which they run as ordinary sweeps.
 extern "C" size_t ld_merge_sparse_workspace(int64_t n, int32_t W, const int64_t* K) {
     if (n <= 0 || W <= 0) return 256;
@@ -471,7 +635,8 @@ extern "C" size_t ld_merge_sparse_workspace(int64_t n, int32_t W, const int64_t*
             const int32_t gw = (W - g0) < kSweepGroup ? (W - g0) : kSweepGroup;
             int64_t most = 0;
             for (int32_t t = g0; t < g0 + gw; ++t) most = K[t] > most ? K[t] : most;
-            if (thin_group(n, gw, most) && sub_table_bytes(n, gw) > need) need = sub_table_bytes(n, gw);
+            const size_t table = group_table_bytes(n, gw, most);
+            if (table > need) need = table;
         }
     }
     return need;
@@ -495,7 +660,8 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
     // measured on 1.56 G elements: a scattered record costs 46 ps, the sweep 1.35 ps per element of w
     // plus little per record: they meet where the window holds n / 34 records
     if (strategy == LD_MERGE_AUTO)
-        strategy = (total * 32 >= n) ? LD_MERGE_SWEEP : LD_MERGE_SCATTER;
+        strategy = (total * 32 >= n || tables_pay(idx, K, W, n, total, workspace, workspace_bytes)) ? LD_MERGE_SWEEP
+                                                                                                : LD_MERGE_SCATTER;
 
     if (strategy == LD_MERGE_SCATTER) {
         for (int32_t t = 0; t < W; ++t) {
@@ -522,16 +688,20 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
             tb.val[t] = live ? val[g0 + t] : nullptr;
             tb.K[t] = live ? static_cast<int32_t>(K[g0 + t]) : 0;
             if (live && K[g0 + t] > most) most = K[g0 + t];
-            if (live && !(ld_aligned(idx[g0 + t], 16) && ld_aligned(val[g0 + t], 16))) aligned16 = false;
+            if (live && !ld_aligned(idx[g0 + t], 16)) aligned16 = false;
         }
         const dim3 wave(LD_WAVE);
-        const bool thin = thin_group(n, gw, most);
-        if (thin && aligned16 && workspace_bytes >= sub_table_bytes(n, gw)) {  // a lane per record (else: the sweep below)
-            const int32_t tsub = static_cast<int32_t>((n + kThinSub - 1) / kThinSub);
-            const dim3 tgrid((tsub + 7) / 8 * 8);
-            k_subtab<<<dim3(static_cast<uint32_t>(most / (256 * kSubtabPer) + 1), gw), dim3(256), 0, s>>>(tb, tsub, ctab);
+        const size_t table = group_table_bytes(n, gw, most);
+        if (table > 0 && aligned16 && workspace_bytes >= table) {  // (else: the sweep below)
+            const bool thin = thin_group(n, gw, most);
+            const int32_t sub = thin ? kThinSub : kRowSub;
+            const int32_t nsub = static_cast<int32_t>((n + sub - 1) / sub);
+            if (thin) launch_subtab<kThinSub>(tb, gw, most, nsub, ctab, s);
+            else launch_subtab<kRowSub>(tb, gw, most, nsub, ctab, s);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-            k_merge_thin<<<tgrid, wave, 0, s>>>(w, n, tsub, tb, gw, ctab, lr);
+            if (thin) k_merge_thin<<<dim3((nsub + 7) / 8 * 8), wave, 0, s>>>(w, n, nsub, tb, gw, ctab, lr);
+            else if (rows_windows(n, most) == 1) launch_rows<17, 1>(w, n, nsub, tb, gw, ctab, lr, s);
+            else launch_rows<10, 2>(w, n, nsub, tb, gw, ctab, lr, s);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
             continue;
         }

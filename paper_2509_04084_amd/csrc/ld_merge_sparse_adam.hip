@@ -61,14 +61,6 @@ __device__ __forceinline__ int32_t window_begin(int32_t b, int32_t e, int32_t pa
     return p < 0 ? 0 : p;
 }
 
-// A lane's address as a scalar one of global memory (loads through a flat address would count as LDS accesses too).
-typedef const __attribute__((address_space(1))) char* GlobalBytes;
-__device__ __forceinline__ GlobalBytes lane_pointer(uint32_t lo, uint32_t hi, int t) {
-    const uint64_t a = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo), t));
-    const uint64_t b = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hi), t));
-    return reinterpret_cast<GlobalBytes>(a | b << 32);
-}
-
 // WIN 64-record windows per diff are loaded ahead.
 template <bool GENERAL, int WIN>
 __global__ __launch_bounds__(LD_WAVE, GENERAL || WIN > 1 ? 4 : 5) void k_sparse_adam(float* __restrict__ w, float* __restrict__ m,

@@ -200,6 +200,60 @@ void launch_chunks(const DiffTable& tb, int32_t ndiff, int64_t n, int32_t nchunk
     k_chunks<<<dim3((nchunk + 1 + kChunkSpan - 1) / kChunkSpan, ndiff), dim3(kChunkThreads), 0, s>>>(tb, n, nchunk, ctab);
 }
 
+// A lane's address as a scalar one of global memory (loads through a flat address would count as LDS accesses too).
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+__device__ __forceinline__ GlobalBytes lane_pointer(uint32_t lo, uint32_t hi, int t) {
+    const uint64_t a = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo), t));
+    const uint64_t b = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hi), t));
+    return reinterpret_cast<GlobalBytes>(a | b << 32);
+}
+
+// Record windows of 64 diffs, a diff per lane: addresses and lengths. A loop over the diffs takes them by lane reads. Scalar
+// loads from the table of diffs would have to be waited for diff by diff, and they share their counter with the
+// LDS's, so that every wait for an LDS access would be one for all.
+struct WindowTable {
+    uint32_t idx_lo, idx_hi, val_lo, val_hi;
+    int32_t count;
+};
+
+// Lane t's entry: diff t's records from position p on.
+__device__ __forceinline__ WindowTable window_at(const DiffTable& tb, int t, int32_t p, int32_t count) {
+    const uint64_t i = reinterpret_cast<uint64_t>(tb.idx[t] + p), v = reinterpret_cast<uint64_t>(tb.val[t] + p);
+    return WindowTable{static_cast<uint32_t>(i), static_cast<uint32_t>(i >> 32), static_cast<uint32_t>(v),
+                       static_cast<uint32_t>(v >> 32), count};
+}
+
+// The first WIN * 64 records of one diff's window, as they are loaded. Lanes beyond its end take its last record again (applied
+// twice, with what was read before the first write, it gives the same); nothing of an empty one.
+template <int WIN>
+struct Window {
+    int32_t count;
+    int32_t ri[WIN];
+    float rv[WIN];
+};
+
+template <int WIN>
+__device__ __forceinline__ void load_window(Window<WIN>& x, const WindowTable& tab, int t, bool live, int lane) {
+    x.count = live ? __builtin_amdgcn_readlane(tab.count, t) : 0;
+    if (x.count <= 0) {
+#pragma unroll
+        for (int u = 0; u < WIN; ++u) {
+            x.ri[u] = INT_MAX;
+            x.rv[u] = 0.0f;
+        }
+        return;
+    }
+    const GlobalBytes i0 = lane_pointer(tab.idx_lo, tab.idx_hi, t), v0 = lane_pointer(tab.val_lo, tab.val_hi, t);
+#pragma unroll
+    for (int u = 0; u < WIN; ++u) {
+        int32_t p = u * LD_WAVE + lane;
+        if (p >= x.count) p = x.count - 1;
+        const uint32_t o = static_cast<uint32_t>(p) * 4u;
+        x.ri[u] = *reinterpret_cast<const __attribute__((address_space(1))) int32_t*>(i0 + o);
+        x.rv[u] = *reinterpret_cast<const __attribute__((address_space(1))) float*>(v0 + o);
+    }
+}
+
 // Argument checks common to the sparse replays.
 ld_status check_diff_args(const void* w, int64_t n, const int32_t* const* idx, const float* const* val,
                           const int64_t* K, int32_t W) {

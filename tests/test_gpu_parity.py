@@ -575,6 +575,75 @@ def test_merge_lane_per_record_dense_sub_tiles_and_columns(n, W, case):
     np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
 
 
+@pytest.mark.parametrize("n", [100, 2047, 2049, 8192 * 3, 300_007])
+@pytest.mark.parametrize("per8192", [21, 100, 168, 169, 900])
+@pytest.mark.parametrize("W", [1, 17, 18, 65, 130])
+def test_merge_rows_edges(n, per8192, W):
+    # small arrays with the workspace their window asks for: records looked up per 2048 elements, one or two windows of 64
+    # per diff, 17 or 10 diffs a batch, one and two diffs per lane, a second group. Every third diff is crowded into
+    # a quarter of the array (more records in a sub-tile than its windows hold), every seventh has none, some share positions.
+    rs = np.random.RandomState(n + per8192 + W)
+    K = max(1, n * per8192 // 8192)
+    idxs = []
+    for t in range(W):
+        hi = n if t % 3 else max(K, n // 4)
+        idxs.append(np.sort(rs.choice(hi, 0 if t % 7 == 3 else K, replace=False)).astype(np.int32))
+    for t in range(5, W, 9):
+        idxs[t] = idxs[t - 1].copy()
+    vals = [(rs.standard_normal(i.size) * 1e-2).astype(np.float32) for i in idxs]
+    w0 = synth.base_weights(n).numpy()
+    ref = oracle.merge_sparse(w0, idxs, vals, 0.1)
+    gi, gv = [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals]
+    for strategy in (ld.LD_MERGE_SWEEP, ld.LD_MERGE_AUTO):
+        w = to_gpu(w0)
+        ws = torch.full((ld.ld_merge_sparse_workspace(n, [i.size for i in idxs]),), 0xA5, dtype=torch.uint8, device=DEV)
+        ld.ld_merge_sparse(w, gi, gv, 0.1, ws, strategy=strategy)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(ref), err_msg=f"strategy {strategy}")
+
+
+@pytest.mark.parametrize("W", [2, 10, 40])
+@pytest.mark.parametrize("way", ["full", "minimum", "misaligned", "static"])
+def test_merge_of_sparse_windows_with_and_without_tables(W, way):
+    # windows that touch little of w: with the workspace that the query gives they run from a table where that is faster,
+    # else, and with index arrays that are not 16-byte aligned, as scatters
+    n, K = 1_000_003, 1000
+    rs = np.random.RandomState(W)
+    idxs = [np.sort(rs.choice(n, K, replace=False)).astype(np.int32) for _ in range(W)]
+    idxs[-1] = idxs[0].copy()
+    vals = [rs.standard_normal(K).astype(np.float32) for _ in range(W)]
+    w0 = synth.base_weights(n).numpy()
+    gi, gv = [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals]
+    if way == "misaligned":
+        buf = torch.empty(K + 1, dtype=torch.int32, device=DEV)
+        buf[1:].copy_(gi[1])
+        gi[1] = buf[1:]
+    w = to_gpu(w0)
+    if way == "static":
+        ld.ld_merge_sparse_static(w, gi, gv, 0.1)
+    else:
+        least = int(ld.load().ld_merge_sparse_workspace(n, W, None))
+        ws = torch.empty(least if way == "minimum" else ld.ld_merge_sparse_workspace(n, [K] * W), dtype=torch.uint8, device=DEV)
+        ld.ld_merge_sparse(w, gi, gv, 0.1, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
+@pytest.mark.parametrize("W", [11, 65])
+def test_merge_lane_per_record_whole_sub_tiles(W):
+    # sub-tiles of 4096 that a diff records whole, four trips of 16 rows, in a window that is sparse all in all
+    n = 2_000_003
+    idxs = [np.concatenate([np.arange(4096 * 7 - t, 4096 * 8 + t), np.arange(n - 60, n)]).astype(np.int32) for t in range(W)]
+    assert max(i.size for i in idxs) * 8192 <= 20 * n
+    rs = np.random.RandomState(W)
+    vals = [(rs.standard_normal(i.size) * 1e-2).astype(np.float32) for i in idxs]
+    w0 = synth.base_weights(n).numpy()
+    w = to_gpu(w0)
+    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, strategy=ld.LD_MERGE_SWEEP)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
 @pytest.mark.parametrize("case", ["random", "identical", "pairs", "clustered", "short_then_long"])
 def test_merge_thin_long_windows(case):
     # Long windows of sparse diffs run a lane per record: the records of a sub-tile go through in rows of
