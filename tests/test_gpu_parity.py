@@ -1655,3 +1655,28 @@ def test_randomised_dense_replays_against_the_oracle():
         for s_, b_ in zip(snaps, gbits):
             np.testing.assert_array_equal(s_.cpu().view(torch.int16).numpy().view(np.uint16), b_)
         check_adam_close((w, m, v), oracle.adam_replay(w0, m0, v0, gbits, step0, **hp), f"case {case}")
+
+
+@pytest.mark.parametrize("n,K", [(5_000_000, 5_000_000), (5_400_013, 5_000_003), (90_000_001, 5_000_064),
+                                 (310_000_007, 6_000_001)])
+@pytest.mark.parametrize("shift", [0, 4])  # floats: 4 leaves w off its granules, word by word
+def test_scatter_by_granules(n, K, shift):
+    """Diffs of 5 M records and more: every element, neighbours within a granule and across waves, an array that ends
+    inside a granule, denormals, infinities and NaNs beside the records. The definition in torch, bit for bit."""
+    print(f"[scatter] granules n={n} K={K} shift={shift}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(n + K)
+    gaps = torch.randint(0, 2 * (n - K) // K + 1, (K,), generator=gen, device=DEV)
+    idx = torch.cumsum(gaps + 1, 0) - 1
+    idx = torch.minimum(idx, n - K + torch.arange(K, device=DEV)).to(torch.int32)
+    idx[-1] = n - 1
+    val = torch.randn(K, generator=gen, device=DEV)
+    w = torch.randn(n + shift, generator=gen, device=DEV)[shift:]
+    odd = torch.randint(0, n, (1000,), generator=gen, device=DEV)
+    w[odd] = torch.tensor([float("inf"), 1e-42, -0.0, float("nan")], device=DEV).repeat(250)
+    val[::997] = 1e-41
+    want = w.clone()
+    for lr in (0.1, -1.0):  # the second pass on updated elements
+        at = idx.long()
+        want[at] = want[at] - torch.tensor(lr, device=DEV) * val
+        ld.ld_merge_sparse(w, [idx], [val], lr, strategy=ld.LD_MERGE_SCATTER)
+        assert torch.equal(w.view(torch.int32), want.view(torch.int32))
