@@ -398,6 +398,25 @@ ld_status ld_combine_sparse(const int32_t* const* idx, const float* const* val, 
                             int32_t* out_idx, float* out_val, int64_t out_cap, int64_t* out_count,
                             void* workspace, size_t workspace_bytes, ld_stream stream);
 
+/* Same operation with the execution strategy chosen by the caller (a tuning and
+ * test hook; the result is identical for every strategy):
+ *   LD_COMBINE_AUTO            library decides from n, N and the K
+ *   LD_COMBINE_TWO_PASSES      the distinct indices are counted, then emitted
+ *   LD_COMBINE_ONE_PASS        one reading of the records; a workgroup learns where its
+ *                              output begins from the ones before it
+ *   LD_COMBINE_ONE_PASS_ALONE  the same, every workgroup counting by itself what the
+ *                              ones before it have not told yet, without waiting
+ */
+#define LD_COMBINE_AUTO           0
+#define LD_COMBINE_TWO_PASSES     1
+#define LD_COMBINE_ONE_PASS       2
+#define LD_COMBINE_ONE_PASS_ALONE 3
+ld_status ld_combine_sparse_strategy(const int32_t* const* idx, const float* const* val, const int64_t* K,
+                            int32_t N, int64_t n, float scale,
+                            int32_t* out_idx, float* out_val, int64_t out_cap, int64_t* out_count,
+                            void* workspace, size_t workspace_bytes, ld_stream stream,
+                            int32_t strategy);
+
 /* ------------------------------------------------------------------------
  * Checkpointing configuration model (Sec. V-C).  Host arithmetic only; nothing is
  * enqueued.  f = full-checkpoint interval in iterations, b = differentials per

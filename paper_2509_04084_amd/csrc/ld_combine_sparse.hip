@@ -6,7 +6,10 @@
 // the workers' values added in worker order (one fp32 add each, starting from +0)
 // and multiplied by `scale` (1 for a sum, 1/N for a mean).
 //
-// The index space is cut into 8192-element sub-tiles, one wave each, in two passes:
+// Two ways with the same result. Usually one pass over the records, a workgroup per 49152-element chunk (k_combine_chunk,
+// below: as soon as it has counted its records it learns from the chunks before where its output begins). Where the lists
+// are so dense that a chunk's records outgrow a workgroup (chunk_shape), the index space is cut
+// into 8192-element sub-tiles, one wave each, in two passes:
 //   k_combine_count  marks the sub-tile's recorded positions in an LDS bitmap, counts
 //                    them and leaves the bitmap in the workspace (1 KB per sub-tile);
 //   k_combine_groups / k_combine_scan   scan the counts (inside groups of 1024
@@ -20,8 +23,10 @@
 //                    of the sub-tile would cost 32 KB of LDS per wave and leave one
 //                    wave per SIMD; the ranked array takes 7.5 KB.
 // The records of a sub-tile are found as in ld_merge_sparse: chunk table +
-// interpolated 128-record windows, verified. HBM traffic: the indices twice, the values
-// once, the bitmaps out and in, the output once.
+// interpolated 128-record windows, verified. HBM traffic of the two passes: the indices twice, the values
+// once, the bitmaps out and in, the output once; of the one pass: records and output once.
+#include <type_traits>
+
 #include "ld_sparse_common.h"
 
 namespace {
@@ -258,6 +263,299 @@ __global__ __launch_bounds__(LD_WAVE) void k_combine_emit(int64_t n, int32_t nch
     }
 }
 
+// ------------------------------------------------------------------ one pass, a workgroup per chunk
+//
+// Everything in one reading of the records. A workgroup takes a chunk of the range table, so that it knows exactly which
+// records are its own: no guesses, and a list's records lie in one piece of some 2 KB. It marks the recorded positions in a
+// bitmap, publishes how many there are, adds the values list after list at their ranks, and by then the counts of the
+// chunks before it have been published too: it adds them up back to the nearest chunk that has published everything before
+// itself (a word per chunk: the count and what it counts, so that no fence is needed), and writes its records.
+// The wait for a count is bounded: a workgroup that has asked often enough counts that chunk itself, so it ends whatever
+// order the workgroups run in.
+// Measured, two passes / one, us per call: 8 lists of 1 % of 1.56 G elements 635 / 541 (439 with the places of the output given
+// instead of found), of 0.1 % of 1.4 G 288 / 170, of 1.7 % of 400 M 397 / 243, of 1 % of 50 M 44 / 35, of 1.7 % of 5 M 46 / 24.
+// What it took there (first cases, 1080 at first): the ranges by lane reads instead of scalar loads list after list and 64
+// chunks asked at a time instead of 256, 660; LDS accesses that nothing branches around; the published words 64 bytes apart (in
+// a row 790, 8 bytes apart 670, 16: 640; they are written and asked from all XCDs at once) and asked for only when the values
+// are added (earlier, they mostly say nothing yet), 595; four waves to a workgroup, so that every SIMD has one, and the lists'
+// addresses by scalar loads ahead of the ranges, 540. What bounds it: chains of latencies (ranges, records, a dozen
+// barriers, the counts before) at 16 waves per CU.
+constexpr int kChunkWords = static_cast<int>(kChunk / 32);  // bitmap words: 1536
+constexpr int32_t kPolls = 4096;
+constexpr int kApart = 16;                                  // words between the chunks' published ones
+// What a chunk publishes: 0 nothing yet, 1 + its own count, or kSummed + the count up to its end (at most n <= 2^31 - 1).
+constexpr uint32_t kSummed = 1u << 31;
+
+__global__ __launch_bounds__(256) void k_combine_clear(uint32_t* __restrict__ state, int32_t nchunk) {
+    const int32_t c = static_cast<int32_t>(blockIdx.x * 256 + threadIdx.x);
+    if (c < nchunk) state[static_cast<int64_t>(c) * kApart] = 0;
+}
+
+// Distinct positions recorded in a chunk, counted by one wave; bits: kChunkWords words of LDS.
+__device__ __forceinline__ uint32_t count_chunk(const DiffTable& tb, int32_t N, const int32_t* __restrict__ ctab,
+                                                int32_t nchunk, int64_t n, int32_t chunk, uint32_t* bits, int lane) {
+    const int64_t lo64 = static_cast<int64_t>(chunk) * kChunk;
+    const uint32_t lo = static_cast<uint32_t>(lo64), len = static_cast<uint32_t>(n - lo64 < kChunk ? n - lo64 : kChunk);
+    for (int j = lane; j < kChunkWords; j += LD_WAVE) bits[j] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int32_t t = 0; t < N; ++t) {
+        const int32_t* row = ctab + static_cast<int64_t>(t) * (nchunk + 1) + chunk;
+        const uint32_t end = static_cast<uint32_t>(row[1]);  // unsigned: positions may pass INT_MAX by a window
+        for (uint32_t p = static_cast<uint32_t>(row[0]) + lane; p < end; p += LD_WAVE) {
+            const uint32_t q = static_cast<uint32_t>(tb.idx[t][p]) - lo;
+            if (q < len) atomicOr(&bits[q >> 5], 1u << (q & 31));
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint32_t c = 0;
+    for (int j = lane; j < kChunkWords; j += LD_WAVE) c += __popc(bits[j]);
+    return ld_wave_sum(c);
+}
+
+// HELD: at most kPre lists, their records stay in registers between the marks and the sums.
+// kDeep: records per thread and list loaded ahead.
+template <int THREADS, int kDeep, int CAP, bool HELD>
+__global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nchunk, DiffTable tb, int32_t N,
+                                                           const int32_t* __restrict__ ctab, uint32_t* state,
+                                                           float scale, int32_t* __restrict__ out_idx,
+                                                           float* __restrict__ out_val, int64_t out_cap,
+                                                           int64_t* __restrict__ out_count, int32_t polls) {
+    static_assert(CAP >= kChunkWords && kChunk <= 65536, "a bitmap in acc, 16-bit positions");
+    constexpr int kWaves = THREADS / LD_WAVE;
+    constexpr int kOwners = THREADS < 256 ? THREADS : 256;  // threads that own bitmap words
+    constexpr int kOwn = kChunkWords / kOwners;
+    static_assert(kOwn * kOwners == kChunkWords, "");
+    // Lanes without a record work on a word of their own behind each array: nothing branches around an LDS access.
+    __shared__ uint32_t bm[kChunkWords + LD_WAVE];   // recorded positions of the chunk
+    __shared__ uint16_t wpre[kChunkWords + LD_WAVE]; // recorded positions before each bitmap word
+    __shared__ float acc[CAP + LD_WAVE];             // sums, at the rank of their position among the recorded ones
+    __shared__ uint16_t accq[CAP + LD_WAVE];         // ... and the positions themselves
+    __shared__ uint32_t sums[kWaves];
+    __shared__ uint32_t offset;
+    const int tid = threadIdx.x, lane = tid & (LD_WAVE - 1), wave = tid / LD_WAVE;
+    const int32_t chunk = blockIdx.x;
+    const int64_t lo64 = static_cast<int64_t>(chunk) * kChunk;
+    const uint32_t lo = static_cast<uint32_t>(lo64), len = static_cast<uint32_t>(n - lo64 < kChunk ? n - lo64 : kChunk);
+
+    // Lane t: where list t's records of this chunk lie. The loops take them by lane reads: scalar loads from the table would
+    // be waited for list after list.
+    int32_t first = 0, have = 0;
+    if (lane < N) {
+        const int32_t* row = ctab + static_cast<int64_t>(lane) * (nchunk + 1) + chunk;
+        first = row[0];
+        have = row[1] > first ? row[1] - first : 0;
+    }
+    // Records of kPre lists, kDeep per thread and list; at: their positions in the chunk (spare: none).
+    const uint32_t spare = static_cast<uint32_t>(kChunk) + lane * 32u;
+    uint32_t at[kPre][kDeep];
+    float rv[kPre][kDeep];
+    auto fetch = [&](int32_t t0, auto (&x)[kPre][kDeep], auto* const (&list)[kTableMax]) {
+        typedef std::remove_reference_t<decltype(x[0][0])> T;
+#pragma unroll
+        for (int g = 0; g < kPre; ++g) {
+            const int t = t0 + g;  // kPre divides 64: past N the count is 0
+            const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t));
+            const auto* base = list[t] + __builtin_amdgcn_readlane(first, t);
+#pragma unroll
+            for (int u = 0; u < kDeep; ++u) {
+                x[g][u] = T(0);
+                if (static_cast<uint32_t>(u * THREADS + wave * LD_WAVE) < count) {  // uniform in the wave
+                    uint32_t p = u * THREADS + tid;
+                    p = p < count ? p : count - 1;
+                    x[g][u] = static_cast<T>(base[p]);
+                }
+            }
+        }
+    };
+    auto load = [&](int32_t t0, bool values) {
+        fetch(t0, at, tb.idx);
+        if (values) fetch(t0, rv, tb.val);
+    };
+    auto place = [&](int32_t t0) {
+#pragma unroll
+        for (int g = 0; g < kPre; ++g) {
+            const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t0 + g));
+#pragma unroll
+            for (int u = 0; u < kDeep; ++u) {
+                const uint32_t q = at[g][u] - lo;
+                at[g][u] = static_cast<uint32_t>(u * THREADS + tid) < count && q < len ? q : spare;
+            }
+        }
+    };
+    // f(q, v) for the records of list t beyond those that load() takes (crowded chunks)
+    auto rest = [&](int32_t t, bool values, auto&& f) {
+        const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t));
+        if (count <= kDeep * THREADS) return;
+        const int32_t* ip = tb.idx[t] + __builtin_amdgcn_readlane(first, t);
+        const float* vp = tb.val[t] + __builtin_amdgcn_readlane(first, t);
+#pragma unroll 1
+        for (uint32_t b = kDeep * THREADS; b < count; b += 4 * THREADS) {
+            uint32_t q[4];
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t p = b + u * THREADS + tid;
+                q[u] = 0xFFFFFFFFu;
+                v[u] = 0.0f;
+                if (p < count) {
+                    q[u] = static_cast<uint32_t>(ip[p]) - lo;
+                    if (values) v[u] = vp[p];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (q[u] < len) f(q[u], v[u]);
+        }
+    };
+    auto mark = [&](uint32_t q) { atomicOr(&bm[q >> 5], 1u << (q & 31)); };
+    load(0, HELD);
+    for (int j = tid; j < kChunkWords; j += THREADS) bm[j] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();  // the records stay on their way
+#pragma unroll 1
+    for (int32_t t0 = 0; t0 < (HELD ? 1 : N); t0 += kPre) {
+        if (!HELD && t0 > 0) load(t0, false);
+        place(t0);
+#pragma unroll
+        for (int g = 0; g < kPre; ++g)
+#pragma unroll
+            for (int u = 0; u < kDeep; ++u) mark(at[g][u]);
+#pragma unroll 1
+        for (int32_t t = t0; t < t0 + kPre && t < N; ++t) rest(t, false, [&](uint32_t q, float) { mark(q); });
+    }
+    __syncthreads();
+
+    uint32_t before = 0;  // of the thread's words
+    uint32_t word[kOwn], sum = 0;
+    if (tid < kOwners) {
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) {
+            word[j] = __popc(bm[tid * kOwn + j]);
+            sum += word[j];
+        }
+    }
+    before = ld_wave_iscan(sum);
+    if (lane == LD_WAVE - 1) sums[wave] = before;
+    before -= sum;
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+        if (i < wave) before += sums[i];
+        total += sums[i];
+    }
+    if (tid < kOwners) {
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) {
+            wpre[tid * kOwn + j] = static_cast<uint16_t>(before);  // below kChunk
+            before += word[j];
+        }
+    }
+    auto publish = [&](uint32_t x) { __hip_atomic_store(state + static_cast<int64_t>(chunk) * kApart, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (tid == 0) publish(chunk > 0 ? total + 1 : kSummed + total);
+
+    // Records before this chunk's; the first wave finds them, the others wait at the next barrier. bits: kChunkWords free words.
+    auto ask = [&](int32_t c) {
+        return c < 0 ? kSummed : __hip_atomic_load(state + static_cast<int64_t>(c) * kApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto find_offset = [&](uint32_t* bits) {
+        if (wave != 0) return;
+        uint32_t off = 0;
+        bool found = chunk == 0;
+        int32_t asked = 0;
+#pragma unroll 1
+        for (int32_t pos = chunk - 1; !found; pos -= LD_WAVE) {
+            uint32_t told = ask(pos - lane);
+            int last;  // lanes up to it count
+            while (true) {
+                const uint64_t summed = __ballot(told >= kSummed), none = __ballot(told == 0);
+                last = summed ? __builtin_ctzll(summed) : LD_WAVE - 1;
+                found = summed != 0;
+                const uint64_t missing = none & (~0ull >> (LD_WAVE - 1 - last));
+                if (!missing) break;
+                if (asked < polls) {
+                    ++asked;
+                    __builtin_amdgcn_s_sleep(1);
+                    if (told == 0) told = ask(pos - lane);
+                } else {  // asked often enough: count the nearest one here
+                    const int l = __builtin_ctzll(missing);
+                    const uint32_t c = count_chunk(tb, N, ctab, nchunk, n, pos - l, bits, lane);
+                    if (lane == l) told = c + 1;
+                }
+            }
+            const uint32_t own = told >= kSummed ? told - kSummed : told - 1;
+            off += ld_wave_sum(lane <= last ? own : 0u);
+        }
+        if (lane == 0) {
+            publish(kSummed + (off + total));
+            offset = off;
+            if (chunk == nchunk - 1) *out_count = static_cast<int64_t>(off) + total;
+        }
+    };
+    const bool once = total <= static_cast<uint32_t>(CAP);  // one round, unless the chunk is crowded
+    if (!once) find_offset(reinterpret_cast<uint32_t*>(acc));
+    __syncthreads();
+
+    // Rounds of CAP distinct positions: the values are added, list after list, at the rank of their position; then
+    // the round is written out as one run.
+#pragma unroll 1
+    for (uint32_t r0 = 0; r0 == 0 || r0 < total; r0 += CAP) {
+        const uint32_t cnt = total - r0 < static_cast<uint32_t>(CAP) ? total - r0 : static_cast<uint32_t>(CAP);
+        for (uint32_t j = tid; j < cnt; j += THREADS) acc[j] = 0.0f;
+        // at most CAP: of another round
+        auto rank = [&](uint32_t q) {
+            const uint32_t r = wpre[q >> 5] + __popc(bm[q >> 5] & ((1u << (q & 31)) - 1u)) - r0;
+            return r < cnt && q < static_cast<uint32_t>(kChunk) ? r : static_cast<uint32_t>(CAP) + lane;
+        };
+        __syncthreads();
+#pragma unroll 1
+        for (int32_t t0 = 0; t0 < (HELD ? 1 : N); t0 += kPre) {
+            if (!HELD || r0 > 0) {
+                load(t0, true);
+                place(t0);
+            }
+            uint32_t to[kPre][kDeep];
+#pragma unroll
+            for (int g = 0; g < kPre; ++g)
+#pragma unroll
+                for (int u = 0; u < kDeep; ++u) {
+                    to[g][u] = rank(at[g][u]);
+                    accq[to[g][u]] = static_cast<uint16_t>(at[g][u]);
+                }
+#pragma unroll
+            for (int g = 0; g < kPre; ++g) {
+                if (t0 + g < N) {  // uniform
+                    // the positions of one list are distinct: all are read before any is written
+                    float cur[kDeep];
+#pragma unroll
+                    for (int u = 0; u < kDeep; ++u) cur[u] = acc[to[g][u]];
+#pragma unroll
+                    for (int u = 0; u < kDeep; ++u) acc[to[g][u]] = __fadd_rn(cur[u], rv[g][u]);
+                    rest(t0 + g, true, [&](uint32_t q, float v) {
+                        const uint32_t d = rank(q);
+                        acc[d] = __fadd_rn(acc[d], v);
+                        accq[d] = static_cast<uint16_t>(q);
+                    });
+                    __syncthreads();  // list after list
+                }
+            }
+        }
+        if (once) {
+            find_offset(bm);
+            __syncthreads();
+        }
+        const int64_t off = static_cast<int64_t>(offset) + r0;
+        for (uint32_t j = tid; j < cnt; j += THREADS) {
+            if (off + j < out_cap) {
+                out_idx[off + j] = static_cast<int32_t>(lo + accq[j]);
+                out_val[off + j] = __fmul_rn(scale, acc[j]);
+            }
+        }
+        if (once) return;
+        __syncthreads();
+    }
+}
+
 }  // namespace
 
 namespace {
@@ -278,6 +576,29 @@ CombineLayout combine_layout(int64_t n, int32_t N) {
 }
 }  // namespace
 
+namespace {
+// Shape of the one pass: its threads hold a list's records of a chunk with room above their mean (the others are read in a
+// second go), and the distinct positions of a chunk fit one round, or two where the lists are dense. Two passes / one, us
+// per call of 400 M elements: kNarrow 8 lists of 0.25 % 101 / 70, kFew 2 of 1 % 81 / 79 (1.4 G: 272 / 249) and 4 of 1 % 117 / 91,
+// kMiddle 8 of 1 % 179 / 157, kLong 2 of 2 % 135 / 131, kWide 8 of 1.7 % 397 / 243, 16 of 2 % 1185 / 709 (two rounds).
+// Two passes where that was no gain: large arrays with two lists of 1.7 % (117 / 129, though 24.6 / 21.7 at 5 M elements) or
+// with 16 of 1 % (406 / 408, 1.4 G 1358 / 1390; 84 / 65 at 50 M), whose records are read twice by the one pass too.
+enum ChunkShape { kTwoPasses, kNarrow, kFew, kMiddle, kLong, kWide };
+ChunkShape chunk_shape(int64_t n, int32_t N, int64_t most, int64_t total, int32_t strategy) {
+    if (strategy == LD_COMBINE_TWO_PASSES) return kTwoPasses;
+    const double list = static_cast<double>(most) * kChunk / static_cast<double>(n);
+    const double all = static_cast<double>(total) * kChunk / static_cast<double>(n);
+    const bool large = n > 100000000 && strategy == LD_COMBINE_AUTO;
+    if (large && ((N <= 2 && list > 500) || (N > kPre && list > 400 && list <= 640))) return kTwoPasses;
+    if (list <= 190 && all <= 1850) return kNarrow;
+    if (list <= 500 && all <= 2100) return kFew;
+    if (list <= 640 && all <= 4300) return kMiddle;
+    if (list <= 1000 && all <= 4300) return kLong;
+    if ((list <= 1350 && all <= 17000) || strategy != LD_COMBINE_AUTO) return kWide;
+    return kTwoPasses;
+}
+}  // namespace
+
 extern "C" size_t ld_combine_sparse_workspace(int64_t n, int32_t N) {
     if (n <= 0 || N <= 0 || N > LD_MAX_WORKERS) return 256;
     return combine_layout(n, N).total;
@@ -287,13 +608,23 @@ extern "C" ld_status ld_combine_sparse(const int32_t* const* idx, const float* c
                                        int32_t N, int64_t n, float scale, int32_t* out_idx, float* out_val,
                                        int64_t out_cap, int64_t* out_count, void* workspace,
                                        size_t workspace_bytes, ld_stream stream) {
+    return ld_combine_sparse_strategy(idx, val, K, N, n, scale, out_idx, out_val, out_cap, out_count, workspace,
+                                      workspace_bytes, stream, LD_COMBINE_AUTO);
+}
+
+extern "C" ld_status ld_combine_sparse_strategy(const int32_t* const* idx, const float* const* val, const int64_t* K,
+                                                int32_t N, int64_t n, float scale, int32_t* out_idx, float* out_val,
+                                                int64_t out_cap, int64_t* out_count, void* workspace,
+                                                size_t workspace_bytes, ld_stream stream, int32_t strategy) {
+    if (strategy < LD_COMBINE_AUTO || strategy > LD_COMBINE_ONE_PASS_ALONE) return LD_ERR_RANGE;
     if (n < 0 || n > INT32_MAX || N < 0 || N > LD_MAX_WORKERS || out_cap < 0) return LD_ERR_RANGE;
     if (!out_count) return LD_ERR_NULL;
     if (!ld_aligned(out_count, 8)) return LD_ERR_ALIGN;
     if (N > 0 && (!idx || !val || !K)) return LD_ERR_NULL;
-    int64_t total = 0;
+    int64_t total = 0, most = 0;
     for (int32_t t = 0; t < N; ++t) {
         if (K[t] < 0 || K[t] > n) return LD_ERR_RANGE;
+        if (K[t] > most) most = K[t];
         if (K[t] > 0 && (!idx[t] || !val[t])) return LD_ERR_NULL;
         if (!ld_aligned(idx[t], 4) || !ld_aligned(val[t], 4)) return LD_ERR_ALIGN;
         total += K[t];
@@ -329,6 +660,24 @@ extern "C" ld_status ld_combine_sparse(const int32_t* const* idx, const float* c
     const dim3 grid(static_cast<uint32_t>((nsub + 7) / 8 * 8)), wave(LD_WAVE);
     launch_chunks(tb, N, n, nchunk, ctab, s);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+    const ChunkShape shape = chunk_shape(n, N, most, total, strategy);
+    if (shape != kTwoPasses) {
+        uint32_t* state = bitmaps;  // 64 bytes per chunk, where the two passes keep a bit per element
+        const int32_t polls = strategy == LD_COMBINE_ONE_PASS_ALONE ? 0 : kPolls;
+        k_combine_clear<<<dim3((nchunk + 255) / 256), dim3(256), 0, s>>>(state, nchunk);
+        if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+        auto launch = [&](auto kernel, uint32_t threads) {
+            kernel<<<dim3(nchunk), dim3(threads), 0, s>>>(n, nchunk, tb, N, ctab, state, scale, out_idx, out_val, out_cap,
+                                                        out_count, polls);
+        };
+        const bool held = N <= kPre;
+        if (shape == kNarrow) held ? launch(k_combine_chunk<128, 2, 2048, true>, 128) : launch(k_combine_chunk<128, 2, 2048, false>, 128);
+        else if (shape == kFew) held ? launch(k_combine_chunk<192, 3, 2304, true>, 192) : launch(k_combine_chunk<192, 3, 2304, false>, 192);
+        else if (shape == kMiddle) held ? launch(k_combine_chunk<256, 3, 4608, true>, 256) : launch(k_combine_chunk<256, 3, 4608, false>, 256);
+        else if (shape == kLong) held ? launch(k_combine_chunk<256, 4, 4608, true>, 256) : launch(k_combine_chunk<256, 4, 4608, false>, 256);
+        else held ? launch(k_combine_chunk<512, 3, 9152, true>, 512) : launch(k_combine_chunk<512, 3, 9152, false>, 512);
+        return ld_launch_status();
+    }
     k_combine_count<<<grid, wave, 0, s>>>(n, nchunk, tb, N, ctab, counts, bitmaps);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     k_combine_groups<<<dim3(ngrp), dim3(256), 0, s>>>(counts, nsub, gsum);

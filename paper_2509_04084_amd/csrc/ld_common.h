@@ -127,7 +127,7 @@ __device__ __forceinline__ float ld_bf16_widen(uint32_t h) { return __uint_as_fl
 //   g1 = (1 - beta1) g, g2 = ((1 - beta2) g) g  (ld_adam_terms)
 // The folded form divides numerator and denominator of the update by lr / (1 - beta1^s): two
 // moments, a square root, a fused multiply-add for the denominator, a reciprocal and a fused
-// multiply-add for w - four full-rate operations and two of four issue slots each, and fewer
+// multiply-add for w - four full-rate operations and two of two issue slots each, and fewer
 // roundings than the formula as written.
 // The general form keeps the learning rate apart. The hardware square root takes a denormal
 // argument for zero, which with eps = 0 (or tiny) would decide the result (a zero denominator):

@@ -125,6 +125,8 @@ def load() -> ctypes.CDLL:
     lib.ld_combine_sparse_workspace.restype = sz
     lib.ld_combine_sparse.argtypes = [vp, vp, vp, i32, i64, f32, vp, vp, i64, vp, vp, sz, vp]
     lib.ld_combine_sparse.restype = i32
+    lib.ld_combine_sparse_strategy.argtypes = lib.ld_combine_sparse.argtypes + [i32]
+    lib.ld_combine_sparse_strategy.restype = i32
     dbl = ctypes.c_double
     lib.ld_config_wasted_time.argtypes = [vp, dbl, dbl, dbl, dbl]
     lib.ld_config_wasted_time.restype = dbl

@@ -5,6 +5,8 @@ Bars: bit-exact for indices, values, residuals, snapshots and sparse merges;
 |x - y| <= 1e-7 + 1e-6 |y| for the dense Adam replay (and a relative-only check
 on v, which never cancels).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -1680,3 +1682,58 @@ def test_scatter_by_granules(n, K, shift):
         want[at] = want[at] - torch.tensor(lr, device=DEV) * val
         ld.ld_merge_sparse(w, [idx], [val], lr, strategy=ld.LD_MERGE_SCATTER)
         assert torch.equal(w.view(torch.int32), want.view(torch.int32))
+
+
+def combine_by(strategy, idxs, vals, n, scale, cap=None):
+    """ld_combine_sparse_strategy on numpy lists: (idx, val, count) with what lies past the count or cap cut off."""
+    lib = ld.load()
+    gi, gv = [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals]
+    N, total = len(idxs), sum(len(i) for i in idxs)
+    cap = total if cap is None else cap
+    oi = torch.full((cap + 64,), -1, dtype=torch.int32, device=DEV)
+    ov = torch.full((cap + 64,), 7.0, device=DEV)
+    cnt = torch.full((1,), -1, dtype=torch.int64, device=DEV)
+    ws = torch.full((ld.ld_combine_sparse_workspace(n, N),), 0xA5, dtype=torch.uint8, device=DEV)
+    V = ctypes.c_void_p
+    ip, vp = (V * N)(*[t.data_ptr() for t in gi]), (V * N)(*[t.data_ptr() for t in gv])
+    K = (ctypes.c_int64 * N)(*[len(i) for i in idxs])
+    st = lib.ld_combine_sparse_strategy(ip, vp, K, N, n, ctypes.c_float(scale), V(oi.data_ptr()), V(ov.data_ptr()), cap,
+                                        V(cnt.data_ptr()), V(ws.data_ptr()), ws.numel(), V(0), strategy)
+    assert st == 0
+    torch.cuda.synchronize()
+    count = int(cnt.item())
+    kept = min(count, cap)
+    assert bool((oi[kept:] == -1).all()) and bool((ov[kept:] == 7.0).all())
+    return oi[:kept].cpu().numpy(), ov[:kept].cpu().numpy(), count
+
+
+COMBINE_LISTS = {
+    # lists, records per list, where they lie: the widths of the one pass and what outgrows them
+    "one record": (49152 * 3 + 5, [1], None), "sparse, 3 of 70 chunks": (49152 * 70 + 1, [2000, 1, 0, 1900], (0, 140000)),
+    "narrow": (49152 * 9 + 77, [1500] * 8, None), "middle": (49152 * 300, [147000] * 8, None),
+    "wide": (49152 * 11 + 4096, [11000, 10000, 9000], None), "more than 8 lists": (49152 * 6 + 1, [2500] * 17, None),
+    "crowded chunk": (49152 * 4, [9000] * 5, (60000, 75000)), "all of it": (49152 * 2 + 3, [98307] * 3, None),
+    "64 lists": (200000, [700] * 64, None),
+}
+
+
+@pytest.mark.parametrize("name", list(COMBINE_LISTS))
+@pytest.mark.parametrize("strategy", [1, 2, 3])
+def test_combine_strategies(name, strategy):
+    """Two passes, one pass, and one pass whose workgroups wait for nobody, on a dirty workspace: the oracle bit for bit."""
+    n, counts, span = COMBINE_LISTS[name]
+    print(f"[combine] strategy {strategy} {name} n={n}", flush=True)
+    rs = np.random.RandomState(len(name))
+    a, b = span or (0, n)
+    idxs = [np.sort(rs.choice(b - a, k, replace=False)).astype(np.int32) + a for k in counts]
+    vals = [rs.standard_normal(k).astype(np.float32) for k in counts]
+    ei, ev = oracle.combine_sparse(idxs, vals, n, 0.125)
+    gi, gv, count = combine_by(strategy, idxs, vals, n, 0.125)
+    assert count == ei.size
+    np.testing.assert_array_equal(gi, ei)
+    np.testing.assert_array_equal(bits(gv), bits(ev))
+    cap = ei.size // 2
+    gi, gv, count = combine_by(strategy, idxs, vals, n, 0.125, cap)
+    assert count == ei.size
+    np.testing.assert_array_equal(gi, ei[:cap])
+    np.testing.assert_array_equal(bits(gv), bits(ev[:cap]))
