@@ -280,6 +280,9 @@ __global__ __launch_bounds__(LD_WAVE) void k_combine_emit(int64_t n, int32_t nch
 // are added (earlier, they mostly say nothing yet), 595; four waves to a workgroup, so that every SIMD has one, and the lists'
 // addresses by scalar loads ahead of the ranges, 540. What bounds it: chains of latencies (ranges, records, a dozen
 // barriers, the counts before) at 16 waves per CU.
+// Crowded chunks (much of the lists in little of the index space): their rounds take pieces of the lists, not all of them again,
+// and what goes beyond the records that a workgroup loads at once is streamed. 8 lists of 0.4 % of 400 M elements, all
+// in the first fiftieth: two passes 2220 us, with every round reading all of it 2906, now 283; 8 lists of 13 K of 5 M 313 / 1680 / 226.
 constexpr int kChunkWords = static_cast<int>(kChunk / 32);  // bitmap words: 1536
 constexpr int32_t kPolls = 4096;
 constexpr int kApart = 16;                                  // words between the chunks' published ones
@@ -332,13 +335,14 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
     __shared__ uint16_t accq[CAP + LD_WAVE];         // ... and the positions themselves
     __shared__ uint32_t sums[kWaves];
     __shared__ uint32_t offset;
+    __shared__ uint32_t used[LD_WAVE];               // crowded chunks: the records that a round takes of every list
     const int tid = threadIdx.x, lane = tid & (LD_WAVE - 1), wave = tid / LD_WAVE;
     const int32_t chunk = blockIdx.x;
     const int64_t lo64 = static_cast<int64_t>(chunk) * kChunk;
     const uint32_t lo = static_cast<uint32_t>(lo64), len = static_cast<uint32_t>(n - lo64 < kChunk ? n - lo64 : kChunk);
 
-    // Lane t: where list t's records of this chunk lie. The loops take them by lane reads: scalar loads from the table would
-    // be waited for list after list.
+    // Lane t: where list t's records of this chunk lie (in the rounds of a crowded chunk: those still to come). The loops take
+    // them by lane reads: scalar loads from the table would be waited for list after list.
     int32_t first = 0, have = 0;
     if (lane < N) {
         const int32_t* row = ctab + static_cast<int64_t>(lane) * (nchunk + 1) + chunk;
@@ -367,6 +371,12 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
             }
         }
     };
+    auto drop = [&]() {  // ends the registers' lifetime where the records will not be asked for again
+#pragma unroll
+        for (int g = 0; g < kPre; ++g)
+#pragma unroll
+            for (int u = 0; u < kDeep; ++u) at[g][u] = 0, rv[g][u] = 0.0f;
+    };
     auto load = [&](int32_t t0, bool values) {
         fetch(t0, at, tb.idx);
         if (values) fetch(t0, rv, tb.val);
@@ -382,29 +392,34 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
             }
         }
     };
-    // f(q, v) for the records of list t beyond those that load() takes (crowded chunks)
-    auto rest = [&](int32_t t, bool values, auto&& f) {
-        const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t));
-        if (count <= kDeep * THREADS) return;
-        const int32_t* ip = tb.idx[t] + __builtin_amdgcn_readlane(first, t);
-        const float* vp = tb.val[t] + __builtin_amdgcn_readlane(first, t);
-#pragma unroll 1
-        for (uint32_t b = kDeep * THREADS; b < count; b += 4 * THREADS) {
-            uint32_t q[4];
-            float v[4];
+    // Crowded chunks (a list has more records than load() takes): list after list, kBatch records per thread, the next ones
+    // requested while the present ones are applied.
+    const bool crowded = __ballot(have > kDeep * THREADS) != 0;  // uniform in the workgroup
+    constexpr int kBatch = 5;
+    struct Batch {
+        int32_t i[kBatch];
+        float v[kBatch];
+    };
+    // Records [b, b + kBatch * THREADS) of list t; past its end its last one again, of no list or an empty one anything. The loads
+    // are unconditional: around conditional ones every wait would be one for the next batch too.
+    auto take = [&](Batch& x, int32_t t, uint32_t b, bool values) {
+        const uint32_t count = t < N ? static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t)) : 0u;
+        const int32_t* ip = count ? tb.idx[t] + __builtin_amdgcn_readlane(first, t) : ctab;
+        const float* vp = count ? tb.val[t] + __builtin_amdgcn_readlane(first, t) : reinterpret_cast<const float*>(ctab);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t p = b + u * THREADS + tid;
-                q[u] = 0xFFFFFFFFu;
-                v[u] = 0.0f;
-                if (p < count) {
-                    q[u] = static_cast<uint32_t>(ip[p]) - lo;
-                    if (values) v[u] = vp[p];
-                }
-            }
+        for (int u = 0; u < kBatch; ++u) {
+            uint32_t p = b + u * THREADS + tid;
+            p = p < count ? p : (count ? count - 1 : 0u);
+            x.i[u] = ip[p];
+            if (values) x.v[u] = vp[p];
+        }
+    };
+    // x.i: position in the chunk (spare: none) instead of the index
+    auto place_batch = [&](Batch& x, uint32_t b, uint32_t count) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (q[u] < len) f(q[u], v[u]);
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t q = static_cast<uint32_t>(x.i[u]) - lo;
+            x.i[u] = static_cast<int32_t>(b + u * THREADS + tid < count && q < len ? q : spare);
         }
     };
     auto mark = [&](uint32_t q) { atomicOr(&bm[q >> 5], 1u << (q & 31)); };
@@ -420,8 +435,30 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
         for (int g = 0; g < kPre; ++g)
 #pragma unroll
             for (int u = 0; u < kDeep; ++u) mark(at[g][u]);
+    }
+    if (crowded) {
+        auto next = [&](int32_t& t, uint32_t& b) {  // past the batch's end: the next list with more than load() took
+            b += kBatch * THREADS;
+            while (t < N && b >= static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t))) {
+                ++t;
+                b = kDeep * THREADS;
+            }
+        };
+        int32_t t = __builtin_ctzll(__ballot(have > kDeep * THREADS));
+        uint32_t b = kDeep * THREADS;
+        Batch now, later;
+        take(now, t, b, false);
 #pragma unroll 1
-        for (int32_t t = t0; t < t0 + kPre && t < N; ++t) rest(t, false, [&](uint32_t q, float) { mark(q); });
+        while (t < N) {
+            const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t)), b0 = b;
+            next(t, b);
+            take(later, t, b, false);
+            place_batch(now, b0, count);
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) mark(static_cast<uint32_t>(now.i[u]));
+            now = later;
+        }
+        drop();
     }
     __syncthreads();
 
@@ -497,48 +534,105 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
     __syncthreads();
 
     // Rounds of CAP distinct positions: the values are added, list after list, at the rank of their position; then
-    // the round is written out as one run.
+    // the round is written out as one run. Lists ascend, so a round takes a piece of every list: in a crowded chunk it begins
+    // where the last round's ended, which the first record past the round tells.
 #pragma unroll 1
     for (uint32_t r0 = 0; r0 == 0 || r0 < total; r0 += CAP) {
         const uint32_t cnt = total - r0 < static_cast<uint32_t>(CAP) ? total - r0 : static_cast<uint32_t>(CAP);
         for (uint32_t j = tid; j < cnt; j += THREADS) acc[j] = 0.0f;
-        // at most CAP: of another round
+        // at least CAP: of another round
         auto rank = [&](uint32_t q) {
             const uint32_t r = wpre[q >> 5] + __popc(bm[q >> 5] & ((1u << (q & 31)) - 1u)) - r0;
             return r < cnt && q < static_cast<uint32_t>(kChunk) ? r : static_cast<uint32_t>(CAP) + lane;
         };
+        uint64_t over = 0;  // lists of a crowded chunk of which this round takes all that load() would and more
+        if (crowded) {
+            uint32_t end = static_cast<uint32_t>(kChunk);
+            if (have > kDeep * THREADS) end = static_cast<uint32_t>(tb.idx[lane][first + kDeep * THREADS - 1]) - lo;
+            over = __ballot(end < len && rank(end) < static_cast<uint32_t>(CAP));
+            if (tid < LD_WAVE) used[tid] = static_cast<uint32_t>(have);
+        }
+        // the first of the wave's records past the round; p: a lane's, counted from the list's first
+        auto past_round = [&](int32_t t, bool past, uint32_t p) {
+            const uint64_t lanes = __ballot(past);
+            if (lanes && lane == __builtin_ctzll(lanes)) atomicMin(&used[t], p);
+            return lanes != 0;
+        };
         __syncthreads();
 #pragma unroll 1
         for (int32_t t0 = 0; t0 < (HELD ? 1 : N); t0 += kPre) {
-            if (!HELD || r0 > 0) {
-                load(t0, true);
-                place(t0);
-            }
-            uint32_t to[kPre][kDeep];
-#pragma unroll
-            for (int g = 0; g < kPre; ++g)
-#pragma unroll
-                for (int u = 0; u < kDeep; ++u) {
-                    to[g][u] = rank(at[g][u]);
-                    accq[to[g][u]] = static_cast<uint16_t>(at[g][u]);
+            if (!(over >> t0 & ((1u << kPre) - 1u))) {
+                if (!HELD || r0 > 0 || crowded) {
+                    load(t0, true);
+                    place(t0);
                 }
+                uint32_t to[kPre][kDeep];
 #pragma unroll
-            for (int g = 0; g < kPre; ++g) {
-                if (t0 + g < N) {  // uniform
-                    // the positions of one list are distinct: all are read before any is written
-                    float cur[kDeep];
+                for (int g = 0; g < kPre; ++g)
 #pragma unroll
-                    for (int u = 0; u < kDeep; ++u) cur[u] = acc[to[g][u]];
+                    for (int u = 0; u < kDeep; ++u) {
+                        to[g][u] = rank(at[g][u]);
+                        accq[to[g][u]] = static_cast<uint16_t>(at[g][u]);
+                    }
 #pragma unroll
-                    for (int u = 0; u < kDeep; ++u) acc[to[g][u]] = __fadd_rn(cur[u], rv[g][u]);
-                    rest(t0 + g, true, [&](uint32_t q, float v) {
-                        const uint32_t d = rank(q);
-                        acc[d] = __fadd_rn(acc[d], v);
-                        accq[d] = static_cast<uint16_t>(q);
-                    });
-                    __syncthreads();  // list after list
+                for (int g = 0; g < kPre; ++g) {
+                    if (t0 + g < N) {  // uniform
+                        // the positions of one list are distinct: all are read before any is written
+                        float cur[kDeep];
+#pragma unroll
+                        for (int u = 0; u < kDeep; ++u) cur[u] = acc[to[g][u]];
+#pragma unroll
+                        for (int u = 0; u < kDeep; ++u) acc[to[g][u]] = __fadd_rn(cur[u], rv[g][u]);
+                        __syncthreads();  // list after list
+                    }
                 }
+                if (crowded) {
+#pragma unroll
+                    for (int g = 0; g < kPre; ++g)
+#pragma unroll
+                        for (int u = 0; u < kDeep; ++u)
+                            past_round(t0 + g, to[g][u] >= static_cast<uint32_t>(CAP) && at[g][u] < static_cast<uint32_t>(kChunk), u * THREADS + tid);
+                    drop();
+                }
+            } else {
+                Batch now, later;
+                take(now, t0, 0, true);
+#pragma unroll 1
+                for (int32_t t = t0; t < t0 + kPre && t < N; ++t) {
+                    const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t));
+                    take(later, t + 1, 0, true);
+                    bool past = false;  // the wave has seen a record past the round
+#pragma unroll 1
+                    for (uint32_t b = 0; b < count && !past; b += kBatch * THREADS) {
+                        if (b > 0) take(now, t, b, true);
+                        place_batch(now, b, count);
+                        uint32_t to[kBatch];
+                        float cur[kBatch];
+#pragma unroll
+                        for (int u = 0; u < kBatch; ++u) {
+                            to[u] = rank(static_cast<uint32_t>(now.i[u]));
+                            cur[u] = acc[to[u]];
+                        }
+#pragma unroll
+                        for (int u = 0; u < kBatch; ++u) {
+                            acc[to[u]] = __fadd_rn(cur[u], now.v[u]);
+                            accq[to[u]] = static_cast<uint16_t>(now.i[u]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kBatch; ++u)
+                            past |= past_round(t, to[u] >= static_cast<uint32_t>(CAP) && now.i[u] < static_cast<int32_t>(kChunk), b + u * THREADS + tid);
+                    }
+                    if (count) __syncthreads();  // list after list
+                    now = later;
+                }
+                drop();
             }
+        }
+        if (crowded) {
+            __syncthreads();
+            const int32_t took = static_cast<int32_t>(used[lane]);
+            first += took;
+            have -= took;
         }
         if (once) {
             find_offset(bm);

@@ -1714,6 +1714,18 @@ COMBINE_LISTS = {
     "wide": (49152 * 11 + 4096, [11000, 10000, 9000], None), "more than 8 lists": (49152 * 6 + 1, [2500] * 17, None),
     "crowded chunk": (49152 * 4, [9000] * 5, (60000, 75000)), "all of it": (49152 * 2 + 3, [98307] * 3, None),
     "64 lists": (200000, [700] * 64, None),
+    # a few chunks crowded in lists that are sparse all in all: the workgroups are made for few records and take the chunk in
+    # many rounds, each a piece of every list (up to 8 lists / more of them, lists that end early or begin late among them)
+    "crowded, narrow": (49152 * 60, [11000] * 4, (50000, 110000)),
+    "crowded, narrow, 9 lists": (49152 * 45, [8000] * 8 + [100], (49000, 100000)),
+    "crowded, few": (49152 * 50, [20000, 300, 20000], (0, 60000)),
+    "crowded, few, 9 lists": (49152 * 50, [11000] * 9, (49152, 49152 * 2)),
+    "crowded, middle": (49152 * 50, [30000, 29000, 0, 30000, 1], (100000, 160000)),
+    "crowded, middle, 10 lists": (49152 * 50, [20000] * 10, (49152 * 50 - 60000, 49152 * 50)),
+    "crowded, long": (49152 * 50, [45000] * 3, (49152 * 7 + 1000, 49152 * 8)),
+    "crowded, long, 9 lists": (49152 * 50, [40000] + [15000] * 8, (49152 * 7 - 100, 49152 * 8)),
+    "crowded, wide": (49152 * 50, [60000] * 8, (49152 * 10, 49152 * 13)),
+    "crowded, wide, 17 lists": (49152 * 50, [40000] * 17, (49152 * 10, 49152 * 11 + 2)),
 }
 
 
@@ -1737,3 +1749,57 @@ def test_combine_strategies(name, strategy):
     assert count == ei.size
     np.testing.assert_array_equal(gi, ei[:cap])
     np.testing.assert_array_equal(bits(gv), bits(ev[:cap]))
+
+
+def lowest_times(calls, reps=5, turns=5):
+    """Milliseconds per call of each of `calls`, the lowest of several turns in which they take turns."""
+    best = [float("inf")] * len(calls)
+    for f in calls:
+        f()
+    for _ in range(turns):
+        for j, f in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(reps):
+                f()
+            b.record()
+            b.synchronize()
+            best[j] = min(best[j], a.elapsed_time(b) / reps)
+    return best
+
+
+def combine_times(strategies, idxs, n):
+    """Milliseconds per combine by each of the strategies; their outputs agree."""
+    lib, N = ld.load(), len(idxs)
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    vals = [torch.randn(i.numel(), device=DEV, generator=gen) for i in idxs]
+    cap = sum(i.numel() for i in idxs)
+    ws = torch.empty(ld.ld_combine_sparse_workspace(n, N), dtype=torch.uint8, device=DEV)
+    V = ctypes.c_void_p
+    ip, vp = (V * N)(*[t.data_ptr() for t in idxs]), (V * N)(*[t.data_ptr() for t in vals])
+    K = (ctypes.c_int64 * N)(*[i.numel() for i in idxs])
+    outs = [(torch.full((cap,), -1, dtype=torch.int32, device=DEV), torch.zeros(cap, device=DEV),
+             torch.zeros(1, dtype=torch.int64, device=DEV)) for _ in strategies]
+
+    def call(strategy, out):
+        assert lib.ld_combine_sparse_strategy(ip, vp, K, N, n, ctypes.c_float(0.125), V(out[0].data_ptr()),
+                                              V(out[1].data_ptr()), cap, V(out[2].data_ptr()), V(ws.data_ptr()), ws.numel(),
+                                              V(0), strategy) == 0
+
+    times = lowest_times([lambda s=s, o=o: call(s, o) for s, o in zip(strategies, outs)])
+    for o in outs[1:]:
+        assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1].view(torch.int32), outs[0][1].view(torch.int32))
+        assert torch.equal(o[2], outs[0][2])
+    return times
+
+
+@pytest.mark.parametrize("n,N,K,part", [(5_000_000, 8, 13_000, 50), (20_000_000, 16, 28_000, 50), (3_200_000, 24, 4_800, 50),
+                                        (400_000_000, 8, 1_600_000, 50)])
+def test_combine_of_crowded_lists_takes_no_longer_in_one_pass(n, N, K, part):
+    """All records in the first fiftieth: a round reads its pieces of the lists, not all of them again. Reading them
+    all took two to six times the two passes' time here; a fifth above it is room for the noise of short calls."""
+    print(f"[combine] crowded n={n} N={N} K={K}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    idxs = [torch.randperm(n // part, device=DEV, generator=gen)[:K].sort().values.int() for _ in range(N)]
+    one, two = combine_times((0, 1), idxs, n)
+    assert one <= 1.2 * two, f"{one * 1e3:.0f} us, two passes {two * 1e3:.0f}"
