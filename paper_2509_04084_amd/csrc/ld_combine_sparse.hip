@@ -425,8 +425,10 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
     auto mark = [&](uint32_t q) { atomicOr(&bm[q >> 5], 1u << (q & 31)); };
     load(0, HELD);
     for (int j = tid; j < kChunkWords; j += THREADS) bm[j] = 0;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();  // the records stay on their way
+    // __syncthreads, but for LDS alone: the records stay on their way
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 #pragma unroll 1
     for (int32_t t0 = 0; t0 < (HELD ? 1 : N); t0 += kPre) {
         if (!HELD && t0 > 0) load(t0, false);

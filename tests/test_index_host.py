@@ -123,3 +123,22 @@ def test_small_segments_are_spread_over_the_xcds(shim, tiles, run, used):
         shim.xcd_pieces(run, 1, grid, ctypes.c_void_p(piece.ctypes.data))
         work = np.bincount(np.arange(grid)[piece % tiles < used] % 8, minlength=8)
         assert work.max() <= 1.25 * used * n_seg / 8 + 4 * used, (n_seg, work)
+
+
+def test_bare_barriers_are_fenced_on_both_sides():
+    # s_barrier alone does not order memory accesses for the compiler: a release fence has to stand before it and an acquire
+    # fence behind it, next to it (as __syncthreads has them), whatever they are restricted to
+    bare = 0
+    for name in sorted(os.listdir(CSRC)):
+        if not name.endswith((".hip", ".h")):
+            continue
+        with open(os.path.join(CSRC, name)) as f:
+            lines = [line.split("//")[0].strip() for line in f]
+        lines = [line for line in lines if line]
+        for i, line in enumerate(lines):
+            if "__builtin_amdgcn_s_barrier()" in line:
+                bare += 1
+                for fence, kinds in ((lines[i - 1], ("__ATOMIC_RELEASE", "__ATOMIC_ACQ_REL")),
+                                     (lines[i + 1], ("__ATOMIC_ACQUIRE", "__ATOMIC_ACQ_REL"))):
+                    assert "__builtin_amdgcn_fence(" in fence and any(k in fence for k in kinds), f"{name}: {line}"
+    assert bare == 1  # the rule above looks at lines: a barrier written in another way would pass it unseen
