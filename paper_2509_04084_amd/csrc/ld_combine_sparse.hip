@@ -520,6 +520,7 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
                     const int l = __builtin_ctzll(missing);
                     const uint32_t c = count_chunk(tb, N, ctab, nchunk, n, pos - l, bits, lane);
                     if (lane == l) told = c + 1;
+                    else if (told == 0) told = ask(pos - lane);  // it may have been told meanwhile
                 }
             }
             const uint32_t own = told >= kSummed ? told - kSummed : told - 1;

@@ -1803,3 +1803,17 @@ def test_combine_of_crowded_lists_takes_no_longer_in_one_pass(n, N, K, part):
     idxs = [torch.randperm(n // part, device=DEV, generator=gen)[:K].sort().values.int() for _ in range(N)]
     one, two = combine_times((0, 1), idxs, n)
     assert one <= 1.2 * two, f"{one * 1e3:.0f} us, two passes {two * 1e3:.0f}"
+
+
+def test_combine_asks_again_what_it_waited_for_in_vain():
+    """Workgroups that wait for nobody: a chunk that has been told meanwhile is not counted from its records again. Without
+    asking again a workgroup counts up to 64 chunks one after another here, 28 times the time with waiting; asking, 1.8 times."""
+    n, N, K = 1_500_000_000, 8, 15_000_000
+    print(f"[combine] asking again n={n}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    idxs = []
+    for _ in range(N):
+        at = torch.randint(1, 2 * n // K - 1, (K,), device=DEV, generator=gen).cumsum(0) - 1
+        idxs.append(torch.minimum(at, n - K + torch.arange(K, device=DEV)).int())
+    waiting, alone = combine_times((2, 3), idxs, n)
+    assert alone <= 6 * waiting, f"{alone * 1e3:.0f} us, waiting {waiting * 1e3:.0f}"
