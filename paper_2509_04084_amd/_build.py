@@ -42,7 +42,7 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
     """Compiles every HIP source into liblowdiff.so; returns its path."""
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
     deps = srcs + [os.path.join(CSRC, "ld_common.h"), os.path.join(CSRC, "ld_sparse_common.h"), os.path.join(CSRC, "ld_thin.h"),
-                   os.path.join(CSRC, "ld_map.h"),
+                   os.path.join(CSRC, "ld_map.h"), os.path.join(CSRC, "ld_combine_shape.h"),
                    os.path.join(ROOT, "include", "lowdiff.h")]
     if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
         return LIB

@@ -8,7 +8,7 @@
 //
 // Two ways with the same result. Usually one pass over the records, a workgroup per 49152-element chunk (k_combine_chunk,
 // below: as soon as it has counted its records it learns from the chunks before where its output begins). Where the lists
-// are so dense that a chunk's records outgrow a workgroup (chunk_shape), the index space is cut
+// are so dense that a chunk's records outgrow a workgroup (ld_combine_shape), the index space is cut
 // into 8192-element sub-tiles, one wave each, in two passes:
 //   k_combine_count  marks the sub-tile's recorded positions in an LDS bitmap, counts
 //                    them and leaves the bitmap in the workspace (1 KB per sub-tile);
@@ -27,6 +27,7 @@
 // once, the bitmaps out and in, the output once; of the one pass: records and output once.
 #include <type_traits>
 
+#include "ld_combine_shape.h"
 #include "ld_sparse_common.h"
 
 namespace {
@@ -673,29 +674,6 @@ CombineLayout combine_layout(int64_t n, int32_t N) {
 }
 }  // namespace
 
-namespace {
-// Shape of the one pass: its threads hold a list's records of a chunk with room above their mean (the others are read in a
-// second go), and the distinct positions of a chunk fit one round, or two where the lists are dense. Two passes / one, us
-// per call of 400 M elements: kNarrow 8 lists of 0.25 % 101 / 70, kFew 2 of 1 % 81 / 79 (1.4 G: 272 / 249) and 4 of 1 % 117 / 91,
-// kMiddle 8 of 1 % 179 / 157, kLong 2 of 2 % 135 / 131, kWide 8 of 1.7 % 397 / 243, 16 of 2 % 1185 / 709 (two rounds).
-// Two passes where that was no gain: large arrays with two lists of 1.7 % (117 / 129, though 24.6 / 21.7 at 5 M elements) or
-// with 16 of 1 % (406 / 408, 1.4 G 1358 / 1390; 84 / 65 at 50 M), whose records are read twice by the one pass too.
-enum ChunkShape { kTwoPasses, kNarrow, kFew, kMiddle, kLong, kWide };
-ChunkShape chunk_shape(int64_t n, int32_t N, int64_t most, int64_t total, int32_t strategy) {
-    if (strategy == LD_COMBINE_TWO_PASSES) return kTwoPasses;
-    const double list = static_cast<double>(most) * kChunk / static_cast<double>(n);
-    const double all = static_cast<double>(total) * kChunk / static_cast<double>(n);
-    const bool large = n > 100000000 && strategy == LD_COMBINE_AUTO;
-    if (large && ((N <= 2 && list > 500) || (N > kPre && list > 400 && list <= 640))) return kTwoPasses;
-    if (list <= 190 && all <= 1850) return kNarrow;
-    if (list <= 500 && all <= 2100) return kFew;
-    if (list <= 640 && all <= 4300) return kMiddle;
-    if (list <= 1000 && all <= 4300) return kLong;
-    if ((list <= 1350 && all <= 17000) || strategy != LD_COMBINE_AUTO) return kWide;
-    return kTwoPasses;
-}
-}  // namespace
-
 extern "C" size_t ld_combine_sparse_workspace(int64_t n, int32_t N) {
     if (n <= 0 || N <= 0 || N > LD_MAX_WORKERS) return 256;
     return combine_layout(n, N).total;
@@ -757,8 +735,9 @@ extern "C" ld_status ld_combine_sparse_strategy(const int32_t* const* idx, const
     const dim3 grid(static_cast<uint32_t>((nsub + 7) / 8 * 8)), wave(LD_WAVE);
     launch_chunks(tb, N, n, nchunk, ctab, s);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    const ChunkShape shape = chunk_shape(n, N, most, total, strategy);
-    if (shape != kTwoPasses) {
+    const LdCombineShape shape = ld_combine_shape(n, N, most, total, strategy);
+    if (shape != kCombineTwoPasses) {
+        static_assert(kCombineChunk == kChunk && kCombineHeld == kPre, "as the kernels have them");
         uint32_t* state = bitmaps;  // 64 bytes per chunk, where the two passes keep a bit per element
         const int32_t polls = strategy == LD_COMBINE_ONE_PASS_ALONE ? 0 : kPolls;
         k_combine_clear<<<dim3((nchunk + 255) / 256), dim3(256), 0, s>>>(state, nchunk);
@@ -768,10 +747,10 @@ extern "C" ld_status ld_combine_sparse_strategy(const int32_t* const* idx, const
                                                         out_count, polls);
         };
         const bool held = N <= kPre;
-        if (shape == kNarrow) held ? launch(k_combine_chunk<128, 2, 2048, true>, 128) : launch(k_combine_chunk<128, 2, 2048, false>, 128);
-        else if (shape == kFew) held ? launch(k_combine_chunk<192, 3, 2304, true>, 192) : launch(k_combine_chunk<192, 3, 2304, false>, 192);
-        else if (shape == kMiddle) held ? launch(k_combine_chunk<256, 3, 4608, true>, 256) : launch(k_combine_chunk<256, 3, 4608, false>, 256);
-        else if (shape == kLong) held ? launch(k_combine_chunk<256, 4, 4608, true>, 256) : launch(k_combine_chunk<256, 4, 4608, false>, 256);
+        if (shape == kCombineNarrow) held ? launch(k_combine_chunk<128, 2, 2048, true>, 128) : launch(k_combine_chunk<128, 2, 2048, false>, 128);
+        else if (shape == kCombineFew) launch(k_combine_chunk<192, 3, 2304, true>, 192);
+        else if (shape == kCombineMiddle) held ? launch(k_combine_chunk<256, 3, 4608, true>, 256) : launch(k_combine_chunk<256, 3, 4608, false>, 256);
+        else if (shape == kCombineLong) launch(k_combine_chunk<256, 4, 4608, true>, 256);
         else held ? launch(k_combine_chunk<512, 3, 9152, true>, 512) : launch(k_combine_chunk<512, 3, 9152, false>, 512);
         return ld_launch_status();
     }

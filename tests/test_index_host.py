@@ -7,13 +7,19 @@ import subprocess
 import numpy as np
 import pytest
 
+from combine_lists import COMBINE_LISTS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2509_04084_amd", "csrc")
 
 SHIM = """
+#include "ld_combine_shape.h"
 #include "ld_map.h"
 #include "ld_thin.h"
 extern "C" {
+int32_t combine_shape(int64_t n, int32_t N, int64_t most, int64_t total, int32_t strategy) {
+    return ld_combine_shape(n, N, most, total, strategy);
+}
 // the table row of one diff, each entry taken by the first (order 0) or the last (1) of the records that fill it
 void thin_row(const int32_t* idx, int32_t K, int32_t sub, int32_t nsub, int32_t order, int32_t* row) {
     for (int32_t s = 0; s <= nsub; ++s) row[s] = -1;
@@ -45,7 +51,7 @@ def shim(tmp_path_factory):
     with open(src, "w") as f:
         f.write(SHIM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-fPIC", "-shared", "-fsanitize=undefined",
-                    "-fno-sanitize-recover", "-I", CSRC, src, "-o", lib], check=True)
+                    "-fno-sanitize-recover", "-I", CSRC, "-I", os.path.join(ROOT, "include"), src, "-o", lib], check=True)
     L = ctypes.CDLL(lib)
     L.thin_count.restype = L.thin_slot.restype = ctypes.c_uint32
     return L
@@ -142,3 +148,44 @@ def test_bare_barriers_are_fenced_on_both_sides():
                                      (lines[i + 1], ("__ATOMIC_ACQUIRE", "__ATOMIC_ACQ_REL"))):
                     assert "__builtin_amdgcn_fence(" in fence and any(k in fence for k in kinds), f"{name}: {line}"
     assert bare == 1  # the rule above looks at lines: a barrier written in another way would pass it unseen
+
+
+TWO, NARROW, FEW, MIDDLE, LONG, WIDE = range(6)
+
+
+def combine_shape(shim, n, counts, strategy=0):
+    return shim.combine_shape(ctypes.c_int64(n), len(counts), ctypes.c_int64(max(counts)), ctypes.c_int64(sum(counts)), strategy)
+
+
+@pytest.mark.parametrize("n,N,rho,shape", [
+    (1_557_611_200, 8, 100, MIDDLE), (1_400_000_000, 8, 1000, NARROW), (5_000_000, 8, 1000, NARROW), (400_000_000, 8, 60, WIDE),
+    # where one pass was the slower one: 300 us two passes / 502 one, 187 / 291, 66 / 88, 119 / 210, 612 / 1043, 258 / 411, 53 / 76
+    (119_177_435, 64, 313, TWO), (329_999_869, 12, 129, TWO), (76_868_857, 16, 150, TWO), (31_779_675, 64, 294, TWO),
+    (1_087_848_157, 16, 170, TWO), (445_490_825, 16, 175, TWO), (65_608_085, 9, 120, TWO),
+    # and where two are: 288 / 170, 84 / 65, 1185 / 709, 8 lists of 0.35 % whose layers differ in density 50 / 46 (narrow 58)
+    (1_400_000_000, 16, 1000, NARROW), (10_000_000, 16, 100, WIDE), (400_000_000, 16, 50, WIDE), (20_000_000, 8, 290, MIDDLE)])
+def test_combine_takes_the_way_that_measured_faster(shim, n, N, rho, shape):
+    assert combine_shape(shim, n, [n // rho] * N) == shape
+
+
+def test_combine_strategies_are_what_the_caller_says(shim):
+    for n, N, rho in ((1000, 1, 2), (10 ** 6, 64, 3), (2 ** 31 - 1, 64, 2), (2 ** 31 - 1, 2, 1), (400_000_000, 12, 129)):
+        assert combine_shape(shim, n, [n // rho] * N, 1) == TWO
+        for strategy in (2, 3):
+            assert combine_shape(shim, n, [n // rho] * N, strategy) != TWO
+        for k in range(N):  # shapes without a kernel for more than 8 lists are not chosen for them
+            assert k < 8 or combine_shape(shim, n, [n // rho] * (k + 1)) not in (FEW, LONG)
+
+
+def test_combine_lists_reach_the_kernels_that_they_are_made_for(shim):
+    names = ["two", "narrow", "few", "middle", "long", "wide"]
+    ran = set()
+    for name, (n, counts, span, shape) in COMBINE_LISTS.items():
+        assert names[combine_shape(shim, n, counts)] == (shape or "two"), name
+        one = names[combine_shape(shim, n, counts, 2)]
+        assert one == (shape or "wide"), name
+        ran.add((one, len(counts) > 8, name.startswith("crowded")))
+    for many in (False, True):
+        for crowded in (False, True):
+            for shape in ("narrow", "middle", "wide") + (() if many else ("few", "long")):
+                assert (shape, many, crowded) in ran, (shape, many, crowded)
