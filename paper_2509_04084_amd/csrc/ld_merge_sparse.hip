@@ -542,42 +542,60 @@ __global__ __launch_bounds__(256) void k_merge_scatter(float* __restrict__ w,
     w[i] = __fsub_rn(w[i], p);
 }
 
-// A large diff scattered by granules of 64 bytes: four lanes read a granule that some record falls into, the first record's
-// lanes apply all of its records (at most 16, one after the other in the list) and write it back whole.
+// A large diff scattered by granules of 64 bytes: four lanes read a granule that some record falls into, apply all of its
+// records (at most 16, one after the other in the list) and write it back whole.
 // What bounds the scatter of more records than the last-level cache takes granules for are the partial writes: 15.6 M updated
 // words in 1.56 G elements take 294 us to read and 666 to write alone, as whole granules 259. Whole 128-byte lines
 // are more bytes (676 us for both), plain loads or stores leave the granules in the caches (720).
-// Records from which it is the faster one, as measured, us word by word / by granules (another 0.8 GB written in between): 3 % of the
-// elements, 12 M records 442 / 347 (432 / 387), 4 M 128 / 118 (141 / 129), 3 M 75 / 90; 1 %, 15.6 M 719 / 656 (719 / 700), 6 M
-// 282 / 255 (276 / 271), 4 M 187 / 174 (183 / 180), 3 M 115 / 128; 0.3 %, 4 M 206 / 195 (200 / 208), 2 M 74 / 100.
-// A list that does not ascend or leaves [0, n) (a damaged file's) stays within the list and w here: at most
-// kGran records from each leader on, granules inside w only.
+// A wave whose records crowd into few granules (rows that every iteration touches) updates them word by word instead: its words
+// are whole lines already, and a granule's records are a chain. kCrowded: granules of a wave's 64 records up to which it does.
+// 15.6 M records in as many elements / 0.15 / 0.1 / 0.06 of theirs, us word by word 41 / 205 / 293 / 422, all by granules 470 / 241 /
+// 241 / 297, now 41 / 204 / 230 / 294.
+// Granules that hold records of two waves are updated word by word by both, so no wave reads another's records.
+// A list that does not ascend or leaves [0, n) (a damaged file's) stays within the list and w here.
 constexpr int kGran = 16;                    // elements
 constexpr int kGranLanes = kGran / 4;        // lanes per granule
 constexpr int kGranPer = LD_WAVE / kGranLanes;
-constexpr int32_t kGranulesFrom = 5000000;
+constexpr int kCrowded = 32;
+
+// Diffs that it is the faster way for, us word by word / by granules, and the same with another 0.8 GB written in between (a diff
+// read back from storage finds neither itself nor its granules in the cache): 3 %, 15.6 M records 571 / 449 (565 / 507), 6 M 220 / 170 (212 /
+// 192), 2 M 45 / 59 (79 / 68); 1 %, 15.6 M 718 / 650 (715 / 694), 6 M 279 / 249 (275 / 268), 5.1 M 1.2 % 228 / 200 (213 / 215); but
+// 0.3-0.7 %, 5 to 8 M 270 / 255 (250 / 258), equidistant 6 M 308 / 301 (302 / 321), 9 M 407 / 394 (407 / 412).
+bool granules_pay(int64_t n, int64_t k) { return k >= 9000000 || (k >= 5000000 && k * 80 >= n); }
 
 __global__ __launch_bounds__(256) void k_merge_granules(float* __restrict__ w, int32_t n, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ val, int32_t K, float lr) {
-    constexpr int kHold = LD_WAVE + kGran;   // a wave's records and those that may share its last one's granule
-    __shared__ int32_t at[256 / LD_WAVE][kHold];
-    __shared__ float by[256 / LD_WAVE][kHold];
+    __shared__ int32_t at[256 / LD_WAVE][LD_WAVE];
+    __shared__ float by[256 / LD_WAVE][LD_WAVE];
     const int lane = threadIdx.x & (LD_WAVE - 1), wave = threadIdx.x / LD_WAVE;
     const int32_t base = static_cast<int32_t>(blockIdx.x) * 256 + wave * LD_WAVE;  // K <= n <= INT_MAX: the grid ends below 2^31
     if (base >= K) return;
-    int32_t* qi = at[wave];
-    float* qp = by[wave];
     const int32_t left = K - base;           // >= 1
-    qi[lane] = lane < left ? idx[base + lane] : -1;
-    qp[lane] = lane < left ? __fmul_rn(lr, val[base + lane]) : 0.0f;
-    if (lane < kGran) {
-        const bool have = LD_WAVE + lane < left;
-        qi[LD_WAVE + lane] = have ? idx[base + LD_WAVE + lane] : -1;
-        qp[LD_WAVE + lane] = have ? __fmul_rn(lr, val[base + LD_WAVE + lane]) : 0.0f;
+    const int32_t i = lane < left ? idx[base + lane] : -1;
+    const float p = lane < left ? __fmul_rn(lr, val[base + lane]) : 0.0f;
+    const int32_t g = i >= 0 && i < n ? i / kGran : -1;
+    // the granule of the lane before (lane 0: none)
+    const int32_t g_before = __builtin_amdgcn_update_dpp(-1, g, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+    const uint64_t first = __ballot(g >= 0 && g != g_before);  // the first record of its granule in the wave
+    if (__popcll(first) <= kCrowded) {
+        if (g >= 0) w[i] = __fsub_rn(w[i], p);
+        return;
     }
-    const int32_t ahead = base > 0 ? idx[base - 1] : -1;
+    // lane 0: the record before the wave's, lane 63: the one behind (loaded ahead, a crowded wave would be a third slower)
+    int32_t beside = -1;
+    if (lane == 0 && base > 0) beside = idx[base - 1];
+    if (lane == LD_WAVE - 1 && left > LD_WAVE) beside = idx[base + LD_WAVE];
+    const int32_t g_beside = beside >= 0 && beside < n ? beside / kGran : -1;
+    const int32_t shared0 = __builtin_amdgcn_readlane(g_beside, 0), shared1 = __builtin_amdgcn_readlane(g_beside, LD_WAVE - 1);
+    // of a granule that a neighbouring wave has records of too, or one that w ends in
+    const bool alone = g >= 0 && (g == shared0 || g == shared1 || g >= n / kGran);
+    at[wave][lane] = alone ? -1 : g < 0 ? -1 : i;
+    by[wave][lane] = p;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own words: its LDS operations complete in order
     __builtin_amdgcn_wave_barrier();
+    const int32_t* qi = at[wave];
+    const float* qp = by[wave];
 
     const int part = lane % kGranLanes;
     ld_f32x4 x[kGranLanes];
@@ -585,37 +603,28 @@ __global__ __launch_bounds__(256) void k_merge_granules(float* __restrict__ w, i
 #pragma unroll
     for (int t = 0; t < kGranLanes; ++t) {
         const int r = t * kGranPer + lane / kGranLanes;
-        const int32_t i = qi[r], prev = r > 0 ? qi[r - 1] : ahead;
-        gran[t] = i >= 0 && i < n && (prev < 0 || i / kGran != prev / kGran) ? i / kGran : -1;
+        gran[t] = first >> r & 1u && qi[r] >= 0 ? qi[r] / kGran : -1;
         x[t] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (gran[t] >= 0 && gran[t] < n / kGran)
-            x[t] = ld_nt_load(reinterpret_cast<const ld_f32x4*>(w) + static_cast<int64_t>(gran[t]) * kGranLanes + part);
+        if (gran[t] >= 0) x[t] = ld_nt_load(reinterpret_cast<const ld_f32x4*>(w) + static_cast<int64_t>(gran[t]) * kGranLanes + part);
     }
+    if (alone) w[i] = __fsub_rn(w[i], p);
 #pragma unroll
     for (int t = 0; t < kGranLanes; ++t) {
-        const int r = t * kGranPer + lane / kGranLanes;
         if (gran[t] < 0) continue;
-        if (gran[t] < n / kGran) {
-            int32_t i = qi[r];
-            int k = r;
-            do {
-                const float p = qp[k];
-                const int c = i % kGran - part * 4;  // the lane's own elements: 0 to 3
-                x[t].x = c == 0 ? __fsub_rn(x[t].x, p) : x[t].x;
-                x[t].y = c == 1 ? __fsub_rn(x[t].y, p) : x[t].y;
-                x[t].z = c == 2 ? __fsub_rn(x[t].z, p) : x[t].z;
-                x[t].w = c == 3 ? __fsub_rn(x[t].w, p) : x[t].w;
-                ++k;
-                i = k < r + kGran ? qi[k] : -1;
-            } while (i >= 0 && i / kGran == gran[t]);
-            ld_nt_store(x[t], reinterpret_cast<ld_f32x4*>(w) + static_cast<int64_t>(gran[t]) * kGranLanes + part);
-        } else if (part == 0) {  // w ends inside this granule
-            for (int k = r; k < r + kGran; ++k) {
-                const int32_t i = qi[k];
-                if (i < 0 || i >= n || i / kGran != gran[t]) break;
-                w[i] = __fsub_rn(w[i], qp[k]);
-            }
-        }
+        const int r = t * kGranPer + lane / kGranLanes;
+        int32_t e = qi[r];
+        int k = r;
+        do {
+            const float q = qp[k];
+            const int c = e % kGran - part * 4;  // the lane's own elements: 0 to 3
+            x[t].x = c == 0 ? __fsub_rn(x[t].x, q) : x[t].x;
+            x[t].y = c == 1 ? __fsub_rn(x[t].y, q) : x[t].y;
+            x[t].z = c == 2 ? __fsub_rn(x[t].z, q) : x[t].z;
+            x[t].w = c == 3 ? __fsub_rn(x[t].w, q) : x[t].w;
+            ++k;
+            e = k < LD_WAVE ? qi[k] : -1;
+        } while (e >= 0 && e / kGran == gran[t]);
+        ld_nt_store(x[t], reinterpret_cast<ld_f32x4*>(w) + static_cast<int64_t>(gran[t]) * kGranLanes + part);
     }
 }
 
@@ -745,7 +754,7 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
             if (K[t] == 0) continue;
             const int32_t k = static_cast<int32_t>(K[t]);
             const dim3 grid((static_cast<uint32_t>(k) + 255) / 256);
-            if (k >= kGranulesFrom && ld_aligned(w, kGran * 4))
+            if (granules_pay(n, k) && ld_aligned(w, kGran * 4))
                 k_merge_granules<<<grid, dim3(256), 0, s>>>(w, static_cast<int32_t>(n), idx[t], val[t], k, lr);
             else
                 k_merge_scatter<<<grid, dim3(256), 0, s>>>(w, idx[t], val[t], k, lr);

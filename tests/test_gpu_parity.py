@@ -1811,3 +1811,42 @@ def test_combine_asks_again_what_it_waited_for_in_vain():
         idxs.append(torch.minimum(at, n - K + torch.arange(K, device=DEV)).int())
     waiting, alone = combine_times((2, 3), idxs, n)
     assert alone <= 6 * waiting, f"{alone * 1e3:.0f} us, waiting {waiting * 1e3:.0f}"
+
+
+def records_of(kind, n, K, gen):
+    """About K ascending positions of [0, n): rows of 768, all in the first fiftieth, one in nine, or runs and gaps in turn."""
+    if kind == "rows":
+        rows = torch.randperm(n // 768, device=DEV, generator=gen)[:K // 768].sort().values
+        at = (rows[:, None] * 768 + torch.arange(768, device=DEV)).reshape(-1)
+    elif kind == "first fiftieth":
+        at = torch.arange(max(K, n // 50), device=DEV)[:K]
+    elif kind == "one in nine":  # about half of the waves are crowded
+        at = torch.arange(n, device=DEV)[torch.rand(n, device=DEV, generator=gen) < K / n]
+    else:  # 40 records in a run, then 40 some way apart, with ends at every place of a granule and of a wave
+        gaps = torch.randint(1, 60, (K,), device=DEV, generator=gen)
+        gaps[(torch.arange(K, device=DEV) // 40) % 2 == 0] = 1
+        at = gaps.cumsum(0)
+        at = at[at < n]
+    return at.int()
+
+
+@pytest.mark.parametrize("kind,n,K", [("one in nine", 50_000_003, 5_600_000), ("runs and gaps", 200_000_001, 9_500_000),
+                                      ("rows", 700_000_000, 9_600_000), ("first fiftieth", 700_000_017, 14_000_000)])
+def test_scatter_of_crowded_and_sparse_waves(kind, n, K):
+    """Waves that go by granules beside waves that go word by word, granules that both have records of. Bit for bit, and where
+    the records crowd no slower than all of it word by word (w off its granules): as chains of one granule's records ten times."""
+    print(f"[scatter] {kind} n={n} K={K}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    idx = records_of(kind, n, K, gen)
+    assert idx.numel() >= 9_000_000 or (idx.numel() >= 5_000_000 and idx.numel() * 80 >= n)
+    val = torch.randn(idx.numel(), generator=gen, device=DEV)
+    w = torch.randn(n, generator=gen, device=DEV)
+    want = w.clone()
+    want[idx.long()] -= torch.tensor(0.1, device=DEV) * val
+    ld.ld_merge_sparse(w, [idx], [val], 0.1, strategy=ld.LD_MERGE_SCATTER)
+    assert torch.equal(w.view(torch.int32), want.view(torch.int32))
+    if kind in ("rows", "first fiftieth"):
+        del want
+        off = torch.zeros(n + 4, device=DEV)[4:]
+        here, words = lowest_times([lambda x=x: ld.ld_merge_sparse(x, [idx], [val], 0.1, strategy=ld.LD_MERGE_SCATTER) for x in (w, off)])
+        assert here <= 1.25 * words, f"{here * 1e3:.0f} us, word by word {words * 1e3:.0f}"
