@@ -1850,3 +1850,22 @@ def test_scatter_of_crowded_and_sparse_waves(kind, n, K):
         off = torch.zeros(n + 4, device=DEV)[4:]
         here, words = lowest_times([lambda x=x: ld.ld_merge_sparse(x, [idx], [val], 0.1, strategy=ld.LD_MERGE_SCATTER) for x in (w, off)])
         assert here <= 1.25 * words, f"{here * 1e3:.0f} us, word by word {words * 1e3:.0f}"
+
+
+@pytest.mark.parametrize("n,W,K,kind", [(52_583_779, 8, 142_000, "first fiftieth"), (35_059_415, 4, 252_000, "rows"),
+                                        (81_993_579, 3, 811_000, "first fiftieth"), (300_176_903, 13, 622_000, "rows")])
+def test_merge_of_crowded_sparse_windows_is_scattered(n, W, K, kind):
+    """Windows that touch little of w, all of it in one place: with the workspace that the query gives they take no longer than
+    with the least, with which they are scattered. Priced as if every record cost a line of its own they went through a table
+    of all of w: three to nine times as long."""
+    print(f"[merge] {kind} n={n} W={W} K={K}", flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    idx = [records_of(kind, n, K, gen) for _ in range(W)]
+    val = [torch.randn(i.numel(), generator=gen, device=DEV) for i in idx]
+    w = [torch.zeros(n, device=DEV) for _ in range(2)]
+    nbytes = (ld.ld_merge_sparse_workspace(n, [i.numel() for i in idx]), int(ld.load().ld_merge_sparse_workspace(n, W, None)))
+    assert nbytes[0] > nbytes[1]
+    ws = [torch.empty(b, dtype=torch.uint8, device=DEV) for b in nbytes]
+    asked, least = lowest_times([lambda j=j: ld.ld_merge_sparse(w[j], idx, val, 0.1, ws[j]) for j in range(2)])
+    assert torch.equal(w[0].view(torch.int32), w[1].view(torch.int32))
+    assert asked <= 1.25 * least, f"{asked * 1e3:.0f} us, with the least workspace {least * 1e3:.0f}"
