@@ -449,6 +449,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
 // 250 -> 85. Sub-tiles of 4096: 73 us for the first (nine waves per CU), of 2560: 65; 10 / 13 / 17 / 25 diffs a batch 67.6 / 66.8 /
 // 66.8 / 67.5. The update left to the LDS unit's float add: 25 us more (sub-tiles of 4096).
 constexpr int kRowSub = 2048;
+constexpr int kRowBatch = 17;   // diffs whose windows are requested together (ten if they are two windows each)
 
 template <int PRE, int WIN, int SETS>
 __global__ __launch_bounds__(LD_WAVE) void k_merge_rows(float* __restrict__ w, int64_t n, int32_t nsub, DiffTable tb,
@@ -656,9 +657,12 @@ namespace {
 // A group of `gw` diffs whose largest holds `most` records is "thin" when a diff brings few records to 8192 elements and the
 // group is long: it then runs a lane per record (k_merge_thin). At most 48 for large arrays; measured,
 // us with the sweep / a lane per record: 20 diffs of 0.25 % on 100 M elements 164 / 148, 40 of 0.5 % 240 / 228; 20 of 1 %
-// 199 / 225. At most 20 for small ones, where k_merge_rows is the other way: 60 diffs of 0.25 % on 25 M 60 us either way, 30 of
-// 0.5 % 49 (a lane per record 62), 100 of 0.1 % 83 (57).
-bool thin_group(int64_t n, int32_t gw, int64_t most) { return gw > 10 && most * kSub <= (n < kFewSubs ? 20 : 48) * n; }
+// 199 / 225. At most 20 for small ones whose diffs are one batch of k_merge_rows (17), which is the faster way then; with more
+// batches it is not (3 M elements, 87 diffs of 0.3 %: rows 30 us, a lane per record 19; 5.9 M, 84 diffs of 0.27 % whose density
+// differs from layer to layer 52 / 31; 30 diffs of 0.25 % on 25 M 55 / 49).
+bool thin_group(int64_t n, int32_t gw, int64_t most) {
+    return gw > 10 && most * kSub <= (n < kFewSubs && gw <= kRowBatch ? 20 : 48) * n;
+}
 
 // Windows from a table (k_merge_rows), sweep / rows in us: 200 M elements, 4 diffs of 1 % 280 / 279, 100 M, 20 of 1 % 192 / 176,
 // 60 of 1 % 361 / 298; but 170 M, 30 of 2 % 449 / 462, 300 M, 9 of 0.5 % 413 / 424 and 600 M, 20 of 1 % 996 / 1100: the pass
@@ -792,7 +796,7 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
             else launch_subtab<kRowSub>(tb, gw, most, nsub, ctab, s);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
             if (thin) k_merge_thin<<<dim3((nsub + 7) / 8 * 8), wave, 0, s>>>(w, n, nsub, tb, gw, ctab, lr);
-            else if (rows_windows(n, most) == 1) launch_rows<17, 1>(w, n, nsub, tb, gw, ctab, lr, s);
+            else if (rows_windows(n, most) == 1) launch_rows<kRowBatch, 1>(w, n, nsub, tb, gw, ctab, lr, s);
             else launch_rows<10, 2>(w, n, nsub, tb, gw, ctab, lr, s);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
             continue;

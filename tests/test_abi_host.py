@@ -312,3 +312,16 @@ def test_compress_paths_argument_errors():
     assert lib.ld_compress_topk_paths(V(0), wsb, 2, _p(off), V(FAKE), V(0), V(0)) == -3
     assert lib.ld_compress_topk_paths(V(FAKE), wsb, -1, _p(off), V(FAKE), V(0), V(0)) == -2
     assert lib.ld_compress_topk_paths(V(FAKE), wsb, 0, _p(off), V(FAKE), V(0), V(0)) == 0
+
+
+@pytest.mark.parametrize("n,W,per8192,sub", [
+    # a lane per record (sub-tiles of 4096): us of the windows of records from a table (2048) and of it
+    (5_912_473, 84, 22, 4096), (2_592_267, 90, 21, 4096), (332_287, 60, 23, 4096), (25_000_000, 30, 41, 4096),  # 52/31 47/30 29/17 55/49
+    (124_000_000, 100, 9, 4096), (100_000_000, 40, 41, 4096),
+    # one batch of windows, or denser diffs
+    (3_000_000, 17, 30, 2048), (25_600_000, 50, 82, 2048), (5_000_000, 10, 9, 2048), (3_000_000, 90, 49, 2048)])
+def test_windows_take_the_table_that_measured_faster(n, W, per8192, sub):
+    lib = ld.load()
+    K = np.full(W, n * per8192 // 8192, np.int64)
+    size = -(-(W * (-(-n // sub) + 1) * 4) // 256) * 256
+    assert lib.ld_merge_sparse_workspace(n, W, _p(K)) == size

@@ -522,6 +522,12 @@ def test_merge_sweep_shapes_of_large_arrays(n, per8192, W, kind):
     assert torch.equal(w.view(torch.int32), ref.view(torch.int32))
 
 
+def table_of(n, W, sub):
+    """Bytes of the table of records per sub-tile that a window asks for: the sub-tile tells which kernel merges it (4096: a
+    lane per record, 2048: a window of records per diff)."""
+    return -(-(W * (-(-n // sub) + 1) * 4) // 256) * 256
+
+
 @pytest.mark.parametrize("n", [100, 4095, 4097, 100003])
 @pytest.mark.parametrize("per8192", [3, 47, 49])
 @pytest.mark.parametrize("W", [11, 64, 65, 128, 131])
@@ -546,7 +552,8 @@ def test_merge_lane_per_record_edges(n, per8192, W):
 @pytest.mark.parametrize("W", [11, 64, 65, 131])
 @pytest.mark.parametrize("case", ["line", "rows", "full", "column", "columns"])
 def test_merge_lane_per_record_dense_sub_tiles_and_columns(n, W, case):
-    # Windows that the rule takes for sparse (at most 48 records per 8192 elements of all) and that are not evenly so:
+    # Windows that the rule takes for sparse (at most 48 records per 8192 elements of all, with 11 diffs 20: the last two cases
+    # go by windows of records there) and that are not evenly so:
     #   line     every sub-tile a few records either side of where it goes through diff after diff
     #   rows     runs of 768 elements in the first, a middle and the ragged last sub-tile, the same in every diff
     #   full     whole sub-tiles, four trips of records and more
@@ -573,6 +580,29 @@ def test_merge_lane_per_record_dense_sub_tiles_and_columns(n, W, case):
     w0 = synth.base_weights(n).numpy()
     w = to_gpu(w0)
     ws = torch.empty(ld.ld_merge_sparse_workspace(n, [i.size for i in idxs]), dtype=torch.uint8, device=DEV)
+    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, ws, strategy=ld.LD_MERGE_SWEEP)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
+@pytest.mark.parametrize("W,per8192,case", [(11, 19, "even"), (11, 20, "even"), (11, 21, "even"), (17, 20, "even"), (18, 20, "even"),
+                                            (18, 48, "even"), (18, 49, "even"), (11, 16, "column"), (18, 32, "column"), (131, 32, "column")])
+def test_merge_lane_per_record_where_its_line_lies(W, per8192, case):
+    # either side of the line, 20 records per 8192 elements up to 17 diffs and 48 with more, and the same column of
+    # elements 512 or 256 apart in every diff (all on one slot of the owner table, were it not for the hash)
+    n = 8192 * 41
+    rs = np.random.RandomState(W + per8192)
+    K = n * per8192 // 8192
+    idxs = [np.arange(5, n, 8192 // per8192) if case == "column" else np.sort(rs.choice(n, K, replace=False)) for _ in range(W)]
+    idxs = [i.astype(np.int32) for i in idxs]
+    assert max(i.size for i in idxs) == K
+    nbytes = ld.ld_merge_sparse_workspace(n, [i.size for i in idxs])
+    lanes = per8192 <= (48 if W > 17 else 20)
+    assert nbytes == max(table_of(n, min(W, 128), 4096 if lanes else 2048), table_of(n, W - 128, 2048) if W > 128 else 0)
+    vals = [(rs.standard_normal(i.size) * 1e-2).astype(np.float32) for i in idxs]
+    w0 = synth.base_weights(n).numpy()
+    w = to_gpu(w0)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
     ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, ws, strategy=ld.LD_MERGE_SWEEP)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
@@ -691,7 +721,7 @@ def test_merge_thin_long_windows(case):
     K = [i.size for i in idxs]
     full_ws = ld.ld_merge_sparse_workspace(n, K)
     min_ws = int(ld.load().ld_merge_sparse_workspace(n, len(K), None))
-    assert full_ws > min_ws, "this window was meant to qualify for the per-sub-tile table"
+    assert full_ws == table_of(n, len(K), 4096) > min_ws, "this window was meant to run a lane per record"
     for nbytes in (full_ws, min_ws):
         w = to_gpu(w0)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
