@@ -667,10 +667,12 @@ bool thin_group(int64_t n, int32_t gw, int64_t most) {
 // Windows from a table (k_merge_rows), sweep / rows in us: 200 M elements, 4 diffs of 1 % 280 / 279, 100 M, 20 of 1 % 192 / 176,
 // 60 of 1 % 361 / 298; but 170 M, 30 of 2 % 449 / 462, 300 M, 9 of 0.5 % 413 / 424 and 600 M, 20 of 1 % 996 / 1100: the pass
 // over the index arrays costs what the windows save. Two windows where a sub-tile's records outgrow one (2 % a diff): 25 M, 50 of 3.3 %
-// 170 / 127, 3 M, 20 of 2.5 % 29 / 18, but 100 M, 30 of 3.3 % 358 / 368.
+// 170 / 127, 3 M, 20 of 2.5 % 29 / 18, but 100 M, 30 of 3.3 % 358 / 368. The larger the array the earlier: a sub-tile with more records than its
+// window is served diff after diff, which few are of even records but many where layers differ in density (75 M elements,
+// 53 diffs of 2 %: sweep 408, one window 478, two 372; 46 M, 85 of 1.7 % 420 / 458 / 348; 87 M, 18 of 1.6 % 175 / 200).
 constexpr int64_t kRowsMost = 120000000;
 int rows_windows(int64_t n, int64_t most) {  // 64-record windows per diff, 0: another way
-    if (n < kRowsMost && most * kSub <= 168 * n) return 1;
+    if (n < kRowsMost && most * kSub <= (n < 20000000 ? 168 : n < kFewSubs ? 120 : 100) * n) return 1;
     return n < kFewSubs ? 2 : 0;
 }
 
