@@ -247,33 +247,35 @@ constexpr int kThinDeep = 16;
 static_assert(kThinSub % (4 * LD_WAVE) == 0 && kThinSub <= 4096 && kOwner == 256, "whole rows of 16-byte accesses; see ld_thin_slot");
 
 // tab[t * (nsub + 1) + s] = number of records of diff t with idx < s * SUB, s = 0 .. nsub.
-// A thread looks at kSubtabPer consecutive records (16-byte loads; the index arrays of these paths are
+// A thread looks at PER consecutive records (16-byte loads; the index arrays of these paths are
 // 16-byte aligned) and at the one before them, and fills the entries between the sub-tiles of
 // neighbouring records; the thread that meets record K closes the row.
-// Records per thread: 4 / 8 / 16 67.1 / 65.3 / 67.8 us per call with 51 MB of indices, 307 / 298 / 312 with 240 MB.
-constexpr int kSubtabPer = 8;
+// PER records per thread, by the records of the table's diffs: 4 / 8 / 16 67.1 / 65.3 / 67.8 us per call with 12.8 M of them,
+// 307 / 298 / 312 with 60 M, but the work of a thread is a chain, and short lists leave most of the chip to few
+// threads: 4 takes 3 to 9 % less of a call below 1 M records (up to 40 % where the lists are sparser than the sub-tiles), as much at 10 M.
+constexpr int64_t kSubtabMany = 10000000;
 // Sub-tiles without a record that a thread fills by itself; the lanes of its wave share longer stretches (12 diffs of
 // 1 % in the first tenth of 110 M elements: 1890 us a call with one thread filling the other nine).
 constexpr int32_t kSubtabWide = 16;
 
-template <int SUB>
+template <int SUB, int PER>
 __global__ __launch_bounds__(256) void k_subtab(DiffTable tb, int32_t nsub, int32_t* __restrict__ tab) {
     const int t = blockIdx.y;
     const int32_t K = tb.K[t];
     const int32_t* __restrict__ idx = tb.idx[t];
-    const int32_t j0 = (static_cast<int32_t>(blockIdx.x) * 256 + static_cast<int32_t>(threadIdx.x)) * kSubtabPer;
+    const int32_t j0 = (static_cast<int32_t>(blockIdx.x) * 256 + static_cast<int32_t>(threadIdx.x)) * PER;
     const int lane = ld_lane();
     // a block of four that begins at a record lies inside the array's last 16 bytes at worst
-    ld_u32x4 q[kSubtabPer / 4];
+    ld_u32x4 q[PER / 4];
 #pragma unroll
-    for (int u = 0; u < kSubtabPer / 4; ++u) {
+    for (int u = 0; u < PER / 4; ++u) {
         q[u] = ld_u32x4{0u, 0u, 0u, 0u};
         if (j0 + 4 * u < K) q[u] = *reinterpret_cast<const ld_u32x4*>(idx + j0 + 4 * u);
     }
     int32_t a = j0 == 0 || j0 > K ? -1 : idx[j0 - 1] / SUB;
     int32_t* row = tab + static_cast<int64_t>(t) * (nsub + 1);
 #pragma unroll
-    for (int c = 0; c < kSubtabPer; ++c) {
+    for (int c = 0; c < PER; ++c) {
         const int32_t j = j0 + c;
         const int32_t b = j >= K ? nsub : static_cast<int32_t>(q[c / 4][c % 4]) / SUB;
         LdThinEntries fill = ld_thin_entries(a, b, nsub);
@@ -640,7 +642,10 @@ void launch_sweep(float* w, int64_t n, int32_t nchunk, const DiffTable& tb, int3
 
 template <int SUB>
 void launch_subtab(const DiffTable& tb, int32_t gw, int64_t most, int32_t nsub, int32_t* tab, hipStream_t s) {
-    k_subtab<SUB><<<dim3(static_cast<uint32_t>(most / (256 * kSubtabPer) + 1), gw), dim3(256), 0, s>>>(tb, nsub, tab);
+    int64_t records = 0;
+    for (int32_t t = 0; t < gw; ++t) records += tb.K[t];
+    if (records < kSubtabMany) k_subtab<SUB, 4><<<dim3(static_cast<uint32_t>(most / (256 * 4) + 1), gw), dim3(256), 0, s>>>(tb, nsub, tab);
+    else k_subtab<SUB, 8><<<dim3(static_cast<uint32_t>(most / (256 * 8) + 1), gw), dim3(256), 0, s>>>(tb, nsub, tab);
 }
 
 template <int PRE, int WIN>

@@ -635,6 +635,28 @@ def test_merge_rows_edges(n, per8192, W):
         np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(ref), err_msg=f"strategy {strategy}")
 
 
+@pytest.mark.parametrize("n,sub", [(3_000_001, 2048), (14_000_003, 4096)])
+@pytest.mark.parametrize("K", [78_100, 78_150])
+def test_merge_tables_of_few_and_of_many_records(n, sub, K):
+    # either side of 10 M records, from which a thread of the table's pass looks at eight of them instead of four
+    W = 128
+    gen = torch.Generator(device=DEV).manual_seed(K + n)
+    idx = [torch.randperm(n, device=DEV, generator=gen)[:K - t % 2].sort().values.int() for t in range(4)]
+    idx = [idx[t % 4] for t in range(W)]
+    val = [torch.randn(i.numel(), generator=gen, device=DEV) for i in idx]
+    counts = [i.numel() for i in idx]
+    assert ld.ld_merge_sparse_workspace(n, counts) == table_of(n, W, sub)
+    w = torch.randn(n, generator=gen, device=DEV)
+    ref = w.clone()
+    ws = torch.full((table_of(n, W, sub),), 0xA5, dtype=torch.uint8, device=DEV)
+    ld.ld_merge_sparse(w, idx, val, 0.1, ws)
+    lr = torch.tensor(0.1, device=DEV)
+    for i, v in zip(idx, val):
+        at = i.long()
+        ref[at] = ref[at] - lr * v
+    assert torch.equal(w.view(torch.int32), ref.view(torch.int32))
+
+
 @pytest.mark.parametrize("W", [2, 10, 40])
 @pytest.mark.parametrize("way", ["full", "minimum", "misaligned", "static"])
 def test_merge_of_sparse_windows_with_and_without_tables(W, way):
