@@ -54,10 +54,15 @@ __device__ __forceinline__ void clear_tiles(float* tile1, float* tile2, int lane
     }
 }
 
-// First record of the window for sub-tile `part` of a chunk whose records are [b, e): ahead of where the sub-tile's begin
-// if the chunk's are evenly spread. Records of a neighbouring chunk that it reaches do not matter.
-__device__ __forceinline__ int32_t window_begin(int32_t b, int32_t e, int32_t part) {
-    const int32_t p = b + ((e - b) * part) / kChunkSubs - kMargin;
+// First record of the window for sub-tile `part` of a chunk of `len` elements whose records are [b, e): ahead of where the
+// sub-tile's begin if the chunk's are evenly spread. Records of a neighbouring chunk that it reaches do not matter. The last chunk is
+// short: its records lie in its first sub-tiles (as if they filled 48, its last windows ended too early, and its waves were what a
+// call on a small array waited for: 450 K elements, 37 diffs of 0.5 %, 44 us instead of 33).
+__device__ __forceinline__ int32_t window_begin(int32_t b, int32_t e, int32_t part, int32_t len) {
+    const uint32_t of = e > b ? static_cast<uint32_t>(e - b) : 0u;  // at most an element's worth each: products below 2^32
+    const uint32_t ahead = len == kChunk ? of * static_cast<uint32_t>(part) / kChunkSubs
+                                         : of * static_cast<uint32_t>(part * kSub) / static_cast<uint32_t>(len);
+    const int32_t p = static_cast<int32_t>(static_cast<uint32_t>(b) + ahead) - kMargin;
     return p < 0 ? 0 : p;
 }
 
@@ -125,7 +130,9 @@ __global__ __launch_bounds__(LD_WAVE, GENERAL || WIN > 1 ? 4 : 5) void k_sparse_
         }
     }
 
-    const int32_t start = window_begin(c0, c1, part);
+    const int64_t chunk_left = n - static_cast<int64_t>(chunk) * kChunk;
+    const int32_t chunk_len = static_cast<int32_t>(chunk_left < kChunk ? chunk_left : kChunk);
+    const int32_t start = window_begin(c0, c1, part, chunk_len);
     const uint64_t ia = reinterpret_cast<uint64_t>(ip + start), va = reinterpret_cast<uint64_t>(vp + start);
     const uint32_t ia_lo = static_cast<uint32_t>(ia), ia_hi = static_cast<uint32_t>(ia >> 32);
     const uint32_t va_lo = static_cast<uint32_t>(va), va_hi = static_cast<uint32_t>(va >> 32);
@@ -181,7 +188,7 @@ __global__ __launch_bounds__(LD_WAVE, GENERAL || WIN > 1 ? 4 : 5) void k_sparse_
         if (more) {  // the records ahead of the window too where it began too late: all there are
             const int32_t* row = ctab + static_cast<int64_t>(t) * (nchunk + 1) + chunk;
             const int32_t b = row[0], e = row[1];
-            const int32_t from = hit ? window_begin(b, e, part) + WIN * LD_WAVE : lower_bound_idx(tb.idx[t], b, e, lo);
+            const int32_t from = hit ? window_begin(b, e, part, chunk_len) + WIN * LD_WAVE : lower_bound_idx(tb.idx[t], b, e, lo);
             scatter_from(tile1, tile2, tb.idx[t], tb.val[t], from, e, lo, hi, omb1, omb2, lane);
         }
         return more;

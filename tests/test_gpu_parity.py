@@ -1921,3 +1921,21 @@ def test_merge_of_crowded_sparse_windows_is_scattered(n, W, K, kind):
     asked, least = lowest_times([lambda j=j: ld.ld_merge_sparse(w[j], idx, val, 0.1, ws[j]) for j in range(2)])
     assert torch.equal(w[0].view(torch.int32), w[1].view(torch.int32))
     assert asked <= 1.25 * least, f"{asked * 1e3:.0f} us, with the least workspace {least * 1e3:.0f}"
+
+
+@pytest.mark.parametrize("part", [7453, 10559, 14391])
+def test_sparse_adam_finds_the_records_of_a_short_last_chunk(part):
+    """An array that ends early in a chunk of the range table is not slower than one that fills it: the last sub-tiles' windows lie
+    where the records do. Guessed as if the chunk were whole, they missed, and the call took a third longer."""
+    W, rho = 37, 197
+    calls = []
+    for n in (49152 * 9 + part, 49152 * 10):
+        gen = torch.Generator(device=DEV).manual_seed(n)
+        idx = [torch.randperm(n, device=DEV, generator=gen)[:n // rho].sort().values.int() for _ in range(W)]
+        val = [torch.randn(i.numel(), device=DEV, generator=gen) * 1e-2 for i in idx]
+        w, m, v = (torch.randn(n, device=DEV, generator=gen), torch.zeros(n, device=DEV), torch.ones(n, device=DEV) * 1e-6)
+        ws = torch.empty(ld.ld_merge_sparse_adam_workspace(n, [i.numel() for i in idx]), dtype=torch.uint8, device=DEV)
+        calls.append(lambda w=w, m=m, v=v, idx=idx, val=val, ws=ws: ld.ld_merge_sparse_adam(
+            w, m, v, idx, val, 2, workspace=ws, lr=1e-4, **synth.ADAM))
+    short, whole = lowest_times(calls, reps=20)
+    assert short <= 1.12 * whole, f"{short * 1e3:.1f} us, {whole * 1e3:.1f}"
