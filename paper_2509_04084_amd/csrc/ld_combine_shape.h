@@ -41,7 +41,7 @@ inline LdCombineShape ld_combine_shape_held(int64_t n, int32_t N, double list, d
 // threads without a record and barriers cost the more the more lists there are. Geometric means of two passes over one, of a
 // sweep of 1700 even inputs: narrow 1.5 for 16 lists of up to 0.2 % on more than 100 M elements, 1.1 below 50 M; middle 1.05 up to 50 M
 // (16 lists of 0.4 %) and on larger arrays 0.96 to 1 while a chunk is one round (it stays there: lists that crowd cost two passes
-// several times as much); wide 1.3-1.9 where the lists have more than 640 records a chunk (1.3 %) and, on small arrays, whose
+// up to twice as much); wide 1.3-1.9 where the lists have more than 640 records a chunk (1.3 %) and, on small arrays, whose
 // workgroups all run at once, from 200 on. Elsewhere the one pass lost: middle 0.76 in two rounds, wide 0.6 to
 // 0.73 with 16 to 32 lists of 0.3-0.8 % on more than 100 M elements (330 M, 12 lists of 0.8 %: two passes 186 us, one 295; 119 M, 64
 // of 0.3 %: 300 / 502), 0.84 with 64 lists of 0.3 % on 30 M. Lists of very different lengths: wide 0.7, middle 0.91 to 1.2.

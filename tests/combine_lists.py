@@ -31,4 +31,5 @@ COMBINE_LISTS = {
     "crowded, wide, 9 lists": (49152 * 50, [40000] + [15000] * 8, (49152 * 7 - 100, 49152 * 8), "wide"),
     "crowded, wide": (49152 * 50, [60000] * 8, (49152 * 10, 49152 * 13), "wide"),
     "crowded, wide, 17 lists": (49152 * 50, [40000] * 17, (49152 * 10, 49152 * 11 + 2), "wide"),
+    "crowded, wide, 64 lists": (49152 * 40, [7000] * 60 + [0, 1, 300, 49000], (49152 * 3 - 20, 49152 * 5), "wide"),
 }
