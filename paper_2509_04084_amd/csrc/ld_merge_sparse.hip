@@ -673,12 +673,15 @@ bool thin_group(int64_t n, int32_t gw, int64_t most) {
 // 60 of 1 % 361 / 298; but 170 M, 30 of 2 % 449 / 462, 300 M, 9 of 0.5 % 413 / 424 and 600 M, 20 of 1 % 996 / 1100: the pass
 // over the index arrays costs what the windows save. Two windows where a sub-tile's records outgrow one (2 % a diff): 25 M, 50 of 3.3 %
 // 170 / 127, 3 M, 20 of 2.5 % 29 / 18, but 100 M, 30 of 3.3 % 358 / 368. The larger the array the earlier: a sub-tile with more records than its
-// window is served diff after diff, which few are of even records but many where layers differ in density (75 M elements,
-// 53 diffs of 2 %: sweep 408, one window 478, two 372; 46 M, 85 of 1.7 % 420 / 458 / 348; 87 M, 18 of 1.6 % 175 / 200).
+// window is served diff after diff, which few are of even records but many where layers differ in density. Sweep / one window / two,
+// densities even and log-normal over 60 layers (sigma 0.7): 82 M elements, 18 diffs of 1.6 % 157 / 157 / 155 and 195 / 163 / 149, 72 of
+// 1.25 % 401 / 314 / 340 and 550 / 361 / 356, 118 M, 18 of 1.25 % 211 / 207 / 199 and 250 / 211 / 197, 76 M, 40 of 1.6 % 273 / 229 / 232 and 333 / 236 /
+// 232, 110 of 1.6 % 603 / 525 / 538 and 840 / 502 / 474: two windows are ten diffs a batch, which even records of many diffs lose by.
 constexpr int64_t kRowsMost = 120000000;
-int rows_windows(int64_t n, int64_t most) {  // 64-record windows per diff, 0: another way
-    if (n < kRowsMost && most * kSub <= (n < 20000000 ? 168 : n < kFewSubs ? 120 : 100) * n) return 1;
-    return n < kFewSubs ? 2 : 0;
+int rows_windows(int64_t n, int32_t gw, int64_t most) {  // 64-record windows per diff, 0: another way
+    if (n >= kRowsMost || most * kSub > 168 * n) return n < kFewSubs ? 2 : 0;
+    if (n < 20000000) return 1;
+    return n < kFewSubs ? (gw <= 64 && most * kSub > 120 * n ? 2 : 1) : (gw <= 32 && most * kSub > 100 * n ? 2 : 1);
 }
 
 
@@ -694,7 +697,7 @@ size_t sub_table_bytes(int64_t n, int32_t gw, int32_t sub) {
 // Bytes of the per-sub-tile table that a group would run with (0: it runs as a sweep).
 size_t group_table_bytes(int64_t n, int32_t gw, int64_t most) {
     if (thin_group(n, gw, most)) return sub_table_bytes(n, gw, kThinSub);
-    return rows_windows(n, most) ? sub_table_bytes(n, gw, kRowSub) : 0;
+    return rows_windows(n, gw, most) ? sub_table_bytes(n, gw, kRowSub) : 0;
 }
 
 // Whether a window that would be scattered runs faster in groups with tables, and can. What is certain of a scatter is 2.4 us a
@@ -803,7 +806,7 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
             else launch_subtab<kRowSub>(tb, gw, most, nsub, ctab, s);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
             if (thin) k_merge_thin<<<dim3((nsub + 7) / 8 * 8), wave, 0, s>>>(w, n, nsub, tb, gw, ctab, lr);
-            else if (rows_windows(n, most) == 1) launch_rows<kRowBatch, 1>(w, n, nsub, tb, gw, ctab, lr, s);
+            else if (rows_windows(n, gw, most) == 1) launch_rows<kRowBatch, 1>(w, n, nsub, tb, gw, ctab, lr, s);
             else launch_rows<10, 2>(w, n, nsub, tb, gw, ctab, lr, s);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
             continue;
@@ -846,10 +849,11 @@ extern "C" ld_status ld_merge_sparse(float* w, int64_t n, const int32_t* const* 
 
 // ------------------------------------------------ the entry point that allocates nothing
 //
-// The chunk table is the only scratch memory of the merge. Here it lives in a file-scope
+// The merge's only scratch memory is a group's table: the chunks' (k_chunks), or the sub-tiles' (k_subtab) where the
+// window calls for that and it fits. Here it lives in a file-scope
 // device array instead of a caller's workspace: one copy per GPU, held until the process
-// ends, shared by every call on that GPU. Nothing in it has to start at zero (k_chunks
-// writes every entry the sweep reads), so nothing is cleared between calls.
+// ends, shared by every call on that GPU. Nothing in it has to start at zero (both kernels
+// write every entry that is read), so nothing is cleared between calls.
 static __device__ __align__(256) unsigned char scratch[LD_MERGE_STATIC_SCRATCH];
 
 namespace {

@@ -328,10 +328,11 @@ def test_windows_take_the_table_that_measured_faster(n, W, per8192, sub):
 
 
 def test_windows_from_a_table_end_where_the_sweep_measured_faster():
-    # 87 M elements, 18 diffs of 1.6 % in layers of different density: the sweep 175 us, windows from a table 200; 100 M, 20 of 1 % 192 / 176
+    # 100 M elements, 20 diffs of 1 %: the sweep 192 us, windows from a table 176; 91 M, 72 of 1.25 % 432 / 350; 100 M, 30 of 3.3 % 358 / 368
     lib = ld.load()
     least = lambda n, W: lib.ld_merge_sparse_workspace(n, W, ctypes.c_void_p(0))
-    for n, W, per8192, table in ((87_000_000, 18, 128, False), (100_000_000, 20, 82, True), (100_000_000, 20, 101, False),
+    for n, W, per8192, table in ((87_000_000, 18, 128, True), (100_000_000, 20, 82, True), (90_568_583, 72, 102, True),
+                                 (100_000_000, 20, 168, True), (100_000_000, 20, 169, False),
                                  (79_000_000, 18, 300, True), (125_000_000, 20, 82, False)):
         K = np.full(W, n * per8192 // 8192, np.int64)
         assert (lib.ld_merge_sparse_workspace(n, W, _p(K)) > least(n, W)) == table, (n, per8192)
