@@ -842,8 +842,8 @@ def main():
         # vector ALU ceilings of the chip: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-operations/s.
         # Plain fp32 FMA: 2 flops per lane-operation = 78.6 TFLOP/s (the published 157.3 counts packed
         # two-wide FMA, which this build does not emit). Issue model of one Adam step on one element:
-        # 6 vector instructions, 2 of them (sqrt, rcp) quarter-rate: 12 issue slots if those do not overlap
-        # with full-rate issue, 8 if they overlap completely.
+        # 6 vector instructions, 2 of them (sqrt, rcp) of 2.1 issue slots each, as measured against
+        # v_fma_f32: 8.2 slots. The rest of a call is what is done per record and the memory traffic.
         lane_ops = 256 * 4 * 16 * 2.4e9
         steps = sparse.n * sparse.W
         next_rows["ld_merge_sparse_adam"] = {
@@ -852,11 +852,10 @@ def main():
             "hbm_frac": sparse.bytes_sparse_adam() / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             "roofline": {"bound": "alu", "achieved": tf, "peak": 78.6, "unit": "TFLOP/s", "frac": tf / 78.6,
                          "peak_packed_fma": 157.3, "frac_of_packed_peak": tf / 157.3,
-                         "issue_model_ms": {"12_slots_no_overlap": 12 * steps / lane_ops * 1e3,
-                                            "8_slots_full_overlap": 8 * steps / lane_ops * 1e3},
+                         "issue_model_ms": {"8.2_slots": 8.2 * steps / lane_ops * 1e3},
                          "note": "14 flops per element and step; peak = plain (non-packed) fp32 FMA rate of the vector "
-                                 "ALUs, 256 CUs x 4 SIMDs x 16 lanes x 2 x 2.4 GHz; the issue models count the 6 vector "
-                                 "instructions an element's step takes, 2 of them quarter-rate (sqrt, rcp)"},
+                                 "ALUs, 256 CUs x 4 SIMDs x 16 lanes x 2 x 2.4 GHz; the issue model counts the 6 vector "
+                                 "instructions an element's step takes, 2 of them (sqrt, rcp) as the 2.1 slots measured"},
             "note": "same gpt2xl window replayed through Adam on (w, m, v); not part of `value`"}
         ms, k_in, k_out = sparse.time_combine()
         log(f"[next row] ld_combine_sparse: {ms:.3f} ms per call (8 lists, {k_in:,} records -> {k_out:,})")

@@ -294,9 +294,10 @@ ld_status ld_merge_sparse_strategy(float* w, int64_t n,
  * ld_merge_sparse_static - ld_merge_sparse for callers that cannot allocate:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same operation, same results bit for bit, no workspace argument:
- * the chunk table (the merge's only scratch memory) lies in a device array that
- * is part of the library image, LD_MERGE_STATIC_SCRATCH bytes per GPU, held
- * until the process ends.  The call allocates and frees nothing and calls no
+ * the merge's only scratch memory (the table that tells where in a diff's lists
+ * the records of a part of w begin: per chunk, or per sub-tile where that fits too
+ * and is faster) lies in a device array that is part of the library image,
+ * LD_MERGE_STATIC_SCRATCH bytes per GPU, held until the process ends.  The call allocates and frees nothing and calls no
  * allocating routine; the first call on a device looks up that device's copy
  * of the array (hipGetSymbolAddress), later calls only enqueue kernels.
  *

@@ -314,7 +314,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_combine_emit(int64_t n, int32_t nch
 // a row 790, 8 bytes apart 670, 16: 640; they are written and asked from all XCDs at once) and asked for only when the values
 // are added (earlier, they mostly say nothing yet), 595; four waves to a workgroup, so that every SIMD has one, and the lists'
 // addresses by scalar loads ahead of the ranges, 540. What bounds it: chains of latencies (ranges, records, a dozen
-// barriers, the counts before) at 16 waves per CU.
+// barriers, the counts before) at 15 waves per CU.
 // Crowded chunks (much of the lists in little of the index space): their rounds take pieces of the lists, not all of them again,
 // and what goes beyond the records that a workgroup loads at once is streamed. 8 lists of 0.4 % of 400 M elements, all
 // in the first fiftieth: with every round reading all of it 2906 us, now 284; 8 lists of 13 K of 5 M 1680 / 226. Two passes take 490 for the first.

@@ -345,7 +345,7 @@ def ld_merge_sparse_static_limit() -> int:
 
 def ld_merge_sparse_static(w: torch.Tensor, idx: Sequence[torch.Tensor], val: Sequence[torch.Tensor], lr: float,
                            stream=None) -> None:
-    """ld_merge_sparse without a workspace and without any allocation (the chunk table lies in a
+    """ld_merge_sparse without a workspace and without any allocation (its table lies in a
     device array of the library); refuses windows beyond ld_merge_sparse_static_limit()."""
     lib = load()
     W = len(idx)
