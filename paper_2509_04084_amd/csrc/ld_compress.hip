@@ -308,15 +308,7 @@ __device__ __forceinline__ void find_bins(const uint32_t* h, const int (&own)[R]
             v[i][j] = h[own[i] * kBins + top - j];
             sum[i] += v[i][j];
         }
-        inc[i] = sum[i];
-    }
-#pragma unroll
-    for (int d = 1; d < LD_WAVE; d <<= 1) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const uint32_t y = __shfl_up(inc[i], d, LD_WAVE);
-            if (ld_lane() >= d) inc[i] += y;
-        }
+        inc[i] = ld_wave_iscan(sum[i]);
     }
 #pragma unroll
     for (int i = 0; i < R; ++i)
@@ -834,19 +826,10 @@ __device__ __forceinline__ uint32_t wave_counts(const Ctx& c, int32_t group) {
 }
 
 template <int ROW>
-__device__ __forceinline__ uint32_t row_iscan(uint32_t x) {  // inclusive scan over a row of ROW lanes
-#pragma unroll
-    for (int d = 1; d < ROW; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d, ROW);
-        if ((ld_lane() & (ROW - 1)) >= d) x += y;
-    }
-    return x;
-}
-
-template <int ROW>
-__device__ __forceinline__ uint32_t row_sum(uint32_t x) {
-#pragma unroll
-    for (int d = ROW / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, ROW);
+__device__ __forceinline__ uint32_t row_sum(uint32_t x) {  // over a row of ROW lanes, in every lane
+    if (ROW == LD_WAVE) return ld_wave_sum(x);
+    x = ld_row16_sum(x);
+    if (ROW == 32) x += __shfl_xor(x, 16, ROW);
     return x;
 }
 
@@ -939,7 +922,7 @@ __device__ __forceinline__ void slow_tiles(const Ctx& c, const float* __restrict
     while (todo) {
         const int u = __builtin_ctzll(todo);
         todo &= todo - 1;
-        const uint32_t cn = static_cast<uint32_t>(__shfl(static_cast<int>(mycnt), u, LD_WAVE));
+        const uint32_t cn = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(mycnt), u));
         const bool stored = cn != kOverflow;
         const uint32_t total = stored ? cn : static_cast<uint32_t>(kTile);
         const int64_t slot = static_cast<int64_t>(tile0 + u) * slot_of<RW>(c);
@@ -1147,11 +1130,11 @@ __device__ __attribute__((noinline)) Unplaced gather_lane_keys(SegState* st, uin
     const int lane = ld_lane();
     const uint32_t n_in = __popc(in);
     const uint32_t inc = ld_wave_iscan(n_in);
-    const uint32_t total = static_cast<uint32_t>(__shfl(static_cast<int>(inc), LD_WAVE - 1, LD_WAVE));
+    const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), LD_WAVE - 1));
     uint32_t base = gcap;
     if (!full) {
         if (lane == 0) base = atomicAdd(&st->gcount, total);
-        base = static_cast<uint32_t>(__shfl(static_cast<int>(base), 0, LD_WAVE));
+        base = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
         un.full = base + total > gcap;
     }
     uint32_t pos = base + inc - n_in;
@@ -1326,7 +1309,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
                 uint32_t base = gcap;
                 if (!full) {
                     if (lane == 0) base = atomicAdd(&st->gcount, total);
-                    base = static_cast<uint32_t>(__shfl(static_cast<int>(base), 0, LD_WAVE));
+                    base = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
                     full = base + total > gcap;
                 }
                 const uint32_t pos = base + mbcnt(min_);
@@ -1574,7 +1557,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
             eqm |= static_cast<uint32_t>(valid && key == T) << j;
         }
         const uint32_t mine = __popc(gtm) | (__popc(eqm) << 16);  // a tile holds at most 512 here
-        const uint32_t before = row_iscan<ROW>(mine) - mine;
+        const uint32_t before = ld_row_iscan<ROW>(mine) - mine;
         uint32_t gt_before = before & 0xFFFFu;
         uint32_t eq_rank = eq_tile + (before >> 16);
         float* rt = r + gr.base + static_cast<int64_t>(tl0 + Q.u) * kTile;
@@ -1603,7 +1586,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
 #pragma unroll
         for (int row = 0; row < kTiles; ++row) {
-            const uint32_t cnt = static_cast<uint32_t>(__shfl(static_cast<int>(rank), row * ROW + ROW - 1, LD_WAVE));
+            const uint32_t cnt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(rank), row * ROW + ROW - 1));
             const int64_t o0 = gr.out0 + tile_out[tl0 + kTiles * q + row];
             for (uint32_t i = lane; i < cnt; i += LD_WAVE) {
                 // streamed past the caches: the records are read much later, by another call
