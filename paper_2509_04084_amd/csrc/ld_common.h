@@ -72,6 +72,7 @@ static inline void ld_fill_adam_steps(LdAdamSteps& a, int32_t W, int64_t step0, 
 #ifdef __HIPCC__
 
 typedef float ld_f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t ld_u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t ld_u32x4 __attribute__((ext_vector_type(4)));
 
 // Streaming (non-temporal) 16-byte accesses; p must be 16-byte aligned.
@@ -81,6 +82,11 @@ __device__ __forceinline__ void ld_nt_store(ld_f32x4 x, ld_f32x4* p) { __builtin
 __device__ __forceinline__ void ld_nt_store(ld_u32x4 x, ld_u32x4* p) { __builtin_nontemporal_store(x, p); }
 
 __device__ __forceinline__ int ld_lane() { return __lane_id(); }
+
+__device__ __forceinline__ uint32_t ld_mbcnt(uint64_t mask) {  // set bits of `mask` below this lane
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+}
 
 // |x| as an integer that orders like the magnitude (sign bit cleared).
 __device__ __forceinline__ uint32_t ld_key(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
@@ -112,6 +118,18 @@ __device__ __forceinline__ uint32_t ld_row_iscan(uint32_t x) {
 
 // Inclusive scan over the 64 lanes of a wave.
 __device__ __forceinline__ uint32_t ld_wave_iscan(uint32_t x) { return ld_row_iscan<LD_WAVE>(x); }
+
+// Inclusive maximum over the lanes up to each (x >= 0).
+__device__ __forceinline__ uint32_t ld_wave_imax(uint32_t x) {
+    const auto more = [&](uint32_t y) { x = y > x ? y : x; };
+    more(ld_dpp0<kDppShr + 1>(x));
+    more(ld_dpp0<kDppShr + 2>(x));
+    more(ld_dpp0<kDppShr + 4>(x));
+    more(ld_dpp0<kDppShr + 8>(x));
+    more(ld_dpp0<kDppLast16, 0xa>(x));
+    more(ld_dpp0<kDppLast32, 0xc>(x));
+    return x;
+}
 
 // Sum over a row of 16 lanes, in every lane.
 __device__ __forceinline__ uint32_t ld_row16_sum(uint32_t x) {

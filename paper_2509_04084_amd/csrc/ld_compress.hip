@@ -378,11 +378,6 @@ __device__ __forceinline__ void block_select_multi(const uint32_t (&key)[ITEMS],
     for (int i = 0; i < R; ++i) out[i] = (p[i] << kShift1) | (res[3 * i] << kShift2);
 }
 
-__device__ __forceinline__ uint32_t mbcnt(uint64_t mask) {  // set bits of `mask` below this lane
-    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
-}
-
 __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 __device__ __forceinline__ uint32_t fine_bin(uint32_t key, uint32_t tau, uint32_t sh) {
@@ -736,7 +731,7 @@ __global__ __launch_bounds__(LD_WAVE) void k_main(const float* __restrict__ g, f
             flag[j] |= static_cast<uint32_t>(f) << q;
             zero[j] |= static_cast<uint32_t>(f && key >= test) << q;
             const uint64_t m = __ballot(f);
-            pos0[j] += mbcnt(m);
+            pos0[j] += ld_mbcnt(m);
             total += __popcll(m);
         }
     }
@@ -1312,7 +1307,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
                     base = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
                     full = base + total > gcap;
                 }
-                const uint32_t pos = base + mbcnt(min_);
+                const uint32_t pos = base + ld_mbcnt(min_);
                 if (in) {
                     if (pos < gcap) {
                         gkey[pos] = key;
@@ -1610,11 +1605,11 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
             const bool is_gt = have && key > T;
             const bool is_eq = have && key == T;
             const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
-            const uint32_t eq_rank = run_eq + mbcnt(me);
+            const uint32_t eq_rank = run_eq + ld_mbcnt(me);
             const bool selected = is_gt || (is_eq && eq_rank < m);
             const int64_t e = tbase + local;
             if (selected) {
-                const int64_t pos = gr.out0 + run_out + mbcnt(mg) + (umin(eq_rank, m) - umin(run_eq, m));
+                const int64_t pos = gr.out0 + run_out + ld_mbcnt(mg) + (umin(eq_rank, m) - umin(run_eq, m));
                 out_idx[pos] = static_cast<int32_t>(e);
                 out_val[pos] = v;
             }

@@ -115,7 +115,7 @@ constexpr int kAdamThreads = 256;
 constexpr int kAdamH = 4;                          // 16-byte fp32 vectors per thread and array
 constexpr int kAdamBlockElems = kAdamThreads * 4 * kAdamH; // elements per workgroup
 
-typedef uint32_t ld_u32x2 __attribute__((ext_vector_type(2)));
+
 
 // Replays steps [t0, t0 + WT) of the window (those below a.W). One workgroup per
 // kAdamBlockElems consecutive elements; every load instruction of a wave covers

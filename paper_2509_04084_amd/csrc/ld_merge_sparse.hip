@@ -222,22 +222,28 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
 // hundred times in a row. Here the records of all diffs that fall into the wave's sub-tile form one
 // list in diff order, and the lanes take 64 of it at a time. Where
 // exactly a diff's records for a sub-tile begin comes from a table of its own (k_subtab: one
-// streaming pass over the index arrays, which are small when diffs are this sparse); the diff that a
-// list position belongs to comes from a binary search over the diffs' running counts in LDS.
+// streaming pass over the index arrays, which are small when diffs are this sparse); which diff a list position
+// belongs to comes from marks where the diffs begin.
 //
-// Order: rows of 64 go through one after another. Inside a row, every pending record bids for
-// its element's slot of a small owner table with its lane, the smallest lane wins the
-// slot (atomic minimum), applies its update and leaves; lanes are in diff order, so the updates of one
-// element go through in diff order whatever else shares the slot, and any number of records is served.
+// Order: a list goes through in blocks of 512 records. Most elements are named by one record of the block: those are updated
+// at once, all rows together. A record whose element was met before in the block, and the one it met, wait: they are lined
+// up in list order and go through in rows of 64. There every pending record bids for its element's slot of a small owner
+// table with its lane, the smallest lane wins the slot (atomic minimum), applies its update and leaves; lanes are in list order, so
+// the updates of one element go through in list order whatever else shares the slot, and any number of records is
+// served. Where many of the first 128 records meet (diffs that share their positions) all rows bid, without lining up.
 // Sub-tiles where the diffs are dense go through diff after diff (kThinDense).
 //
-// Bound by the instructions and LDS round trips per row (two to three bids each), next the tile's 16 KB
-// of LDS, which leave eight waves per CU. 124 M elements, 100 diffs of 0.1 %: 296 -> 235-240 us against a lane per
-// DIFF, whose slots were mostly empty; sub-tiles of 2048 / 8192 elements: 272 / 267 us, 1024 owner slots: 239. Diffs that
-// share half of their positions with the one before (the bids of a row then go through in turn): 265 us.
+// Bound by w's bytes up to some 200 records a sub-tile (100 M elements, 20 diffs of 1/400: 6.1 TB/s), beyond by the records: pieces of
+// 16 bytes of as many lists as there are diffs. us a call when all rows bid / now: 124 M elements, 100 diffs of 0.1 % 223 / 217 (without records
+// 187, with their loads alone 212), 50 of 0.4 % 255 / 220, 100 M, 40 of 0.5 % 210 / 180, 5.9 M, 84 of 0.27 % 25 / 21; diffs that share half of their
+// positions with the one before 265 / 263 (lined up 277). Waiting records of all rows bidding together instead of lined up: 244 for
+// the second. A wave that loads its next tile while it serves one, eight waves per CU: 239 and 236 us for the first two (its waits are for the
+// records requested last). Sub-tiles of 2048 / 8192 elements: slower.
 constexpr int kThinSub = 4096;     // elements of a wave's sub-tile in this kernel
 constexpr int kThinAhead = 8;      // rows of 64 records requested together
 constexpr int kOwner = 256;        // slots of the owner table
+constexpr int kThinAlike = 16;     // of a block's first 128 records, those of an element met before beyond which the diffs count as alike
+static_assert(kOwner * 32 >= 2 * kThinSub, "two bits per element");
 // Records per diff from which a sub-tile goes through diff after diff (rows of an embedding that every iteration
 // touches) instead of in rows of the list, and the rows of 64 of one diff requested together there. 50 diffs of
 // 0.4 % on 124 M elements, all of them the same dense rows of 64 / 192 / 768 / 8192 elements: 264 / 251 / 292 / 478 us, as
@@ -297,10 +303,11 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
                                                         DiffTable tb, int32_t W, const int32_t* __restrict__ tab,
                                                         float lr) {
     __shared__ float tile[kThinSub + 4];                     // and the spare word of apply_records
-    __shared__ uint32_t before[kTableMax];                   // records of the sub-tile before diff t's
     __shared__ const int32_t* ibase[kTableMax];              // diff t's record with list position k: ibase[t][k]
     __shared__ const float* vbase[kTableMax];
-    __shared__ uint32_t owner[kOwner];
+    // of a block: the diff whose records begin at a list position; then 64 records that wait for their turn
+    __shared__ union { __align__(8) unsigned char whose[kThinAhead * LD_WAVE]; struct { uint32_t e; float p; } wait[LD_WAVE]; } line;
+    __shared__ __align__(16) uint32_t mark[kOwner];          // elements seen / seen again (a bit each), then the owner table
     constexpr int kSets = kTableMax / LD_WAVE;
     const int lane = threadIdx.x;
     const int64_t per = (static_cast<int64_t>(gridDim.x) + 7) / 8;   // each XCD walks one contiguous eighth of w
@@ -331,19 +338,17 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
 #pragma unroll
         for (int j = 0; j < kThinSub / 4 / LD_WAVE; ++j) x[j] = ld_nt_load(src + j * LD_WAVE + lane);
     }
-    uint32_t total = 0;
+    uint32_t total = 0, first[kSets];                        // first: list position of the diff's first record here
 #pragma unroll
     for (int h = 0; h < kSets; ++h) {
         const int t = h * LD_WAVE + lane;
         const uint32_t inc = ld_wave_iscan(cnt[h]);
-        const uint32_t first = total + inc - cnt[h];
-        before[t] = first;
+        first[h] = total + inc - cnt[h];
         // only positions first .. first + cnt - 1 are ever looked up through these
-        ibase[t] = t < W ? tb.idx[t] + (static_cast<int64_t>(p0[h]) - first) : nullptr;
-        vbase[t] = t < W ? tb.val[t] + (static_cast<int64_t>(p0[h]) - first) : nullptr;
+        ibase[t] = t < W ? tb.idx[t] + (static_cast<int64_t>(p0[h]) - first[h]) : nullptr;
+        vbase[t] = t < W ? tb.val[t] + (static_cast<int64_t>(p0[h]) - first[h]) : nullptr;
         total += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), LD_WAVE - 1));
     }
-    for (int q = lane; q < kOwner; q += LD_WAVE) owner[q] = 0xFFFFFFFFu;
     __syncthreads();  // one wave: orders the fills before what follows
 
     bool staged = false;
@@ -384,48 +389,119 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_thin(float* __restrict__ w, i
         }
     }
 
-    // The list's records in diff order, 64 at a time, kThinAhead rows requested together. Lane and row give
-    // the position; the diff it belongs to is the last one with `before` at or below it.
+    // The list's records in diff order, kThinAhead rows of 64 at a time.
+    constexpr uint32_t kBlock = kThinAhead * LD_WAVE;
+    const auto ordered = [] {  // the wave's own LDS operations complete in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // A row's records in lane order, which is list order, whatever they share: see above. The owner table is left as it was.
+    const auto take_turns = [&](uint32_t e, float p, bool pend) {
+        uint32_t* own = mark + ld_thin_slot(e);
+        while (__ballot(pend)) {
+            if (pend) atomicMin(own, static_cast<uint32_t>(lane));
+            ordered();
+            const bool won = pend && *own == static_cast<uint32_t>(lane);
+            ordered();
+            if (won) {
+                tile[e] = __fsub_rn(tile[e], p);
+                *own = 0xFFFFFFFFu;
+            }
+            ordered();
+            pend = pend && !won;
+        }
+    };
 #pragma unroll 1
-    for (uint32_t k0 = 0; k0 < total || !staged; k0 += kThinAhead * LD_WAVE) {
+    for (uint32_t k0 = 0; k0 < total || !staged; k0 += kBlock) {
+        // Lane and row give the list position. The diff it belongs to is the last one that begins at or before it: every diff with
+        // records in the block marks where they begin, and a running maximum carries the marks on.
+        reinterpret_cast<ld_u32x2*>(line.whose)[lane] = ld_u32x2{0u, 0u};
+        ordered();
+#pragma unroll
+        for (int h = 0; h < kSets; ++h)
+            if (cnt[h] > 0 && first[h] < k0 + kBlock && first[h] + cnt[h] > k0)
+                line.whose[first[h] > k0 ? first[h] - k0 : 0u] = static_cast<unsigned char>(h * LD_WAVE + lane);
+        ordered();
+        uint32_t t[kThinAhead], carry = 0;
+#pragma unroll
+        for (int u = 0; u < kThinAhead; ++u) t[u] = line.whose[u * LD_WAVE + lane];
         int32_t ri[kThinAhead];
         float rv[kThinAhead];
 #pragma unroll
         for (int u = 0; u < kThinAhead; ++u) {
             const uint32_t k = k0 + u * LD_WAVE + lane;
+            const uint32_t reach = ld_wave_imax(t[u]);
+            t[u] = reach > carry ? reach : carry;
+            carry = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(t[u]), LD_WAVE - 1));
             ri[u] = 0;
             rv[u] = 0.0f;
-            if (k0 + u * LD_WAVE < total) {  // uniform
-                int t = 0;
-#pragma unroll
-                for (int step = kTableMax / 2; step > 0; step >>= 1) t += before[t + step] <= k ? step : 0;
-                if (k < total) {
-                    ri[u] = ibase[t][k];
-                    rv[u] = vbase[t][k];
-                }
+            if (k < total) {
+                ri[u] = ibase[t[u]][k];
+                rv[u] = vbase[t[u]][k];
             }
         }
+        reinterpret_cast<ld_u32x4*>(mark)[lane] = ld_u32x4{0u, 0u, 0u, 0u};
         if (!staged) stage();  // the tile arrives while the first records travel
+        ordered();
+        // Elements that only one record of the block names, most of them, are updated in any order, all rows at once: a bit per
+        // element tells a record that it is not the first there, a second one tells the first.
+        uint32_t e[kThinAhead], old[kThinAhead];
+        bool in[kThinAhead];
+        const auto meet = [&](int u) {
+            if (in[u]) old[u] = atomicOr(&mark[e[u] >> 5], 1u << (e[u] & 31));
+        };
+        const auto met = [&](int u) { return in[u] && (old[u] >> (e[u] & 31) & 1u); };
 #pragma unroll
         for (int u = 0; u < kThinAhead; ++u) {
-            if (k0 + u * LD_WAVE < total) {  // uniform
-                const uint32_t e = static_cast<uint32_t>(ri[u] - lo);
-                const float p = __fmul_rn(lr, rv[u]);   // rounded product: never fused
-                uint32_t* own = owner + ld_thin_slot(e);
-                bool pend = k0 + u * LD_WAVE + lane < total && e < static_cast<uint32_t>(len);
-                while (__ballot(pend)) {
-                    if (pend) atomicMin(own, static_cast<uint32_t>(lane));
-                    __builtin_amdgcn_wave_barrier();
-                    const bool won = pend && *own == static_cast<uint32_t>(lane);
-                    __builtin_amdgcn_wave_barrier();
-                    if (won) {
-                        tile[e] = __fsub_rn(tile[e], p);
-                        *own = 0xFFFFFFFFu;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    pend = pend && !won;
+            e[u] = static_cast<uint32_t>(ri[u] - lo);
+            in[u] = k0 + u * LD_WAVE + lane < total && e[u] < static_cast<uint32_t>(len);
+            rv[u] = __fmul_rn(lr, rv[u]);   // rounded product: never fused
+        }
+        meet(0);
+        meet(1);
+        if (__popcll(__ballot(met(0))) + __popcll(__ballot(met(1))) > kThinAlike) {
+            // diffs that share their positions: row after row, every pending record bids for its element
+            reinterpret_cast<ld_u32x4*>(mark)[lane] = ld_u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+            ordered();
+#pragma unroll
+            for (int u = 0; u < kThinAhead; ++u) take_turns(e[u], rv[u], in[u]);
+            continue;
+        }
+#pragma unroll
+        for (int u = 2; u < kThinAhead; ++u) meet(u);
+#pragma unroll
+        for (int u = 0; u < kThinAhead; ++u)
+            if (met(u)) atomicOr(&mark[kThinSub / 32 + (e[u] >> 5)], 1u << (e[u] & 31));
+        ordered();
+#pragma unroll
+        for (int u = 0; u < kThinAhead; ++u) old[u] = in[u] ? mark[kThinSub / 32 + (e[u] >> 5)] : 0u;
+        float cur[kThinAhead];
+        uint32_t rank[kThinAhead], waiting = 0;  // among the records of the block that wait, in list order
+#pragma unroll
+        for (int u = 0; u < kThinAhead; ++u) {
+            const bool again = met(u);
+            const uint64_t all = __ballot(again);
+            rank[u] = again ? waiting + ld_mbcnt(all) : 0xFFFFFFFFu;
+            waiting += __popcll(all);
+            old[u] = in[u] && !again ? e[u] : static_cast<uint32_t>(kThinSub);  // the spare word
+            cur[u] = tile[old[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kThinAhead; ++u) tile[old[u]] = __fsub_rn(cur[u], rv[u]);
+        if (waiting == 0) continue;
+        reinterpret_cast<ld_u32x4*>(mark)[lane] = ld_u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+#pragma unroll 1
+        for (uint32_t r0 = 0; r0 < waiting; r0 += LD_WAVE) {
+            ordered();
+#pragma unroll
+            for (int u = 0; u < kThinAhead; ++u)
+                if (rank[u] - r0 < static_cast<uint32_t>(LD_WAVE)) {
+                    line.wait[rank[u] - r0].e = e[u];
+                    line.wait[rank[u] - r0].p = rv[u];
                 }
-            }
+            ordered();
+            const bool mine = r0 + lane < waiting;
+            take_turns(mine ? line.wait[lane].e : 0u, line.wait[lane].p, mine);
         }
     }
 

@@ -752,6 +752,34 @@ def test_merge_thin_long_windows(case):
         np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(ref), err_msg=f"{case}, workspace {nbytes}")
 
 
+@pytest.mark.parametrize("W", [11, 40, 65, 128])
+def test_merge_lane_per_record_blocks(W):
+    # Lists of a sub-tile around the 512 records of a block and the 64 that wait their turn together, over element pools from the
+    # whole sub-tile (few wait) to 16 elements (rows take turns), within the ragged last sub-tile too. With the table
+    # of sub-tiles of 4096 all of them run a lane per record.
+    n = 4096 * 900 + 1234
+    rs = np.random.RandomState(W)
+    recs = [set() for _ in range(W)]
+    totals = [1, 2, 63, 64, 65, 127, 128, 129, 511, 512, 513, 575, 1023, 1024, 1025, 1400]
+    for s, (total, pool) in enumerate([(t, p) for t in totals for p in (4096, 1000, 300, 60, 16)] + [(300, 1234)]):
+        base, span = (4096 * 900, 1234) if pool == 1234 else (4096 * (11 * s + 3), 4096)
+        where = base + rs.choice(span, min(pool, span), replace=False)
+        owner = rs.randint(0, W, min(total, W * where.size))
+        for t, count in zip(*np.unique(owner, return_counts=True)):
+            recs[t].update(rs.choice(where, min(count, where.size), replace=False).tolist())
+    idxs = [np.array(sorted(r), np.int32) for r in recs]
+    vals = [(rs.standard_normal(i.size) * 10.0 ** rs.uniform(-4, 1, i.size)).astype(np.float32) for i in idxs]
+    K = [i.size for i in idxs]
+    nbytes = table_of(n, W, 4096)
+    assert max(K) * 8192 <= 48 * n and ld.ld_merge_sparse_workspace(n, K) >= nbytes
+    w0 = synth.base_weights(n).numpy()
+    w = to_gpu(w0)
+    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1,
+                       workspace=torch.empty(nbytes, dtype=torch.uint8, device=DEV), strategy=ld.LD_MERGE_SWEEP)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
+
+
 def test_merge_uneven_diffs_across_many_chunks():
     # Record positions are looked up per 49152-element chunk from guesses that assume evenly
     # spread records; these diffs are anything but (dense runs between long gaps, everything
