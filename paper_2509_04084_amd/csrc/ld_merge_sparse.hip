@@ -735,16 +735,6 @@ void launch_rows(float* w, int64_t n, int32_t nsub, const DiffTable& tb, int32_t
 
 namespace {
 
-// A group of `gw` diffs whose largest holds `most` records is "thin" when a diff brings few records to 8192 elements and the
-// group is long: it then runs a lane per record (k_merge_thin). At most 48 for large arrays; measured,
-// us with the sweep / a lane per record: 20 diffs of 0.25 % on 100 M elements 164 / 148, 40 of 0.5 % 240 / 228; 20 of 1 %
-// 199 / 225. At most 20 for small ones whose diffs are one batch of k_merge_rows (17), which is the faster way then; with more
-// batches it is not (3 M elements, 87 diffs of 0.3 %: rows 30 us, a lane per record 19; 5.9 M, 84 diffs of 0.27 % whose density
-// differs from layer to layer 52 / 31; 30 diffs of 0.25 % on 25 M 55 / 49).
-bool thin_group(int64_t n, int32_t gw, int64_t most) {
-    return gw > 10 && most * kSub <= (n < kFewSubs && gw <= kRowBatch ? 20 : 48) * n;
-}
-
 // Windows from a table (k_merge_rows), sweep / rows in us: 200 M elements, 4 diffs of 1 % 280 / 279, 100 M, 20 of 1 % 192 / 176,
 // 60 of 1 % 361 / 298; but 170 M, 30 of 2 % 449 / 462, 300 M, 9 of 0.5 % 413 / 424 and 600 M, 20 of 1 % 996 / 1100: the pass
 // over the index arrays costs what the windows save. Two windows where a sub-tile's records outgrow one (2 % a diff): 25 M, 50 of 3.3 %
@@ -761,6 +751,20 @@ int rows_windows(int64_t n, int32_t gw, int64_t most) {  // 64-record windows pe
 }
 
 
+// Up to which density a group of `gw` diffs runs a lane per record (k_merge_thin), in records of its largest diff per 8192 elements
+// (0: not at all): that pays by the record, windows from a table and the sweep by the diff. us a call, windows / a lane per record:
+// 24 diffs of 1/250 17 / 20 on 6 M elements, 46 / 50 on 25 M, 99 / 100 on 60 M, 170 / 171 on 110 M, of 1/1000 17 / 19, -, 85 / 85, 137 / 138; 48 of
+// 1/500 20 / 20, 53 / 54, 114 / 99, 195 / 174; 80 of 1/250 31 / 29, 83 / 78, 176 / 157, 306 / 276, of 1/180 33 / 33, 85 / 88, 175 / 180,
+// 332 / 342; below 2 M elements it is the launches. Sweep / a lane per record, where there is no table of windows: 150 M elements, 20 diffs of
+// 1/150 244 / 233, 32 of 1/120 343 / 313, 100 of 1/120 845 / 718; 400 M, 20 of 1/150 627 / 641, 32 of 1/150 773 / 751, of 1/120 793 / 831, 64 of
+// 1/150 1192 / 1107, 100 of 1/120 2035 / 1845; 1.5 G, 20 of 1/200 2220 / 2305.
+int thin_line(int64_t n, int32_t gw) {
+    if (gw <= 10) return 0;
+    if (n < 2000000) return gw > kRowBatch ? 48 : 20;
+    if (n < kRowsMost) return gw > 24 ? 48 : 10;
+    return gw <= 24 ? (n < 180000000 ? 60 : 27) : gw <= LD_WAVE ? 56 : 72;
+}
+
 size_t chunk_table_bytes(int64_t n, int32_t W) {
     const int64_t group = W < kSweepGroup ? W : kSweepGroup;
     return ld_round_up(static_cast<size_t>(group) * (static_cast<size_t>(chunks(n)) + 1) * 4, 256);
@@ -770,10 +774,19 @@ size_t sub_table_bytes(int64_t n, int32_t gw, int32_t sub) {
     return ld_round_up(static_cast<size_t>(gw) * (static_cast<size_t>((n + sub - 1) / sub) + 1) * 4, 256);
 }
 
-// Bytes of the per-sub-tile table that a group would run with (0: it runs as a sweep).
-size_t group_table_bytes(int64_t n, int32_t gw, int64_t most) {
-    if (thin_group(n, gw, most)) return sub_table_bytes(n, gw, kThinSub);
-    return rows_windows(n, gw, most) ? sub_table_bytes(n, gw, kRowSub) : 0;
+// The per-sub-tile table that a group runs with, if it fits the workspace.
+struct GroupTable {
+    int32_t sub;     // elements per sub-tile: kThinSub (a lane per record), kRowSub (windows); 0: none, it runs as a sweep
+    size_t bytes;
+};
+GroupTable group_table(int64_t n, int32_t gw, int64_t most, size_t workspace_bytes) {
+    const GroupTable none{0, 0}, thin{kThinSub, sub_table_bytes(n, gw, kThinSub)}, rows{kRowSub, sub_table_bytes(n, gw, kRowSub)};
+    const int line = thin_line(n, gw);
+    if (line > 0 && most * kSub <= line * n) return thin.bytes <= workspace_bytes ? thin : none;
+    if (!rows_windows(n, gw, most)) return none;
+    if (rows.bytes <= workspace_bytes) return rows;
+    // half the table of the windows: still faster than the sweep (20 diffs of 1/400 on 100 M elements 148 / 164)
+    return gw > 10 && most * kSub <= 48 * n && thin.bytes <= workspace_bytes ? thin : none;
 }
 
 // Whether a window that would be scattered runs faster in groups with tables, and can. What is certain of a scatter is 2.4 us a
@@ -795,8 +808,7 @@ bool tables_pay(const int32_t* const* idx, const int64_t* K, int32_t W, int64_t 
             most = K[t] > most ? K[t] : most;
             if (!ld_aligned(idx[t], 16)) return false;
         }
-        const size_t table = group_table_bytes(n, gw, most);
-        if (table == 0 || workspace_bytes < table) return false;
+        if (group_table(n, gw, most, workspace_bytes).sub == 0) return false;
     }
     return true;
 }
@@ -813,7 +825,7 @@ extern "C" size_t ld_merge_sparse_workspace(int64_t n, int32_t W, const int64_t*
             const int32_t gw = (W - g0) < kSweepGroup ? (W - g0) : kSweepGroup;
             int64_t most = 0;
             for (int32_t t = g0; t < g0 + gw; ++t) most = K[t] > most ? K[t] : most;
-            const size_t table = group_table_bytes(n, gw, most);
+            const size_t table = group_table(n, gw, most, SIZE_MAX).bytes;
             if (table > need) need = table;
         }
     }
@@ -873,11 +885,10 @@ ld_status merge_sparse_impl(float* w, int64_t n, const int32_t* const* idx, cons
             if (live && !ld_aligned(idx[g0 + t], 16)) aligned16 = false;
         }
         const dim3 wave(LD_WAVE);
-        const size_t table = group_table_bytes(n, gw, most);
-        if (table > 0 && aligned16 && workspace_bytes >= table) {  // (else: the sweep below)
-            const bool thin = thin_group(n, gw, most);
-            const int32_t sub = thin ? kThinSub : kRowSub;
-            const int32_t nsub = static_cast<int32_t>((n + sub - 1) / sub);
+        const GroupTable table = group_table(n, gw, most, workspace_bytes);
+        if (table.sub > 0 && aligned16) {  // (else: the sweep below)
+            const bool thin = table.sub == kThinSub;
+            const int32_t nsub = static_cast<int32_t>((n + table.sub - 1) / table.sub);
             if (thin) launch_subtab<kThinSub>(tb, gw, most, nsub, ctab, s);
             else launch_subtab<kRowSub>(tb, gw, most, nsub, ctab, s);
             if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
