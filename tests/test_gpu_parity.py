@@ -915,6 +915,26 @@ def test_snapshot_many_layers_one_launch():
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
+@pytest.mark.parametrize("count", [1, 15, 16, 17, 175, 176, 177, 353])
+def test_snapshot_layers_around_a_launch(count):
+    # a launch takes 176 layers, found in groups of 16; whole blocks of 8192 elements, one element less and more, empty layers,
+    # sources and destinations an element apart in alignment, nothing around them written
+    rs = np.random.RandomState(count)
+    sizes = [int(rs.choice([1, 7, 64, 8191, 8192, 8193, 16384, 30_001, 0])) for _ in range(count)]
+    sizes[-1] = 8193
+    src = torch.randint(-32768, 32767, (sum(sizes) + 3 * count,), dtype=torch.int16, device=DEV)
+    dst, want = torch.full_like(src, 77), torch.full_like(src, 77)
+    at, srcs, dsts = 0, [], []
+    for s in sizes:
+        srcs.append(src[at + 1:at + 1 + s].view(torch.bfloat16))
+        dsts.append(dst[at + 2:at + 2 + s].view(torch.bfloat16))
+        want[at + 2:at + 2 + s] = src[at + 1:at + 1 + s]
+        at += s + 3
+    ld.ld_snapshot_layers(srcs, dsts)
+    torch.cuda.synchronize()
+    assert torch.equal(dst, want)
+
+
 # ---------------------------------------------------------------------- Adam
 
 def _bf16_bits_t(t):
