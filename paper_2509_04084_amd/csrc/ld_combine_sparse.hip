@@ -312,9 +312,13 @@ __global__ __launch_bounds__(LD_WAVE) void k_combine_emit(int64_t n, int32_t nch
 // What it took there (first cases, 1080 at first): the ranges by lane reads instead of scalar loads list after list and 64
 // chunks asked at a time instead of 256, 660; LDS accesses that nothing branches around; the published words 64 bytes apart (in
 // a row 790, 8 bytes apart 670, 16: 640; they are written and asked from all XCDs at once) and asked for only when the values
-// are added (earlier, they mostly say nothing yet), 595; four waves to a workgroup, so that every SIMD has one, and the lists'
-// addresses by scalar loads ahead of the ranges, 540. What bounds it: chains of latencies (ranges, records, a dozen
-// barriers, the counts before) at 15 waves per CU.
+// are added (earlier, they mostly say nothing yet), 595; four waves to a workgroup, so that every SIMD has one, 540; the lists'
+// addresses by lane reads too, no wait between the lists' loads, the sums cleared while these are on their way and
+// written out in fours, 531 -> 522 (scans over lanes by data-parallel primitives before that, 538 -> 531). What bounds it: a workgroup waits for
+// the slowest of the thousand before it that are running. Of its 27 K clocks 9 K go to the loads, 5 K to the sums and 5 K to that wait, which takes up
+// whatever the others are shortened by: with waits for the indices alone 530, with the counts of 64 chunks summed in a word, so that one question
+// finds the offset, no less, with the results kept in registers until the next chunk's loads have come 610 (three
+// workgroups per CU then, or spills).
 // Crowded chunks (much of the lists in little of the index space): their rounds take pieces of the lists, not all of them again,
 // and what goes beyond the records that a workgroup loads at once is streamed. 8 lists of 0.4 % of 400 M elements, all
 // in the first fiftieth: with every round reading all of it 2906 us, now 284; 8 lists of 13 K of 5 M 1680 / 226. Two passes take 490 for the first.
@@ -350,6 +354,10 @@ __device__ __forceinline__ uint32_t count_chunk(const DiffTable& tb, int32_t N, 
     return ld_wave_sum(c);
 }
 
+// Four words at any 4-byte address (global accesses need no more).
+typedef int32_t I32x4Any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float F32x4Any __attribute__((ext_vector_type(4), aligned(4)));
+
 // HELD: at most kPre lists, their records stay in registers between the marks and the sums.
 // kDeep: records per thread and list loaded ahead.
 template <int THREADS, int kDeep, int CAP, bool HELD>
@@ -364,44 +372,49 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
     constexpr int kOwn = kChunkWords / kOwners;
     static_assert(kOwn * kOwners == kChunkWords, "");
     // Lanes without a record work on a word of their own behind each array: nothing branches around an LDS access.
-    __shared__ uint32_t bm[kChunkWords + LD_WAVE];   // recorded positions of the chunk
+    __shared__ __align__(16) uint32_t bm[kChunkWords + LD_WAVE];  // recorded positions of the chunk
     __shared__ uint16_t wpre[kChunkWords + LD_WAVE]; // recorded positions before each bitmap word
-    __shared__ float acc[CAP + LD_WAVE];             // sums, at the rank of their position among the recorded ones
-    __shared__ uint16_t accq[CAP + LD_WAVE];         // ... and the positions themselves
+    __shared__ __align__(16) float acc[CAP + LD_WAVE];      // sums, at the rank of their position among the recorded ones
+    __shared__ __align__(16) uint16_t accq[CAP + LD_WAVE];  // ... and the positions themselves
     __shared__ uint32_t sums[kWaves];
     __shared__ uint32_t offset;
     __shared__ uint32_t used[LD_WAVE];               // crowded chunks: the records that a round takes of every list
-    const int tid = threadIdx.x, lane = tid & (LD_WAVE - 1), wave = tid / LD_WAVE;
+    const int tid = threadIdx.x, lane = tid & (LD_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / LD_WAVE);
     const int32_t chunk = blockIdx.x;
     const int64_t lo64 = static_cast<int64_t>(chunk) * kChunk;
     const uint32_t lo = static_cast<uint32_t>(lo64), len = static_cast<uint32_t>(n - lo64 < kChunk ? n - lo64 : kChunk);
 
-    // Lane t: where list t's records of this chunk lie (in the rounds of a crowded chunk: those still to come). The loops take
-    // them by lane reads: scalar loads from the table would be waited for list after list.
+    // Lane t: where list t's records of this chunk lie (in the rounds of a crowded chunk: those still to come), and the list itself.
+    // The loops take them by lane reads: scalar loads from the table would be waited for list after list.
     int32_t first = 0, have = 0;
+    uint32_t idx_lo = 0, idx_hi = 0, val_lo = 0, val_hi = 0;
     if (lane < N) {
         const int32_t* row = ctab + static_cast<int64_t>(lane) * (nchunk + 1) + chunk;
+        const uint64_t i = reinterpret_cast<uint64_t>(tb.idx[lane]), v = reinterpret_cast<uint64_t>(tb.val[lane]);
         first = row[0];
         have = row[1] > first ? row[1] - first : 0;
+        idx_lo = static_cast<uint32_t>(i), idx_hi = static_cast<uint32_t>(i >> 32);
+        val_lo = static_cast<uint32_t>(v), val_hi = static_cast<uint32_t>(v >> 32);
     }
+    asm volatile("" : "+v"(idx_lo), "+v"(idx_hi), "+v"(val_lo), "+v"(val_hi));  // waited for here, not behind the first records
     // Records of kPre lists, kDeep per thread and list; at: their positions in the chunk (spare: none).
     const uint32_t spare = static_cast<uint32_t>(kChunk) + lane * 32u;
     uint32_t at[kPre][kDeep];
     float rv[kPre][kDeep];
-    auto fetch = [&](int32_t t0, auto (&x)[kPre][kDeep], auto* const (&list)[kTableMax]) {
+    auto fetch = [&](int32_t t0, auto (&x)[kPre][kDeep], uint32_t list_lo, uint32_t list_hi) {
         typedef std::remove_reference_t<decltype(x[0][0])> T;
 #pragma unroll
         for (int g = 0; g < kPre; ++g) {
             const int t = t0 + g;  // kPre divides 64: past N the count is 0
             const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readlane(have, t));
-            const auto* base = list[t] + __builtin_amdgcn_readlane(first, t);
+            const GlobalBytes base = lane_pointer(list_lo, list_hi, t) + static_cast<int64_t>(__builtin_amdgcn_readlane(first, t)) * 4;
 #pragma unroll
             for (int u = 0; u < kDeep; ++u) {
-                x[g][u] = T(0);
+                asm volatile("" : "=v"(x[g][u]));  // anything: a value set here would be a wait for the loads of the lists before
                 if (static_cast<uint32_t>(u * THREADS + wave * LD_WAVE) < count) {  // uniform in the wave
                     uint32_t p = u * THREADS + tid;
                     p = p < count ? p : count - 1;
-                    x[g][u] = static_cast<T>(base[p]);
+                    x[g][u] = *reinterpret_cast<const __attribute__((address_space(1))) T*>(base + p * 4u);
                 }
             }
         }
@@ -413,8 +426,8 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
             for (int u = 0; u < kDeep; ++u) at[g][u] = 0, rv[g][u] = 0.0f;
     };
     auto load = [&](int32_t t0, bool values) {
-        fetch(t0, at, tb.idx);
-        if (values) fetch(t0, rv, tb.val);
+        fetch(t0, at, idx_lo, idx_hi);
+        if (values) fetch(t0, rv, val_lo, val_hi);
     };
     auto place = [&](int32_t t0) {
 #pragma unroll
@@ -459,7 +472,9 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
     };
     auto mark = [&](uint32_t q) { atomicOr(&bm[q >> 5], 1u << (q & 31)); };
     load(0, HELD);
-    for (int j = tid; j < kChunkWords; j += THREADS) bm[j] = 0;
+    for (int j = tid; j < kChunkWords / 4; j += THREADS) reinterpret_cast<ld_u32x4*>(bm)[j] = ld_u32x4{0u, 0u, 0u, 0u};
+    static_assert(CAP % 4 == 0, "");
+    for (int j = tid; j < CAP / 4; j += THREADS) reinterpret_cast<ld_f32x4*>(acc)[j] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // __syncthreads, but for LDS alone: the records stay on their way
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
@@ -577,7 +592,8 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
 #pragma unroll 1
     for (uint32_t r0 = 0; r0 == 0 || r0 < total; r0 += CAP) {
         const uint32_t cnt = total - r0 < static_cast<uint32_t>(CAP) ? total - r0 : static_cast<uint32_t>(CAP);
-        for (uint32_t j = tid; j < cnt; j += THREADS) acc[j] = 0.0f;
+        if (!once)  // the only round's are cleared already
+            for (uint32_t j = tid; j < cnt; j += THREADS) acc[j] = 0.0f;
         // at least CAP: of another round
         auto rank = [&](uint32_t q) {
             const uint32_t r = wpre[q >> 5] + __popc(bm[q >> 5] & ((1u << (q & 31)) - 1u)) - r0;
@@ -677,10 +693,25 @@ __global__ __launch_bounds__(THREADS) void k_combine_chunk(int64_t n, int32_t nc
             __syncthreads();
         }
         const int64_t off = static_cast<int64_t>(offset) + r0;
-        for (uint32_t j = tid; j < cnt; j += THREADS) {
-            if (off + j < out_cap) {
-                out_idx[off + j] = static_cast<int32_t>(lo + accq[j]);
-                out_val[off + j] = __fmul_rn(scale, acc[j]);
+        const uint32_t room = off >= out_cap ? 0u : out_cap - off < cnt ? static_cast<uint32_t>(out_cap - off) : cnt;
+#pragma unroll 2
+        for (uint32_t j = tid * 4; j < room; j += THREADS * 4) {  // four neighbours a thread, wherever the run begins
+            const ld_f32x4 x = *reinterpret_cast<const ld_f32x4*>(acc + j);
+            const ld_u32x2 q = *reinterpret_cast<const ld_u32x2*>(accq + j);
+            const int32_t i[4] = {static_cast<int32_t>(lo + (q.x & 0xFFFFu)), static_cast<int32_t>(lo + (q.x >> 16)),
+                                  static_cast<int32_t>(lo + (q.y & 0xFFFFu)), static_cast<int32_t>(lo + (q.y >> 16))};
+            const float v[4] = {__fmul_rn(scale, x.x), __fmul_rn(scale, x.y), __fmul_rn(scale, x.z), __fmul_rn(scale, x.w)};
+            if (j + 4 <= room) {
+                *reinterpret_cast<I32x4Any*>(out_idx + off + j) = I32x4Any{i[0], i[1], i[2], i[3]};
+                *reinterpret_cast<F32x4Any*>(out_val + off + j) = F32x4Any{v[0], v[1], v[2], v[3]};
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    if (j + c < room) {
+                        out_idx[off + j + c] = i[c];
+                        out_val[off + j + c] = v[c];
+                    }
+                }
             }
         }
         if (once) return;
