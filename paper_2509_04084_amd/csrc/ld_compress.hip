@@ -32,10 +32,10 @@
 //             per segment; with small groups each workgroup of k_gather for itself) finds the
 //             bin b holding the k-th largest key.
 //   k_gather  per tile: #candidates in bins above b; the (few) keys inside bin b are
-//             gathered per segment. k_select (one workgroup per segment) selects the
-//             exact threshold T and tie count among them, fixes the per-tile counts
-//             up, and scans them into output offsets.
-//   k_emit    ordered emission of (idx, val); repairs the residual where the
+//             gathered per segment.
+//   k_emit    each workgroup selects the exact threshold T and tie count among the
+//             gathered keys for itself and completes its tiles' counts with them;
+//             ordered emission of (idx, val); repairs the residual where the
 //             T_est guess and the true selection differ.
 //
 // The estimates can never make the result wrong, only slower:
@@ -125,8 +125,8 @@ struct SegState {       // 64 bytes
     uint32_t tau;       // candidate threshold (key); 0: every element, 0xFFFFFFFF: none
     uint32_t sh;        // fine bin of a candidate: min(kTopBin, (key - tau) >> sh)
     uint32_t test;      // guessed threshold T_est >= tau: k_main stores +0 where key >= T_est
-    uint32_t prefix;    // k_bin (small groups: k_gather): threshold bin; k_select: exact threshold T (k_full: radix prefix)
-    uint32_t krem;      // rank left inside prefix; finally the number of ties to keep
+    uint32_t prefix;    // k_bin (small groups: k_gather): threshold bin, kModeTies: the threshold (k_full: radix prefix)
+    uint32_t krem;      // rank left inside prefix, kModeTies: the number of ties to keep
     uint32_t mode;      // kModeCand | kModeFull | kModeTies
     uint32_t gcount;    // keys gathered from the threshold bin
     uint32_t fdone[4];  // tickets of the full-segment path: level 1, 2, 3, count
@@ -135,7 +135,7 @@ struct SegState {       // 64 bytes
     // that taking it as candidate threshold would make nearly every element a candidate. The
     // candidates are then the keys ABOVE it (tau = that key + 1) and nothing is pre-zeroed. If the
     // candidates turn out fewer than k, the threshold can only be that key or a smaller one:
-    // k_gather counts the key per tile in the residual, k_select checks that with those ties k is
+    // k_gather counts the key per tile in the residual, k_emit checks that with those ties k is
     // reached (else: the full path), and k_emit takes the ties in index order (kModeTies).
     uint32_t tied;
     uint32_t pad[2];
@@ -149,10 +149,10 @@ struct Ctx {
     uint32_t* cnt;          // [n_group * tiles] candidates stored per tile, or kOverflow
     float* cval;            // [n_group * tiles][slot]
     uint16_t* cidx;         // [n_group * tiles][slot] element offset inside the tile
-    uint32_t* tile_gt;      // [n_group * tiles] keys above T
-    uint32_t* tile_eq;      // [n_group * tiles] keys equal to T
-    uint32_t* group_gt;     // [n_group] sums over the group -> records emitted before the group
-    uint32_t* group_eq;     // [n_group]                       -> ties before the group
+    uint32_t* tile_gt;      // [n_group * tiles] keys above the threshold bin
+    uint32_t* tile_eq;      // [n_group * tiles] keys in it (kModeTies: equal to the threshold)
+    uint32_t* group_gt;     // [n_group] sums over the group (full path: records emitted before the group)
+    uint32_t* group_eq;     // [n_group]                       (ties before the group)
     uint32_t* gkey;         // per segment gather_cap entries from gather_first
     int32_t* gtile;         // per segment gather_cap entries from gather_first
     int32_t* fail_groups;   // [n_group] groups of segments in kModeFull
@@ -966,22 +966,6 @@ __device__ __forceinline__ void mark_full(const Ctx& c, SegState* st, const Grou
     for (int32_t q = threadIdx.x; q < gr.ngroup; q += blockDim.x) c.fail_groups[*list0 + q] = gr.group0 + q;
 }
 
-__device__ __forceinline__ GroupRange seg_range(const Ctx& c, int32_t s) {
-    GroupRange r;
-    const SegDesc d = c.desc[s];
-    const SegDesc dn = c.desc[s + 1];
-    r.seg = s;
-    r.base = align_down4(d.off);
-    r.lo = d.off;
-    r.hi = dn.off;
-    r.k = d.k;
-    r.group0 = d.group0;
-    r.ngroup = dn.group0 - d.group0;
-    r.out0 = d.out0;
-    r.tau = r.sh = r.test = r.tied = 0;
-    return r;
-}
-
 // Fine-bin histogram of the candidates of kHistGroups consecutive groups (256 threads each),
 // added to their segments'. Updates of one counter from many workgroups queue up behind one
 // another, and the largest segment has hundreds of groups: the groups of a workgroup that
@@ -1075,7 +1059,7 @@ __device__ __forceinline__ uint32_t threshold_bin(const Ctx& c, const GroupRange
         return kModeCand;
     }
     if (gr.tied) {
-        // every candidate is selected; the rest must be ties of the repeated key (k_select checks)
+        // every candidate is selected; the rest must be ties of the repeated key (k_emit checks)
         if (note && threadIdx.x == 0) {
             st->mode = kModeTies;
             st->prefix = gr.tau - 1u;                           // T
@@ -1278,7 +1262,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
         const uint32_t eqc = both >> 16;
         if ((lane & (RW::kRow - 1)) == 0 && Q.cn <= RW::kFast) {
             c.tile_gt[tile0 + Q.u] = cnt;
-            if (!ties_mode) c.tile_eq[tile0 + Q.u] = eqc;  // keys in the threshold bin; k_select takes out those that are not T
+            if (!ties_mode) c.tile_eq[tile0 + Q.u] = eqc;  // keys in the threshold bin: ties if the bin is overfull
             part_gt += cnt;
             part_eq += eqc;
         }
@@ -1359,38 +1343,66 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
     }
 }
 
-// One workgroup per segment: the exact threshold T and the number m of its ties to
-// keep, selected among the gathered keys; per-tile counts completed; group sums
-// scanned into output offsets. All gathered keys lie in one fine bin, so the radix
-// select runs on (key - first key of the bin): one 11-bit level per 11 bits of bin
-// width, and the digits spread over the histogram instead of piling on one counter.
-__global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
-    __shared__ uint32_t lh[kBins];
-    __shared__ uint32_t sh[kWaves];
-    __shared__ uint32_t res[3];
-    __shared__ uint32_t list0;
-    const GroupRange gr = seg_range(c, blockIdx.x);
-    SegState* st = c.state + gr.seg;
-    const uint32_t mode = st->mode;
-    if (gr.k == 0 || gr.ngroup == 0) return;
-    uint32_t* h = c.hist + static_cast<int64_t>(gr.seg) * kBins;
-    for (int b = threadIdx.x; b < kBins; b += kThreads) h[b] = 0;  // the full path uses the row again
-    if (mode == kModeFull) return;
-    const uint32_t ng = st->gcount;
-    const uint32_t* gkey = c.gkey + gather_first(gr.seg, gr.lo);
-    const int32_t* gtile = c.gtile + gather_first(gr.seg, gr.lo);
-    const uint32_t gcap = gather_cap(gr.lo, gr.hi);
+// The exact threshold T of a segment and the number m of its ties to keep, selected among the gathered keys by every workgroup of
+// k_emit for itself, and what lies before the workgroup's tiles: as a launch of its own between k_gather and k_emit (one workgroup per segment,
+// which also completed the per-tile counts and scanned the groups' sums) it was a link more in the chain:
+// flat 1 M elements 42.0 -> 37.7 us a call, ResNet-50 96.5 -> 91.0, GPT-2 small 300.4 -> 294.8, GPT-2 XL 3263 -> 3255.
+// All gathered keys lie in one fine bin, so the select runs on (key - first key of the bin).
+struct Picked {
     uint32_t T, m;
-    uint32_t seen = 0;
-    if (mode == kModeTies) {  // both were found with the threshold bin: nothing to select
-        T = st->prefix;
-        m = st->krem;
-    } else if (ng > gcap) {
+    uint32_t gt_before, eq_before;               // keys above T and equal to T in the segment's groups before this one
+    uint32_t full;                               // 1: not to be decided here, the segment goes the full way
+};
+constexpr uint32_t kFewPicks = 512;              // keys that one wave selects among, in registers; 256 of them requested ahead
+
+// By the first wave, among ng <= 64 R keys held by its lanes (row r: lane l holds key 64 r + l): bit by bit from the top, the
+// keys still in question are a bit each.
+template <int R>
+__device__ __forceinline__ void pick_few(const uint32_t* key, const int32_t* tile, uint32_t ng, uint32_t base, int bits,
+                                         uint32_t krem, int32_t tile0, int32_t tiles, Picked& out, uint32_t* own_gt, uint32_t* own_eq) {
+    const int lane = ld_lane();
+    uint64_t in[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) in[r] = __ballot(static_cast<uint32_t>(r * LD_WAVE + lane) < ng);
+    uint32_t rel = 0;
+#pragma unroll 1
+    for (int b = bits - 1; b >= 0; --b) {
+        uint64_t one[R];
+        uint32_t ones = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            one[r] = in[r] & __ballot((key[r] - base) >> b & 1u);
+            ones += __popcll(one[r]);
+        }
+        const bool up = ones >= krem;
+        if (up) rel |= 1u << b; else krem -= ones;
+#pragma unroll
+        for (int r = 0; r < R; ++r) in[r] = up ? one[r] : in[r] & ~one[r];
+    }
+    const uint32_t T = base + rel;
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool have = static_cast<uint32_t>(r * LD_WAVE + lane) < ng, above = have && key[r] > T, tie = have && key[r] == T;
+        gt += __popcll(__ballot(above && tile[r] < tile0));
+        eq += __popcll(__ballot(tie && tile[r] < tile0));
+        const uint32_t t = static_cast<uint32_t>(tile[r] - tile0);
+        if ((above || tie) && t < static_cast<uint32_t>(tiles)) atomicAdd((above ? own_gt : own_eq) + t, 1u);
+    }
+    if (lane == 0) out = Picked{T, krem, gt, eq, 0u};
+}
+
+// By the whole workgroup, among more keys, whole or (ng > gcap) more than the list holds. lh: kBins words.
+__device__ __attribute__((noinline)) void pick_many(const uint32_t* gkey, const int32_t* gtile, uint32_t ng, uint32_t gcap, uint32_t kmin,
+                                                    uint32_t kmax, uint32_t base, int bits, uint32_t krem, int32_t tile0, int32_t tiles,
+                                                    Picked* out, uint32_t* own_gt, uint32_t* own_eq, uint32_t* lh, uint32_t* sh,
+                                                    uint32_t* res) {
+    if (ng > gcap) {
         // More keys in the threshold bin than the list holds. If they are all one value (massive
         // ties: a frozen layer's zeros, values on a coarse grid) nothing has to be selected among
         // them: T is that value, and the rank left inside the bin is the number of ties to keep,
         // lowest index first. k_gather's per-tile counts of the bin are then the tie counts.
-        if (threadIdx.x == 0) { res[0] = st->kmin; res[1] = st->kmax; }
+        if (threadIdx.x == 0) { res[0] = kmin; res[1] = kmax; }
         __syncthreads();
         uint32_t lmin = 0xFFFFFFFFu, lmax = 0;
 #pragma unroll 1
@@ -1402,83 +1414,43 @@ __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
         atomicMin(&res[0], lmin);
         atomicMax(&res[1], lmax);
         __syncthreads();
-        if (res[0] != res[1]) {
-            mark_full(c, st, gr, &list0);  // several values share an overfull bin
-            return;
-        }
-        T = res[0];
-        m = st->krem;
+        if (threadIdx.x == 0) *out = Picked{res[0], krem, 0u, 0u, res[0] != res[1]};  // several values share an overfull bin: full
         __syncthreads();
-    } else {
-        const uint32_t b1 = st->prefix, binsh = st->sh;
-        const uint32_t base = st->tau + (b1 << binsh);
-        const int bits = (b1 == static_cast<uint32_t>(kTopBin)) ? 31 : static_cast<int>(binsh);  // the top bin is open-ended
-        const int nlev = bits == 0 ? 1 : (bits + 10) / 11;
-        uint32_t prefix = 0, krem = st->krem;
-#pragma unroll 1
-        for (int lev = 0; lev < nlev; ++lev) {
-            const int shift = 11 * (nlev - 1 - lev);
-            for (int b = threadIdx.x; b < kBins; b += kThreads) lh[b] = 0;
-            __syncthreads();
-#pragma unroll 1
-            for (uint32_t p = threadIdx.x; p < ng; p += kThreads) {
-                const uint32_t rel = gkey[p] - base;
-                if (lev == 0 || ((rel ^ prefix) >> (shift + 11)) == 0) atomicAdd(&lh[(rel >> shift) & 0x7FFu], 1u);
-            }
-            __syncthreads();
-            find_bin<kThreads, false>(lh, krem, sh, res);
-            prefix |= res[0] << shift;
-            krem = res[1];
-            __syncthreads();
-        }
-        T = base + prefix;
-        m = krem;
-        // k_gather counted every key of the bin as a tie: move those above T to the counts of the
-        // selected, drop those below. The group sums are read back below by this same workgroup.
-        // The updates return their old value, so each has been performed when its result arrives;
-        // with the barrier that orders them before the reads. (A device-scope fence would do too,
-        // but it writes back the whole L2 and costs 30 us here.)
-#pragma unroll 1
-        for (uint32_t p = threadIdx.x; p < ng; p += kThreads) {
-            const uint32_t key = gkey[p];
-            if (key == T) continue;
-            const int32_t tile = gtile[p];
-            atomicSub(c.tile_eq + tile, 1u);
-            seen |= atomicSub(c.group_eq + tile / c.tiles, 1u);
-            if (key > T) {
-                atomicAdd(c.tile_gt + tile, 1u);
-                seen |= atomicAdd(c.group_gt + tile / c.tiles, 1u);
-            }
-        }
-    }
-    if (seen == 0xFFFFFFFFu) res[0] = seen;  // never true: keeps the results, and so the waits, alive
-    __syncthreads();
-    // exclusive scan over the segment's groups: records emitted / ties seen before each
-    uint32_t carry_out = 0, carry_eq = 0;
-#pragma unroll 1
-    for (int32_t q0 = 0; q0 < gr.ngroup; q0 += kThreads) {
-        const int32_t q = q0 + threadIdx.x;
-        uint32_t cg = 0, ce = 0;
-        if (q < gr.ngroup) {
-            cg = ld_load_coherent(c.group_gt + gr.group0 + q);
-            ce = ld_load_coherent(c.group_eq + gr.group0 + q);
-        }
-        uint32_t te, tg;
-        const uint32_t eq_before = carry_eq + block_escan<kThreads>(ce, sh, te);
-        const uint32_t take = umin(eq_before + ce, m) - umin(eq_before, m);  // ties kept: lowest index first
-        const uint32_t out_before = carry_out + block_escan<kThreads>(cg + take, sh, tg);
-        if (q < gr.ngroup) {
-            c.group_gt[gr.group0 + q] = out_before;
-            c.group_eq[gr.group0 + q] = eq_before;
-        }
-        carry_eq += te;
-        carry_out += tg;
-    }
-    if (mode == kModeTies && carry_eq < m) {
-        mark_full(c, st, gr, &list0);  // the repeated key does not fill k either: the threshold lies below it
         return;
     }
-    if (threadIdx.x == 0) { st->prefix = T; st->krem = m; }
+    const int nlev = bits == 0 ? 1 : (bits + 10) / 11;  // one 11-bit radix level per 11 bits of bin width
+    uint32_t prefix = 0;
+#pragma unroll 1
+    for (int lev = 0; lev < nlev; ++lev) {
+        const int shift = 11 * (nlev - 1 - lev);
+        for (int b = threadIdx.x; b < kBins; b += kThreads) lh[b] = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t p = threadIdx.x; p < ng; p += kThreads) {
+            const uint32_t rel = gkey[p] - base;
+            if (lev == 0 || ((rel ^ prefix) >> (shift + 11)) == 0) atomicAdd(&lh[(rel >> shift) & 0x7FFu], 1u);
+        }
+        __syncthreads();
+        find_bin<kThreads, false>(lh, krem, sh, res);
+        prefix |= res[0] << shift;
+        krem = res[1];
+        __syncthreads();
+    }
+    const uint32_t T = base + prefix;
+    if (threadIdx.x == 0) *out = Picked{T, krem, 0u, 0u, 0u};
+    __syncthreads();
+    uint32_t gt = 0, eq = 0;
+#pragma unroll 1
+    for (uint32_t p = threadIdx.x; p < ng; p += kThreads) {
+        const uint32_t key = gkey[p];
+        if (key < T) continue;
+        const int32_t tile = gtile[p];
+        if (tile < tile0) ++(key > T ? gt : eq);
+        else if (tile < tile0 + tiles) atomicAdd((key > T ? own_gt : own_eq) + (tile - tile0), 1u);
+    }
+    if (gt) atomicAdd(&out->gt_before, gt);
+    if (eq) atomicAdd(&out->eq_before, eq);
+    __syncthreads();
 }
 
 // Ordered emission of the records. k_main left +0 in the residual exactly where a
@@ -1489,24 +1461,109 @@ template <class RW>
 __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_t* __restrict__ out_idx,
                                                    float* __restrict__ out_val, Ctx c) {
     __shared__ uint32_t tile_out[RW::kGroupTiles], tile_eqb[RW::kGroupTiles], tile_take[RW::kGroupTiles];
+    __shared__ uint32_t own_gt[RW::kGroupTiles], own_eq[RW::kGroupTiles];  // gathered keys of the group's tiles: above T, equal to T
+    __shared__ Picked picked;
+    __shared__ uint32_t sums[3][kWaves], sh[kWaves], res[3], list0;
     constexpr int ROW = RW::kRow, kTiles = RW::kTiles, kTilesPerWave = RW::kTilesPerWave;
     constexpr uint32_t kFast = RW::kFast;
     __shared__ int32_t stage_i[kWaves][kTiles * kFast];
     __shared__ float stage_v[kWaves][kTiles * kFast];
+    static_assert(sizeof(stage_i) >= kBins * 4, "a histogram in stage_i");
+    const int lane = ld_lane();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t mycnt = wave_counts<RW>(c, blockIdx.x);
     const GroupRange gr = group_range(c, blockIdx.x);
     TripRaw raw[RW::kAhead];
-    first_trips<true, RW>(c, blockIdx.x * RW::kGroupTiles + (threadIdx.x >> 6) * kTilesPerWave, mycnt, raw);
-    const SegState* st = c.state + gr.seg;
+    first_trips<true, RW>(c, blockIdx.x * RW::kGroupTiles + w * kTilesPerWave, mycnt, raw);
+    SegState* st = c.state + gr.seg;
     if (gr.k == 0) return;
-    const uint32_t mode = st->mode;
-    const uint32_t tau = gr.tau, test = gr.test, T = st->prefix, m = st->krem;
-    const int lane = ld_lane();
-    const int w = threadIdx.x >> 6;
+    uint32_t mode = st->mode;
+    const uint32_t ng = st->gcount, bin = st->prefix, krem = st->krem;
+    const uint32_t tau = gr.tau, test = gr.test;
     const int tl0 = w * kTilesPerWave;
-    const int32_t tile0 = blockIdx.x * RW::kGroupTiles + tl0;
+    const int32_t group_tile0 = blockIdx.x * RW::kGroupTiles, tile0 = group_tile0 + tl0;
     int64_t tbase = 0;
-    if (mode == kModeFull) {
+    if (mode != kModeFull) {
+        // The first wave selects, the others add up what the segment's groups before this one count: keys above the
+        // threshold bin, and where ties are counted per tile (kModeTies, an overfull bin) those too, before this group and in all.
+        const uint32_t* gkey = c.gkey + gather_first(gr.seg, gr.lo);
+        const int32_t* gtile = c.gtile + gather_first(gr.seg, gr.lo);
+        const uint32_t gcap = gather_cap(gr.lo, gr.hi);
+        const bool counted = mode == kModeTies || ng > gcap;  // uniform, as is what follows
+        if (w == 0) {
+            constexpr int kRows = kFewPicks / LD_WAVE;
+            uint32_t key[kRows];
+            int32_t tile[kRows];
+#pragma unroll
+            for (int i = 0; i < kRows / 2; ++i) {  // whatever the list holds there: it is longer
+                key[i] = gkey[i * LD_WAVE + lane];
+                tile[i] = gtile[i * LD_WAVE + lane];
+            }
+            static_assert(kGatherBase > kFewPicks, "");
+            if (lane < RW::kGroupTiles) own_gt[lane] = own_eq[lane] = 0;
+            const uint32_t base = tau + (bin << gr.sh);
+            const int bits = bin == static_cast<uint32_t>(kTopBin) ? 31 : static_cast<int>(gr.sh);  // the top bin is open-ended
+            if (mode == kModeTies) {  // both were found with the threshold bin: nothing to select
+                if (lane == 0) picked = Picked{bin, krem, 0u, 0u, 0u};
+            } else if (ng <= LD_WAVE) {
+                pick_few<1>(key, tile, ng, base, bits, krem, group_tile0, RW::kGroupTiles, picked, own_gt, own_eq);
+            } else if (ng <= kFewPicks / 2) {
+                pick_few<kRows / 2>(key, tile, ng, base, bits, krem, group_tile0, RW::kGroupTiles, picked, own_gt, own_eq);
+            } else if (ng <= kFewPicks) {
+#pragma unroll
+                for (int i = kRows / 2; i < kRows; ++i) {
+                    key[i] = gkey[i * LD_WAVE + lane];
+                    tile[i] = gtile[i * LD_WAVE + lane];
+                }
+                pick_few<kRows>(key, tile, ng, base, bits, krem, group_tile0, RW::kGroupTiles, picked, own_gt, own_eq);
+            }
+        } else {
+            uint32_t gt = 0, eq = 0, all = 0;
+            const int32_t before = static_cast<int32_t>(blockIdx.x) - gr.group0, upto = counted ? gr.ngroup : before;
+#pragma unroll 4
+            for (int32_t q = (w - 1) * LD_WAVE + lane; q < upto; q += (kWaves - 1) * LD_WAVE) {
+                if (q < before) gt += c.group_gt[gr.group0 + q];
+                if (counted) {
+                    const uint32_t x = c.group_eq[gr.group0 + q];
+                    all += x;
+                    eq += q < before ? x : 0u;
+                }
+            }
+            gt = ld_wave_sum(gt), eq = ld_wave_sum(eq), all = ld_wave_sum(all);
+            if (lane == 0) { sums[0][w] = gt; sums[1][w] = eq; sums[2][w] = all; }
+        }
+        __syncthreads();
+        if (mode == kModeCand && ng > kFewPicks)
+            pick_many(gkey, gtile, ng, gcap, st->kmin, st->kmax, tau + (bin << gr.sh), bin == static_cast<uint32_t>(kTopBin) ? 31 : static_cast<int>(gr.sh),
+                      krem, group_tile0, RW::kGroupTiles, &picked, own_gt, own_eq, reinterpret_cast<uint32_t*>(stage_i), sh, res);
+        if (w == 0) {  // offsets of the group's tiles
+            const Picked p = picked;
+            const uint32_t m = p.m;
+            const int32_t tile = group_tile0 + lane;
+            const bool live = lane < RW::kGroupTiles && gr.base + static_cast<int64_t>(lane) * kTile < gr.hi;
+            const uint32_t cg = live ? c.tile_gt[tile] + (counted ? 0u : own_gt[lane]) : 0u;
+            const uint32_t ce = live ? (counted ? c.tile_eq[tile] : own_eq[lane]) : 0u;
+            const uint32_t eq0 = counted ? sums[1][1] + sums[1][2] + sums[1][3] : p.eq_before;
+            const uint32_t eq_before = eq0 + ld_wave_iscan(ce) - ce;
+            const uint32_t take = umin(eq_before + ce, m) - umin(eq_before, m);  // ties kept: lowest index first
+            const uint32_t out0 = sums[0][1] + sums[0][2] + sums[0][3] + p.gt_before + umin(eq0, m);
+            const uint32_t out_before = out0 + ld_wave_iscan(cg + take) - (cg + take);
+            if (lane < RW::kGroupTiles) {
+                tile_out[lane] = out_before;
+                tile_eqb[lane] = eq_before;
+                tile_take[lane] = take;
+            }
+            // the repeated key does not fill k either: the threshold lies below it
+            if (lane == 0 && mode == kModeTies && sums[2][1] + sums[2][2] + sums[2][3] < m) picked.full = 1;
+        }
+        __syncthreads();
+    }
+    if (mode == kModeFull || picked.full) {
+        // handed to the full path: every pre-zeroed position back; the segment's first workgroup lists it, if k_gather's has not
+        if (static_cast<int32_t>(blockIdx.x) == gr.group0) {
+            for (int b = threadIdx.x; b < kBins; b += kThreads) c.hist[static_cast<int64_t>(gr.seg) * kBins + b] = 0;  // used again there
+            if (mode != kModeFull) mark_full(c, st, gr, &list0);
+        }
         for_trips<true, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
             float* rt = r + gr.base + static_cast<int64_t>(tl0 + Q.u) * kTile;
 #pragma unroll
@@ -1522,20 +1579,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
             [](int) {});
         return;
     }
-    if (w == 0) {  // offsets of the group's tiles
-        const int32_t tile = blockIdx.x * RW::kGroupTiles + lane;
-        const bool live = lane < RW::kGroupTiles && gr.base + static_cast<int64_t>(lane) * kTile < gr.hi;
-        const uint32_t cg = live ? c.tile_gt[tile] : 0u, ce = live ? c.tile_eq[tile] : 0u;
-        const uint32_t eq_before = c.group_eq[blockIdx.x] + ld_wave_iscan(ce) - ce;
-        const uint32_t take = umin(eq_before + ce, m) - umin(eq_before, m);
-        const uint32_t out_before = c.group_gt[blockIdx.x] + ld_wave_iscan(cg + take) - (cg + take);
-        if (lane < RW::kGroupTiles) {
-            tile_out[lane] = out_before;
-            tile_eqb[lane] = eq_before;
-            tile_take[lane] = take;
-        }
-    }
-    __syncthreads();
+    const uint32_t T = picked.T, m = picked.m;
     // kModeTies: the ties are not among the stored candidates. A tile that keeps some of them is
     // read back from the residual (nothing was pre-zeroed in a tied segment), where candidates and
     // ties come in index order; keys at or above T pass the filter there.
@@ -2062,8 +2106,6 @@ ld_status candidate_passes(const Ctx& c, float* residual, int32_t* out_idx, floa
         if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     }
     k_gather<RW><<<groups, block, 0, st>>>(residual, c);
-    if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    k_select<<<segments, block, 0, st>>>(c);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     k_emit<RW><<<groups, block, 0, st>>>(residual, out_idx, out_val, c);
     return ld_launch_status();

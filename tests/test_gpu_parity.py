@@ -264,6 +264,24 @@ def test_compress_density_range(rho):
     np.testing.assert_array_equal(bits(r_gpu.cpu().numpy()), bits(orr))
 
 
+@pytest.mark.parametrize("cluster", [1, 64, 65, 256, 257, 512, 513, 2049, 4090, 6000])
+@pytest.mark.parametrize("distinct", [True, False])
+def test_compress_selects_among_the_keys_of_one_bin(cluster, distinct):
+    # the threshold bin holds about `cluster` keys around rank k, below magnitudes of twenty binades that make the bins wide: either side of what
+    # one wave selects among in one, four and eight rows of registers, of what the workgroup does, and of what the list holds
+    # (6000: several values redone in full, one value by index order); several groups, and ties on both sides of their borders
+    n, k, above = 400_000, 3000, 3000 - min(cluster, 4000) // 2 - 1
+    rs = np.random.RandomState(cluster + distinct)
+    a = (rs.standard_normal(n) * 1e-6).astype(np.float32)
+    where = rs.permutation(n)
+    a[where[:above]] = np.exp2(rs.uniform(1.0, 20.0, above)).astype(np.float32)
+    a[where[above:above + cluster]] = 1.0 + (rs.permutation(cluster) * 2.0 ** -23 if distinct else 0.0)
+    a *= np.where(rs.rand(n) < 0.5, 1, -1).astype(np.float32)
+    for off, kk in ((np.array([0, n], np.int64), [k]), (np.array([0, 50_000, 50_000 + n], np.int64), [500, k])):
+        x = a if off.size == 2 else np.concatenate([(rs.standard_normal(50_000)).astype(np.float32), a])
+        check_compress(x, np.zeros(x.size, np.float32), off, np.array(kk, np.int32), tag=f"{cluster} keys, distinct {distinct}", large_groups=True)
+
+
 def test_compress_massive_ties_at_the_threshold():
     # More equal keys at the threshold than a segment's gather list holds (4096 + n_s / 4096).
     # One repeated value (zeros of a frozen layer, values on a grid): taken by index order without
