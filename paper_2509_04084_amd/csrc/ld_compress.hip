@@ -34,7 +34,8 @@
 //   k_gather  per tile: #candidates in bins above b; the (few) keys inside bin b are
 //             gathered per segment.
 //   k_emit    each workgroup selects the exact threshold T and tie count among the
-//             gathered keys for itself and completes its tiles' counts with them;
+//             gathered keys for itself and completes its tiles' counts with them
+//             (tables with segments of more than 100 M elements: k_select before it);
 //             ordered emission of (idx, val); repairs the residual where the
 //             T_est guess and the true selection differ.
 //
@@ -1392,73 +1393,173 @@ __device__ __forceinline__ void pick_few(const uint32_t* key, const int32_t* til
     if (lane == 0) out = Picked{T, krem, gt, eq, 0u};
 }
 
-// By the whole workgroup, among more keys, whole or (ng > gcap) more than the list holds. lh: kBins words.
-__device__ __attribute__((noinline)) void pick_many(const uint32_t* gkey, const int32_t* gtile, uint32_t ng, uint32_t gcap, uint32_t kmin,
-                                                    uint32_t kmax, uint32_t base, int bits, uint32_t krem, int32_t tile0, int32_t tiles,
-                                                    Picked* out, uint32_t* own_gt, uint32_t* own_eq, uint32_t* lh, uint32_t* sh,
-                                                    uint32_t* res) {
-    if (ng > gcap) {
-        // More keys in the threshold bin than the list holds. If they are all one value (massive
-        // ties: a frozen layer's zeros, values on a coarse grid) nothing has to be selected among
-        // them: T is that value, and the rank left inside the bin is the number of ties to keep,
-        // lowest index first. k_gather's per-tile counts of the bin are then the tie counts.
-        if (threadIdx.x == 0) { res[0] = kmin; res[1] = kmax; }
-        __syncthreads();
-        uint32_t lmin = 0xFFFFFFFFu, lmax = 0;
+// body(key, position) for every key of a list, eight of a thread requested together.
+template <class Body>
+__device__ __forceinline__ void for_keys(const uint32_t* __restrict__ gkey, uint32_t ng, Body&& body) {
+    constexpr int kAhead = 8;
 #pragma unroll 1
-        for (uint32_t p = threadIdx.x; p < gcap; p += kThreads) {
-            const uint32_t key = gkey[p];
-            lmin = umin(lmin, key);
-            lmax = key > lmax ? key : lmax;
+    for (uint32_t p0 = 0; p0 < ng; p0 += kAhead * kThreads) {
+        uint32_t key[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const uint32_t p = p0 + i * kThreads + threadIdx.x;
+            key[i] = gkey[p < ng ? p : ng - 1];
         }
-        atomicMin(&res[0], lmin);
-        atomicMax(&res[1], lmax);
-        __syncthreads();
-        if (threadIdx.x == 0) *out = Picked{res[0], krem, 0u, 0u, res[0] != res[1]};  // several values share an overfull bin: full
-        __syncthreads();
-        return;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const uint32_t p = p0 + i * kThreads + threadIdx.x;
+            if (p < ng) body(key[i], p);
+        }
     }
-    const int nlev = bits == 0 ? 1 : (bits + 10) / 11;  // one 11-bit radix level per 11 bits of bin width
+}
+
+// The threshold by the whole workgroup, among more keys, whole or (ng > gcap) more than the list holds. lh: kBins words. Ends with a
+// barrier; every thread gets the result.
+__device__ __attribute__((noinline)) Picked select_many(const uint32_t* gkey, uint32_t ng, uint32_t gcap, uint32_t kmin, uint32_t kmax,
+                                                        uint32_t krem, uint32_t* lh, uint32_t* sh, uint32_t* res) {
+    // More keys in the threshold bin than the list holds: if they are all one value (massive
+    // ties: a frozen layer's zeros, values on a coarse grid) nothing has to be selected among
+    // them: T is that value, and the rank left inside the bin is the number of ties to keep,
+    // lowest index first. k_gather's per-tile counts of the bin are then the tie counts.
+    if (threadIdx.x == 0) { res[0] = ng > gcap ? kmin : 0xFFFFFFFFu; res[1] = ng > gcap ? kmax : 0u; }
+    __syncthreads();
+    uint32_t lmin = 0xFFFFFFFFu, lmax = 0;
+    for_keys(gkey, ng > gcap ? gcap : ng, [&](uint32_t key, uint32_t) {
+        lmin = umin(lmin, key);
+        lmax = key > lmax ? key : lmax;
+    });
+    atomicMin(&res[0], lmin);
+    atomicMax(&res[1], lmax);
+    __syncthreads();
+    const uint32_t base = res[0], range = res[1] - base;
+    __syncthreads();
+    if (range == 0) return Picked{base, krem, 0u, 0u, 0u};
+    if (ng > gcap) return Picked{base, krem, 0u, 0u, 1u};  // several values share an overfull bin: full
+    const int bits = 32 - __builtin_clz(range);
+    const int nlev = (bits + 10) / 11;  // one 11-bit radix level per 11 bits between the least and the largest
     uint32_t prefix = 0;
 #pragma unroll 1
     for (int lev = 0; lev < nlev; ++lev) {
         const int shift = 11 * (nlev - 1 - lev);
         for (int b = threadIdx.x; b < kBins; b += kThreads) lh[b] = 0;
         __syncthreads();
-#pragma unroll 1
-        for (uint32_t p = threadIdx.x; p < ng; p += kThreads) {
-            const uint32_t rel = gkey[p] - base;
+        for_keys(gkey, ng, [&](uint32_t key, uint32_t) {
+            const uint32_t rel = key - base;
             if (lev == 0 || ((rel ^ prefix) >> (shift + 11)) == 0) atomicAdd(&lh[(rel >> shift) & 0x7FFu], 1u);
-        }
+        });
         __syncthreads();
         find_bin<kThreads, false>(lh, krem, sh, res);
         prefix |= res[0] << shift;
         krem = res[1];
         __syncthreads();
     }
-    const uint32_t T = base + prefix;
-    if (threadIdx.x == 0) *out = Picked{T, krem, 0u, 0u, 0u};
+    return Picked{base + prefix, krem, 0u, 0u, 0u};
+}
+
+// As pick_few, by the whole workgroup.
+__device__ __attribute__((noinline)) void pick_many(const uint32_t* gkey, const int32_t* gtile, uint32_t ng, uint32_t gcap, uint32_t kmin,
+                                                    uint32_t kmax, uint32_t krem, int32_t tile0, int32_t tiles, Picked* out, uint32_t* own_gt, uint32_t* own_eq, uint32_t* lh, uint32_t* sh,
+                                                    uint32_t* res) {
+    const Picked x = select_many(gkey, ng, gcap, kmin, kmax, krem, lh, sh, res);
+    if (threadIdx.x == 0) *out = x;
     __syncthreads();
+    if (ng > gcap) return;
     uint32_t gt = 0, eq = 0;
-#pragma unroll 1
-    for (uint32_t p = threadIdx.x; p < ng; p += kThreads) {
-        const uint32_t key = gkey[p];
-        if (key < T) continue;
+    for_keys(gkey, ng, [&](uint32_t key, uint32_t p) {
+        if (key < x.T) return;
         const int32_t tile = gtile[p];
-        if (tile < tile0) ++(key > T ? gt : eq);
-        else if (tile < tile0 + tiles) atomicAdd((key > T ? own_gt : own_eq) + (tile - tile0), 1u);
-    }
+        if (tile < tile0) ++(key > x.T ? gt : eq);
+        else if (tile < tile0 + tiles) atomicAdd((key > x.T ? own_gt : own_eq) + (tile - tile0), 1u);
+    });
     if (gt) atomicAdd(&out->gt_before, gt);
     if (eq) atomicAdd(&out->eq_before, eq);
     __syncthreads();
+}
+
+// Segments up to which k_emit's workgroups select for themselves. A larger one has more keys in the threshold bin than a wave selects
+// among, and thousands of groups before its last: one workgroup per segment does all that ahead of k_emit then (k_select). us per
+// call with / without that launch: 400 M elements 885 / 873, rounded to bf16 1155 / 1315, 1.2 G 2690 / 2767; GPT-2 XL, up to 80 M a segment, 3263 / 3255.
+constexpr int64_t kOwnPick = 100000000;
+
+// One workgroup per segment: threshold and ties; per-tile counts completed; group sums scanned into output offsets.
+__global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
+    __shared__ uint32_t lh[kBins];
+    __shared__ uint32_t sh[kWaves];
+    __shared__ uint32_t res[3];
+    __shared__ uint32_t list0;
+    const SegDesc d = c.desc[blockIdx.x];
+    if (d.k == 0 || c.desc[blockIdx.x + 1].group0 == d.group0) return;
+    const GroupRange gr = group_range(c, d.group0);
+    SegState* st = c.state + gr.seg;
+    const uint32_t mode = st->mode;
+    if (mode == kModeFull) return;
+    const uint32_t ng = st->gcount;
+    const uint32_t* gkey = c.gkey + gather_first(gr.seg, gr.lo);
+    const int32_t* gtile = c.gtile + gather_first(gr.seg, gr.lo);
+    const uint32_t gcap = gather_cap(gr.lo, gr.hi);
+    Picked x{st->prefix, st->krem, 0u, 0u, 0u};  // kModeTies: both were found with the threshold bin
+    uint32_t seen = 0;
+    if (mode != kModeTies) {
+        x = select_many(gkey, ng, gcap, st->kmin, st->kmax, x.m, lh, sh, res);
+        if (x.full) {
+            mark_full(c, st, gr, &list0);
+            return;
+        }
+        // k_gather counted every key of the bin as a tie: move those above T to the counts of the
+        // selected, drop those below. The group sums are read back below by this same workgroup.
+        // The updates return their old value, so each has been performed when its result arrives;
+        // with the barrier that orders them before the reads. (A device-scope fence would do too,
+        // but it writes back the whole L2 and costs 30 us here.)
+        if (ng <= gcap)
+            for_keys(gkey, ng, [&](uint32_t key, uint32_t p) {
+                if (key == x.T) return;
+                const int32_t tile = gtile[p];
+                atomicSub(c.tile_eq + tile, 1u);
+                seen |= atomicSub(c.group_eq + tile / c.tiles, 1u);
+                if (key > x.T) {
+                    atomicAdd(c.tile_gt + tile, 1u);
+                    seen |= atomicAdd(c.group_gt + tile / c.tiles, 1u);
+                }
+            });
+    }
+    if (seen == 0xFFFFFFFFu) res[0] = seen;  // never true: keeps the results, and so the waits, alive
+    __syncthreads();
+    // exclusive scan over the segment's groups: records emitted / ties seen before each
+    uint32_t carry_out = 0, carry_eq = 0;
+#pragma unroll 1
+    for (int32_t q0 = 0; q0 < gr.ngroup; q0 += kThreads) {
+        const int32_t q = q0 + threadIdx.x;
+        uint32_t cg = 0, ce = 0;
+        if (q < gr.ngroup) {
+            cg = ld_load_coherent(c.group_gt + gr.group0 + q);
+            ce = ld_load_coherent(c.group_eq + gr.group0 + q);
+        }
+        uint32_t te, tg;
+        const uint32_t eq_before = carry_eq + block_escan<kThreads>(ce, sh, te);
+        const uint32_t take = umin(eq_before + ce, x.m) - umin(eq_before, x.m);  // ties kept: lowest index first
+        const uint32_t out_before = carry_out + block_escan<kThreads>(cg + take, sh, tg);
+        if (q < gr.ngroup) {
+            c.group_gt[gr.group0 + q] = out_before;
+            c.group_eq[gr.group0 + q] = eq_before;
+        }
+        carry_eq += te;
+        carry_out += tg;
+    }
+    if (mode == kModeTies && carry_eq < x.m) {
+        mark_full(c, st, gr, &list0);  // the repeated key does not fill k either: the threshold lies below it
+        return;
+    }
+    if (threadIdx.x == 0) { st->prefix = x.T; st->krem = x.m; }
 }
 
 // Ordered emission of the records. k_main left +0 in the residual exactly where a
 // stored candidate's key reaches T_est; only where that guess and the selection
 // differ is the residual written again. A segment handed to the full path gets
 // every pre-zeroed position back instead.
-template <class RW>
-__global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_t* __restrict__ out_idx,
+// OWN: the threshold is selected here. Four waves per SIMD: the selection's registers would leave three (GPT-2 XL 3225 us a call, so 3217); five spill
+// them (3276).
+template <class RW, bool OWN>
+__global__ __launch_bounds__(kThreads, 4) void k_emit(float* __restrict__ r, int32_t* __restrict__ out_idx,
                                                    float* __restrict__ out_val, Ctx c) {
     __shared__ uint32_t tile_out[RW::kGroupTiles], tile_eqb[RW::kGroupTiles], tile_take[RW::kGroupTiles];
     __shared__ uint32_t own_gt[RW::kGroupTiles], own_eq[RW::kGroupTiles];  // gathered keys of the group's tiles: above T, equal to T
@@ -1483,7 +1584,23 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
     const int tl0 = w * kTilesPerWave;
     const int32_t group_tile0 = blockIdx.x * RW::kGroupTiles, tile0 = group_tile0 + tl0;
     int64_t tbase = 0;
-    if (mode != kModeFull) {
+    if (!OWN && mode != kModeFull) {
+        if (w == 0) {  // offsets of the group's tiles
+            const int32_t tile = group_tile0 + lane;
+            const bool live = lane < RW::kGroupTiles && gr.base + static_cast<int64_t>(lane) * kTile < gr.hi;
+            const uint32_t cg = live ? c.tile_gt[tile] : 0u, ce = live ? c.tile_eq[tile] : 0u;
+            const uint32_t eq_before = c.group_eq[blockIdx.x] + ld_wave_iscan(ce) - ce;
+            const uint32_t take = umin(eq_before + ce, krem) - umin(eq_before, krem);
+            const uint32_t out_before = c.group_gt[blockIdx.x] + ld_wave_iscan(cg + take) - (cg + take);
+            if (lane < RW::kGroupTiles) {
+                tile_out[lane] = out_before;
+                tile_eqb[lane] = eq_before;
+                tile_take[lane] = take;
+            }
+        }
+        __syncthreads();
+    }
+    if (OWN && mode != kModeFull) {
         // The first wave selects, the others add up what the segment's groups before this one count: keys above the
         // threshold bin, and where ties are counted per tile (kModeTies, an overfull bin) those too, before this group and in all.
         const uint32_t* gkey = c.gkey + gather_first(gr.seg, gr.lo);
@@ -1534,8 +1651,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
         }
         __syncthreads();
         if (mode == kModeCand && ng > kFewPicks)
-            pick_many(gkey, gtile, ng, gcap, st->kmin, st->kmax, tau + (bin << gr.sh), bin == static_cast<uint32_t>(kTopBin) ? 31 : static_cast<int>(gr.sh),
-                      krem, group_tile0, RW::kGroupTiles, &picked, own_gt, own_eq, reinterpret_cast<uint32_t*>(stage_i), sh, res);
+            pick_many(gkey, gtile, ng, gcap, st->kmin, st->kmax, krem, group_tile0, RW::kGroupTiles, &picked, own_gt, own_eq, reinterpret_cast<uint32_t*>(stage_i), sh, res);
         if (w == 0) {  // offsets of the group's tiles
             const Picked p = picked;
             const uint32_t m = p.m;
@@ -1558,11 +1674,11 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
         }
         __syncthreads();
     }
-    if (mode == kModeFull || picked.full) {
+    if (mode == kModeFull || (OWN && picked.full)) {
         // handed to the full path: every pre-zeroed position back; the segment's first workgroup lists it, if k_gather's has not
         if (static_cast<int32_t>(blockIdx.x) == gr.group0) {
             for (int b = threadIdx.x; b < kBins; b += kThreads) c.hist[static_cast<int64_t>(gr.seg) * kBins + b] = 0;  // used again there
-            if (mode != kModeFull) mark_full(c, st, gr, &list0);
+            if (OWN && mode != kModeFull) mark_full(c, st, gr, &list0);
         }
         for_trips<true, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
             float* rt = r + gr.base + static_cast<int64_t>(tl0 + Q.u) * kTile;
@@ -1579,7 +1695,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(float* __restrict__ r, int32_
             [](int) {});
         return;
     }
-    const uint32_t T = picked.T, m = picked.m;
+    const uint32_t T = OWN ? picked.T : bin, m = OWN ? picked.m : krem;  // (k_select's, where the bin and its rank were)
     // kModeTies: the ties are not among the stored candidates. A tile that keeps some of them is
     // read back from the residual (nothing was pre-zeroed in a tied segment), where candidates and
     // ties come in index order; keys at or above T pass the filter there.
@@ -2095,7 +2211,7 @@ int32_t full_grid_limit() {
 
 // The passes over the candidates.
 template <class RW>
-ld_status candidate_passes(const Ctx& c, float* residual, int32_t* out_idx, float* out_val, hipStream_t st) {
+ld_status candidate_passes(const Ctx& c, bool own, float* residual, int32_t* out_idx, float* out_val, hipStream_t st) {
     const dim3 groups(static_cast<uint32_t>(c.n_group)), segments(static_cast<uint32_t>(c.n_seg)), block(kThreads);
     const dim3 hgroups(static_cast<uint32_t>((c.n_group + kHistGroups - 1) / kHistGroups));
     if (c.n_group <= kFewGroups) k_hist<RW, 1><<<groups, block, 0, st>>>(residual, c);
@@ -2107,7 +2223,13 @@ ld_status candidate_passes(const Ctx& c, float* residual, int32_t* out_idx, floa
     }
     k_gather<RW><<<groups, block, 0, st>>>(residual, c);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    k_emit<RW><<<groups, block, 0, st>>>(residual, out_idx, out_val, c);
+    if (!own) {
+        k_select<<<segments, block, 0, st>>>(c);
+        if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
+        k_emit<RW, false><<<groups, block, 0, st>>>(residual, out_idx, out_val, c);
+    } else {
+        k_emit<RW, true><<<groups, block, 0, st>>>(residual, out_idx, out_val, c);
+    }
     return ld_launch_status();
 }
 
@@ -2216,15 +2338,18 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     if (K == 0) return LD_OK;
     // lanes per tile in the candidate passes: enough for the candidates a tile is expected to hold
     const int row = (per_tile <= 128 && slot == kSlotMin) ? 16 : (per_tile <= 256 ? 32 : 64);  // 16 implies the minimum slot
+    int64_t largest = 0;
+    for (int32_t s = 0; s < n_seg; ++s) largest = seg_off[s + 1] - seg_off[s] > largest ? seg_off[s + 1] - seg_off[s] : largest;
+    const bool own = largest <= kOwnPick;
     ld_status passes;
     if (tiles == kTilesPerGroup) {
-        if (row == 16) passes = candidate_passes<Rows<16, kTilesPerGroup>>(c, residual, out_idx, out_val, st);
-        else if (row == 32) passes = candidate_passes<Rows<32, kTilesPerGroup>>(c, residual, out_idx, out_val, st);
-        else passes = candidate_passes<Rows<64, kTilesPerGroup>>(c, residual, out_idx, out_val, st);
+        if (row == 16) passes = candidate_passes<Rows<16, kTilesPerGroup>>(c, own, residual, out_idx, out_val, st);
+        else if (row == 32) passes = candidate_passes<Rows<32, kTilesPerGroup>>(c, own, residual, out_idx, out_val, st);
+        else passes = candidate_passes<Rows<64, kTilesPerGroup>>(c, own, residual, out_idx, out_val, st);
     } else {
-        if (row == 16) passes = candidate_passes<Rows<16, kTilesPerSmallGroup>>(c, residual, out_idx, out_val, st);
-        else if (row == 32) passes = candidate_passes<Rows<32, kTilesPerSmallGroup>>(c, residual, out_idx, out_val, st);
-        else passes = candidate_passes<Rows<64, kTilesPerSmallGroup>>(c, residual, out_idx, out_val, st);
+        if (row == 16) passes = candidate_passes<Rows<16, kTilesPerSmallGroup>>(c, own, residual, out_idx, out_val, st);
+        else if (row == 32) passes = candidate_passes<Rows<32, kTilesPerSmallGroup>>(c, own, residual, out_idx, out_val, st);
+        else passes = candidate_passes<Rows<64, kTilesPerSmallGroup>>(c, own, residual, out_idx, out_val, st);
     }
     if (passes != LD_OK) return passes;
     // segments handed to the full path (normally none: the launch returns at once). Its grid must be
