@@ -28,10 +28,9 @@
 //             elsewhere - so that the scattered repair writes of the last pass touch
 //             only the elements between T_est and the true threshold (a few percent
 //             of k) instead of all k selected positions.
-//   k_hist    histogram of the candidates over 2048 fine bins; k_bin (one workgroup
-//             per segment; with small groups each workgroup of k_gather for itself) finds the
-//             bin b holding the k-th largest key.
-//   k_gather  per tile: #candidates in bins above b; the (few) keys inside bin b are
+//   k_hist    histogram of the candidates over 2048 fine bins.
+//   k_gather  finds the bin b holding the k-th largest key;
+//             per tile: #candidates in bins above b; the (few) keys inside bin b are
 //             gathered per segment.
 //   k_emit    each workgroup selects the exact threshold T and tie count among the
 //             gathered keys for itself and completes its tiles' counts with them
@@ -126,7 +125,7 @@ struct SegState {       // 64 bytes
     uint32_t tau;       // candidate threshold (key); 0: every element, 0xFFFFFFFF: none
     uint32_t sh;        // fine bin of a candidate: min(kTopBin, (key - tau) >> sh)
     uint32_t test;      // guessed threshold T_est >= tau: k_main stores +0 where key >= T_est
-    uint32_t prefix;    // k_bin (small groups: k_gather): threshold bin, kModeTies: the threshold (k_full: radix prefix)
+    uint32_t prefix;    // k_gather: threshold bin, kModeTies: the threshold (k_full: radix prefix)
     uint32_t krem;      // rank left inside prefix, kModeTies: the number of ties to keep
     uint32_t mode;      // kModeCand | kModeFull | kModeTies
     uint32_t gcount;    // keys gathered from the threshold bin
@@ -794,10 +793,7 @@ template <int ROW, int TILES>
 struct Rows {
     static constexpr int kRow = ROW, kGroupTiles = TILES;
     static constexpr int kTilesPerWave = TILES / kWaves;
-    // k_gather finds the threshold bin itself instead of leaving it to a launch of its own: with few groups
-    // each repeats it at once (flat 1 M 50.5 -> 49.2 us per call, ResNet-50 109.0 -> 107.5, 24 M 102.7 -> 100.6);
-    // thousands of groups would repeat it in rounds
-    static constexpr bool kOwnBin = TILES == kTilesPerSmallGroup;
+    static constexpr bool kSmall = TILES == kTilesPerSmallGroup;
     static constexpr int kTiles = LD_WAVE / ROW;                 // tiles per trip
     static constexpr uint32_t kFast = ROW * kPerLane;            // candidates a tile may hold
     static constexpr int kTrips = kTilesPerWave / kTiles;
@@ -1072,15 +1068,6 @@ __device__ __forceinline__ uint32_t threshold_bin(const Ctx& c, const GroupRange
     return kModeFull;
 }
 
-// One workgroup per segment, where k_gather's workgroups do not look for themselves (Rows::kOwnBin).
-__global__ __launch_bounds__(kThreads) void k_bin(Ctx c) {
-    __shared__ uint32_t sh[kWaves], res[3], list0;
-    const SegDesc d = c.desc[blockIdx.x];
-    if (d.k == 0 || c.desc[blockIdx.x + 1].group0 == d.group0) return;
-    const GroupRange gr = group_range(c, d.group0);
-    threshold_bin(c, gr, c.state + gr.seg, true, sh, res, &list0);
-}
-
 // Elements of the tile starting at tbase whose key is `key`, counted by the whole wave from the
 // residual (which holds r + g wherever nothing was zeroed).
 __device__ __forceinline__ uint32_t count_key_in_tile(const float* __restrict__ r, int64_t tbase, int64_t lo,
@@ -1143,7 +1130,9 @@ __device__ __attribute__((noinline)) Unplaced gather_lane_keys(SegState* st, uin
 constexpr uint32_t kFewKeys = 256;
 
 // Per tile: candidates in bins above the threshold bin; the keys inside the bin
-// are gathered per segment.
+// are gathered per segment. The bin is found by each workgroup for itself: as a launch of one workgroup per segment ahead of this one it
+// cost more, with any number of groups (GPT-2 small 299.2 -> 297.3 us a call, 520 segments of up to 5000 elements 82.2 -> 80.3, 3000 of up to
+// 3000 258.7 -> 254, 800 of 30,000 to 400,000 489 -> 485; GPT-2 XL, 400 M, 1.2 G: the same).
 template <class RW>
 __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r, Ctx c) {
     __shared__ uint32_t wsum[2][kWaves], wmin[kWaves], wmax[kWaves];
@@ -1153,18 +1142,11 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
     first_trips<false, RW>(c, blockIdx.x * RW::kGroupTiles + (threadIdx.x >> 6) * RW::kTilesPerWave, mycnt, raw);
     SegState* st = c.state + gr.seg;
     if (gr.k == 0) return;
-    uint32_t mode, b1;
-    bool many = false;  // small groups: one reservation per workgroup (see below)
-    if (RW::kOwnBin) {
-        // each workgroup finds the threshold bin for itself, the segment's first one notes it down
-        __shared__ uint32_t sh[kWaves], res[3], list0;
-        mode = threshold_bin(c, gr, st, static_cast<int32_t>(blockIdx.x) == gr.group0, sh, res, &list0);
-        b1 = res[0];
-        many = mode == kModeCand && res[2] > kFewKeys;
-    } else {
-        mode = st->mode;
-        b1 = st->prefix;
-    }
+    // each workgroup finds the threshold bin for itself, the segment's first one notes it down
+    __shared__ uint32_t sh[kWaves], res[3], list0;
+    const uint32_t mode = threshold_bin(c, gr, st, static_cast<int32_t>(blockIdx.x) == gr.group0, sh, res, &list0);
+    const uint32_t b1 = res[0];
+    const bool many = RW::kSmall && mode == kModeCand && res[2] > kFewKeys;  // one reservation per workgroup (see below)
     if (mode == kModeFull) return;
     // kModeTies: every candidate lies above the threshold and nothing is gathered; the ties of a
     // tile are what k_main counted
@@ -1196,8 +1178,8 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
         }
     }
     uint32_t place = 0;  // small groups: where this lane's next key goes
-    if (RW::kOwnBin && many) {  // uniform
-        static_assert(!RW::kOwnBin || RW::kTrips == RW::kAhead, "all trips of a wave are in registers");
+    if (RW::kSmall && many) {  // uniform
+        static_assert(!RW::kSmall || RW::kTrips == RW::kAhead, "all trips of a wave are in registers");
         __shared__ uint32_t wkeys[kWaves], first;
         uint32_t mine = 0, before = 0, total = 0;
 #pragma unroll
@@ -1235,7 +1217,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(const float* __restrict__ r
         const uint32_t n_in = __popc(in);
         const uint64_t who = __ballot(in != 0);
         if (who) {
-            if (!RW::kOwnBin && (full || __popcll(who) >= 4)) {  // massive ties: one reservation for the wave, or none
+            if (!RW::kSmall && (full || __popcll(who) >= 4)) {  // massive ties: one reservation for the wave, or none
                 const Unplaced un = gather_lane_keys(st, gkey, gtile, gcap, ld_f32x4{Q.v[0], Q.v[1], Q.v[2], Q.v[3]},
                                                      ld_f32x4{Q.v[4], Q.v[5], Q.v[6], Q.v[7]}, in, tile0 + Q.u, full);
                 lmin = umin(lmin, un.kmin);
@@ -2217,10 +2199,6 @@ ld_status candidate_passes(const Ctx& c, bool own, float* residual, int32_t* out
     if (c.n_group <= kFewGroups) k_hist<RW, 1><<<groups, block, 0, st>>>(residual, c);
     else k_hist<RW, kHistGroups><<<hgroups, dim3(kHistGroups * kThreads), 0, st>>>(residual, c);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    if (!RW::kOwnBin) {
-        k_bin<<<segments, block, 0, st>>>(c);
-        if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
-    }
     k_gather<RW><<<groups, block, 0, st>>>(residual, c);
     if (ld_launch_status() != LD_OK) return LD_ERR_HIP;
     if (!own) {
