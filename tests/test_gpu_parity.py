@@ -1483,6 +1483,23 @@ def test_check_diff_at_workgroup_edges(K, skip):
     assert tuple(got.cpu().tolist()) == oracle.check_diff(i[skip:], v[skip:], n)
 
 
+@pytest.mark.parametrize("K", [4098, 16381, 16383, 16384, 16385, 33_000])
+def test_check_diff_in_one_workgroup_and_beyond(K):
+    # up to 16384 records one workgroup writes the counts itself, whatever they held before; damage in the last, broken vectors too
+    rs = np.random.RandomState(K)
+    n = 1 << 20
+    i = np.sort(rs.choice(n, K, replace=False)).astype(np.int32)
+    v = rs.standard_normal(K).astype(np.float32)
+    for j in (0, 63, 255, 256, 1024, 4096, K - 5, K - 2, K - 1):
+        i[j] = [-3, n + 9, i[j - 1]][j % 3] if j else i[j]
+        v[j] = np.nan
+    counts = torch.full((3,), -1, dtype=torch.int64, device=DEV)
+    for _ in range(2):
+        ld.ld_check_diff(to_gpu(i), to_gpu(v), n, counts)
+        torch.cuda.synchronize()
+        assert tuple(counts.cpu().tolist()) == oracle.check_diff(i, v, n)
+
+
 # ------------------------------------------------------------ graph capture
 
 def test_calls_can_be_captured_in_a_graph_and_replayed():
