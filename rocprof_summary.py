@@ -20,7 +20,7 @@ from __future__ import annotations
 import sqlite3
 import sys
 
-OURS = ("k_main", "k_prep", "k_upload", "k_hist", "k_bin", "k_gather", "k_select", "k_emit", "k_full", "k_paths",
+OURS = ("k_main", "k_prep", "k_upload", "k_hist", "k_gather", "k_select", "k_emit", "k_full", "k_paths",
         "k_chunks", "k_subtab", "k_merge_", "k_sparse_adam", "k_combine_", "k_check_", "k_snapshot", "k_adam")
 
 
@@ -63,7 +63,7 @@ def pmc(db_paths) -> str:
 
 
 # kernel-name prefixes (template arguments follow some of them)
-COMPRESS_KERNELS = ("k_upload", "k_prep", "k_main", "k_hist", "k_bin", "k_gather", "k_select", "k_emit", "k_full")
+COMPRESS_KERNELS = ("k_upload", "k_prep", "k_main", "k_hist", "k_gather", "k_select", "k_emit", "k_full")
 
 
 def _table(path):
