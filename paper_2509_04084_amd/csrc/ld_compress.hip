@@ -138,7 +138,8 @@ struct SegState {       // 64 bytes
     // k_gather counts the key per tile in the residual, k_emit checks that with those ties k is
     // reached (else: the full path), and k_emit takes the ties in index order (kModeTies).
     uint32_t tied;
-    uint32_t pad[2];
+    uint32_t late;      // 1: handed to the full path by k_emit, whose workgroups still read `mode`
+    uint32_t pad;
 };
 
 struct Ctx {
@@ -992,9 +993,9 @@ __device__ __forceinline__ void slow_tiles(const Ctx& c, const float* __restrict
     }
 }
 
-__device__ __forceinline__ void mark_full(const Ctx& c, SegState* st, const GroupRange& gr, uint32_t* list0) {
+__device__ __forceinline__ void mark_full(const Ctx& c, SegState* st, const GroupRange& gr, uint32_t* list0, bool late = false) {
     if (threadIdx.x == 0) {
-        st->mode = kModeFull;
+        if (late) st->late = 1; else st->mode = kModeFull;
         *list0 = atomicAdd(c.fail_count + kSyncCount, static_cast<uint32_t>(gr.ngroup));
     }
     __syncthreads();
@@ -1698,7 +1699,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_emit(float* __restrict__ r, int
         // handed to the full path: every pre-zeroed position back; the segment's first workgroup lists it, if k_gather's has not
         if (static_cast<int32_t>(blockIdx.x) == gr.group0) {
             for (int b = threadIdx.x; b < kBins; b += kThreads) c.hist[static_cast<int64_t>(gr.seg) * kBins + b] = 0;  // used again there
-            if (OWN && mode != kModeFull) mark_full(c, st, gr, &list0);
+            // (not in `mode`: a wave that read it so would leave before the others have its part of the sums)
+            if (OWN && mode != kModeFull) mark_full(c, st, gr, &list0, true);
         }
         for_trips<true, RW>(c, tile0, mycnt, raw, [&](const Trip& Q, int) {
             float* rt = r + gr.base + static_cast<int64_t>(tl0 + Q.u) * kTile;
@@ -2151,7 +2153,7 @@ __global__ __launch_bounds__(kThreads) void k_paths(Ctx wanted, Ctx large, int32
     block_escan<kThreads>(over, sh, total);
     if (threadIdx.x == 0) {
         const SegState st = c.state[s];
-        paths[s] = static_cast<int32_t>(st.mode | (st.tied ? 0x100u : 0u) |
+        paths[s] = static_cast<int32_t>((st.late ? kModeFull : st.mode) | (st.tied ? 0x100u : 0u) |
                                         (c.fail_count[kSyncGaveUp] ? 0x10000u : 0u));
         if (overflowed) overflowed[s] = static_cast<int32_t>(total);
     }
