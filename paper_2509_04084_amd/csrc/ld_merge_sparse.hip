@@ -755,14 +755,17 @@ int rows_windows(int64_t n, int32_t gw, int64_t most) {  // 64-record windows pe
 // (0: not at all): that pays by the record, windows from a table and the sweep by the diff. us a call, windows / a lane per record:
 // 24 diffs of 1/250 17 / 20 on 6 M elements, 46 / 50 on 25 M, 99 / 100 on 60 M, 170 / 171 on 110 M, of 1/1000 17 / 19, -, 85 / 85, 137 / 138; 48 of
 // 1/500 20 / 20, 53 / 54, 114 / 99, 195 / 174; 80 of 1/250 31 / 29, 83 / 78, 176 / 157, 306 / 276, of 1/180 33 / 33, 85 / 88, 175 / 180,
-// 332 / 342; below 2 M elements it is the launches. Sweep / a lane per record, where there is no table of windows: 150 M elements, 20 diffs of
-// 1/150 244 / 233, 32 of 1/120 343 / 313, 100 of 1/120 845 / 718; 400 M, 20 of 1/150 627 / 641, 32 of 1/150 773 / 751, of 1/120 793 / 831, 64 of
-// 1/150 1192 / 1107, 100 of 1/120 2035 / 1845; 1.5 G, 20 of 1/200 2220 / 2305.
+// 332 / 342; below 2 M elements it is the launches. Sweep / a lane per record, where there is no table of windows: 150 M elements, 32 diffs of
+// 1/120 343 / 313, 100 of 1/120 845 / 718; 400 M, 32 of 1/150 773 / 751, of 1/120 793 / 831, 64 of 1/150 1192 / 1107, 100 of 1/120 2035 / 1845.
+// 11 to 24 diffs, sweep over a lane per record, densities even and log-normal over 60 layers (sigma 1): up to 74 records 1.01 to 1.15 and 1.05 to 1.30 on
+// 130, 185 and 250 M elements (20 diffs of 1/290 on 250 M 439 / 395 us, 24 of 1/300 on 185 M 326 / 301); 24 diffs on 400 to 800 M at 37 records 1.01 to 1.04 and 1.14 to 1.17, at 54
+// 0.97 to 0.99 and 1.22; on 1.4 G at 28 1.00 and 1.13, at 37 1.00 and 1.14, 16 diffs there 0.98 and 1.05 to 1.07.
 int thin_line(int64_t n, int32_t gw) {
     if (gw <= 10) return 0;
     if (n < 2000000) return gw > kRowBatch ? 48 : 20;
     if (n < kRowsMost) return gw > 24 ? 48 : 10;
-    return gw <= 24 ? (n < 180000000 ? 60 : 27) : gw <= LD_WAVE ? 56 : 72;
+    if (gw <= 24) return n < 300000000 ? 60 : n < 1000000000 ? 48 : 27;
+    return gw <= LD_WAVE ? 56 : 72;
 }
 
 size_t chunk_table_bytes(int64_t n, int32_t W) {

@@ -327,6 +327,23 @@ def test_windows_take_the_table_that_measured_faster(n, W, per8192, sub):
     assert lib.ld_merge_sparse_workspace(n, W, _p(K)) == size
 
 
+@pytest.mark.parametrize("n,W,per8192,thin", [
+    # large arrays, 11 to 24 diffs: us of the sweep and of a lane per record, densities even and differing from layer to layer
+    (185_000_000, 24, 28, True),      # 326 / 301, 381 / 328
+    (250_000_000, 20, 28, True),      # 439 / 395, 488 / 416
+    (400_000_000, 24, 33, True),      # 678 / 646, 821 / 711
+    (800_000_000, 24, 37, True),      # 1298 / 1282, 1651 / 1434
+    # either side of the line
+    (250_000_000, 20, 60, True), (250_000_000, 20, 61, False), (400_000_000, 20, 48, True), (400_000_000, 20, 49, False),
+    (1_400_000_000, 20, 37, False)])  # 2114 / 2158 (densities even)
+def test_few_diffs_of_large_arrays_run_a_lane_per_record_where_it_measured_faster(n, W, per8192, thin):
+    lib = ld.load()
+    K = np.full(W, n * per8192 // 8192, np.int64)
+    table = -(-(W * (-(-n // 4096) + 1) * 4) // 256) * 256
+    want = table if thin else lib.ld_merge_sparse_workspace(n, W, ctypes.c_void_p(0))
+    assert lib.ld_merge_sparse_workspace(n, W, _p(K)) == want
+
+
 def test_windows_from_a_table_end_where_the_sweep_measured_faster():
     # 100 M elements, 20 diffs of 1 %: the sweep 192 us, windows from a table 176; 91 M, 72 of 1.25 % 432 / 350; 100 M, 30 of 3.3 % 358 / 368
     lib = ld.load()
