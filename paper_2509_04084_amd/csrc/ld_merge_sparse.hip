@@ -750,20 +750,24 @@ int rows_windows(int64_t n, int32_t gw, int64_t most) {  // 64-record windows pe
     return n < kFewSubs ? (gw <= 64 && most * kSub > 120 * n ? 2 : 1) : (gw <= 32 && most * kSub > 100 * n ? 2 : 1);
 }
 
-
 // Up to which density a group of `gw` diffs runs a lane per record (k_merge_thin), in records of its largest diff per 8192 elements
-// (0: not at all): that pays by the record, windows from a table and the sweep by the diff. us a call, windows / a lane per record:
-// 24 diffs of 1/250 17 / 20 on 6 M elements, 46 / 50 on 25 M, 99 / 100 on 60 M, 170 / 171 on 110 M, of 1/1000 17 / 19, -, 85 / 85, 137 / 138; 48 of
-// 1/500 20 / 20, 53 / 54, 114 / 99, 195 / 174; 80 of 1/250 31 / 29, 83 / 78, 176 / 157, 306 / 276, of 1/180 33 / 33, 85 / 88, 175 / 180,
-// 332 / 342; below 2 M elements it is the launches. Sweep / a lane per record, where there is no table of windows: 150 M elements, 32 diffs of
-// 1/120 343 / 313, 100 of 1/120 845 / 718; 400 M, 32 of 1/150 773 / 751, of 1/120 793 / 831, 64 of 1/150 1192 / 1107, 100 of 1/120 2035 / 1845.
+// (0: not at all): that pays by the record, windows from a table and the sweep by the diff. us a call, windows / a lane per record, densities even (and
+// log-normal over 60 layers, sigma 0.7): 30 diffs of 1/200 49 / 62 (49 / 62) on
+// 25 M elements, 29 / 32 (28 / 37) on 10 M, 20 / 18 (20 / 27) on 6 M; 40 of 1/270 53 / 63 (53 / 63) on 25 M, 19 / 18 (18 / 28) on 4 M, 159 / 161 (158 / 168) on 90 M,
+// of 1/200 182 / 184 (180 / 206) on 100 M; 60 of 1/250 40 / 37 (40 / 48) on 10 M, 64 of 1/330 154 / 122 (153 / 134) on 60 M, 56 of 1/200 250 / 266 (250 / 301)
+// on 118 M; 100 of 1/270 53 / 45 on 10 M, 338 / 294 on 118 M. Up to 24 diffs sparser than the line are scattered more often than
+// not; below 2 M elements it is the launches. Sweep / a lane per record, where there is no table of windows: 150 M elements, 32 diffs of 1/120 343 / 313, 100 of 1/120 845 / 718; 400 M, 32 of 1/150 773 / 751, of 1/120 793 / 831, 64 of 1/150 1192 / 1107, 100 of 1/120 2035 / 1845.
 // 11 to 24 diffs, sweep over a lane per record, densities even and log-normal over 60 layers (sigma 1): up to 74 records 1.01 to 1.15 and 1.05 to 1.30 on
 // 130, 185 and 250 M elements (20 diffs of 1/290 on 250 M 439 / 395 us, 24 of 1/300 on 185 M 326 / 301); 24 diffs on 400 to 800 M at 37 records 1.01 to 1.04 and 1.14 to 1.17, at 54
 // 0.97 to 0.99 and 1.22; on 1.4 G at 28 1.00 and 1.13, at 37 1.00 and 1.14, 16 diffs there 0.98 and 1.05 to 1.07.
 int thin_line(int64_t n, int32_t gw) {
     if (gw <= 10) return 0;
     if (n < 2000000) return gw > kRowBatch ? 48 : 20;
-    if (n < kRowsMost) return gw > 24 ? 48 : 10;
+    if (n < kRowsMost) {
+        if (gw <= 24) return 10;
+        if (gw > LD_WAVE) return 48;
+        return gw <= 32 || (n >= 20000000 && n < 45000000) ? 24 : 36;
+    }
     if (gw <= 24) return n < 300000000 ? 60 : n < 1000000000 ? 48 : 27;
     return gw <= LD_WAVE ? 56 : 72;
 }

@@ -316,10 +316,14 @@ def test_compress_paths_argument_errors():
 
 @pytest.mark.parametrize("n,W,per8192,sub", [
     # a lane per record (sub-tiles of 4096): us of the windows of records from a table (2048) and of it
-    (5_912_473, 84, 22, 4096), (2_592_267, 90, 21, 4096), (332_287, 60, 23, 4096), (25_000_000, 30, 41, 4096),  # 52/31 47/30 29/17 55/49
-    (124_000_000, 100, 9, 4096), (100_000_000, 40, 41, 4096),
-    # one batch of windows, or denser diffs
-    (3_000_000, 17, 30, 2048), (25_600_000, 50, 82, 2048), (5_000_000, 10, 9, 2048), (3_000_000, 90, 49, 2048)])
+    (5_912_473, 84, 22, 4096), (2_592_267, 90, 21, 4096), (332_287, 60, 23, 4096),                                # 52/31 47/30 29/17
+    (124_000_000, 100, 9, 4096), (60_000_000, 64, 24, 4096), (118_000_000, 100, 30, 4096),                          # -, 154/122 338/294
+    # denser diffs, one batch of windows
+    (25_000_000, 30, 41, 2048), (25_000_000, 40, 30, 2048), (100_000_000, 40, 41, 2048), (10_000_000, 30, 41, 2048),  # 49/62 53/63 182/184 29/32
+    (3_000_000, 17, 30, 2048), (25_600_000, 50, 82, 2048), (5_000_000, 10, 9, 2048), (3_000_000, 90, 49, 2048),
+    # either side of the lines
+    (60_000_000, 64, 36, 4096), (60_000_000, 64, 37, 2048), (60_000_000, 65, 48, 4096), (60_000_000, 65, 49, 2048), (60_000_000, 32, 24, 4096),
+    (60_000_000, 32, 25, 2048), (60_000_000, 33, 36, 4096), (44_000_000, 64, 24, 4096), (44_000_000, 64, 25, 2048), (19_000_000, 64, 25, 4096)])
 def test_windows_take_the_table_that_measured_faster(n, W, per8192, sub):
     lib = ld.load()
     K = np.full(W, n * per8192 // 8192, np.int64)
