@@ -17,10 +17,11 @@ __global__ void k_check_zero(unsigned long long* out) {
     if (threadIdx.x < 3) out[threadIdx.x] = 0;
 }
 
-// Records up to which one workgroup (of 1024 threads, or of 256 where that is enough) checks them all in one round and writes the counts, which
-// nothing has to clear for it then: check and merge of 501 records 6.0 -> 4.9 us, of 5001 6.6 -> 5.9, of 10,001 7.6 -> 6.1; a second
-// round is 2 us. The last vectors are read like the others, record by record only where they end: 100,001 records 8.8 -> 8.0 us,
-// 333,334 17.9 -> 16.5 (33,334 6.8 -> 7.0).
+// Records up to which one workgroup (of 1024 threads, or of 256 where that is enough) checks them all in one round and writes the counts,
+// which nothing has to clear for it then: check and merge of 501 records 6.0 -> 4.9 us, of 5001 6.6 -> 5.9, of 10,001 7.6 -> 6.1; a second
+// round is 2 us. Where the records end, or an array is not 16-byte aligned, the vectors are read one by one, 100,001 records 8.8 -> 8.0 us,
+// 333,334 17.9 -> 16.5, unaligned 1 M 23.2 -> 11.7; the workgroups inside load without a branch (1 M records, 256 MB written in between, 13.1 -> 11.5 us;
+// 32,768 11.4 -> 10.2).
 constexpr int64_t kCheckFew = 16384;
 
 // A workgroup per THREADS * 16 records. ALONE: the only one; else they add to cleared counts.
@@ -39,25 +40,36 @@ __global__ __launch_bounds__(THREADS) void k_check_diff(const int32_t* __restric
     ld_u32x4 q[kCheckPer];
     ld_f32x4 x[kCheckPer];
     int32_t before[kCheckPer], have[kCheckPer];
+    if (vec && base + THREADS * kCheckPer * 4 <= K) {  // uniform
 #pragma unroll
-    for (int u = 0; u < kCheckPer; ++u) {
-        const int64_t e0 = base + (u * THREADS + threadIdx.x) * 4, left = K - e0;
-        have[u] = left < 0 ? 0 : left < 4 ? static_cast<int32_t>(left) : 4;
-        q[u] = ld_u32x4{0u, 0u, 0u, 0u};
-        x[u] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (vec && have[u] == 4) {
+        for (int u = 0; u < kCheckPer; ++u) {
+            const int64_t e0 = base + (u * THREADS + threadIdx.x) * 4;
+            have[u] = 4;
             q[u] = *reinterpret_cast<const ld_u32x4*>(idx + e0);  // cached: a merge of the same records follows
-            if (val) x[u] = *reinterpret_cast<const ld_f32x4*>(val + e0);
-        } else {
+            x[u] = val ? *reinterpret_cast<const ld_f32x4*>(val + e0) : ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            before[u] = ld_lane() == 0 && e0 > 0 ? idx[e0 - 1] : INT_MIN;  // nothing precedes record 0
+        }
+    } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (c < have[u]) {
-                    q[u][c] = static_cast<uint32_t>(idx[e0 + c]);
-                    if (val) x[u][c] = val[e0 + c];
+        for (int u = 0; u < kCheckPer; ++u) {
+            const int64_t e0 = base + (u * THREADS + threadIdx.x) * 4, left = K - e0;
+            have[u] = left < 0 ? 0 : left < 4 ? static_cast<int32_t>(left) : 4;
+            q[u] = ld_u32x4{0u, 0u, 0u, 0u};
+            x[u] = ld_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (vec && have[u] == 4) {
+                q[u] = *reinterpret_cast<const ld_u32x4*>(idx + e0);
+                if (val) x[u] = *reinterpret_cast<const ld_f32x4*>(val + e0);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (c < have[u]) {
+                        q[u][c] = static_cast<uint32_t>(idx[e0 + c]);
+                        if (val) x[u][c] = val[e0 + c];
+                    }
                 }
             }
+            before[u] = ld_lane() == 0 && e0 > 0 && have[u] > 0 ? idx[e0 - 1] : INT_MIN;
         }
-        before[u] = ld_lane() == 0 && e0 > 0 && have[u] > 0 ? idx[e0 - 1] : INT_MIN;  // nothing precedes record 0
     }
 #pragma unroll
     for (int u = 0; u < kCheckPer; ++u) {

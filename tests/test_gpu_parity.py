@@ -1483,7 +1483,7 @@ def test_check_diff_at_workgroup_edges(K, skip):
     assert tuple(got.cpu().tolist()) == oracle.check_diff(i[skip:], v[skip:], n)
 
 
-@pytest.mark.parametrize("K", [4098, 16381, 16383, 16384, 16385, 33_000])
+@pytest.mark.parametrize("K", [4098, 16381, 16383, 16384, 16385, 20_480, 33_000])
 def test_check_diff_in_one_workgroup_and_beyond(K):
     # up to 16384 records one workgroup writes the counts itself, whatever they held before; damage in the last, broken vectors too
     rs = np.random.RandomState(K)
