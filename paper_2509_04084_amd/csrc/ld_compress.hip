@@ -1577,10 +1577,15 @@ __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
 // stored candidate's key reaches T_est; only where that guess and the selection
 // differ is the residual written again. A segment handed to the full path gets
 // every pre-zeroed position back instead.
-// OWN: the threshold is selected here. Four waves per SIMD: the selection's registers would leave three (GPT-2 XL 3225 us a call, so 3217); five spill
-// them (3276).
+// OWN: the threshold is selected here. Four waves per SIMD: the selection's registers would leave three (GPT-2 XL 3225 us a call, so 3217; one segment of 60 M at
+// 5 and 10 % 224 and 249 / 218 and 243); five spill them (3276). But large groups of tiles of 32 and 64 lanes, denser than 1.2 %, take 158 registers without the
+// selection, and forced into 128 spill 20 to 32 of them: three waves there (20 segments of 60 M at 2 and 5 % 2729 and 3062 -> 2659 and 3035 us, 400 M at 5 % 1108 ->
+// 1080, 160 M at 5 % 485 -> 477).
+template <class RW>
+constexpr int kEmitWaves = RW::kSmall || RW::kRow == 16 ? 4 : 3;
+
 template <class RW, bool OWN>
-__global__ __launch_bounds__(kThreads, 4) void k_emit(float* __restrict__ r, int32_t* __restrict__ out_idx,
+__global__ __launch_bounds__(kThreads, kEmitWaves<RW>) void k_emit(float* __restrict__ r, int32_t* __restrict__ out_idx,
                                                    float* __restrict__ out_val, Ctx c) {
     __shared__ uint32_t tile_out[RW::kGroupTiles], tile_eqb[RW::kGroupTiles], tile_take[RW::kGroupTiles];
     __shared__ uint32_t own_gt[RW::kGroupTiles], own_eq[RW::kGroupTiles];  // gathered keys of the group's tiles: above T, equal to T

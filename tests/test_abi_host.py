@@ -3,6 +3,7 @@ symbol the header declares, and rejects bad arguments before touching the device
 import ctypes
 import os
 import re
+import struct
 
 import numpy as np
 import pytest
@@ -357,3 +358,38 @@ def test_windows_from_a_table_end_where_the_sweep_measured_faster():
                                  (79_000_000, 18, 300, True), (125_000_000, 20, 82, False)):
         K = np.full(W, n * per8192 // 8192, np.int64)
         assert (lib.ld_merge_sparse_workspace(n, W, _p(K)) > least(n, W)) == table, (n, per8192)
+
+
+def _kernel_metadata():
+    """{mangled name: what the compiler noted about it} for every kernel in the built library: the code objects bundled in it are
+    ELF files whose AMDGPU note is a msgpack map."""
+    msgpack = pytest.importorskip("msgpack")
+    ld.load()
+    image = open(ld.library_path(), "rb").read()
+    kernels, magic, at = {}, b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := image.find(magic, at)) >= 0:
+        entry = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", image, at + len(magic))[0]):
+            offset, size, chars = struct.unpack_from("<QQQ", image, entry)
+            target, entry = image[entry + 24:entry + 24 + chars], entry + 24 + chars
+            if b"gfx950" not in target or size == 0:
+                continue
+            elf = image[at + offset:at + offset + size]
+            phoff, phentsize, phnum = struct.unpack_from("<Q", elf, 32)[0], *struct.unpack_from("<HH", elf, 54)
+            for p in range(phnum):
+                kind, _, start, _, _, length = struct.unpack_from("<IIQQQQ", elf, phoff + p * phentsize)
+                if kind == 4 and elf[start + 12:start + 18] == b"AMDGPU":
+                    desc = struct.unpack_from("<I", elf, start + 4)[0]
+                    for k in msgpack.unpackb(elf[start + 20:start + 20 + desc])["amdhsa.kernels"]:
+                        kernels[k[".name"]] = k
+        at += len(magic)
+    return kernels
+
+
+def test_emission_of_dense_segments_keeps_its_registers():
+    # large groups of tiles of 32 and 64 lanes need 158 registers a thread: bounded to 128, they spilled up to 35 of them to memory
+    # (20 segments of 60 M elements at 2 % 2729 us a call instead of 2659)
+    dense = {n: k for n, k in _kernel_metadata().items() if "k_emit" in n and ("RowsILi32ELi64EE" in n or "RowsILi64ELi64EE" in n)}
+    assert len(dense) == 4
+    for name, k in dense.items():
+        assert k[".vgpr_spill_count"] == 0, name
