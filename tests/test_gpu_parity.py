@@ -44,7 +44,9 @@ def check_compress(g, r, seg_off, seg_k, select=True, tag="",
     returns (idx, val, r_new) of the oracle. `want(path, tied, overflowed)` is called with what
     the AUTO call reports about the way each segment went. With `large_groups` all of it once more
     with 520 segments of one element behind the others: every segment is a group at least, and from 512 groups of
-    64 tiles on a call runs with those (and other kernels) instead of groups of 16."""
+    64 tiles on a call runs with those (and other kernels) instead of groups of 16; and with a large segment
+    behind them, whose size has the thresholds of all selected in a launch of their own."""
+    alone = large_groups
     if large_groups:
         more = 520
         rs = np.random.RandomState(more)
@@ -71,7 +73,44 @@ def check_compress(g, r, seg_off, seg_k, select=True, tag="",
                 assert np.all(path[seg_k > 0] == ld.LD_PATH_FULL), tg
             elif want is not None:
                 want(path, tied, over)
+    if alone:
+        check_compress_before_a_large_segment(g_gpu, r, seg_off, seg_k, (oi, ov, orr), tag, want)
     return oi, ov, orr
+
+
+_large = {}
+
+
+def check_compress_before_a_large_segment(g, r, seg_off, seg_k, expected, tag, want):
+    """The same segments once more with one of 66 M elements behind them (groups of 16 tiles) or of 135 M (groups of 64), that keeps one
+    element, 2 % or 6 % (which has 16, 32 and 64 lanes serve a tile): k_select, and k_emit without a selection of its own. The large
+    segment's records are checked by what holds at any size."""
+    oi, ov, orr = expected
+    n, K = int(seg_off[-1]), len(oi)
+    if "g" not in _large:
+        gen = torch.Generator(device=DEV).manual_seed(66)
+        _large["g"] = torch.randn(135_000_001, generator=gen, device=DEV)
+    for size in (66_000_001, 135_000_001):
+        for k in (1, size // 50, size * 6 // 100):
+            tg = f"{tag}, before {size} elements of which {k} are kept"
+            gx, rx = torch.cat([g, _large["g"][:size]]), torch.cat([to_gpu(r), torch.zeros(size, device=DEV)])
+            off, kk = np.append(seg_off, n + size), np.append(seg_k, k).astype(np.int32)
+            ws = torch.empty(ld.ld_compress_topk_workspace(off, kk), dtype=torch.uint8, device=DEV)
+            idx, val = ld.ld_compress_topk(gx, rx, off, kk, workspace=ws)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(idx[:K].cpu().numpy(), oi, err_msg=f"idx {tg}")
+            np.testing.assert_array_equal(bits(val[:K].cpu().numpy()), bits(ov), err_msg=f"val {tg}")
+            np.testing.assert_array_equal(bits(rx[:n].cpu().numpy()), bits(orr), err_msg=f"residual {tg}")
+            li, lv, left = idx[K:].long(), val[K:], gx
+            assert li.numel() == k and bool((li[1:] > li[:-1]).all()) and int(li[0]) >= n and int(li[-1]) < n + size, tg
+            assert torch.equal(lv.view(torch.int32), left[li].view(torch.int32)), tg
+            left[li] = 0.0
+            assert torch.equal(left[n:].view(torch.int32), rx[n:].view(torch.int32)), tg
+            assert float(left[n:].abs().max()) <= float(lv.abs().min()), tg
+            path, tied, over = compress_paths(ws, off)
+            assert path[-1] == ld.LD_PATH_CANDIDATES, tg
+            if want is not None:
+                want(path[:-1], tied[:-1], over[:-1])
 
 
 # ------------------------------------------------------------------ compress
