@@ -34,7 +34,7 @@
 //             gathered per segment.
 //   k_emit    each workgroup selects the exact threshold T and tie count among the
 //             gathered keys for itself and completes its tiles' counts with them
-//             (tables with segments of more than 100 M elements: k_select before it);
+//             (tables with segments of more than 65 or 100 M elements: k_select before it);
 //             ordered emission of (idx, val); repairs the residual where the
 //             T_est guess and the true selection differ.
 //
@@ -1498,9 +1498,12 @@ __device__ __attribute__((noinline)) void pick_many(const uint32_t* gkey, const 
 }
 
 // Segments up to which k_emit's workgroups select for themselves. A larger one has more keys in the threshold bin than a wave selects
-// among, and thousands of groups before its last: one workgroup per segment does all that ahead of k_emit then (k_select). us per
-// call with / without that launch: 400 M elements 885 / 873, rounded to bf16 1155 / 1315, 1.2 G 2690 / 2767; GPT-2 XL, up to 80 M a segment, 3263 / 3255.
-constexpr int64_t kOwnPick = 100000000;
+// among, and more groups before its last: one workgroup per segment does all that ahead of k_emit then (k_select). With small groups
+// the line is where the segment's workgroups no longer all run at once and begin another round of reading the list (1024, 67 M elements). us per call with
+// / without that launch, small groups, one segment of 60 M elements 190 / 180, 70 M 213 / 210, 80 M 235 / 236, 99 M 281 / 283, at 5 % of values rounded to fp16
+// 221 / 228, 250 / 269, 276 / 295, 332 / 361. Large groups: 140 M 365 / 366, at 5 % 434 / 425, of values rounded to fp16 579 / 594, 230 M 907 / 973,
+// 400 M 916 / 915 and 1499 / 1609; ten of 80 M 1698 / 1708, at 5 % 2030 / 2021 and 2277 / 2334; GPT-2 XL, up to 80 M a segment, 3263 / 3255.
+constexpr int64_t kOwnPick = 100000000, kOwnPickSmall = 65000000;
 
 // One workgroup per segment: threshold and ties; per-tile counts completed; group sums scanned into output offsets.
 __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
@@ -2363,7 +2366,7 @@ extern "C" ld_status ld_compress_topk_strategy(const float* grad, float* residua
     const int row = (per_tile <= 128 && slot == kSlotMin) ? 16 : (per_tile <= 256 ? 32 : 64);  // 16 implies the minimum slot
     int64_t largest = 0;
     for (int32_t s = 0; s < n_seg; ++s) largest = seg_off[s + 1] - seg_off[s] > largest ? seg_off[s + 1] - seg_off[s] : largest;
-    const bool own = largest <= kOwnPick;
+    const bool own = largest <= (tiles == kTilesPerGroup ? kOwnPick : kOwnPickSmall);
     ld_status passes;
     if (tiles == kTilesPerGroup) {
         if (row == 16) passes = candidate_passes<Rows<16, kTilesPerGroup>>(c, own, residual, out_idx, out_val, st);
