@@ -165,6 +165,8 @@ def test_dense_argument_errors():
     assert lib.ld_snapshot_layer(V(FAKE), V(FAKE), -1, V(0)) == -2
     assert lib.ld_snapshot_layer(V(FAKE + 1), V(FAKE), 10, V(0)) == -5
     assert lib.ld_snapshot_layer(V(0), V(0), 0, V(0)) == 0
+    nothing, at = np.zeros(200, np.int64), np.zeros(200, np.uint64)  # 200 layers without an element: no launch
+    assert lib.ld_snapshot_layers(_p(at), _p(at), _p(nothing), 200, V(0)) == 0
     g = (ctypes.c_void_p * 2)(FAKE, FAKE)
     f = ctypes.c_float
 

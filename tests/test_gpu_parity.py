@@ -972,10 +972,11 @@ def test_snapshot_many_layers_one_launch():
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-@pytest.mark.parametrize("count", [1, 15, 16, 17, 175, 176, 177, 353])
+@pytest.mark.parametrize("count", [1, 2, 3, 8, 15, 16, 17, 18, 175, 176, 177, 353])
 def test_snapshot_layers_around_a_launch(count):
-    # a launch takes 176 layers, found in groups of 16; whole blocks of 8192 elements, one element less and more, empty layers,
-    # sources and destinations an element apart in alignment, nothing around them written
+    # a launch takes 176 layers, found in groups of 16, up to 16 by a binary search; more are shared out evenly;
+    # whole blocks of 8192 elements, one element less and more, empty layers, sources and destinations an element apart in alignment, nothing
+    # around them written
     rs = np.random.RandomState(count)
     sizes = [int(rs.choice([1, 7, 64, 8191, 8192, 8193, 16384, 30_001, 0])) for _ in range(count)]
     sizes[-1] = 8193
