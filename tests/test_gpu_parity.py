@@ -811,15 +811,15 @@ def test_merge_thin_long_windows(case):
 
 @pytest.mark.parametrize("W", [11, 40, 65, 128])
 def test_merge_lane_per_record_blocks(W):
-    # Lists of a sub-tile around the 512 records of a block and the 64 that wait their turn together, over element pools from the
+    # Lists of a sub-tile around the 512 records of a block, the 128 of its end and the 64 that wait their turn together, over element pools from the
     # whole sub-tile (few wait) to 16 elements (rows take turns), within the ragged last sub-tile too. With the table
     # of sub-tiles of 4096 all of them run a lane per record.
     n = 4096 * 900 + 1234
     rs = np.random.RandomState(W)
     recs = [set() for _ in range(W)]
-    totals = [1, 2, 63, 64, 65, 127, 128, 129, 511, 512, 513, 575, 1023, 1024, 1025, 1400]
+    totals = [1, 2, 63, 64, 65, 127, 128, 129, 511, 512, 513, 575, 1023, 1024, 1025, 1400, 640, 641]
     for s, (total, pool) in enumerate([(t, p) for t in totals for p in (4096, 1000, 300, 60, 16)] + [(300, 1234)]):
-        base, span = (4096 * 900, 1234) if pool == 1234 else (4096 * (11 * s + 3), 4096)
+        base, span = (4096 * 900, 1234) if pool == 1234 else (4096 * (9 * s + 3), 4096)
         where = base + rs.choice(span, min(pool, span), replace=False)
         owner = rs.randint(0, W, min(total, W * where.size))
         for t, count in zip(*np.unique(owner, return_counts=True)):
