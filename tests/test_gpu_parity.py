@@ -645,7 +645,7 @@ def test_merge_lane_per_record_dense_sub_tiles_and_columns(n, W, case):
 @pytest.mark.parametrize("W,per8192,case", [(11, 19, "even"), (11, 20, "even"), (11, 21, "even"), (17, 20, "even"), (18, 20, "even"),
                                             (18, 48, "even"), (18, 49, "even"), (11, 16, "column"), (18, 32, "column"), (131, 32, "column")])
 def test_merge_lane_per_record_where_its_line_lies(W, per8192, case):
-    # either side of the line, 20 records per 8192 elements up to 17 diffs and 48 with more, and the same column of
+    # either side of the line of small arrays, 20 records per 8192 elements up to 17 diffs and 48 with more, and the same column of
     # elements 512 or 256 apart in every diff (all on one slot of the owner table, were it not for the hash)
     n = 8192 * 41
     rs = np.random.RandomState(W + per8192)
@@ -743,15 +743,19 @@ def test_merge_of_sparse_windows_with_and_without_tables(W, way):
 
 @pytest.mark.parametrize("W", [11, 65])
 def test_merge_lane_per_record_whole_sub_tiles(W):
-    # sub-tiles of 4096 that a diff records whole, four trips of 16 rows, in a window that is sparse all in all
+    # sub-tiles of 4096 that a diff records whole, four trips of 16 rows, in a window that is sparse all in all; the workspace
+    # holds the table of sub-tiles of 4096 and no larger one, and so has both windows run a lane per record
     n = 2_000_003
     idxs = [np.concatenate([np.arange(4096 * 7 - t, 4096 * 8 + t), np.arange(n - 60, n)]).astype(np.int32) for t in range(W)]
-    assert max(i.size for i in idxs) * 8192 <= 20 * n
+    K = [i.size for i in idxs]
+    nbytes = table_of(n, W, 4096)
+    assert max(K) * 8192 <= 20 * n and int(ld.load().ld_merge_sparse_workspace(n, W, None)) < nbytes <= ld.ld_merge_sparse_workspace(n, K)
     rs = np.random.RandomState(W)
     vals = [(rs.standard_normal(i.size) * 1e-2).astype(np.float32) for i in idxs]
     w0 = synth.base_weights(n).numpy()
     w = to_gpu(w0)
-    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1, strategy=ld.LD_MERGE_SWEEP)
+    ld.ld_merge_sparse(w, [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals], 0.1,
+                       workspace=torch.empty(nbytes, dtype=torch.uint8, device=DEV), strategy=ld.LD_MERGE_SWEEP)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(bits(w.cpu().numpy()), bits(oracle.merge_sparse(w0, idxs, vals, 0.1)))
 

@@ -133,13 +133,13 @@ def test_random_chain_compress_merge_adam_combine(seed, strategy):
 @pytest.mark.parametrize("seed", range(7100, 7148))
 def test_random_long_thin_windows(seed):
     """Windows of more than ten sparse diffs (the lane-per-record kernel's domain and the cases
-    just outside it), with the workspace that admits that kernel, with the smallest one, and
-    through the entry point that brings its own scratch memory."""
+    just outside it), with the workspace that the query gives, with the smallest one, with one that holds the
+    table of that kernel and not the larger one of windows, and through the entry point that brings its own scratch memory."""
     rs = np.random.RandomState(seed)
     n = int(rs.choice([rs.randint(5000, 200000), rs.randint(200000, 6000000)]))
     W = int(rs.choice([11, 12, 40, 64, 65, 70, 100, 128, 130, 200]))
     mode = str(rs.choice(["indep", "shared", "cluster", "mixed", "tiny"]))
-    dens = 16 if seed < 7124 else 50                    # records per 8192 elements at most; the kernel's line is 48, up to 17 diffs 20
+    dens = 16 if seed < 7124 else 50                    # records per 8192 elements at most; the kernel serves up to 48
     base_k = int(rs.randint(1, max(1, n * dens // 8192) + 1))
     pool = np.sort(rs.choice(n, min(n, base_k * 3), replace=False))
     idxs, vals = [], []
@@ -161,9 +161,10 @@ def test_random_long_thin_windows(seed):
     K = [i.size for i in idxs]
     full_ws = ld.ld_merge_sparse_workspace(n, K)
     min_ws = int(ld.load().ld_merge_sparse_workspace(n, len(K), None))
+    lanes_ws = -(-(min(W, 128) * (-(-n // 4096) + 1) * 4) // 256) * 256
     print(f"[random thin window] seed={seed} n={n} W={W} mode={mode} k={base_k} table={full_ws > min_ws}", flush=True)
     gi, gv = [to_gpu(i) for i in idxs], [to_gpu(v) for v in vals]
-    for nbytes in sorted({full_ws, min_ws}):
+    for nbytes in sorted({full_ws, min_ws, max(min_ws, lanes_ws)}):
         w = to_gpu(w0)
         ld.ld_merge_sparse(w, gi, gv, 0.1, workspace=torch.empty(nbytes, dtype=torch.uint8, device=DEV),
                            strategy=ld.LD_MERGE_SWEEP)
