@@ -1478,8 +1478,9 @@ __device__ __attribute__((noinline)) Picked select_many(const uint32_t* gkey, ui
 }
 
 // As pick_few, by the whole workgroup.
-__device__ __attribute__((noinline)) void pick_many(const uint32_t* gkey, const int32_t* gtile, uint32_t ng, uint32_t gcap, uint32_t kmin,
-                                                    uint32_t kmax, uint32_t krem, int32_t tile0, int32_t tiles, Picked* out, uint32_t* own_gt, uint32_t* own_eq, uint32_t* lh, uint32_t* sh,
+__device__ __attribute__((noinline)) void pick_many(const uint32_t* gkey, const int32_t* gtile, uint32_t ng, uint32_t gcap,
+                                                    uint32_t kmin, uint32_t kmax, uint32_t krem, int32_t tile0, int32_t tiles,
+                                                    Picked* out, uint32_t* own_gt, uint32_t* own_eq, uint32_t* lh, uint32_t* sh,
                                                     uint32_t* res) {
     const Picked x = select_many(gkey, ng, gcap, kmin, kmax, krem, lh, sh, res);
     if (threadIdx.x == 0) *out = x;
@@ -1497,12 +1498,13 @@ __device__ __attribute__((noinline)) void pick_many(const uint32_t* gkey, const 
     __syncthreads();
 }
 
-// Segments up to which k_emit's workgroups select for themselves. A larger one has more keys in the threshold bin than a wave selects
-// among, and more groups before its last: one workgroup per segment does all that ahead of k_emit then (k_select). With small groups
-// the line is where the segment's workgroups no longer all run at once and begin another round of reading the list (1024, 67 M elements). us per call with
-// / without that launch, small groups, one segment of 60 M elements 190 / 180, 70 M 213 / 210, 80 M 235 / 236, 99 M 281 / 283, at 5 % of values rounded to fp16
-// 221 / 228, 250 / 269, 276 / 295, 332 / 361. Large groups: 140 M 365 / 366, at 5 % 434 / 425, of values rounded to fp16 579 / 594, 230 M 907 / 973,
-// 400 M 916 / 915 and 1499 / 1609; ten of 80 M 1698 / 1708, at 5 % 2030 / 2021 and 2277 / 2334; GPT-2 XL, up to 80 M a segment, 3263 / 3255.
+// Segments up to which k_emit's workgroups select for themselves. A larger one has more keys in the threshold bin than a wave
+// selects among, and more groups before its last: one workgroup per segment does all that ahead of k_emit then (k_select). With small
+// groups the line is where the segment's workgroups no longer all run at once and begin another round of reading the list (1024 of
+// them, 67 M elements). us per call with / without that launch, small groups, one segment of 60 M elements 190 / 180, 70 M 213 / 210, 80 M
+// 235 / 236, 99 M 281 / 283, at 5 % of values rounded to fp16 221 / 228, 250 / 269, 276 / 295, 332 / 361. Large groups: 140 M 365 / 366,
+// at 5 % 434 / 425, of values rounded to fp16 579 / 594, 230 M 907 / 973, 400 M 916 / 915 and 1499 / 1609; ten of 80 M 1698 / 1708, at 5 %
+// 2030 / 2021 and 2277 / 2334; GPT-2 XL, up to 80 M a segment, 3263 / 3255.
 constexpr int64_t kOwnPick = 100000000, kOwnPickSmall = 65000000;
 
 // One workgroup per segment: threshold and ties; per-tile counts completed; group sums scanned into output offsets.
@@ -1580,10 +1582,10 @@ __global__ __launch_bounds__(kThreads) void k_select(Ctx c) {
 // stored candidate's key reaches T_est; only where that guess and the selection
 // differ is the residual written again. A segment handed to the full path gets
 // every pre-zeroed position back instead.
-// OWN: the threshold is selected here. Four waves per SIMD: the selection's registers would leave three (GPT-2 XL 3225 us a call, so 3217; one segment of 60 M at
-// 5 and 10 % 224 and 249 / 218 and 243); five spill them (3276). But large groups of tiles of 32 and 64 lanes, denser than 1.2 %, take 158 registers without the
-// selection, and forced into 128 spill 20 to 32 of them: three waves there (20 segments of 60 M at 2 and 5 % 2729 and 3062 -> 2659 and 3035 us, 400 M at 5 % 1108 ->
-// 1080, 160 M at 5 % 485 -> 477).
+// OWN: the threshold is selected here. Four waves per SIMD: the selection's registers would leave three (GPT-2 XL 3225 us a call, so
+// 3217; one segment of 60 M at 5 and 10 % 224 and 249 / 218 and 243); five spill them (3276). But large groups of tiles of 32 and 64 lanes,
+// denser than 1.2 %, take 158 registers without the selection, and forced into 128 spill 20 to 32 of them: three waves there (20 segments of
+// 60 M at 2 and 5 % 2729 and 3062 -> 2659 and 3035 us, 400 M at 5 % 1108 -> 1080, 160 M at 5 % 485 -> 477).
 template <class RW>
 constexpr int kEmitWaves = RW::kSmall || RW::kRow == 16 ? 4 : 3;
 
@@ -1680,7 +1682,8 @@ __global__ __launch_bounds__(kThreads, kEmitWaves<RW>) void k_emit(float* __rest
         }
         __syncthreads();
         if (mode == kModeCand && ng > kFewPicks)
-            pick_many(gkey, gtile, ng, gcap, st->kmin, st->kmax, krem, group_tile0, RW::kGroupTiles, &picked, own_gt, own_eq, reinterpret_cast<uint32_t*>(stage_i), sh, res);
+            pick_many(gkey, gtile, ng, gcap, st->kmin, st->kmax, krem, group_tile0, RW::kGroupTiles, &picked, own_gt, own_eq,
+                      reinterpret_cast<uint32_t*>(stage_i), sh, res);
         if (w == 0) {  // offsets of the group's tiles
             const Picked p = picked;
             const uint32_t m = p.m;

@@ -230,8 +230,9 @@ __global__ __launch_bounds__(LD_WAVE) void k_merge_sweep(float* __restrict__ w, 
 // up in list order and go through in rows of 64. There every pending record bids for its element's slot of a small owner
 // table with its lane, the smallest lane wins the slot (atomic minimum), applies its update and leaves; lanes are in list order, so
 // the updates of one element go through in list order whatever else shares the slot, and any number of records is
-// served. Where many of the first 128 records meet (diffs that share their positions), and the last 128 of a list, all rows bid, without lining up
-// (short lists that went through all of it: 1 M elements, 11 diffs of 0.1 % 12.5 us instead of 11.5 with 256 MB written in between, 6 M, 100 of 1/3000 32.4, so 31.0).
+// served. Where many of the first 128 records meet (diffs that share their positions), and at the last 128 of a list, all rows bid,
+// without lining up (short lists that went through all of it: 1 M elements, 11 diffs of 0.1 % 12.5 us instead of 11.5, 6 M, 100 of
+// 1/3000 32.4 instead of 31.0, with 256 MB written in between).
 // Sub-tiles where the diffs are dense go through diff after diff (kThinDense).
 //
 // Bound by w's bytes up to some 200 records a sub-tile (100 M elements, 20 diffs of 1/400: 6.1 TB/s), beyond by the records: pieces of
@@ -764,15 +765,17 @@ int rows_windows(int64_t n, int32_t gw, int64_t most) {  // 64-record windows pe
 }
 
 // Up to which density a group of `gw` diffs runs a lane per record (k_merge_thin), in records of its largest diff per 8192 elements
-// (0: not at all): that pays by the record, windows from a table and the sweep by the diff. us a call, windows / a lane per record, densities even (and
-// log-normal over 60 layers, sigma 0.7): 30 diffs of 1/200 49 / 62 (49 / 62) on
-// 25 M elements, 29 / 32 (28 / 37) on 10 M, 20 / 18 (20 / 27) on 6 M; 40 of 1/270 53 / 63 (53 / 63) on 25 M, 19 / 18 (18 / 28) on 4 M, 159 / 161 (158 / 168) on 90 M,
-// of 1/200 182 / 184 (180 / 206) on 100 M; 60 of 1/250 40 / 37 (40 / 48) on 10 M, 64 of 1/330 154 / 122 (153 / 134) on 60 M, 56 of 1/200 250 / 266 (250 / 301)
-// on 118 M; 100 of 1/270 53 / 45 on 10 M, 338 / 294 on 118 M. Up to 24 diffs sparser than the line are scattered more often than
-// not; below 2 M elements it is the launches. Sweep / a lane per record, where there is no table of windows: 150 M elements, 32 diffs of 1/120 343 / 313, 100 of 1/120 845 / 718; 400 M, 32 of 1/150 773 / 751, of 1/120 793 / 831, 64 of 1/150 1192 / 1107, 100 of 1/120 2035 / 1845.
-// 11 to 24 diffs, sweep over a lane per record, densities even and log-normal over 60 layers (sigma 1): up to 74 records 1.01 to 1.15 and 1.05 to 1.30 on
-// 130, 185 and 250 M elements (20 diffs of 1/290 on 250 M 439 / 395 us, 24 of 1/300 on 185 M 326 / 301); 24 diffs on 400 to 800 M at 37 records 1.01 to 1.04 and 1.14 to 1.17, at 54
-// 0.97 to 0.99 and 1.22; on 1.4 G at 28 1.00 and 1.13, at 37 1.00 and 1.14, 16 diffs there 0.98 and 1.05 to 1.07.
+// (0: not at all): that pays by the record, windows from a table and the sweep by the diff.
+// Windows / a lane per record, us a call, densities even (and log-normal over 60 layers, sigma 0.7): 30 diffs of 1/200 49 / 62
+// (49 / 62) on 25 M elements, 29 / 32 (28 / 37) on 10 M, 20 / 18 (20 / 27) on 6 M; 40 of 1/270 53 / 63 (53 / 63) on 25 M, 19 / 18
+// (18 / 28) on 4 M, 159 / 161 (158 / 168) on 90 M, of 1/200 182 / 184 (180 / 206) on 100 M; 60 of 1/250 40 / 37 (40 / 48) on 10 M;
+// 64 of 1/330 154 / 122 (153 / 134) on 60 M; 56 of 1/200 250 / 266 (250 / 301) on 118 M; 100 of 1/270 53 / 45 on 10 M, 338 / 294 on
+// 118 M. Up to 24 diffs sparser than the line are scattered more often than not; below 2 M elements it is the launches.
+// Sweep / a lane per record, where there is no table of windows: 150 M elements, 32 diffs of 1/120 343 / 313, 100 of 1/120 845 / 718;
+// 400 M, 32 of 1/150 773 / 751, of 1/120 793 / 831, 64 of 1/150 1192 / 1107, 100 of 1/120 2035 / 1845. 11 to 24 diffs, sweep over a lane
+// per record, densities even and log-normal (sigma 1): up to 74 records 1.01 to 1.15 and 1.05 to 1.30 on 130, 185 and 250 M elements (20
+// diffs of 1/290 on 250 M 439 / 395 us, 24 of 1/300 on 185 M 326 / 301); 24 diffs on 400 to 800 M at 37 records 1.01 to 1.04 and 1.14 to
+// 1.17, at 54 0.97 to 0.99 and 1.22; on 1.4 G at 28 1.00 and 1.13, at 37 1.00 and 1.14, 16 diffs there 0.98 and 1.05 to 1.07.
 int thin_line(int64_t n, int32_t gw) {
     if (gw <= 10) return 0;
     if (n < 2000000) return gw > kRowBatch ? 48 : 20;
