@@ -133,8 +133,6 @@ constexpr int kAdamThreads = 256;
 constexpr int kAdamH = 4;                          // 16-byte fp32 vectors per thread and array
 constexpr int kAdamBlockElems = kAdamThreads * 4 * kAdamH; // elements per workgroup
 
-
-
 // Replays steps [t0, t0 + WT) of the window (those below a.W). One workgroup per
 // kAdamBlockElems consecutive elements; every load instruction of a wave covers
 // one contiguous run (16 bytes of fp32 state or 8 bytes of bf16 gradient per
